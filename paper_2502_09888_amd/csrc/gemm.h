@@ -67,6 +67,24 @@ hipError_t gemm_bf16(int epi, const void *A, int64_t lda, const void *w_packed, 
                      void *C, int64_t ldc, const float *resid, int64_t ldr, const RowNormIn &in_norm,
                      const RowNormOut &out_norm, int tiled, hipStream_t s, const QkvToCache *to_cache = nullptr);
 
+// The arguments of one projection launch, as the kernels' host side passes them around.
+struct GemmArgs {
+    const void *A;
+    int64_t lda;
+    const void *W;
+    int M, N, K;
+    void *C;
+    int64_t ldc;
+    const float *resid;
+    int64_t ldr;
+    RowNormIn nin;
+    RowNormOut nout;
+    int tiled;
+    QkvToCache qc;
+};
+// gemm_small_bf16.hip: few rows.  N % 64 == 0, K % 128 == 0.
+hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s);
+
 // What the first projection of a stack call needs of its input rows: the sum of squares of every
 // row into ss[row][0] (ss[row][1 .. n_part-1] = 0) and
 //   from bf16 rows x (the embeddings): the fp32 copy x32 (the residual stream);

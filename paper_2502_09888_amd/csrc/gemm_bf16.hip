@@ -17,7 +17,7 @@
 //         here have K = 512 or 2048: short k-loops, and they sit near the HBM/MFMA ridge);
 //   2 x 2 (macro tile 128 x 128): for problems too small to fill the chip with larger tiles.
 // Workgroups that share A rows are launched onto the same XCD (see the kernel).
-#include "gemm.h"
+#include "gemm_common.h"
 #include "lanes.h"
 
 #include <algorithm>
@@ -29,9 +29,8 @@
 namespace climber {
 namespace {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+using namespace gemm;
+
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef const __attribute__((address_space(1))) uint8_t glb_u8;
 
@@ -68,24 +67,6 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const PackJobs jobs)
     for (int64_t chunk = (int64_t)blockIdx.x * 256 + threadIdx.x; chunk < n_chunks;
          chunk += (int64_t)gridDim.x * 256)
         pack_chunk((const __bf16 *)jobs.w[j], (const __bf16 *)jobs.gain[j], (__bf16 *)jobs.packed[j], K, N, chunk);
-}
-
-// exact-erf GELU, erf by the rational/exponential formula 7.1.26 of Abramowitz & Stegun
-// (|error| <= 1.5e-7, far below the bf16 rounding of the result).  With a = |x|, z = a/sqrt(2),
-// t = 1/(1 + p z) and h = (1 - erf z)/2 = (poly(t)/2) t exp(-z^2):
-//   GELU(x) = x (1 + erf(x/sqrt 2))/2 = max(x, 0) - a h        (x >= 0: x - x h;  x < 0: x h)
-// which needs no sign select; the constants carry the factors 1/2, 1/sqrt(2) and log2(e)/2.
-__device__ __forceinline__ float gelu_erf(float x)
-{
-    const float a = __builtin_fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(fmaf(a, 0.3275911f * 0.70710678118654752f, 1.f));
-    float poly = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
-    poly = fmaf(poly, t, 0.5f * 1.421413741f);
-    poly = fmaf(poly, t, 0.5f * -0.284496736f);
-    poly = fmaf(poly, t, 0.5f * 0.254829592f);
-    const float e = __builtin_amdgcn_exp2f((x * x) * -0.72134752044448170f);
-    const float h = (poly * t) * e;
-    return fmaf(-a, h, fmaxf(x, 0.f));
 }
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), unrolled at compile time
@@ -203,24 +184,13 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
         }
     }
 
-    // Direct cache write: the user that block row i of this wave (32 tokens) belongs to -- first
-    // row, padded and valid length -- by arithmetic for uniform batches, from the cache's tables for
-    // ragged ones (wave-uniform loads, requested here and first used in the epilogue).
-    int u_t0[WM], u_lp[WM], u_lv[WM];
+    // Direct cache write: the user of block row i of this wave (requested here, first used in the epilogue)
+    CacheUser user[WM];
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
-        u_t0[i] = 0, u_lp[i] = 64, u_lv[i] = 0;
-        if (EPI == EPI_STORE_BF16 && qc.layer_base) {
-            const int rb = __builtin_amdgcn_readfirstlane(min(m0 + 32 * (WM * wm + i), M - 32));
-            if (qc.l_pad > 0) {
-                u_t0[i] = rb / qc.l_pad * qc.l_pad, u_lp[i] = qc.l_pad, u_lv[i] = qc.l_valid;
-            } else {
-                const int u = qc.seg[rb >> 6];
-                u_t0[i] = qc.tok_off[u];
-                u_lp[i] = qc.tok_off[u + 1] - u_t0[i];
-                u_lv[i] = qc.hist_len[u];
-            }
-        }
+        user[i] = CacheUser{0, 64, 0};
+        if (EPI == EPI_STORE_BF16 && qc.layer_base)
+            user[i] = cache_user(qc, __builtin_amdgcn_readfirstlane(min(m0 + 32 * (WM * wm + i), M - 32)));
     }
 
     // One k-tile: wait for it, read both halves' fragments, then the MFMAs with the copies of tile
@@ -280,12 +250,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
         for (; kt < n_kt; ++kt, advance()) k_tile(kt, st_cur, st_fill, std::false_type{});
     }
 
-    // Epilogue.  The operands were fed as (W fragment, A fragment), so a block accumulator is the
-    // transposed product: lane holds C[32i + l32][32j + 8g + 4hf + 0..3] for g = r/4 -- four
-    // consecutive columns of ONE row.  Each wave turns 32 rows x (WN*32) columns around in its own
-    // corner of the (now idle) LDS ring and stores whole rows, 16 bytes per lane.
     __syncthreads();  // every wave is done reading the last k-tile
-    constexpr bool F32 = EPI == EPI_RESID_F32;
     float rs[WM];
 #pragma unroll
     for (int i = 0; i < WM; ++i) rs[i] = 1.f;
@@ -304,144 +269,12 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
         }
     }
 
-    constexpr int CW = WN * 32;                       // columns of a wave's block
-    constexpr int kElem = F32 ? 4 : 2;
-    constexpr int kPitch = CW * kElem + 16;           // bytes per staged row
-    constexpr int kChunksPerRow = CW * kElem / 16;
-    uint8_t *tr = lds + wave * (32 * kPitch);
-    constexpr int kIters = 32 * kChunksPerRow / 64;   // 16-byte pieces per lane and block row
-    const int col_base = n0 + CW * wn;
-    // Residual rows of block row i, all requested before anything waits for them (a load placed
-    // after a store would make the wait for it drain the stores as well: one memory round trip per
-    // 16 bytes).  Block row i + 1 is requested before block row i is stored.
-    float4 rsd[2][F32 ? kIters : 1];
-    auto load_resid = [&](int i, float4 *buf) __attribute__((always_inline)) {
-        if constexpr (F32) {
-#pragma unroll
-            for (int it = 0; it < kIters; ++it) {
-                const int id = it * 64 + lane, r = id / kChunksPerRow, cc = id % kChunksPerRow;
-                const int row = min(m0 + 32 * (WM * wm + i) + r, M - 1);
-                buf[it] = *(const float4 *)(resid + (int64_t)row * ldr + col_base + cc * 4);
-            }
-        }
-    };
-    load_resid(0, rsd[0]);
-    // direct cache write: slots past a user's valid length hold zeros
-    bool zero_row[WM];
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-        zero_row[i] = EPI == EPI_STORE_BF16 && qc.layer_base &&
-                      m0 + 32 * (WM * wm + i) - u_t0[i] + l32 >= u_lv[i];
-#pragma unroll
-    for (int i = 0; i < WM; ++i) {
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int col = 32 * j + 8 * g + 4 * hf;
-                if (F32) {
-                    float4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-                    *(float4 *)(tr + l32 * kPitch + col * 4) = v;
-                } else {
-                    __attribute__((aligned(8))) __bf16 v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float x = acc[i][j][4 * g + e] * rs[i];
-                        v[e] = (__bf16)(EPI == EPI_GELU_BF16 ? gelu_erf(x) : EPI == EPI_RELU_BF16 ? fmaxf(x, 0.f) : x);
-                    }
-                    if (EPI == EPI_STORE_BF16 && zero_row[i]) v[0] = v[1] = v[2] = v[3] = (__bf16)0.f;
-                    *(uint2 *)(tr + l32 * kPitch + col * 2) = *(const uint2 *)v;
-                }
-            }
-        if (i + 1 < WM) load_resid(i + 1, rsd[(i + 1) & 1]);
-        const int row_base = m0 + 32 * (WM * wm + i);
-        if (EPI == EPI_STORE_BF16 && qc.layer_base) {
-            // the wave's 32 x 64 block is one head of the queries, keys or values of 32 tokens of one
-            // user (padded lengths are multiples of 64)
-            static_assert(EPI != EPI_STORE_BF16 || CW == 64, "a wave's block = one head");
-            typedef short s16x4 __attribute__((ext_vector_type(4)));
-            typedef short s16x8 __attribute__((ext_vector_type(8)));
-            const int which = qc.which0 + col_base / qc.d, h = (col_base % qc.d) / 64;
-            if (row_base < M) {
-                const int kb = (row_base - u_t0[i]) / 32;
-                uint8_t *blk = qc.layer_base + ((size_t)u_t0[i] * qc.H + (size_t)h * u_lp[i]) * 256 + (size_t)kb * 8192;
-                if (which == 0) {        // query rows
-#pragma unroll
-                    for (int it = 0; it < kIters; ++it) {
-                        const int id = it * 64 + lane, r = id / kChunksPerRow, cc = id % kChunksPerRow;
-                        if (row_base + r < M)
-                            *(uint4 *)((__bf16 *)C + (int64_t)(row_base + r) * ldc + h * 64 + cc * 8) =
-                                *(const uint4 *)(tr + r * kPitch + cc * 16);
-                    }
-                } else if (which == 1) {  // K fragments: chunk (s, lane) = K[lane % 32][16 s + 8 (lane / 32) ..]
-#pragma unroll
-                    for (int s4 = 0; s4 < 4; ++s4)
-                        *(uint4 *)(blk + (s4 * 64 + lane) * 16) = *(const uint4 *)(tr + l32 * kPitch + (2 * s4 + hf) * 16);
-                } else {                  // V^T chunks by LDS transpose reads (see hist_fused_bf16.hip)
-                    const int G = lane >> 4, i16 = lane & 15;
-#pragma unroll
-                    for (int gg = 0; gg < 2; ++gg)
-#pragma unroll
-                        for (int db = 0; db < 2; ++db) {
-                            s16x4 hv[2];
-#pragma unroll
-                            for (int hh = 0; hh < 2; ++hh) {
-                                const int r = 16 * gg + 8 * hh + 4 * (G >> 1) + (i16 >> 2);
-                                const int cb = 64 * db + 32 * (G & 1) + 8 * (i16 & 3);
-                                hv[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                                    (__attribute__((address_space(3))) s16x4 *)(tr + r * kPitch + cb));
-                            }
-                            const s16x8 both = __builtin_shufflevector(hv[0], hv[1], 0, 1, 2, 3, 4, 5, 6, 7);
-                            *(uint4 *)(blk + 4096 + ((gg * 2 + db) * 64 + lane) * 16) = __builtin_bit_cast(uint4, both);
-                        }
-                }
-            }
-            continue;
-        }
-#pragma unroll
-        for (int it = 0; it < kIters; ++it) {
-            const int id = it * 64 + lane, r = id / kChunksPerRow, cc = id % kChunksPerRow;
-            const int row = row_base + r;
-            uint4 val = *(const uint4 *)(tr + r * kPitch + cc * 16);
-            if (F32) {
-                const int col = col_base + cc * 4;
-                const float4 rd = rsd[i & 1][it];
-                float4 o = *(const float4 *)&val;
-                o.x += rd.x; o.y += rd.y; o.z += rd.z; o.w += rd.w;
-                if (row < M) {
-                    *(float4 *)((float *)C + (int64_t)row * ldc + col) = o;
-                    if (nout.ss) {
-                        bf16x4 ob;
-                        ob[0] = (__bf16)o.x; ob[1] = (__bf16)o.y; ob[2] = (__bf16)o.z; ob[3] = (__bf16)o.w;
-                        *(bf16x4 *)((__bf16 *)nout.xb + (int64_t)row * nout.ldb + col) = ob;
-                    }
-                }
-                if (nout.ss) {  // sums of squares of 64-column slices of the row: 16 lanes each
-                    static_assert(!F32 || kChunksPerRow % 16 == 0, "a 64-column slice = 16 lanes of one row");
-                    const float sq = row_sum16(o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w);
-                    if ((cc & 15) == 0 && row < M)
-                        nout.ss[(int64_t)row * (N / 64) + (col_base + cc * 4) / 64] = sq;
-                }
-            } else if (EPI == EPI_GELU_BF16 && (tiled & kTiledC)) {
-                // piece `it` = (16-row group it / 2, k-tile it % 2) of the block; a lane takes the chunk
-                // that the consuming projection's copy puts at its place in LDS
-                static_assert(EPI != EPI_GELU_BF16 || (CW == 64 && kIters == 4), "block = 2 x 2 pieces");
-                const int rr = 16 * (it >> 1) + (lane >> 2), c = (lane & 3) ^ ((lane >> 4) & 3);
-                val = *(const uint4 *)(tr + rr * kPitch + ((it & 1) * 4 + c) * 16);
-                if (row_base + rr < M)
-                    *(uint4 *)((uint8_t *)C + ((int64_t)((row_base >> 4) + (it >> 1)) * (N / 32) +
-                                               (col_base >> 5) + (it & 1)) * 1024 + lane * 16) = val;
-            } else if (row < M) {
-                *(uint4 *)((__bf16 *)C + (int64_t)row * ldc + col_base + cc * 8) = val;
-            }
-        }
-    }
+    wave_epilogue<EPI, WM, WN>(acc, rs, user, lds + wave * 32 * epilogue_pitch<EPI, WN>(), m0 + 32 * WM * wm, n0 + WN * 32 * wn,
+                               lane, M, N, C, ldc, resid, ldr, nout, tiled, qc);
 }
 
 template <int EPI, int WM, int WN, int kStages>
-hipError_t launch(const __bf16 *a, int64_t lda, const __bf16 *w, int M, int N, int K, void *C,
-                  int64_t ldc, const float *resid, int64_t ldr, const RowNormIn &nin, const RowNormOut &nout,
-                  int tiled, const QkvToCache &qc, hipStream_t s)
+hipError_t launch(const GemmArgs &g, hipStream_t s)
 {
     constexpr int BM = 64 * WM, BN = 64 * WN;
     constexpr size_t lds_bytes = (size_t)kStages * (BM + BN) * BK * 2;
@@ -459,21 +292,24 @@ hipError_t launch(const __bf16 *a, int64_t lda, const __bf16 *w, int M, int N, i
         if (e != hipSuccess) return e;
         raised[dev].store(true, std::memory_order_release);
     }
-    const dim3 grid((N / BN) * ((M + BM - 1) / BM)), block(256);
-    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, WM, WN, kStages>), grid, block, lds_bytes, s, a, lda, w, M, N, K,
-                       C, ldc, resid, ldr, nin, nout, tiled, qc);
+    const dim3 grid((g.N / BN) * ((g.M + BM - 1) / BM)), block(256);
+    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, WM, WN, kStages>), grid, block, lds_bytes, s, (const __bf16 *)g.A, g.lda,
+                       (const __bf16 *)g.W, g.M, g.N, g.K, g.C, g.ldc, g.resid, g.ldr, g.nin, g.nout, g.tiled, g.qc);
     return hipGetLastError();
 }
 
 template <int EPI>
-hipError_t dispatch(const __bf16 *a, int64_t lda, const __bf16 *w, int M, int N, int K, void *C,
-                    int64_t ldc, const float *resid, int64_t ldr, const RowNormIn &nin,
-                    const RowNormOut &nout, int tiled, const QkvToCache &qc, hipStream_t s)
+hipError_t dispatch(const GemmArgs &g, hipStream_t s)
 {
+    // few rows: a wave per 32 x 32 block without LDS, as long as that makes at most 2.5 workgroups per CU --
+    // beyond, the macro tiles' reuse of their operands wins.  us per launch, this / the 128 x 128 tile: K = 512,
+    // N = 1536, 512 rows (384 workgroups) 7.1 / 7.5, 1024 rows (768) 9.9 / 8.2; N = 512, 2048 rows (512) 8.3 / 10.4,
+    // 4096 rows (1024) 13.9 / 11.7; K = 2048, N = 512, 200 rows 8.1 / 19.4, 2048 rows (512) 16.1 / 20.9
+    if ((int64_t)(g.N / 64) * ((g.M + 31) / 32) <= 640 && g.K % 128 == 0) return gemm_small_bf16(EPI, g, s);
     // macro tile 256 x 128 when that still gives every CU two workgroups, else 128 x 128
-    const int64_t big_tiles = (int64_t)(N / 128) * ((M + 255) / 256);
-    if (big_tiles >= 512) return launch<EPI, 4, 2, 3>(a, lda, w, M, N, K, C, ldc, resid, ldr, nin, nout, tiled, qc, s);
-    return launch<EPI, 2, 2, 4>(a, lda, w, M, N, K, C, ldc, resid, ldr, nin, nout, tiled, qc, s);
+    const int64_t big_tiles = (int64_t)(g.N / 128) * ((g.M + 255) / 256);
+    if (big_tiles >= 512) return launch<EPI, 4, 2, 3>(g, s);
+    return launch<EPI, 2, 2, 4>(g, s);
 }
 
 }  // namespace
@@ -514,12 +350,12 @@ hipError_t gemm_bf16(int epi, const void *A, int64_t lda, const void *w_packed, 
     }
     if (N % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
     if ((tiled & ~(kTiledA | kTiledC)) || ((tiled & kTiledC) && epi != EPI_GELU_BF16)) return hipErrorInvalidValue;
-    const __bf16 *a = (const __bf16 *)A, *w = (const __bf16 *)w_packed;
+    const GemmArgs g{A, lda, w_packed, M, N, K, C, ldc, resid, ldr, nin, nout, tiled, qc};
     switch (epi) {
-    case EPI_STORE_BF16: return dispatch<EPI_STORE_BF16>(a, lda, w, M, N, K, C, ldc, resid, ldr, nin, nout, tiled, qc, s);
-    case EPI_GELU_BF16: return dispatch<EPI_GELU_BF16>(a, lda, w, M, N, K, C, ldc, resid, ldr, nin, nout, tiled, qc, s);
-    case EPI_RESID_F32: return dispatch<EPI_RESID_F32>(a, lda, w, M, N, K, C, ldc, resid, ldr, nin, nout, tiled, qc, s);
-    case EPI_RELU_BF16: return dispatch<EPI_RELU_BF16>(a, lda, w, M, N, K, C, ldc, resid, ldr, nin, nout, tiled, qc, s);
+    case EPI_STORE_BF16: return dispatch<EPI_STORE_BF16>(g, s);
+    case EPI_GELU_BF16: return dispatch<EPI_GELU_BF16>(g, s);
+    case EPI_RESID_F32: return dispatch<EPI_RESID_F32>(g, s);
+    case EPI_RELU_BF16: return dispatch<EPI_RELU_BF16>(g, s);
     default: return hipErrorInvalidValue;
     }
 }

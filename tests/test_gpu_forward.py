@@ -118,3 +118,15 @@ def test_randomized_stack_shapes_and_routes():
             run(spec, users=users, flags=flags)
         else:
             run_forward(spec, users=users, want_hist=bool(rng.integers(0, 2)), flags=flags)
+
+
+@pytest.mark.parametrize("m", [1, 33, 95])
+def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(m):
+    # the packed forward runs 10 x 384 history rows and the candidates through one launch (macro tiles), the
+    # scoring call the candidates alone (a wave per 32 x 32 block): a row's bits do not depend on which; candidate
+    # counts at the edges of the 32-row blocks, one of them the smallest launch there is
+    spec = W.StackSpec(f"fwd-tiles-{m}", B=10, L=384, sub_len=128, M=0, n_layers=2, d_model=256, H=4, dh=64, d_ffn=512,
+                       n_scen=8, n_beh=4, seed=95 + m, hist_lens=(384,) * 10, cand_counts=(m,) + (0,) * 9)
+    w, g, yc = run_forward(spec, users=(0,), want_hist=True)
+    g.encode()
+    assert np.array_equal(yc[:g.m_total], g.score())
