@@ -51,22 +51,6 @@ constexpr int kTileKeys = 64;                // keys per LDS tile = 2 cache bloc
 constexpr int kTileBytes = 2 * kBlockBytes;  // 16 KiB
 constexpr int kStages = 3;                   // LDS ring of K/V tiles
 
-struct KParams {
-    const uint8_t *layer_base;
-    const int32_t *hist_len, *tok_off, *order, *cand_off;
-    const __bf16 *q, *k_self, *v_self;
-    const int32_t *scen, *beh;
-    const float *tau;
-    __bf16 *o;
-    int64_t ld_q, ld_kv, ld_o;
-    int B, H, n_scen, n_beh, sub_len, n_qtiles;
-    int uni_len, uni_pad;  // >= 0: every user has this valid / padded history length
-    int uni_cand;          // >= 0: every user has this many candidates (SUMI)
-    float scale_log2e, inv_qk_scale;
-    BiasArgs bias;  // relative attention bias (the BIAS variants of the kernel)
-    int bias_H;
-};
-
 // wait until at most `tiles_in_flight` later tiles (NPRE loads each) are still outstanding
 template <int NPRE>
 __device__ __forceinline__ void wait_tiles(int tiles_in_flight)
@@ -341,7 +325,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     };
     // FAST, SUMI: the candidate's own key/value.  Their rows travel through the same landing
     // buffer while the history loop runs (keys first, values once the keys are consumed), so no
-    // wave ever waits for them: weight w = exp2(<q', k_own>), then O += w * v_own.
+    // wave ever waits for them: weight w = exp2(<q', k_own>), then O += w * v_own
+    // (behind the seventh block of 32 keys; behind the last one against at most 256 keys) and, at the end, l += w.
     float w_own[QB];
     bool fold = false;  // the wave runs the pass with the scale folded into a bf16 query (decided below)
     auto own_k = [&]() __attribute__((always_inline)) {
@@ -361,7 +346,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                 for (int e = 0; e < 8; ++e) dot += (float)qq[e] * (float)kk[e];
             }
             w_own[qb] = __builtin_amdgcn_exp2f((dot + xhalf(dot) + (BIAS ? fb[qb] * bias_self[qb] : 0.f)) * (fold ? 1.f : st.c[qb]));
-            st.l[qb] += hf == 0 ? w_own[qb] : 0.f;
         }
     };
     auto own_v = [&]() __attribute__((always_inline)) {
@@ -607,6 +591,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             wait_tiles<NPRE>(0);
             own_v();
         }
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) st.l[qb] += hf == 0 ? w_own[qb] : 0.f;
     }
 
     // ---- SAFE pass (rare): whole workgroup redoes its rows with a running maximum -----------
@@ -690,40 +676,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     }
 }
 
-KParams make_params(const AttnArgs &a, int n_qtiles)
-{
-    KParams p;
-    p.layer_base = a.cache.layer_base;
-    p.hist_len = a.cache.hist_len;
-    p.tok_off = a.cache.tok_off;
-    p.order = a.cache.order;
-    p.cand_off = a.cand_off;
-    p.q = (const __bf16 *)a.q;
-    p.k_self = (const __bf16 *)a.k_self;
-    p.v_self = (const __bf16 *)a.v_self;
-    p.scen = a.scen;
-    p.beh = a.beh;
-    p.tau = a.tau;
-    p.o = (__bf16 *)a.o;
-    p.ld_q = a.ld_q;
-    p.ld_kv = a.ld_kv;
-    p.ld_o = a.ld_o;
-    p.B = a.cache.B;
-    p.H = a.H;
-    p.n_scen = a.n_scen;
-    p.n_beh = a.n_beh;
-    p.sub_len = a.sub_len;
-    p.n_qtiles = n_qtiles;
-    p.scale_log2e = a.qk_scale * 1.4426950408889634f;
-    p.inv_qk_scale = 1.f / a.qk_scale;
-    p.bias = a.bias;
-    p.bias_H = a.H;
-    p.uni_len = a.uni_len;
-    p.uni_pad = a.uni_pad;
-    p.uni_cand = a.uni_cand;
-    return p;
-}
-
 template <int NW, int QB, bool SUMI, bool CAUSAL = false, bool BIAS = false>
 hipError_t launch(const AttnArgs &a, hipStream_t s)
 {
@@ -740,11 +692,16 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
 // Query-tile shape: 4 waves x QB blocks of 32 queries per workgroup.  QB = 2 (256 queries) re-reads
 // a head's K/V from L2 half as often and reuses every LDS fragment for two MFMAs; QB = 1 (128
 // queries) keeps two waves per SIMD busy when a head has few queries.
+// Launches of at most one wave of 32 queries per SIMD (1024) go to attn_wave_bf16.hip: us per launch there / here
+// for 8 heads and a history of 1000: 200 candidates of one user (56 waves) 11.4 / 19.5, of 16 users (896) 17.6 / 23.4, 256 of
+// 32 users (2048) 31 / 27; history pass over one user's 4096 behaviours (1024) 54 / 73, over 8 x 1024 (2048) 24.5 / 22.5.
+bool few_queries(const AttnArgs &a) { return (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 31) / 32) <= 1024; }
 }  // namespace
 
 hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 {
     if (a.bias.pos_table) return launch<4, 1, true, false, true>(a, s);
+    if (few_queries(a)) return launch_attn_wave_bf16(a, true, s);
     return a.max_rows_per_user > 128 ? launch<4, 2, true>(a, s) : launch<4, 1, true>(a, s);
 }
 
@@ -752,6 +709,7 @@ hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s)
 {
     // a query tile must lie inside one subsequence (sub_len is 0 or a multiple of 128)
     if (a.bias.pos_table) return a.causal ? launch<4, 1, false, true, true>(a, s) : launch<4, 1, false, false, true>(a, s);
+    if (few_queries(a)) return launch_attn_wave_bf16(a, false, s);
     const bool wide = a.sub_len % 256 == 0;
     if (a.causal) return wide ? launch<4, 2, false, true>(a, s) : launch<4, 1, false, true>(a, s);
     return wide ? launch<4, 2, false>(a, s) : launch<4, 1, false>(a, s);

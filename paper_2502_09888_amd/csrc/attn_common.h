@@ -37,6 +37,57 @@ constexpr int kFoldMinKeys = 256;
 constexpr float kSafeNoRef = -1.0e30f;       // SAFE: "no reference yet", below any finite logit
 constexpr int kBiasLdsFloats = 4096;         // LDS floats for one head's rows of the bias tables
 
+// What the attention kernels are given.
+struct KParams {
+    const uint8_t *layer_base;
+    const int32_t *hist_len, *tok_off, *order, *cand_off;
+    const __bf16 *q, *k_self, *v_self;
+    const int32_t *scen, *beh;
+    const float *tau;
+    __bf16 *o;
+    int64_t ld_q, ld_kv, ld_o;
+    int B, H, n_scen, n_beh, sub_len, n_qtiles;
+    int uni_len, uni_pad;  // >= 0: every user has this valid / padded history length
+    int uni_cand;          // >= 0: every user has this many candidates (SUMI)
+    float scale_log2e, inv_qk_scale;
+    BiasArgs bias;  // relative attention bias (the BIAS variants of the kernel)
+    int bias_H;
+};
+
+static inline KParams make_params(const AttnArgs &a, int n_qtiles)
+{
+    KParams p;
+    p.layer_base = a.cache.layer_base;
+    p.hist_len = a.cache.hist_len;
+    p.tok_off = a.cache.tok_off;
+    p.order = a.cache.order;
+    p.cand_off = a.cand_off;
+    p.q = (const __bf16 *)a.q;
+    p.k_self = (const __bf16 *)a.k_self;
+    p.v_self = (const __bf16 *)a.v_self;
+    p.scen = a.scen;
+    p.beh = a.beh;
+    p.tau = a.tau;
+    p.o = (__bf16 *)a.o;
+    p.ld_q = a.ld_q;
+    p.ld_kv = a.ld_kv;
+    p.ld_o = a.ld_o;
+    p.B = a.cache.B;
+    p.H = a.H;
+    p.n_scen = a.n_scen;
+    p.n_beh = a.n_beh;
+    p.sub_len = a.sub_len;
+    p.n_qtiles = n_qtiles;
+    p.scale_log2e = a.qk_scale * 1.4426950408889634f;
+    p.inv_qk_scale = 1.f / a.qk_scale;
+    p.bias = a.bias;
+    p.bias_H = a.H;
+    p.uni_len = a.uni_len;
+    p.uni_pad = a.uni_pad;
+    p.uni_cand = a.uni_cand;
+    return p;
+}
+
 // Per-wave softmax state for QB blocks of 32 queries.
 template <int QB>
 struct QState {

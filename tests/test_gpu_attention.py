@@ -169,6 +169,33 @@ def test_bf16_candidate_isolation_and_chunking_are_bitwise():
         assert np.array_equal(part, full[g.last_idx]), (lo, hi)
 
 
+@pytest.mark.parametrize("L,sub", [(1, 0), (32, 0), (33, 0), (64, 128), (65, 0), (97, 128), (128, 0), (129, 128), (161, 0), (289, 256),
+                                   (700, 512)])
+def test_few_and_many_queries_give_the_same_bits(L, sub):
+    # few queries: a wave per 32 of them, groups of four 32-key blocks; many: 256-query tiles on a ring of 64-key
+    # tiles.  Histories at the edges of blocks, groups and tiles; candidate counts at the edges of the wave's 32
+    spec = W.shrink(W.CONFIG2, name=f"bf16-few-{L}", B=1, L=L, sub_len=sub, M=8400, H=4, pad_to=64, nan_padding=True, seed=700 + L)
+    w = W.make_attention(spec)
+    g = GpuAttention(w)
+    oh, ok = g.history(), valid_rows(w)
+    assert max_abs(oh[ok], oracle_history(w)[ok]) < 2e-2 and np.all(oh[~ok] == 0)
+    full = g.sumi()
+    for n in (1, 31, 33, 200):
+        part = g.sumi(sel=(7, 7 + n))
+        assert np.array_equal(part, full[7:7 + n])
+        if n == 200:
+            assert max_abs(part, oracle_sumi(w)[7:7 + n]) < 2e-2
+
+
+@pytest.mark.parametrize("L", [31, 64, 130, 385])
+def test_few_queries_causal_history(L):
+    spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=2, L=L, sub_len=0, M=4, H=2, pad_to=64, L_min=max(1, L - 20),
+                    nan_padding=True, seed=730 + L)
+    w = W.make_attention(spec)
+    oh, ok = GpuAttention(w, causal=True).history(), valid_rows(w)
+    assert max_abs(oh[ok], oracle_history(w, causal=True)[ok]) < 2e-2 and np.all(oh[~ok] == 0)
+
+
 def test_config2_full():
     check_all(W.make_attention(W.CONFIG2))
 
