@@ -25,8 +25,8 @@
 //     t = <q,k> * c in fp32 (one more multiplication per logit; the denominator only has to stay
 //     inside the exponent range, [kDenomLoExact, kDenomHiExact]; the denominator is summed from the
 //     probabilities as rounded to bf16, so that a one-hot row does not carry the rounding of its
-//     dominant term into the output).  Only the candidate pass folds; history rows and the bias
-//     variants always take the exact form.  The loop is software pipelined
+//     dominant term into the output).  Only the candidate pass folds; history rows always take the
+//     exact form.  The loop is software pipelined
 //     over 32-key blocks: the S^T MFMAs of block i+1 are issued before the exponentials of block
 //     i, so matrix and vector pipes overlap inside one wave.
 //   - SAFE pass.  If any row's denominator leaves its window (or is not finite) the workgroup
@@ -69,12 +69,7 @@ __device__ __forceinline__ void wait_tiles(int tiles_in_flight)
     }
 }
 
-// BIAS: the relative attention bias of Eq. (3) joins the logits before the temperature divide.  A
-// lane works its 16 bias values of a block out of the two bucket tables (clipped relative position,
-// log2 bucket of the time distance; one table row per (scenario, behaviour, head) of the query) and
-// hands them to the S^T MFMAs as the initial value of the accumulator, scaled like the logits
-// (FAST: by log2(e)/tau, SAFE: by 1/qk_scale, the fp32 scale of the pass doing the rest).
-template <int NW, int QB, bool SUMI, bool CAUSAL = false, bool BIAS = false>
+template <int NW, int QB, bool SUMI, bool CAUSAL = false>
 __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
 {
     static_assert(!(SUMI && CAUSAL), "the causal flag concerns the history pass");
@@ -84,10 +79,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     constexpr int WQ = 32 * QB;  // query rows per wave
     constexpr int TQ = NW * WQ;  // query rows per workgroup
     constexpr int NPRE = kTileBytes / 16 / NT;
-    // BIAS: this head's rows of the two bias tables live behind the landing buffer when they fit
-    // (lookups per logit: LDS gathers instead of gathers from global memory)
-    constexpr int kBiasLds = BIAS ? kBiasLdsFloats : 0;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kStages * kTileBytes + TQ * 128 + kBiasLds * 4];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kStages * kTileBytes + TQ * 128];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar
     int l32 = lane & 31;
@@ -175,50 +167,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     };
     auto issue_tile = [&](int t) __attribute__((always_inline)) { issue_tile_at(t, (t % kStages) * kTileBytes); };
     QState<QB> st;
-    // per query row of the lane: position, time stamp, rows of the two bias tables, logit scale
-    int b_pos[QB];
-    uint32_t b_ts[QB];               // time stamp, sign bit flipped (bias_time_key)
-    const float *b_prow[QB], *b_trow[QB];  // the row's slices of the two tables (LDS copy or global)
-    float fb[QB], bias_self[QB];
-    // LDS copy of the head's table rows: [n_tau][n_pos] then [n_tau][n_time]
-    const float *bias_lds = (const float *)(lds + kStages * kTileBytes + TQ * 128);
-    const int n_groups = p.n_scen * p.n_beh;
-    const bool bias_in_lds = BIAS && n_groups * (p.bias.n_pos + p.bias.n_time) <= kBiasLds;
-    if constexpr (BIAS) {
-        if (bias_in_lds) {  // visible to the workgroup after the barrier that follows the first tile's wait
-            float *dst = (float *)(lds + kStages * kTileBytes + TQ * 128);
-            const int np_ = p.bias.n_pos, nt_ = p.bias.n_time;
-            for (int i = tid; i < n_groups * np_; i += NT)
-                dst[i] = p.bias.pos_table[((i / np_) * p.bias_H + h) * np_ + i % np_];
-            for (int i = tid; i < n_groups * nt_; i += NT)
-                dst[n_groups * np_ + i] = p.bias.time_table[((i / nt_) * p.bias_H + h) * nt_ + i % nt_];
-        }
-    }
-    auto qk = [&](const KFrags &kf, f32x16 (&S)[QB], int blk_lo) __attribute__((always_inline)) {
-        if constexpr (BIAS) {
-            const int half = (p.bias.n_pos - 1) >> 1;
-            const int64_t kr = (int64_t)t0 + blk_lo + 4 * hf;  // packed history row of the lane's first key
-#pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-                const int4 kp = *(const int4 *)(p.bias.key_pos + kr + 8 * g4);
-                const int4 kt = *(const int4 *)(p.bias.key_ts + kr + 8 * g4);
-                const int kpe[4] = {kp.x, kp.y, kp.z, kp.w};
-                const uint32_t kte[4] = {bias_time_key(kt.x), bias_time_key(kt.y), bias_time_key(kt.z), bias_time_key(kt.w)};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int qb = 0; qb < QB; ++qb) {
-                        const int ip = bias_bucket_pos(b_pos[qb], kpe[e], half);
-                        const int it = bias_bucket_time_u(b_ts[qb], kte[e], p.bias.n_time);
-                        S[qb][4 * g4 + e] = fb[qb] * (b_prow[qb][ip] + b_trow[qb][it]);
-                    }
-            }
-            qk_block_acc(st, kf, S);
-        } else {
-            qk_block(st, kf, S);
-        }
-    };
-
     // FAST start: the raw query rows stay in st.qf and the row scale in st.c until the first block's
     // logits have shown which form of the pass the wave takes; empty state (the candidate's own
     // key/value joins later, from the landing buffer).
@@ -262,8 +210,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             // maximum the reference (0 would leave rows whose logits are all very negative with an
             // empty sum).  Every row sees a key of its first block, so the reference is finite
             // before the first exponential.
-            if constexpr (BIAS) fb[qb] = p.inv_qk_scale;  // SAFE: logits in raw units, scaled by c in fp32
-            st.m_ref[qb] = SUMI ? dot + xhalf(dot) + (BIAS ? fb[qb] * bias_self[qb] : 0.f) : kSafeNoRef;
+            st.m_ref[qb] = SUMI ? dot + xhalf(dot) : kSafeNoRef;
             st.l[qb] = (SUMI && hfs == 0) ? 1.f : 0.f;
             if (SUMI) {
                 const __bf16 *vp = p.v_self + row * p.ld_kv + h * kDHead + 4 * hfs;
@@ -345,7 +292,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) dot += (float)qq[e] * (float)kk[e];
             }
-            w_own[qb] = __builtin_amdgcn_exp2f((dot + xhalf(dot) + (BIAS ? fb[qb] * bias_self[qb] : 0.f)) * (fold ? 1.f : st.c[qb]));
+            w_own[qb] = __builtin_amdgcn_exp2f((dot + xhalf(dot)) * (fold ? 1.f : st.c[qb]));
         }
     };
     auto own_v = [&]() __attribute__((always_inline)) {
@@ -386,19 +333,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         const int sc = min(max(tau_idx[qb], 0), p.n_scen - 1);
         const int bhv = min(max(beh_id[qb], 0), p.n_beh - 1);
         tau_idx[qb] = sc * p.n_beh + bhv;
-        if constexpr (BIAS) {
-            const int64_t row = row0 + min(wave * WQ + qb * 32 + l32, nq - 1);
-            b_pos[qb] = p.bias.q_pos[row];
-            b_ts[qb] = bias_time_key(p.bias.q_ts[row]);
-            const int grow = (tau_idx[qb] * p.bias_H + h);
-            // a candidate's own key: zero distance in position and time
-            bias_self[qb] = p.bias.pos_table[grow * p.bias.n_pos + ((p.bias.n_pos - 1) >> 1)] +
-                            p.bias.time_table[grow * p.bias.n_time];
-            // rows of the lane's (scenario, behaviour) pair: in the LDS copy, or in the tables themselves
-            b_prow[qb] = bias_in_lds ? bias_lds + tau_idx[qb] * p.bias.n_pos : p.bias.pos_table + grow * p.bias.n_pos;
-            b_trow[qb] = bias_in_lds ? bias_lds + n_groups * p.bias.n_pos + tau_idx[qb] * p.bias.n_time
-                                     : p.bias.time_table + grow * p.bias.n_time;
-        }
     }
     // tile 0 and the query rows of this wave have landed (only tile 1 may still be in flight);
     // tau_lds is visible to the workgroup after the bare barrier (a fence would also wait for
@@ -414,10 +348,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
             c[qb] = p.scale_log2e / (tau_in_lds ? tau_lds[tau_idx[qb]] : p.tau[tau_idx[qb]]);
-        if constexpr (BIAS) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) fb[qb] = p.inv_qk_scale;  // bias in the units of the raw <q, k>
-        }
         load_q_lds();
         init_fast(c);
     }
@@ -430,7 +360,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         __builtin_amdgcn_s_barrier();
         {
             const KFrags k0 = load_k(lds, lane);
-            qk(k0, S0, k_lo);
+            qk_block(st, k0, S0);
             // Which form of the FAST pass?  Folding the row scale c = qk_scale*log2(e)/tau into the bf16
             // query saves a multiplication per logit but rounds q*c to 8 bits, an error of 2^-9 of every
             // logit: harmless while the exponents stay small.  The first block's exponents s*c tell:
@@ -451,9 +381,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             // Only the candidate pass folds, and only against a history of some length: its rows then have
             // many comparable keys to average the per-logit error over.  History rows
             // see one subsequence (a few keys only under the causal flag) and can be sharply peaked, where
-            // the folded form's error shows in the output; the bias variants have larger logits and their
-            // cost lies elsewhere.  Those always take the exact form.
-            fold = SUMI && !BIAS && __builtin_amdgcn_ballot_w64(big) == 0;
+            // the folded form's error shows in the output: they always take the exact form.
+            fold = SUMI && __builtin_amdgcn_ballot_w64(big) == 0;
             if (fold) {
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
@@ -465,7 +394,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                     }
 #pragma unroll
                     for (int r = 0; r < 16; ++r) S0[qb][r] *= st.c[qb];  // the first block's logits, formed already
-                    if constexpr (BIAS) fb[qb] = st.c[qb] * p.inv_qk_scale;  // log2(e) / tau
                 }
             }
             causal(S0, k_lo);
@@ -497,7 +425,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                 const KFrags k1 = load_k(cur + kBlockBytes, lane);
                 const VFrags v0 = load_v(cur, lane);
                 __builtin_amdgcn_sched_barrier(0);
-                qk(k1, S1, k_lo + t * kTileKeys + kBlockKeys);
+                qk_block(st, k1, S1);
                 causal(S1, k_lo + t * kTileKeys + kBlockKeys);
                 soft(S0);
                 pv_block(st, v0, P);
@@ -517,7 +445,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                 const KFrags k0 = load_k(nxt, lane);
                 const VFrags v1 = load_v(cur + kBlockBytes, lane);
                 __builtin_amdgcn_sched_barrier(0);
-                qk(k0, S0, k_lo + (t + 1) * kTileKeys);
+                qk_block(st, k0, S0);
                 causal(S0, k_lo + (t + 1) * kTileKeys);
                 soft(S1);
                 pv_block(st, v1, P);
@@ -550,7 +478,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             const bool two = tile_lo + kBlockKeys < k_hi;
             if (two) {
                 const KFrags k1 = load_k(cur + kBlockBytes, lane);
-                qk(k1, S1, tile_lo + kBlockKeys);
+                qk_block(st, k1, S1);
                 causal(S1, tile_lo + kBlockKeys);
             }
             if (tile_lo + kBlockKeys > k_hi) mask_block(S0, hf, tile_lo, k_hi);
@@ -629,7 +557,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                     f32x16 S[QB];
                     bf16x8 P[QB][2];
                     const KFrags kf = load_k(cur + blk * kBlockBytes, lane);
-                    qk(kf, S, blk_lo);
+                    qk_block(st, kf, S);
                     if (blk_lo + kBlockKeys > k_hi) mask_block(S, hf, blk_lo, k_hi);
                     causal(S, blk_lo);
                     softmax_safe(st, S, P);
@@ -676,7 +604,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     }
 }
 
-template <int NW, int QB, bool SUMI, bool CAUSAL = false, bool BIAS = false>
+template <int NW, int QB, bool SUMI, bool CAUSAL = false>
 hipError_t launch(const AttnArgs &a, hipStream_t s)
 {
     constexpr int TQ = NW * 32 * QB;
@@ -685,7 +613,7 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
     const int64_t grid = (int64_t)8 * n_qtiles * groups;
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
     const KParams p = make_params(a, n_qtiles);
-    hipLaunchKernelGGL((attn_bf16_kernel<NW, QB, SUMI, CAUSAL, BIAS>), dim3((unsigned)grid), dim3(NW * 64), 0, s, p);
+    hipLaunchKernelGGL((attn_bf16_kernel<NW, QB, SUMI, CAUSAL>), dim3((unsigned)grid), dim3(NW * 64), 0, s, p);
     return hipGetLastError();
 }
 
@@ -700,7 +628,7 @@ bool few_queries(const AttnArgs &a) { return (int64_t)a.cache.B * a.H * ((a.max_
 
 hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 {
-    if (a.bias.pos_table) return launch<4, 1, true, false, true>(a, s);
+    if (a.bias.pos_table) return launch_attn_bias_bf16(a, true, s);
     if (few_queries(a)) return launch_attn_wave_bf16(a, true, s);
     return a.max_rows_per_user > 128 ? launch<4, 2, true>(a, s) : launch<4, 1, true>(a, s);
 }
@@ -708,7 +636,7 @@ hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s)
 {
     // a query tile must lie inside one subsequence (sub_len is 0 or a multiple of 128)
-    if (a.bias.pos_table) return a.causal ? launch<4, 1, false, true, true>(a, s) : launch<4, 1, false, false, true>(a, s);
+    if (a.bias.pos_table) return launch_attn_bias_bf16(a, false, s);
     if (few_queries(a)) return launch_attn_wave_bf16(a, false, s);
     const bool wide = a.sub_len % 256 == 0;
     if (a.causal) return wide ? launch<4, 2, false, true>(a, s) : launch<4, 1, false, true>(a, s);

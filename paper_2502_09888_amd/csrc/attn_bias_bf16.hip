@@ -1,0 +1,535 @@
+// bf16 MFMA attention with the relative attention bias of Eq. (3) of Climber (arXiv 2502.09888) for gfx950:
+// R = Q K^T + f_b, divided by the temperature afterwards; candidate pass (SUMI mask of Sec. 3.2) and history
+// pass (subsequences of Sec. 3.1.2, also causal).  Formulation, cache layout, LDS ring and softmax as in
+// attn_bf16.hip; always the exact-scale form of the softmax (the logits are larger by the bias).
+//
+// The bias of a (query, key) pair is two table entries chosen by a clipped position distance and a log2 bucket of
+// the time distance: about a dozen instructions and two LDS gathers per logit, four times the softmax itself.  But
+// buckets are coarse: against a block of 32 keys that lies a clip distance and an octave of time away, all of a
+// wave's 32 queries x 32 keys fall into one position and one time bucket.  So every wave classifies the blocks
+// first (extremes of the keys' positions and times against the extremes of its queries'), and a
+// uniform block costs one pair of gathers per query, its bias joining as the addend of the fused
+// multiply-add that scales the logit.  The other blocks -- those around the query's own place and the ones an
+// octave boundary falls into -- look up every logit and apply it with the same operations, so that a row's bits do
+// not depend on which way its wave took.
+#include "attn_common.h"
+#include "launch.h"
+
+#include <type_traits>
+
+namespace climber {
+namespace {
+
+using namespace attn;
+
+// a ring stage: 64 keys and values as in the cache, their positions, their time stamps
+constexpr int kTileKeys = 64, kTileBytes = 2 * kBlockBytes, kStageBytes = kTileBytes + kTileKeys * 8, kStages = 3, NW = 4;
+
+// minimum over the 32 lanes of a half-wave, as a scalar (both halves hold the same 32 values)
+template <class F>
+__device__ __forceinline__ int half_wave_reduce(int x, F &&f)
+{
+    auto dpp = [](int v, auto ctrl) { return __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, 0xf, 0xf, false); };
+    x = f(x, dpp(x, std::integral_constant<int, 0xB1>{}));   // quad_perm [1,0,3,2]
+    x = f(x, dpp(x, std::integral_constant<int, 0x4E>{}));   // quad_perm [2,3,0,1]
+    x = f(x, dpp(x, std::integral_constant<int, 0x141>{}));  // row_half_mirror
+    x = f(x, dpp(x, std::integral_constant<int, 0x140>{}));  // row_mirror
+    return f(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16));
+}
+
+// LDS: ring, tables of the head, classes [wave][query block][64], one flag per wave
+template <int QB>
+constexpr int kClassBytes = NW * QB * 64 * 4;
+
+// IN_LDS: the head's rows of the tables are copied into LDS (else looked up in global memory)
+template <int QB, bool SUMI, bool CAUSAL, bool IN_LDS>
+__global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
+{
+    static_assert(!(SUMI && CAUSAL), "the causal flag concerns the history pass");
+    constexpr int NT = NW * 64, WQ = 32 * QB, TQ = NW * WQ, NPRE = kTileBytes / 16 / NT;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    int *flag_lds = (int *)(lds + kStages * kStageBytes), *class_lds = flag_lds + NW;
+    float *bias_lds = (float *)(class_lds + kClassBytes<QB> / 4);  // the head's table rows: [n_tau][n_pos], [n_tau][n_time]
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hf = lane >> 5;
+
+    // workgroup -> (user, head, query tile), the tiles of a head on one XCD; geometry as in attn_bf16.hip
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int qt = j % p.n_qtiles, bh = (j / p.n_qtiles) * 8 + xcd;
+    if (bh >= p.B * p.H) return;
+    const int h = bh % p.H;
+    int b = bh / p.H, Lb, t0, Lpad;
+    if (p.uni_len >= 0) {
+        Lb = p.uni_len;
+        Lpad = p.uni_pad;
+        t0 = b * Lpad;
+    } else {
+        b = p.order[b];
+        Lb = p.hist_len[b];
+        t0 = p.tok_off[b];
+        Lpad = p.tok_off[b + 1] - t0;
+    }
+    const int q0 = qt * TQ;
+    int64_t row0;
+    int nq, k_lo, k_hi;
+    if (SUMI) {
+        int c0, Mb;
+        if (p.uni_cand >= 0) {
+            Mb = p.uni_cand;
+            c0 = b * Mb;
+        } else {
+            c0 = p.cand_off[b];
+            Mb = p.cand_off[b + 1] - c0;
+        }
+        if (q0 >= Mb) return;
+        row0 = (int64_t)c0 + q0;
+        nq = min(TQ, Mb - q0);
+        k_lo = 0;
+        k_hi = Lb;
+    } else {
+        if (q0 >= Lpad) return;
+        row0 = (int64_t)t0 + q0;
+        nq = max(0, min(TQ, Lb - q0));
+        if (nq == 0) {  // a tile of padding rows only: defined output, zeros
+            for (int idx = tid; idx < TQ * (kDHead / 8); idx += NT) {
+                const int r = idx / (kDHead / 8), cc = idx % (kDHead / 8);
+                if (q0 + r < Lpad) *(uint4 *)(p.o + (row0 + r) * p.ld_o + h * kDHead + cc * 8) = uint4{0, 0, 0, 0};
+            }
+            return;
+        }
+        k_lo = p.sub_len > 0 ? (q0 / p.sub_len) * p.sub_len : 0;
+        k_hi = p.sub_len > 0 ? min(k_lo + p.sub_len, Lb) : Lb;
+        if (CAUSAL) k_hi = min(k_hi, q0 + TQ);
+    }
+    const int n_tiles = (k_hi - k_lo + kTileKeys - 1) / kTileKeys;
+    const uint8_t *kv = p.layer_base + ((size_t)t0 * p.H + (size_t)h * Lpad) * (kDHead * 4) +
+                        (size_t)(k_lo / kBlockKeys) * kBlockBytes;
+    auto issue_tile = [&](int t, int stage) __attribute__((always_inline)) {
+        glb_u8 *src = (glb_u8 *)(kv + (size_t)t * kTileBytes + (size_t)tid * 16);
+        lds_u8 *dst = (lds_u8 *)lds + stage + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < NPRE; ++i) __builtin_amdgcn_global_load_lds(src + i * NT * 16, dst + i * NT * 16, 16, 0, 0);
+        if (wave < 2)  // wave 0: positions, wave 1: time stamps of the tile's keys, 4 bytes per lane
+            __builtin_amdgcn_global_load_lds((glb_u8 *)((wave ? p.bias.key_ts : p.bias.key_pos) + t0 + k_lo + t * kTileKeys + lane),
+                                             (lds_u8 *)lds + stage + kTileBytes + wave * (kTileKeys * 4), 4, 0, 0);
+    };
+    auto wait_copies = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    if (n_tiles > 0) issue_tile(0, 0);
+
+    // the lane's queries: rows, scales, bias coordinates
+    QState<QB> st;
+    int b_pos[QB], tau_idx[QB];
+    uint32_t b_ts[QB];          // time stamp, sign bit flipped
+    // (recomputed where it is needed: held across the loop, the rows would cost registers the loop has not got)
+    auto row_of = [&](int qb) __attribute__((always_inline)) {
+        int l = l32;
+        asm volatile("" : "+v"(l));
+        return row0 + min(wave * WQ + qb * 32 + l, nq - 1);
+    };
+    const int n_groups = p.n_scen * p.n_beh, n_pos = p.bias.n_pos, n_time = p.bias.n_time, half = (n_pos - 1) >> 1;
+    // (requests of everything the start needs go out before the first of them is waited for)
+    int scen[QB], beh[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int64_t row = row_of(qb);
+        scen[qb] = p.scen[row];
+        beh[qb] = p.beh[row];
+        b_pos[qb] = p.bias.q_pos[row];
+        b_ts[qb] = bias_time_key(p.bias.q_ts[row]);
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const __bf16 *qp = p.q + row_of(qb) * p.ld_q + h * kDHead + 8 * hf;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) st.qf[qb][s] = *(const bf16x8 *)(qp + 16 * s);
+    }
+    if constexpr (IN_LDS) {  // eight table rows per wave and turn, a lane per entry; time rows reversed (see entry)
+        constexpr int kTurn = 8;
+        const bool short_rows = n_pos <= 64 && n_time <= 64;
+        for (int g0 = wave * kTurn; g0 < n_groups; g0 += NW * kTurn) {
+            if (short_rows) {
+                float pr[kTurn], tr[kTurn];
+#pragma unroll
+                for (int k = 0; k < kTurn; ++k) {
+                    const int row = min(g0 + k, n_groups - 1) * p.bias_H + h;
+                    pr[k] = p.bias.pos_table[row * n_pos + min(lane, n_pos - 1)];
+                    tr[k] = p.bias.time_table[row * n_time + min(lane, n_time - 1)];
+                }
+#pragma unroll
+                for (int k = 0; k < kTurn; ++k) {
+                    const int g = min(g0 + k, n_groups - 1);
+                    bias_lds[g * n_pos + min(lane, n_pos - 1)] = pr[k];
+                    bias_lds[n_groups * n_pos + g * n_time + n_time - 1 - min(lane, n_time - 1)] = tr[k];
+                }
+            } else {
+                for (int g = g0; g < min(g0 + kTurn, n_groups); ++g) {
+                    for (int i = lane; i < n_pos; i += 64) bias_lds[g * n_pos + i] = p.bias.pos_table[(g * p.bias_H + h) * n_pos + i];
+                    for (int i = lane; i < n_time; i += 64)
+                        bias_lds[n_groups * n_pos + g * n_time + n_time - 1 - i] = p.bias.time_table[(g * p.bias_H + h) * n_time + i];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        tau_idx[qb] = min(max(scen[qb], 0), p.n_scen - 1) * p.n_beh + min(max(beh[qb], 0), p.n_beh - 1);
+        st.c[qb] = p.scale_log2e / p.tau[tau_idx[qb]];
+        st.l[qb] = 0.f;
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st.O[db][qb][r] = 0.f;
+    }
+    if (n_tiles > 1) issue_tile(1, kStageBytes);
+
+    // Classes of 64 blocks: do a wave's 32 queries of a query block share one position and one time bucket with all
+    // keys of the block, and which.  Distances are monotonic in both ends, so the buckets of the extreme pairs decide.
+    // Eight lanes per block, four keys each.
+    constexpr int kMixed = 0x7fffffff;
+    int qp_min[QB], qp_max[QB];
+    uint32_t qt_min[QB], qt_max[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        qp_min[qb] = half_wave_reduce(b_pos[qb], [](int x, int y) { return min(x, y); });
+        qp_max[qb] = half_wave_reduce(b_pos[qb], [](int x, int y) { return max(x, y); });
+        qt_min[qb] = half_wave_reduce((int)b_ts[qb], [](int x, int y) { return (int)min((uint32_t)x, (uint32_t)y); });
+        qt_max[qb] = half_wave_reduce((int)b_ts[qb], [](int x, int y) { return (int)max((uint32_t)x, (uint32_t)y); });
+    }
+    int *my_class = class_lds + wave * QB * 64;
+    // position distance clipped to the table; leading zeros of a time distance, from those of the last bucket (the
+    // hardware's count of 0 is all ones, which the unsigned clamp takes to 31: bucket 0)
+    int half_v = half, z_min_v = max(32 - n_time, 0);
+    asm volatile("" : "+v"(half_v), "+v"(z_min_v));  // in vector registers: one scalar operand per instruction is the limit
+    auto clip = [&](int d) __attribute__((always_inline)) {
+        int x;
+        asm("v_med3_i32 %0, %1, %2, %3" : "=v"(x) : "v"(d), "v"(-half_v), "v"(half_v));
+        return x;
+    };
+    auto clip_zeros = [&](uint32_t d) __attribute__((always_inline)) {
+        uint32_t z;
+        asm("v_ffbh_u32 %0, %1" : "=v"(z) : "v"(d));
+        asm("v_med3_u32 %0, %1, %2, 31" : "=v"(z) : "v"(z), "v"(z_min_v));
+        return (int)z;
+    };
+    auto zeros = [&](uint32_t a, uint32_t b) __attribute__((always_inline)) {
+        uint32_t d;
+        asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(a), "v"(b));  // |a - b|
+        return clip_zeros(d);
+    };
+    auto classify = [&](int blk0) __attribute__((always_inline)) {
+        auto dpp = [](int v, auto ctrl) { return __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, 0xf, 0xf, false); };
+        auto over8 = [&](int x, auto &&f) {  // over the eight lanes of a block
+            x = f(x, dpp(x, std::integral_constant<int, 0xB1>{}));
+            x = f(x, dpp(x, std::integral_constant<int, 0x4E>{}));
+            return f(x, dpp(x, std::integral_constant<int, 0x141>{}));
+        };
+        constexpr int kTurn = 4;  // 32 blocks per turn
+#pragma unroll 1
+        for (int g0 = 0; g0 < 8 && k_lo + (blk0 + 8 * g0) * kBlockKeys < k_hi; g0 += kTurn) {
+            int4 kp[kTurn], kt[kTurn];
+#pragma unroll
+            for (int k = 0; k < kTurn; ++k) {
+                // (past the range: its last four keys again)
+                const int key = min(k_lo + (blk0 + 8 * (g0 + k)) * kBlockKeys + 4 * lane, (k_hi - 1) & ~3);
+                kp[k] = *(const int4 *)(p.bias.key_pos + (int64_t)t0 + key);
+                kt[k] = *(const int4 *)(p.bias.key_ts + (int64_t)t0 + key);
+            }
+#pragma unroll
+            for (int k = 0; k < kTurn; ++k) {
+                const int key = min(k_lo + (blk0 + 8 * (g0 + k)) * kBlockKeys + 4 * lane, (k_hi - 1) & ~3);
+                const int pe[4] = {kp[k].x, kp[k].y, kp[k].z, kp[k].w}, te[4] = {kt[k].x, kt[k].y, kt[k].z, kt[k].w};
+                int p_min = pe[0], p_max = pe[0], t_min = te[0], t_max = te[0];
+#pragma unroll
+                for (int e = 1; e < 4; ++e) {
+                    const bool in = key + e < k_hi;
+                    const int pp = in ? pe[e] : pe[0], tt = in ? te[e] : te[0];
+                    p_min = min(p_min, pp), p_max = max(p_max, pp), t_min = min(t_min, tt), t_max = max(t_max, tt);
+                }
+                auto lesser = [](int x, int y) { return min(x, y); };
+                auto greater = [](int x, int y) { return max(x, y); };
+                p_min = over8(p_min, lesser), p_max = over8(p_max, greater);
+                const uint32_t kt_min = bias_time_key(over8(t_min, lesser)), kt_max = bias_time_key(over8(t_max, greater));
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    const int ip = clip(__builtin_elementwise_sub_sat(qp_min[qb], p_max)), ip2 = clip(__builtin_elementwise_sub_sat(qp_max[qb], p_min));
+                    uint32_t d_min = 0, d_max;
+                    if (qt_min[qb] >= kt_max) d_min = qt_min[qb] - kt_max, d_max = qt_max[qb] - kt_min;
+                    else if (kt_min >= qt_max[qb]) d_min = kt_min - qt_max[qb], d_max = kt_max - qt_min[qb];
+                    else d_max = max(qt_max[qb] - kt_min, kt_max - qt_min[qb]);
+                    const int it = clip_zeros(d_min);
+                    const int cls = ip == ip2 && it == clip_zeros(d_max) ? (ip << 8) + it : kMixed;
+                    if ((lane & 7) == 0) my_class[qb * 64 + 8 * (g0 + k) + (lane >> 3)] = cls;
+                }
+            }
+        }
+    };
+    if (n_tiles > 0) classify(0);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // tile 0 and the tables are in LDS
+
+    // Bias of the lane's query for a clipped position distance and the leading zeros (32 - n_time .. 31) of a time
+    // distance, in the units of the exponent.  The time rows are kept reversed in LDS: indexed by the leading zeros.
+    uint32_t p_row[QB], t_row[QB];  // LDS byte addresses of entry 0 of either
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        p_row[qb] = (uint32_t)(tau_idx[qb] * n_pos + half) * 4u;
+        t_row[qb] = (uint32_t)(n_groups * n_pos + tau_idx[qb] * n_time + n_time - 32) * 4u;
+    }
+    auto entry = [&](int qb, int dp, int z) __attribute__((always_inline)) {
+        float x;
+        if constexpr (IN_LDS) {
+            x = *(const float *)((const uint8_t *)bias_lds + (p_row[qb] + 4 * dp)) + *(const float *)((const uint8_t *)bias_lds + (t_row[qb] + 4 * z));
+        } else {
+            const int g = tau_idx[qb] * p.bias_H + h;
+            x = p.bias.pos_table[g * n_pos + half + dp] + p.bias.time_table[g * n_time + 31 - z];
+        }
+        return st.c[qb] * p.inv_qk_scale * x;
+    };
+    // S of a block that is not uniform: t = S * c + bias, looked up per logit (coords: the block's positions in LDS)
+    auto lookup_block = [&](int qb, f32x16 (&S)[QB], const uint8_t *coords) __attribute__((always_inline)) {
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+            const int4 kp = *(const int4 *)(coords + 32 * g4 + 16 * hf), kt = *(const int4 *)(coords + kTileKeys * 4 + 32 * g4 + 16 * hf);
+            const int kpe[4] = {kp.x, kp.y, kp.z, kp.w}, kte[4] = {kt.x, kt.y, kt.z, kt.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                S[qb][4 * g4 + e] = fmaf(S[qb][4 * g4 + e], st.c[qb],
+                                         entry(qb, clip(__builtin_elementwise_sub_sat(b_pos[qb], kpe[e])), zeros(b_ts[qb], bias_time_key(kte[e]))));
+        }
+    };
+    // Raw products S of block `blk` of the range -> what the exponentials take: t = S * scale + add, the exponent in
+    // log2 units with the bias in it.  (Class and entries looked up a block ahead: no gain, and registers spill.)
+    auto bias_block = [&](int qb, f32x16 (&S)[QB], int blk, const uint8_t *stage, float &scale, float &add) __attribute__((always_inline)) {
+        const int cls = __builtin_amdgcn_readfirstlane(my_class[qb * 64 + (blk & 63)]);
+        if (cls != kMixed) {
+            scale = st.c[qb];
+            add = entry(qb, cls >> 8, cls & 255);
+        } else {
+            lookup_block(qb, S, stage + kTileBytes + (blk & 1) * (kBlockKeys * 4));
+            scale = 1.f;
+            add = 0.f;
+        }
+    };
+    const int whole_hi = CAUSAL ? min(q0 + wave * WQ, k_hi) : k_hi;  // keys below it are visible to every query of the wave
+    auto mask = [&](f32x16 (&S)[QB], int blk) __attribute__((always_inline)) {
+        const int lo = k_lo + blk * kBlockKeys;
+        if (lo + kBlockKeys > whole_hi) {
+            int lim[QB];
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) lim[qb] = CAUSAL ? min(q0 + wave * WQ + qb * 32 + l32 + 1, k_hi) : k_hi;
+            mask_causal(S, hf, lo, lim);
+        }
+    };
+
+    // FAST pass (exact-scale form), software pipelined over 32-key blocks as in attn_bf16.hip
+    if (n_tiles > 0) {
+        f32x16 S0[QB], S1[QB];
+        bf16x8 P[QB][2];
+        auto soft = [&](f32x16 (&S)[QB], int blk, const uint8_t *stage) __attribute__((always_inline)) {
+            mask(S, blk);
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                float scale, add;
+                bias_block(qb, S, blk, stage, scale, add);
+                st.l[qb] += exp_pack<true>(S[qb], scale, -add, P[qb]);
+            }
+        };
+        qk_block(st, load_k(lds, lane), S0);
+        int so_cur = 0, so_nxt = kStageBytes, so_fill = 2 * kStageBytes;
+        for (int t = 0; t + 1 < n_tiles; ++t) {
+            const uint8_t *cur = lds + so_cur, *nxt = lds + so_nxt;
+            if (t > 0 && (t & 31) == 0) classify(2 * t);
+            {   // block 0 of tile t: its logits are in S0; start block 1's
+                const KFrags k1 = load_k(cur + kBlockBytes, lane);
+                const VFrags v0 = load_v(cur, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                qk_block(st, k1, S1);
+                soft(S0, 2 * t, cur);
+                pv_block(st, v0, P);
+            }
+            wait_copies();  // tile t + 1 has landed; nobody reads tile t - 1 any more
+            __builtin_amdgcn_s_barrier();
+            if (t + 2 < n_tiles) issue_tile(t + 2, so_fill);
+            {   // block 1 of tile t; start block 0 of tile t + 1
+                const KFrags k0 = load_k(nxt, lane);
+                const VFrags v1 = load_v(cur + kBlockBytes, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                qk_block(st, k0, S0);
+                soft(S1, 2 * t + 1, cur);
+                pv_block(st, v1, P);
+            }
+            const int so = so_cur;
+            so_cur = so_nxt, so_nxt = so_fill, so_fill = so;
+        }
+        {   // last tile: 1..64 keys
+            const int blk = 2 * (n_tiles - 1);
+            const uint8_t *cur = lds + so_cur;
+            if (blk > 0 && (blk & 63) == 0) classify(blk);
+            const bool two = k_lo + (blk + 1) * kBlockKeys < k_hi;
+            if (two) qk_block(st, load_k(cur + kBlockBytes, lane), S1);
+            const VFrags v0 = load_v(cur, lane);
+            soft(S0, blk, cur);
+            pv_block(st, v0, P);
+            if (two) {
+                const VFrags v1 = load_v(cur + kBlockBytes, lane);
+                soft(S1, blk + 1, cur);
+                pv_block(st, v1, P);
+            }
+        }
+    }
+    // SUMI: the candidate's own key (its exponent, log2 units) and value
+    float w_own[QB];
+    if (SUMI) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const __bf16 *kp = p.k_self + row_of(qb) * p.ld_kv + h * kDHead + 8 * hf;
+            float dot = 0.f;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const bf16x8 kk = *(const bf16x8 *)(kp + 16 * s);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) dot += (float)st.qf[qb][s][e] * (float)kk[e];
+            }
+            // zero distance in position and time
+            w_own[qb] = fmaf(dot + xhalf(dot), st.c[qb], entry(qb, 0, 31));
+        }
+    }
+    auto own_v = [&](int qb, float w) __attribute__((always_inline)) {  // O += w * v_own
+        const __bf16 *vp = p.v_self + row_of(qb) * p.ld_kv + h * kDHead + 4 * hf;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const bf16x4 vv = *(const bf16x4 *)(vp + 8 * i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                st.O[i >> 2][qb][4 * (i & 3) + e] = fmaf(w, (float)vv[e], st.O[i >> 2][qb][4 * (i & 3) + e]);
+        }
+    };
+    float lt[QB];
+    bool bad = false;
+    if (SUMI) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const float w = __builtin_amdgcn_exp2f(w_own[qb]);
+            st.l[qb] += hf == 0 ? w : 0.f;
+            own_v(qb, w);
+        }
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        lt[qb] = st.l[qb] + xhalf(st.l[qb]);
+        bad |= !(lt[qb] > kDenomLoExact && lt[qb] < kDenomHiExact);
+    }
+    // SAFE pass (rare): the whole workgroup redoes its rows with a running maximum, in log2 units
+    const int wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+    if (lane == 0) flag_lds[wave] = wave_bad;
+    __syncthreads();  // (and every wave is done with the ring)
+    int any_bad = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) any_bad |= flag_lds[w];
+    if (any_bad) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            st.m_ref[qb] = SUMI ? w_own[qb] : kSafeNoRef;
+            st.l[qb] = (SUMI && hf == 0) ? 1.f : 0.f;
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) st.O[db][qb][r] = 0.f;
+        }
+        if (SUMI) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) own_v(qb, 1.f);
+        }
+        for (int t = 0; t < n_tiles; ++t) {
+            __syncthreads();
+            issue_tile(t, 0);
+            wait_copies();
+            __syncthreads();
+            for (int k = 0; k < 2; ++k) {
+                const int blk = 2 * t + k;
+                if (k_lo + blk * kBlockKeys >= k_hi) break;
+                if ((blk & 63) == 0) classify(blk);
+                f32x16 S[QB];
+                bf16x8 P[QB][2];
+                qk_block(st, load_k(lds + k * kBlockBytes, lane), S);
+                mask(S, blk);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    float scale, add;
+                    bias_block(qb, S, blk, lds, scale, add);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) S[qb][r] = fmaf(S[qb][r], scale, add);
+                }
+                float c_keep[QB];
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) c_keep[qb] = st.c[qb], st.c[qb] = 1.f;  // (t is scaled already)
+                softmax_safe(st, S, P);
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) st.c[qb] = c_keep[qb];
+                pv_block(st, load_v(lds + k * kBlockBytes, lane), P);
+            }
+        }
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) lt[qb] = st.l[qb] + xhalf(st.l[qb]);
+        __syncthreads();
+    }
+
+    // normalise and store: each wave turns its 32 x 64 blocks around in its corner of the idle ring
+    constexpr int kRowPitch = 144;
+    uint8_t *tr = lds + wave * (32 * kRowPitch);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const float inv = 1.f / lt[qb];
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                bf16x4 ov;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(st.O[db][qb][4 * g + e] * inv);
+                *(bf16x4 *)(tr + l32 * kRowPitch + (32 * db + 8 * g + 4 * hf) * 2) = ov;
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int id = i * 64 + lane, r = id >> 3, cc = id & 7;
+            const int wq = wave * WQ + qb * 32 + r;
+            const u32x4 val = *(const u32x4 *)(tr + r * kRowPitch + cc * 16);
+            __bf16 *op = p.o + (row0 + wq) * p.ld_o + h * kDHead + cc * 8;
+            if (wq < nq) __builtin_nontemporal_store(val, (u32x4 *)op);
+            else if (!SUMI && q0 + wq < Lpad) *(uint4 *)op = uint4{0, 0, 0, 0};
+        }
+    }
+}
+
+template <int QB, bool SUMI, bool CAUSAL>
+hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
+{
+    constexpr int TQ = NW * 32 * QB;
+    const int n_qtiles = (a.max_rows_per_user + TQ - 1) / TQ;
+    const int64_t grid = (int64_t)8 * n_qtiles * ((a.cache.B * a.H + 7) / 8);
+    if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
+    const KParams p = make_params(a, n_qtiles);
+    const int64_t entries = (int64_t)a.n_scen * a.n_beh * ((int64_t)a.bias.n_pos + a.bias.n_time);
+    const bool in_lds = entries <= kBiasLdsFloats;
+    const size_t lds = kStages * kStageBytes + NW * 4 + kClassBytes<QB> + (in_lds ? (size_t)entries * 4 : 0);
+    auto go = [&](auto in_lds_tag) {
+        constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value>;
+        const hipError_t e = raise_lds_limit<kernel>(kStages * kStageBytes + NW * 4 + kClassBytes<QB> + kBiasLdsFloats * 4);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NW * 64), lds, s, p);
+        return hipGetLastError();
+    };
+    return in_lds ? go(std::true_type{}) : go(std::false_type{});
+}
+
+}  // namespace
+
+hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
+{
+    // candidates: 256-query tiles when a head has more than 128
+    if (sumi) return a.max_rows_per_user > 128 ? launch_bias<2, true, false>(a, s) : launch_bias<1, true, false>(a, s);
+    return a.causal ? launch_bias<1, false, true>(a, s) : launch_bias<1, false, false>(a, s);
+}
+
+}  // namespace climber

@@ -50,7 +50,7 @@ struct KParams {
     int uni_len, uni_pad;  // >= 0: every user has this valid / padded history length
     int uni_cand;          // >= 0: every user has this many candidates (SUMI)
     float scale_log2e, inv_qk_scale;
-    BiasArgs bias;  // relative attention bias (the BIAS variants of the kernel)
+    BiasArgs bias;  // relative attention bias (attn_bias_bf16.hip)
     int bias_H;
 };
 
@@ -147,17 +147,6 @@ static __device__ __forceinline__ void qk_block(const QState<QB> &st, const KFra
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) S[qb][r] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-            S[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.a[s], st.qf[qb][s], S[qb], 0, 0, 0);
-}
-
-// S^T[qb] += K_blk q_qb^T onto whatever S holds (the relative attention bias of the block)
-template <int QB>
-static __device__ __forceinline__ void qk_block_acc(const QState<QB> &st, const KFrags &k, f32x16 (&S)[QB])
-{
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll

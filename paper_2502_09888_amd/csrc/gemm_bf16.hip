@@ -19,9 +19,9 @@
 // Workgroups that share A rows are launched onto the same XCD (see the kernel).
 #include "gemm_common.h"
 #include "lanes.h"
+#include "launch.h"
 
 #include <algorithm>
-#include <atomic>
 #include <cstdlib>
 #include <type_traits>
 #include <utility>
@@ -278,20 +278,8 @@ hipError_t launch(const GemmArgs &g, hipStream_t s)
 {
     constexpr int BM = 64 * WM, BN = 64 * WN;
     constexpr size_t lds_bytes = (size_t)kStages * (BM + BN) * BK * 2;
-    // the kernel's dynamic LDS exceeds the default limit: raised once per device (the attribute belongs
-    // to the function as loaded on the current device)
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> raised[kMaxDevices];
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = raise_lds_limit<gemm_bf16_kernel<EPI, WM, WN, kStages>>(lds_bytes);
     if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    if (!raised[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute((const void *)gemm_bf16_kernel<EPI, WM, WN, kStages>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-        raised[dev].store(true, std::memory_order_release);
-    }
     const dim3 grid((g.N / BN) * ((g.M + BM - 1) / BM)), block(256);
     hipLaunchKernelGGL((gemm_bf16_kernel<EPI, WM, WN, kStages>), grid, block, lds_bytes, s, (const __bf16 *)g.A, g.lda,
                        (const __bf16 *)g.W, g.M, g.N, g.K, g.C, g.ldc, g.resid, g.ldr, g.nin, g.nout, g.tiled, g.qc);

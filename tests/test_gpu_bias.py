@@ -195,3 +195,26 @@ def test_randomized_shapes_scales_masks_with_bias():
         assert np.isfinite(oh[ok]).all() and np.all(oh[~ok] == 0) and e1 < 2e-2 and e2 < 2e-2
         done += 1
     assert done == 60
+
+
+@pytest.mark.parametrize("n_pos,n_time,L,sub,causal,shuffled", [
+    (33, 12, 2300, 0, False, False),     # more than 64 blocks of 32 keys: classified in two turns, the second one ragged
+    (33, 12, 2300, 0, True, True),       # coordinates in no order: hardly any block has one bucket
+    (201, 40, 300, 256, False, False),   # more time buckets than an int32 distance has octaves; table rows longer than a wave
+    (1, 2, 97, 128, False, False),       # one position bucket, two of time: hardly any block is mixed
+    (129, 20, 700, 128, True, False),
+    (3, 31, 65, 0, False, True)])
+def test_bf16_bias_uniform_and_mixed_blocks(n_pos, n_time, L, sub, causal, shuffled):
+    spec = W.shrink(W.CONFIG2, name=f"bias-blocks-{n_pos}-{n_time}-{L}", B=2, L=L, L_min=L - 40, sub_len=sub, M=150, M_min=20, H=2,
+                    nan_padding=True, seed=900 + n_pos + L)
+    w = W.add_bias_inputs(W.make_attention(spec), n_pos=n_pos, n_time=n_time)
+    if shuffled:
+        rng = np.random.Generator(np.random.Philox(5))
+        w["hist_pos"] = rng.permutation(w["hist_pos"]).astype(np.int32)
+        w["hist_ts"] = rng.permutation(w["hist_ts"]).astype(np.int32)
+    check_bias(w, causal=causal)
+
+
+def test_bf16_bias_running_maximum_over_two_turns_of_blocks():
+    spec = W.shrink(W.CONFIG2, name="bias-safe-long", B=1, L=2200, sub_len=0, M=140, H=2, qk_scale=12.0, seed=941)
+    check_bias(W.add_bias_inputs(W.make_attention(spec)))
