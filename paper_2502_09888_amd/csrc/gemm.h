@@ -85,6 +85,22 @@ struct GemmArgs {
 // gemm_small_bf16.hip: few rows.  N % 64 == 0, K % 128 == 0.
 hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s);
 
+// layer_tail_bf16.hip: y = h + GELU(RMSNorm(h) W1) W2 with h = x + o Wo, one launch.  Rows of D columns: o bf16,
+// x / y fp32, yb (nullable) bf16; ss (nullable) [M][D / 64] sums of squares of y; wo [D][D], w1 [D][F] (gains
+// multiplied in), w2 [F][D] packed.  y may be x.
+struct TailArgs {
+    const void *o;
+    const float *x;
+    const void *wo, *w1, *w2;
+    float *y;
+    void *yb;
+    float *ss;
+    int M, D, F;
+    float inv_d, eps;
+};
+bool layer_tail_takes(int M, int D, int F);  // shapes it has a kernel for and is the faster way
+hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s);
+
 // What the first projection of a stack call needs of its input rows: the sum of squares of every
 // row into ss[row][0] (ss[row][1 .. n_part-1] = 0) and
 //   from bf16 rows x (the embeddings): the fp32 copy x32 (the residual stream);

@@ -4,12 +4,27 @@
 #include "gemm.h"
 #include "lanes.h"
 
+#include <type_traits>
+#include <utility>
+
 namespace climber {
 namespace gemm {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), unrolled at compile time
+template <int... Is, class F>
+static __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, Is...>, F &&f)
+{
+    (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, class F>
+static __device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
 
 // exact-erf GELU.  With a = |x| and h = Phi(-a) (the normal tail),
 //   GELU(x) = x Phi(x) = max(x, 0) - a h        (x >= 0: x - x h;  x < 0: x h),
@@ -19,17 +34,40 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 // rounding of the result; it increases monotonically, so h goes to 0 for any large a.  9 instructions and one
 // exponential; the rational form (Abramowitz & Stegun 7.1.26, |error of erf| <= 1.5e-7) takes 11 and a reciprocal as
 // well, and this epilogue is bound by the vector unit.
+// In stages, for a kernel that deals them out between its matrix instructions (x, p: carried from stage to stage).
+template <int STAGE>
+static __device__ __forceinline__ void gelu_stage(float &x, float &p)
+{
+    constexpr float c[8] = {-1.03929294e-06f, 4.95801644e-05f, -8.60018677e-04f, 8.30576403e-03f,
+                            -5.36681604e-02f, -4.58660253e-01f, -1.15120338e+00f, -9.99997089e-01f};
+    if constexpr (STAGE == 0) p = fmaf(__builtin_fabsf(x), c[0], c[1]);
+    else if constexpr (STAGE < 7) p = fmaf(p, __builtin_fabsf(x), c[STAGE + 1]);
+    else if constexpr (STAGE == 7) p = __builtin_amdgcn_exp2f(p);
+    else x = fmaf(-__builtin_fabsf(x), p, fmaxf(x, 0.f));
+}
 static __device__ __forceinline__ float gelu_erf(float x)
 {
-    const float a = __builtin_fabsf(x);
-    float p = fmaf(a, -1.03929294e-06f, 4.95801644e-05f);
-    p = fmaf(p, a, -8.60018677e-04f);
-    p = fmaf(p, a, 8.30576403e-03f);
-    p = fmaf(p, a, -5.36681604e-02f);
-    p = fmaf(p, a, -4.58660253e-01f);
-    p = fmaf(p, a, -1.15120338e+00f);
-    p = fmaf(p, a, -9.99997089e-01f);
-    return fmaf(-a, __builtin_amdgcn_exp2f(p), fmaxf(x, 0.f));
+    float p;
+    static_for<9>([&](auto s) __attribute__((always_inline)) { gelu_stage<decltype(s)::value>(x, p); });
+    return x;
+}
+
+// x^2 + y^2 + z^2 + w^2, one fixed order (the row sums of squares are the same bits whoever forms them)
+static __device__ __forceinline__ float sumsq4(float x, float y, float z, float w)
+{
+    return fmaf(w, w, fmaf(z, z, fmaf(y, y, x * x)));
+}
+
+// A lane's part of a 32 x 32 block of fp32 rows, as its accumulators hold it: x = row l32 of the block, from column
+// 4 (lane / 32) on.  The residual rows are the accumulators' start value: requested ahead of the products, and no
+// separate addition behind them.
+static __device__ __forceinline__ void load_block(f32x16 &acc, const float *x)
+{
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const float4 v = *(const float4 *)(x + 8 * g);
+        acc[4 * g] = v.x, acc[4 * g + 1] = v.y, acc[4 * g + 2] = v.z, acc[4 * g + 3] = v.w;
+    }
 }
 
 // 1/sqrt(mean(x^2) + eps) of one row from its partial sums of squares
@@ -120,8 +158,7 @@ constexpr int epilogue_pitch() { return WN * 32 * (EPI == EPI_RESID_F32 ? 4 : 2)
 template <int EPI, int WM, int WN>
 static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], const float (&rs)[WM], const CacheUser (&user)[WM],
                                                      uint8_t *tr, int row0, int col_base, int lane, int M, int N, void *C,
-                                                     int64_t ldc, const float *resid, int64_t ldr, const RowNormOut &nout,
-                                                     int tiled, const QkvToCache &qc)
+                                                     int64_t ldc, const RowNormOut &nout, int tiled, const QkvToCache &qc)
 {
     const int l32 = lane & 31, hf = lane >> 5;
     constexpr bool F32 = EPI == EPI_RESID_F32;
@@ -130,21 +167,6 @@ static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], cons
     constexpr int kPitch = epilogue_pitch<EPI, WN>();  // bytes per staged row
     constexpr int kChunksPerRow = CW * kElem / 16;
     constexpr int kIters = 32 * kChunksPerRow / 64;   // 16-byte pieces per lane and block row
-    // Residual rows of block row i, all requested before anything waits for them (a load placed
-    // after a store would make the wait for it drain the stores as well: one memory round trip per
-    // 16 bytes).  Block row i + 1 is requested before block row i is stored.
-    float4 rsd[2][F32 ? kIters : 1];
-    auto load_resid = [&](int i, float4 *buf) __attribute__((always_inline)) {
-        if constexpr (F32) {
-#pragma unroll
-            for (int it = 0; it < kIters; ++it) {
-                const int id = it * 64 + lane, r = id / kChunksPerRow, cc = id % kChunksPerRow;
-                const int row = min(row0 + 32 * i + r, M - 1);
-                buf[it] = *(const float4 *)(resid + (int64_t)row * ldr + col_base + cc * 4);
-            }
-        }
-    };
-    load_resid(0, rsd[0]);
     // direct cache write: slots past a user's valid length hold zeros
     bool zero_row[WM];
 #pragma unroll
@@ -172,7 +194,6 @@ static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], cons
                     *(uint2 *)(tr + l32 * kPitch + col * 2) = *(const uint2 *)v;
                 }
             }
-        if (i + 1 < WM) load_resid(i + 1, rsd[(i + 1) & 1]);
         const int row_base = row0 + 32 * i;
         if (EPI == EPI_STORE_BF16 && qc.layer_base) {
             // the wave's 32 x 64 block is one head of the queries, keys or values of 32 tokens of one
@@ -188,9 +209,7 @@ static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], cons
             uint4 val = *(const uint4 *)(tr + r * kPitch + cc * 16);
             if (F32) {
                 const int col = col_base + cc * 4;
-                const float4 rd = rsd[i & 1][it];
-                float4 o = *(const float4 *)&val;
-                o.x += rd.x; o.y += rd.y; o.z += rd.z; o.w += rd.w;
+                const float4 o = *(const float4 *)&val;
                 if (row < M) {
                     *(float4 *)((float *)C + (int64_t)row * ldc + col) = o;
                     if (nout.ss) {
@@ -201,7 +220,7 @@ static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], cons
                 }
                 if (nout.ss) {  // sums of squares of 64-column slices of the row: 16 lanes each
                     static_assert(!F32 || kChunksPerRow % 16 == 0, "a 64-column slice = 16 lanes of one row");
-                    const float sq = row_sum16(o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w);
+                    const float sq = row_sum16(sumsq4(o.x, o.y, o.z, o.w));
                     if ((cc & 15) == 0 && row < M)
                         nout.ss[(int64_t)row * (N / 64) + (col_base + cc * 4) / 64] = sq;
                 }

@@ -1,0 +1,396 @@
+// What follows the attention of a layer, in one kernel (f_FFN of Eq. (3), Climber, arXiv 2502.09888):
+//     h = x + o Wo;   y = h + GELU(RMSNorm(h; g2) W1) W2
+// for row counts that fill the chip.  As three launches, h (fp32 and bf16), its row sums and the feed-forward
+// hidden (d_ffn columns) go out to memory and come back: at d_model 512, d_ffn 2048 a row moves 20 KiB, of which 6
+// are the row's own input and output, and the launches wait for those bytes about as long as for their products.
+// Here a workgroup owns 32*RB rows and all their columns: h stays in accumulators (the feed-forward's second product
+// accumulates right on top of it), its bf16 copy and one chunk of the hidden live in LDS, and only weights -- packed
+// fragments, L2-resident -- stream in, straight into registers.
+//
+// NW waves side by side over the columns: a wave owns D / NW columns of h / y and 32 columns of every chunk of the
+// hidden.  Per chunk: the next chunk's hidden from the bf16 rows, then y += hidden W2 with the next chunk's GELU
+// dealt out between the matrix instructions (neither waits for the other's pipe).  The weight fragments of all
+// products form one stream of loads, R in flight per wave across phase changes and barriers; rows of LDS operands are
+// XOR-swizzled so that the fragment reads are conflict-free.
+// 64 rows (RB = 2, NW = 4), two workgroups per CU (80 KiB of LDS at d_model 512): bound by the matrix cores at the clock
+// that they leave (32768 rows, d_model 512: 1.0 PFLOP/s, a large plain matrix product reaches 1.26) and, nearly as
+// much, by the weights' way through the vector cache (4.7 MB per workgroup at 64 bytes per clock).  32768 rows: d_model
+// 512 154 us against 230 as three launches, d_model 256 52 against 87.  32 rows (RB = 1, NW = 8) where 64 would leave
+// CUs without work: bound by the weights out of L2 (20 TB/s over the chip); 8192 rows 58 us against 69.  (Taller tiles
+// would need less of the caches, but 128 rows do not fit the registers; separate waves for the two products gave
+// the same times.)
+// Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
+// bits.
+#include "gemm_common.h"
+#include "lanes.h"
+#include "launch.h"
+
+#include <utility>
+
+namespace climber {
+namespace {
+
+using namespace gemm;
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef const __attribute__((address_space(1))) uint8_t glb_u8;
+
+// (Inline assembly: the loads stay in flight across barriers and phases, which the compiler would not allow; a
+// fragment is valid after the wait that names its registers, and until then nothing may move them: the kernel has to
+// fit its registers without spills.)
+__device__ __forceinline__ void load_frag(u32x4 &f, uint32_t lane_off, const uint8_t *base)
+{
+    asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(f) : "v"(lane_off), "s"(base));
+}
+template <int VM, int N>
+__device__ __forceinline__ void arrived(u32x4 *f)
+{
+    if constexpr (N == 1) asm volatile("s_waitcnt vmcnt(%1)" : "+v"(f[0]) : "n"(VM));
+    else if constexpr (N == 2) asm volatile("s_waitcnt vmcnt(%2)" : "+v"(f[0]), "+v"(f[1]) : "n"(VM));
+    else asm volatile("s_waitcnt vmcnt(%4)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : "n"(VM));
+}
+// every wave's LDS accesses so far are done (the weights' loads stay in flight)
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// rows of h, a chunk of the hidden (at the end: 32 rows of y, fp32)
+template <int D, int RB, int NW>
+constexpr int tail_lds_bytes()
+{
+    constexpr int operands = 32 * RB * (D + 32 * NW) * 2, rows = 32 * D * 4;
+    return operands > rows ? operands : rows;
+}
+
+// The next fragments of the stream of weights: fragment e at base + (e % NJ) * a + (e / NJ) * b.
+struct Next { const uint8_t *base; int64_t a, b; };
+
+template <int D, int RB, int NW, int R>
+__global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p)
+{
+    constexpr int ROWS = 32 * RB, CW = D / NW, NJ = CW / 32;   // rows of the tile; columns and column blocks of a wave
+    constexpr int kChunk = 32 * NW;                            // hidden columns of a chunk
+    constexpr int S = D / 16, T = kChunk / 16;                 // k-steps of the products over h and over a chunk
+    constexpr int kXPitch = D * 2, kHPitch = kChunk * 2;       // bytes per row of the two LDS operands
+    static_assert(NJ == 2 || NJ == 4, "a wave owns whole 64-column slices of the row sums");
+    static_assert(32 % (T * NJ) == 0, "a share of the GELU for every matrix instruction");
+    static_assert(S % R == 0 && T * NJ % R == 0 && R % (2 * NJ) == 0, "ring slots are compile-time constants");
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    uint8_t *const X = lds, *const H = lds + ROWS * kXPitch;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hf = lane >> 5, r15 = lane & 15;
+    const int m0 = blockIdx.x * ROWS, M = p.M, F = p.F, col0 = CW * wave, n_chunks = F / kChunk;
+
+    // LDS operands: 16-byte chunk c of row r at slot c ^ (r % 16) of its group of 16
+    const uint32_t x_base = (uint32_t)(l32 * kXPitch + ((hf ^ r15) << 4)), h_base = (uint32_t)(l32 * kHPitch + ((hf ^ r15) << 4));
+    auto frag = [](const uint8_t *op, uint32_t base, int pitch, int step, int i) __attribute__((always_inline)) {
+        return *(const bf16x8 *)(op + ((base ^ ((step & 7) << 5)) + (step >> 3) * 256 + i * 32 * pitch));
+    };
+    auto write_a = [&](uint8_t *op, int pitch, int i, int col, bf16x4 v) __attribute__((always_inline)) {  // columns col + 4 hf ..
+        const int c = col / 8;
+        *(bf16x4 *)(op + (32 * i + l32) * pitch + (((c & ~15) | ((c & 15) ^ r15)) * 16) + 8 * hf) = v;
+    };
+
+    // the attention output rows -> X, whole rows
+    {
+        constexpr int kLanes = kXPitch / 16, kPer = 64 / kLanes;  // lanes per row, rows per 1 KiB copy
+#pragma unroll
+        for (int c = 0; c < ROWS / kPer / NW; ++c) {
+            const int r0 = (wave * (ROWS / kPer / NW) + c) * kPer, r = r0 + lane / kLanes, slot = lane % kLanes;
+            const int ch = (slot & ~15) | ((slot & 15) ^ (r & 15));
+            __builtin_amdgcn_global_load_lds((glb_u8 *)((const uint8_t *)p.o + (int64_t)min(m0 + r, M - 1) * kXPitch + ch * 16),
+                                             (lds_u8 *)X + r0 * kXPitch, 16, 0, 0);
+        }
+    }
+    f32x16 acc[RB][NJ];  // the lane's accumulators are [row 32i + l32][col0 + 32j + 8g + 4hf + 0..3]
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            load_block(acc[i][j], p.x + (int64_t)min(m0 + 32 * i + l32, M - 1) * D + col0 + 32 * j + 4 * hf);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (the compiler's own count of these loads ends here, not in the loops below)
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(acc[i][j]));
+
+    // the stream of weight fragments, 1 KiB each: Wo; W1 of chunk 0; then, per chunk, W1 of the next and W2 of this one
+    const uint32_t w_lane = lane * 16;
+    const uint8_t *const wo = (const uint8_t *)p.wo + (int64_t)(col0 / 32) * S * 1024;
+    const uint8_t *const w1 = (const uint8_t *)p.w1 + (int64_t)wave * S * 1024;
+    const uint8_t *const w2 = (const uint8_t *)p.w2 + (int64_t)(col0 / 32) * (F / 16) * 1024;
+    const int64_t w1_chunk = (int64_t)NW * S * 1024, w2_col = (int64_t)(F / 16) * 1024;
+    auto next_up = [&](int ch) __attribute__((always_inline)) { return Next{w1 + ch * w1_chunk, 1024, NJ * 1024}; };
+    auto next_down = [&](int ch) __attribute__((always_inline)) { return Next{w2 + (int64_t)ch * T * 1024, w2_col, 1024}; };
+    u32x4 ring[R];
+    auto load_next = [&](auto slot_tag, const Next &n, int e) __attribute__((always_inline)) {
+        load_frag(ring[decltype(slot_tag)::value], w_lane, n.base + (e % NJ) * n.a + (e / NJ) * n.b);
+    };
+    {
+        const Next n{wo, S * 1024, 1024};
+        static_for<R>([&](auto e) __attribute__((always_inline)) { load_next(e, n, decltype(e)::value); });
+    }
+    lds_barrier();  // o is there
+
+    // One k-step of a product into acc: operand rows fa, NJ fragments from ring slot q on.  Behind every MFMA goes
+    // `between(index)`; operand rows of the next step (`refill(i)`) and fragments (`reload(j)`) as their registers fall free.
+    bf16x8 fa[2][RB];
+    auto mfma_step = [&](auto q_tag, auto &&refill, auto &&reload, auto &&between) __attribute__((always_inline)) {
+        constexpr int q = decltype(q_tag)::value;
+        arrived<R - NJ, NJ>(&ring[q]);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<RB * NJ>([&](auto m_tag) __attribute__((always_inline)) {
+            constexpr int m = decltype(m_tag)::value, i = m / NJ, j = m % NJ;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[q + j]), fa[0][i], acc[i][j], 0, 0, 0);
+            if constexpr (j == NJ - 1) refill(i);
+            if constexpr (i == RB - 1) reload(std::integral_constant<int, j>{});
+            between(m_tag);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto nothing = [](auto) __attribute__((always_inline)) {};
+
+    // ---- h = x + o Wo ----
+#pragma unroll
+    for (int i = 0; i < RB; ++i) fa[0][i] = frag(X, x_base, kXPitch, 0, i);
+    auto o_steps = [&](int s0, auto last_tag) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last_tag)::value;
+        static_for<8>([&](auto u_tag) __attribute__((always_inline)) {
+            constexpr int u = decltype(u_tag)::value, q = (u * NJ) % R, un = u + R / NJ;
+            mfma_step(std::integral_constant<int, q>{},
+                      [&](int i) __attribute__((always_inline)) { if (!LAST || u < 7) fa[0][i] = frag(X, x_base, kXPitch, s0 + u + 1, i); },
+                      [&](auto j_tag) __attribute__((always_inline)) {
+                          constexpr int j = decltype(j_tag)::value;
+                          load_frag(ring[q + j], w_lane, LAST && un >= 8 ? w1 + ((un - 8) * NJ + j) * 1024 : wo + j * (S * 1024) + (s0 + un) * 1024);
+                      },
+                      nothing);
+        });
+    };
+#pragma unroll 1
+    for (int s0 = 0; s0 + 8 < S; s0 += 8) o_steps(s0, std::false_type{});
+    o_steps(S - 8, std::true_type{});
+    // sums of squares of the rows' 64-column slices, as the separate launches form them
+    auto slice_sums = [&](auto &&put) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int sl = 0; sl < NJ / 2; ++sl) {
+                float half8[2];
+#pragma unroll
+                for (int jj = 0; jj < 2; ++jj) {
+                    float pr[4];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const f32x16 &a = acc[i][2 * sl + jj];
+                        const float q4 = sumsq4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+                        pr[g] = q4 + __shfl_xor(q4, 32, 64);
+                    }
+                    half8[jj] = (pr[0] + pr[1]) + (pr[2] + pr[3]);
+                }
+                put(i, sl, half8[0] + half8[1]);
+            }
+    };
+    float *ss = (float *)H;  // [ROWS][D / 64], until the hidden moves in
+    slice_sums([&](int i, int sl, float v) __attribute__((always_inline)) {
+        if (hf == 0) ss[(32 * i + l32) * (D / 64) + wave * (NJ / 2) + sl] = v;
+    });
+    lds_barrier();  // o has been read; the sums are there
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                bf16x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[i][j][4 * g + e];
+                write_a(X, kXPitch, i, col0 + 32 * j + 8 * g, v);
+            }
+    float rs[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) rs[i] = row_scale(RowNormIn{ss, D / 64, p.inv_d, p.eps}, 32 * i + l32);
+    lds_barrier();  // h is there; the sums have been read
+
+    // ---- y = h + GELU(r * (h W1)) W2, a chunk of the hidden at a time ----
+    f32x16 hid[RB];
+    bf16x4 hb[RB][4];
+    // hid = h W1 of a chunk
+    auto up = [&](const uint8_t *w1c, const Next &n) __attribute__((always_inline)) {
+        uint32_t x_at = x_base;
+        asm("" : "+v"(x_at));  // (the k-steps' addresses are made anew for every chunk, not kept in registers throughout)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) hid[i][r] = 0.f;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < RB; ++i) fa[s][i] = frag(X, x_at, kXPitch, s, i);
+        auto steps = [&](int s0, auto last_tag) __attribute__((always_inline)) {
+            constexpr bool LAST = decltype(last_tag)::value;
+            static_for<R>([&](auto u_tag) __attribute__((always_inline)) {
+                constexpr int u = decltype(u_tag)::value;
+                arrived<R - 1, 1>(&ring[u]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    hid[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[u]), fa[u & 1][i], hid[i], 0, 0, 0);
+                    if (!LAST || u < R - 2) fa[u & 1][i] = frag(X, x_at, kXPitch, s0 + u + 2, i);
+                    if (i == RB - 1) {
+                        if constexpr (LAST) load_next(u_tag, n, u);
+                        else load_frag(ring[u], w_lane, w1c + (s0 + u + R) * 1024);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+        };
+#pragma unroll 1
+        for (int s0 = 0; s0 + R < S; s0 += R) steps(s0, std::false_type{});
+        steps(S - R, std::true_type{});
+    };
+    // values 4g .. 4g + 3 of hid[i] through the scale and the GELU, in eight pieces of about 32 clocks
+    float gx[4], gp[4];
+    auto gelu_piece = [&](auto piece_tag, auto group_tag) __attribute__((always_inline)) {
+        constexpr int piece = decltype(piece_tag)::value, i = decltype(group_tag)::value / 4, g = decltype(group_tag)::value % 4;
+        auto each = [&](auto stage, int e0, int e1) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = e0; e < e1; ++e) gelu_stage<decltype(stage)::value>(gx[e], gp[e]);
+        };
+        if constexpr (piece == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) gx[e] = hid[i][4 * g + e] * rs[i];
+            each(std::integral_constant<int, 0>{}, 0, 4);
+        } else if constexpr (piece < 4) {
+            each(std::integral_constant<int, 2 * piece - 1>{}, 0, 4);
+            each(std::integral_constant<int, 2 * piece>{}, 0, 4);
+        } else if constexpr (piece < 6) {
+            each(std::integral_constant<int, 7>{}, 2 * (piece - 4), 2 * (piece - 4) + 2);
+        } else if constexpr (piece == 6) {
+            each(std::integral_constant<int, 8>{}, 0, 4);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) hb[i][g][e] = (__bf16)gx[e];
+        }
+    };
+    auto write_hidden = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) write_a(H, kHPitch, i, 32 * wave + 8 * g, hb[i][g]);
+    };
+    // y += hidden W2 of chunk ch; between the products, the GELU of the chunk in hid
+    auto down = [&](int ch, const Next &n, auto gelu_tag) __attribute__((always_inline)) {
+        constexpr bool GELU = decltype(gelu_tag)::value;
+        const Next own = next_down(ch);
+        uint32_t h_at = h_base;
+        asm("" : "+v"(h_at));
+#pragma unroll
+        for (int i = 0; i < RB; ++i) fa[0][i] = frag(H, h_at, kHPitch, 0, i);
+        static_for<T>([&](auto t_tag) __attribute__((always_inline)) {
+            constexpr int t = decltype(t_tag)::value, q = (t * NJ) % R, tn = t + R / NJ;
+            mfma_step(std::integral_constant<int, q>{},
+                      [&](int i) __attribute__((always_inline)) { if (t + 1 < T) fa[0][i] = frag(H, h_at, kHPitch, t + 1, i); },
+                      [&](auto j_tag) __attribute__((always_inline)) {
+                          constexpr int j = decltype(j_tag)::value;
+                          load_next(std::integral_constant<int, q + j>{}, tn < T ? own : n, (tn < T ? tn : tn - T) * NJ + j);
+                      },
+                      [&](auto m_tag) __attribute__((always_inline)) {
+                          if constexpr (GELU) {
+                              constexpr int per = 32 / (T * NJ), at = (t * RB * NJ + decltype(m_tag)::value) * per;
+                              static_for<per>([&](auto k) __attribute__((always_inline)) {
+                                  constexpr int pc = at + decltype(k)::value;
+                                  gelu_piece(std::integral_constant<int, pc % 8>{}, std::integral_constant<int, pc / 8>{});
+                              });
+                          }
+                      });
+        });
+    };
+
+    up(w1, n_chunks > 1 ? next_up(1) : next_down(0));
+    static_for<RB * 32>([&](auto k) __attribute__((always_inline)) {
+        gelu_piece(std::integral_constant<int, decltype(k)::value % 8>{}, std::integral_constant<int, decltype(k)::value / 8>{});
+    });
+    write_hidden();
+    lds_barrier();
+#pragma unroll 1
+    for (int ch = 0; ch + 1 < n_chunks; ++ch) {
+        up(w1 + (ch + 1) * w1_chunk, next_down(ch));
+        down(ch, ch + 2 < n_chunks ? next_up(ch + 2) : next_down(ch + 1), std::true_type{});
+        lds_barrier();  // chunk ch has been read
+        write_hidden();
+        lds_barrier();  // chunk ch + 1 is there
+    }
+    down(n_chunks - 1, next_down(n_chunks - 1), std::false_type{});  // (what it loads ahead is not used)
+    static_for<R>([&](auto q) __attribute__((always_inline)) { arrived<0, 1>(&ring[decltype(q)::value]); });
+
+    // ---- y out: rows through LDS, whole lines ----
+    if (p.ss) {
+        slice_sums([&](int i, int sl, float v) __attribute__((always_inline)) {
+            const int row = m0 + 32 * i + l32;
+            if (hf == 0 && row < M) p.ss[(int64_t)row * (D / 64) + wave * (NJ / 2) + sl] = v;
+        });
+    }
+    lds_barrier();
+    constexpr int kRowB = CW * 4, kPieces = kRowB / 16;  // fp32 bytes and 16-byte pieces of a wave's part of a row
+    uint8_t *tr = lds + wave * (32 * kRowB);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *(float4 *)(tr + l32 * kRowB + (((8 * j + 2 * g + hf) ^ r15) * 16)) =
+                    float4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+#pragma unroll
+        for (int it = 0; it < 32 * kPieces / 64; ++it) {
+            const int id = it * 64 + lane, r = id / kPieces, c = id % kPieces, row = m0 + 32 * i + r, col = col0 + 4 * c;
+            const float4 v = *(const float4 *)(tr + r * kRowB + ((c ^ (r & 15)) * 16));
+            if (row < M) {
+                *(float4 *)(p.y + (int64_t)row * D + col) = v;
+                if (p.yb) {
+                    bf16x4 b;
+                    b[0] = (__bf16)v.x, b[1] = (__bf16)v.y, b[2] = (__bf16)v.z, b[3] = (__bf16)v.w;
+                    *(bf16x4 *)((__bf16 *)p.yb + (int64_t)row * D + col) = b;
+                }
+            }
+        }
+    }
+}
+
+template <int D, int RB, int NW, int R>
+hipError_t launch_tail(const TailArgs &a, hipStream_t s)
+{
+    constexpr size_t lds = tail_lds_bytes<D, RB, NW>();
+    constexpr auto kernel = layer_tail_kernel<D, RB, NW, R>;
+    const hipError_t e = raise_lds_limit<kernel>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((a.M + 32 * RB - 1) / (32 * RB))), dim3(NW * 64), lds, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// A launch takes the time of one workgroup until every CU has one; the separate launches grow with the rows.  us, this /
+// separate: d_model 512: 3072 rows 49 / 49, 4096 49 / 52, 8192 58 / 69, with 64-row tiles 8192 69 / 69, 12288 75 / 97;
+// d_model 256: 2048 rows 23.4 / 21.1, 3072 23.6 / 26.5, 8192 24 / 40.
+bool layer_tail_takes(int M, int D, int F)
+{
+    return F % 128 == 0 && F > 0 && ((D == 512 && M > (F % 256 == 0 ? 4096 : 8192)) || (D == 256 && M > 2560));
+}
+
+hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)
+{
+    if (a.M < 1 || a.F < 128 || a.F % 128 != 0) return hipErrorInvalidValue;
+    // d_model 512, no more than a 32-row tile per CU: those (fewer rows in line behind one another); needs chunks of 256
+    if (a.D == 512) return a.M <= 8192 && a.F % 256 == 0 ? launch_tail<512, 1, 8, 8>(a, s) : launch_tail<512, 2, 4, 8>(a, s);
+    if (a.D == 256) return launch_tail<256, 2, 4, 8>(a, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace climber

@@ -112,6 +112,27 @@ int pack_layers(const climber_config *cfg, const climber_layer_weights *layers, 
     return CLIMBER_OK;
 }
 
+// attention output rows -> y (f_FFN and the residual stream), `rows` rows from row r0 of the workspace's arrays.
+// x, y: fp32 rows of the residual stream; norm_out: also the bf16 copy and sums of squares of y.
+int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x, float *y, bool norm_out,
+               int64_t r0, int64_t rows, const Workspace &ws, hipStream_t s)
+{
+    const int d = cfg->d_model, F = cfg->d_ffn, M = (int)rows;
+    const uint8_t *o = ws.o + (size_t)r0 * d * 2;
+    uint8_t *xb = ws.xb + (size_t)r0 * d * 2;
+    float *ss = ws.ss + (size_t)r0 * (d / 64);
+    const RowNormIn nin{ss, d / 64, 1.f / (float)d, cfg->rms_eps}, no_in{nullptr, 0, 0.f, 0.f};
+    const RowNormOut nout{ss, xb, d}, no_out{nullptr, nullptr, 0};
+    if (layer_tail_takes(M, d, F))
+        return rt(layer_tail_bf16(TailArgs{o, x, pw.wo, pw.w1, pw.w2, y, norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F,
+                                           nin.inv_d, nin.eps}, s));
+    float *h = ws.h32 + (size_t)r0 * d;
+    uint8_t *u = ws.u + (size_t)r0 * F * 2;
+    TRY(rt(gemm_bf16(EPI_RESID_F32, o, d, pw.wo, M, d, d, h, d, x, d, no_in, nout, 0, s)));
+    TRY(rt(gemm_bf16(EPI_GELU_BF16, xb, d, pw.w1, M, F, d, u, F, nullptr, 0, nin, no_out, kTiledC, s)));
+    return rt(gemm_bf16(EPI_RESID_F32, u, F, pw.w2, M, d, F, y, d, h, d, no_in, norm_out ? nout : no_out, kTiledA, s));
+}
+
 // one layer on `rows` rows.  x_in: fp32 rows (the residual stream); xb_in / ws.ss: their bf16 copy and
 // row sums of squares (from the previous layer's last projection or from a row_prep kernel).
 // norm_out: also emit the bf16 copy and sums of squares of x_out (the next layer needs them).
@@ -120,9 +141,9 @@ int run_layer(const climber_config *cfg, const PackedLayer &pw, const float *tau
               bool norm_out, const int32_t *scen, const int32_t *beh, const int32_t *cand_off,
               int32_t m_total, int32_t m_max, int64_t rows, const Workspace &ws, hipStream_t s)
 {
-    const int d = cfg->d_model, F = cfg->d_ffn, M = (int)rows;
-    const RowNormIn nin{ws.ss, d / 64, 1.f / (float)d, cfg->rms_eps}, no_in{nullptr, 0, 0.f, 0.f};
-    const RowNormOut nout{ws.ss, ws.xb, d}, no_out{nullptr, nullptr, 0};
+    const int d = cfg->d_model, M = (int)rows;
+    const RowNormIn nin{ws.ss, d / 64, 1.f / (float)d, cfg->rms_eps};
+    const RowNormOut no_out{nullptr, nullptr, 0};
     QkvToCache qc;
     if (mode == CLIMBER_MODE_HISTORY && cache_direct_target(cfg, cache, layer, &qc)) {
         // the projection's epilogue writes keys and values into the cache as operand fragments; only
@@ -148,11 +169,7 @@ int run_layer(const climber_config *cfg, const PackedLayer &pw, const float *tau
                                   scen, beh, ws.o, d, s));
         }
     }
-    TRY(rt(gemm_bf16(EPI_RESID_F32, ws.o, d, pw.wo, M, d, d, ws.h32, d, x_in, d, no_in, nout, 0, s)));
-    TRY(rt(gemm_bf16(EPI_GELU_BF16, ws.xb, d, pw.w1, M, F, d, ws.u, F, nullptr, 0, nin, no_out, kTiledC, s)));
-    TRY(rt(gemm_bf16(EPI_RESID_F32, ws.u, F, pw.w2, M, d, F, x_out, d, ws.h32, d, no_in,
-                     norm_out ? nout : no_out, kTiledA, s)));
-    return CLIMBER_OK;
+    return layer_tail(cfg, pw, x_in, x_out, norm_out, 0, rows, ws, s);
 }
 
 int check_layer_weights(const climber_layer_weights *w)
@@ -413,20 +430,18 @@ int climber_bgf_score(const climber_config *cfg, const climber_bgf_weights *w, c
         TRY(rt(pack_weights(jobs, s)));
     }
     const PackedLayer pw = packed_layer(&one, ws, 0);
-    const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps}, no_in{nullptr, 0, 0.f, 0.f};
-    const RowNormOut nout{ws.ss, ws.xb, d}, no_out{nullptr, nullptr, 0};
+    const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps};
+    const RowNormOut no_out{nullptr, nullptr, 0};
     // G = ATL(E) on the m * n_blocks rows: the layer of the stack with the fusion attention in the middle
     TRY(rt(row_prep_f32(e, ws.xb, ws.ss, np, R, d, s)));
     TRY(rt(gemm_bf16(EPI_STORE_BF16, ws.xb, d, pw.wqkv, (int)R, 3 * d, d, ws.qkv, 3 * d, nullptr, 0, nin, no_out, 0, s)));
     TRY(rt(launch_bgf_attention(ws.qkv, ws.o, cand_scen, w->tau_scen, cfg->n_scen, m_total, nb, cfg->n_heads,
                                 cfg->qk_scale, s)));
-    TRY(rt(gemm_bf16(EPI_RESID_F32, ws.o, d, pw.wo, (int)R, d, d, ws.h32, d, e, d, no_in, nout, 0, s)));
-    TRY(rt(gemm_bf16(EPI_GELU_BF16, ws.xb, d, pw.w1, (int)R, F, d, ws.u, F, nullptr, 0, nin, no_out, kTiledC, s)));
-    TRY(rt(gemm_bf16(EPI_RESID_F32, ws.u, F, pw.w2, (int)R, d, F, ws.x32, d, ws.h32, d, no_in, nout, kTiledA, s)));
+    TRY(layer_tail(&one, pw, e, ws.x32, true, 0, R, ws, s));
     // f_gate on the flattened G (its bf16 copy, [m][n_blocks * d]): down, ReLU, up; then sigmoid,
     // Hadamard product and the head in one pass over G
-    TRY(rt(gemm_bf16(EPI_RELU_BF16, ws.xb, nd, down_p, m_total, dg, nd, ws.o, dg, nullptr, 0, no_in, no_out, 0, s)));
-    TRY(rt(gemm_bf16(EPI_STORE_BF16, ws.o, dg, up_p, m_total, nd, dg, ws.qkv, nd, nullptr, 0, no_in, no_out, 0, s)));
+    TRY(rt(gemm_bf16(EPI_RELU_BF16, ws.xb, nd, down_p, m_total, dg, nd, ws.o, dg, nullptr, 0, RowNormIn{}, no_out, 0, s)));
+    TRY(rt(gemm_bf16(EPI_STORE_BF16, ws.o, dg, up_p, m_total, nd, dg, ws.qkv, nd, nullptr, 0, RowNormIn{}, no_out, 0, s)));
     return rt(launch_bgf_gate_head(ws.x32, ws.qkv, w->w_head, w->b_head, y, score, m_total, nd, s));
 }
 
@@ -452,7 +467,7 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
     if (ws_bytes < ws.total) return CLIMBER_ERR_BUFSIZE;
     if (R == 0) return CLIMBER_OK;
     hipStream_t s = (hipStream_t)stream;
-    const int d = cfg->d_model, F = cfg->d_ffn, np = d / 64;
+    const int d = cfg->d_model, np = d / 64;
     TRY(stage_weights(cfg, weights, ws, s));
     // rows [0, T): the padded history rows of the batch; rows [T, R): the candidates
     TRY(rt(row_prep_bf16(x_hist, ws.x32, ws.ss, np, T, d, s)));
@@ -460,7 +475,7 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
     if (T) TRY(rt(hipMemcpyAsync(ws.xb, x_hist, (size_t)T * d * 2, hipMemcpyDeviceToDevice, s)));
     if (m_total)
         TRY(rt(hipMemcpyAsync(ws.xb + (size_t)T * d * 2, x_cand, (size_t)m_total * d * 2, hipMemcpyDeviceToDevice, s)));
-    const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps}, no_in{nullptr, 0, 0.f, 0.f};
+    const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps};
     const RowNormOut no_out{nullptr, nullptr, 0};
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
     for (int l = 0; l < cfg->n_layers; ++l) {
@@ -502,16 +517,7 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
         // output projection and feed-forward on the rows that go on: all of them, or the candidates only
         const int64_t r0 = hist_out ? 0 : T, nr = R - r0;
         if (nr == 0) continue;
-        const RowNormIn nin_r{ws.ss + (size_t)r0 * np, np, 1.f / (float)d, cfg->rms_eps};
-        const RowNormOut nout_r{ws.ss + (size_t)r0 * np, ws.xb + (size_t)r0 * d * 2, d};
-        float *x_r = ws.x32 + (size_t)r0 * d, *h_r = ws.h32 + (size_t)r0 * d;
-        uint8_t *u_r = ws.u + (size_t)r0 * F * 2;  // r0 is a multiple of 64: whole groups of 16 rows
-        TRY(rt(gemm_bf16(EPI_RESID_F32, ws.o + (size_t)r0 * d * 2, d, pw.wo, (int)nr, d, d, h_r, d, x_r, d, no_in,
-                         nout_r, 0, s)));
-        TRY(rt(gemm_bf16(EPI_GELU_BF16, ws.xb + (size_t)r0 * d * 2, d, pw.w1, (int)nr, F, d, u_r, F, nullptr, 0, nin_r,
-                         no_out, kTiledC, s)));
-        TRY(rt(gemm_bf16(EPI_RESID_F32, u_r, F, pw.w2, (int)nr, d, F, x_r, d, h_r, d, no_in, last ? no_out : nout_r,
-                         kTiledA, s)));
+        TRY(layer_tail(cfg, pw, ws.x32 + (size_t)r0 * d, ws.x32 + (size_t)r0 * d, !last, r0, nr, ws, s));
     }
     if (y_hist && T) TRY(rt(hipMemcpyAsync(y_hist, ws.x32, (size_t)T * d * 4, hipMemcpyDeviceToDevice, s)));
     if (m_total)
