@@ -91,7 +91,9 @@ hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s);
 struct TailArgs {
     const void *o;
     const float *x;
-    const void *wo, *w1, *w2;
+    const void *wo;   // the three packed weights are one block of memory: wo here,
+    int w1, w2;       // w1 and w2 that many bytes further on,
+    int w_bytes;      // all of them in so many bytes (< 2^31)
     float *y;
     void *yb;
     float *ss;

@@ -16,7 +16,7 @@
 // that they leave (32768 rows, d_model 512: 1.0 PFLOP/s, a large plain matrix product reaches 1.26) and, nearly as
 // much, by the weights' way through the vector cache (4.7 MB per workgroup at 64 bytes per clock).  32768 rows: d_model
 // 512 154 us against 230 as three launches, d_model 256 52 against 87.  32 rows (RB = 1, NW = 8) where 64 would leave
-// CUs without work: bound by the weights out of L2 (20 TB/s over the chip); 8192 rows 58 us against 69.  (Taller tiles
+// CUs without work: bound by the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 58 us against 69.  (Taller tiles
 // would need less of the caches, but 128 rows do not fit the registers; separate waves for the two products gave
 // the same times.)
 // Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
@@ -36,19 +36,11 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef const __attribute__((address_space(1))) uint8_t glb_u8;
 
-// (Inline assembly: the loads stay in flight across barriers and phases, which the compiler would not allow; a
-// fragment is valid after the wait that names its registers, and until then nothing may move them: the kernel has to
-// fit its registers without spills.)
-__device__ __forceinline__ void load_frag(u32x4 &f, uint32_t lane_off, const uint8_t *base)
+// A fragment of the weights: 16 bytes per lane at a wave-uniform offset.  (Through the buffer builtin: the compiler
+// counts the loads in flight itself, and an address takes one vector register throughout.)
+__device__ __forceinline__ void load_frag(u32x4 &f, uint32_t lane_off, __amdgpu_buffer_rsrc_t w, int at)
 {
-    asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(f) : "v"(lane_off), "s"(base));
-}
-template <int VM, int N>
-__device__ __forceinline__ void arrived(u32x4 *f)
-{
-    if constexpr (N == 1) asm volatile("s_waitcnt vmcnt(%1)" : "+v"(f[0]) : "n"(VM));
-    else if constexpr (N == 2) asm volatile("s_waitcnt vmcnt(%2)" : "+v"(f[0]), "+v"(f[1]) : "n"(VM));
-    else asm volatile("s_waitcnt vmcnt(%4)" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]) : "n"(VM));
+    f = __builtin_amdgcn_raw_buffer_load_b128(w, (int)lane_off, at, 0);
 }
 // every wave's LDS accesses so far are done (the weights' loads stay in flight)
 __device__ __forceinline__ void lds_barrier()
@@ -67,7 +59,7 @@ constexpr int tail_lds_bytes()
 }
 
 // The next fragments of the stream of weights: fragment e at base + (e % NJ) * a + (e / NJ) * b.
-struct Next { const uint8_t *base; int64_t a, b; };
+struct Next { int base, a, b; };
 
 template <int D, int RB, int NW, int R>
 __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p)
@@ -113,8 +105,7 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
             load_block(acc[i][j], p.x + (int64_t)min(m0 + 32 * i + l32, M - 1) * D + col0 + 32 * j + 4 * hf);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    // (the compiler's own count of these loads ends here, not in the loops below)
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), here and not in the loops below
 #pragma unroll
     for (int i = 0; i < RB; ++i)
 #pragma unroll
@@ -122,15 +113,14 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
 
     // the stream of weight fragments, 1 KiB each: Wo; W1 of chunk 0; then, per chunk, W1 of the next and W2 of this one
     const uint32_t w_lane = lane * 16;
-    const uint8_t *const wo = (const uint8_t *)p.wo + (int64_t)(col0 / 32) * S * 1024;
-    const uint8_t *const w1 = (const uint8_t *)p.w1 + (int64_t)wave * S * 1024;
-    const uint8_t *const w2 = (const uint8_t *)p.w2 + (int64_t)(col0 / 32) * (F / 16) * 1024;
-    const int64_t w1_chunk = (int64_t)NW * S * 1024, w2_col = (int64_t)(F / 16) * 1024;
+    const __amdgpu_buffer_rsrc_t w = __builtin_amdgcn_make_buffer_rsrc((void *)p.wo, 0, p.w_bytes, 0x00020000);
+    const int wo = (col0 / 32) * S * 1024, w1 = p.w1 + wave * S * 1024, w2_col = (F / 16) * 1024, w2 = p.w2 + (col0 / 32) * w2_col;
+    constexpr int w1_chunk = NW * S * 1024;
     auto next_up = [&](int ch) __attribute__((always_inline)) { return Next{w1 + ch * w1_chunk, 1024, NJ * 1024}; };
-    auto next_down = [&](int ch) __attribute__((always_inline)) { return Next{w2 + (int64_t)ch * T * 1024, w2_col, 1024}; };
+    auto next_down = [&](int ch) __attribute__((always_inline)) { return Next{w2 + ch * T * 1024, w2_col, 1024}; };
     u32x4 ring[R];
     auto load_next = [&](auto slot_tag, const Next &n, int e) __attribute__((always_inline)) {
-        load_frag(ring[decltype(slot_tag)::value], w_lane, n.base + (e % NJ) * n.a + (e / NJ) * n.b);
+        load_frag(ring[decltype(slot_tag)::value], w_lane, w, n.base + (e % NJ) * n.a + (e / NJ) * n.b);
     };
     {
         const Next n{wo, S * 1024, 1024};
@@ -143,7 +133,6 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
     bf16x8 fa[2][RB];
     auto mfma_step = [&](auto q_tag, auto &&refill, auto &&reload, auto &&between) __attribute__((always_inline)) {
         constexpr int q = decltype(q_tag)::value;
-        arrived<R - NJ, NJ>(&ring[q]);
         __builtin_amdgcn_sched_barrier(0);
         static_for<RB * NJ>([&](auto m_tag) __attribute__((always_inline)) {
             constexpr int m = decltype(m_tag)::value, i = m / NJ, j = m % NJ;
@@ -167,7 +156,7 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
                       [&](int i) __attribute__((always_inline)) { if (!LAST || u < 7) fa[0][i] = frag(X, x_base, kXPitch, s0 + u + 1, i); },
                       [&](auto j_tag) __attribute__((always_inline)) {
                           constexpr int j = decltype(j_tag)::value;
-                          load_frag(ring[q + j], w_lane, LAST && un >= 8 ? w1 + ((un - 8) * NJ + j) * 1024 : wo + j * (S * 1024) + (s0 + un) * 1024);
+                          load_frag(ring[q + j], w_lane, w, LAST && un >= 8 ? w1 + ((un - 8) * NJ + j) * 1024 : wo + j * (S * 1024) + (s0 + un) * 1024);
                       },
                       nothing);
         });
@@ -221,7 +210,7 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
     f32x16 hid[RB];
     bf16x4 hb[RB][4];
     // hid = h W1 of a chunk
-    auto up = [&](const uint8_t *w1c, const Next &n) __attribute__((always_inline)) {
+    auto up = [&](int w1c, const Next &n) __attribute__((always_inline)) {
         uint32_t x_at = x_base;
         asm("" : "+v"(x_at));  // (the k-steps' addresses are made anew for every chunk, not kept in registers throughout)
 #pragma unroll
@@ -236,7 +225,6 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
             constexpr bool LAST = decltype(last_tag)::value;
             static_for<R>([&](auto u_tag) __attribute__((always_inline)) {
                 constexpr int u = decltype(u_tag)::value;
-                arrived<R - 1, 1>(&ring[u]);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int i = 0; i < RB; ++i) {
@@ -244,7 +232,7 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
                     if (!LAST || u < R - 2) fa[u & 1][i] = frag(X, x_at, kXPitch, s0 + u + 2, i);
                     if (i == RB - 1) {
                         if constexpr (LAST) load_next(u_tag, n, u);
-                        else load_frag(ring[u], w_lane, w1c + (s0 + u + R) * 1024);
+                        else load_frag(ring[u], w_lane, w, w1c + (s0 + u + R) * 1024);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -327,7 +315,6 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
         lds_barrier();  // chunk ch + 1 is there
     }
     down(n_chunks - 1, next_down(n_chunks - 1), std::false_type{});  // (what it loads ahead is not used)
-    static_for<R>([&](auto q) __attribute__((always_inline)) { arrived<0, 1>(&ring[decltype(q)::value]); });
 
     // ---- y out: rows through LDS, whole lines ----
     if (p.ss) {
@@ -388,7 +375,7 @@ hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)
 {
     if (a.M < 1 || a.F < 128 || a.F % 128 != 0) return hipErrorInvalidValue;
     // d_model 512, no more than a 32-row tile per CU: those (fewer rows in line behind one another); needs chunks of 256
-    if (a.D == 512) return a.M <= 8192 && a.F % 256 == 0 ? launch_tail<512, 1, 8, 8>(a, s) : launch_tail<512, 2, 4, 8>(a, s);
+    if (a.D == 512) return a.M <= 8192 && a.F % 256 == 0 ? launch_tail<512, 1, 8, 16>(a, s) : launch_tail<512, 2, 4, 8>(a, s);
     if (a.D == 256) return launch_tail<256, 2, 4, 8>(a, s);
     return hipErrorInvalidValue;
 }

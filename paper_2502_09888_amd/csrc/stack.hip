@@ -124,8 +124,8 @@ int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x,
     const RowNormIn nin{ss, d / 64, 1.f / (float)d, cfg->rms_eps}, no_in{nullptr, 0, 0.f, 0.f};
     const RowNormOut nout{ss, xb, d}, no_out{nullptr, nullptr, 0};
     if (layer_tail_takes(M, d, F))
-        return rt(layer_tail_bf16(TailArgs{o, x, pw.wo, pw.w1, pw.w2, y, norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F,
-                                           nin.inv_d, nin.eps}, s));
+        return rt(layer_tail_bf16(TailArgs{o, x, pw.wo, (int)(pw.w1 - pw.wo), (int)(pw.w2 - pw.wo), (int)(pw.w2 - pw.wo) + d * F * 2, y,
+                                           norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F, nin.inv_d, nin.eps}, s));
     float *h = ws.h32 + (size_t)r0 * d;
     uint8_t *u = ws.u + (size_t)r0 * F * 2;
     TRY(rt(gemm_bf16(EPI_RESID_F32, o, d, pw.wo, M, d, d, h, d, x, d, no_in, nout, 0, s)));
