@@ -1,8 +1,8 @@
 // fp32 reference-path attention: one wavefront per (query row, head), every softmax row held in
 // LDS.  Covers both masks of Climber (arXiv 2502.09888): the "single user, multiple items" mask of
 // Sec. 3.2 (a candidate sees the cached history and itself) and the per-subsequence history
-// attention of Sec. 3.1.2, with the per-row temperature of Eq. (3).  Any d_head <= 256; meant for
-// the small fp32 configuration and as a second opinion, not for throughput.
+// attention of Sec. 3.1.2, with the per-row temperature of Eq. (3).  Any d_head <= 256, with or without the relative
+// bias; the usual widths without a bias go to attn_tile_f32.hip.
 #include "internal.h"
 
 namespace climber {
@@ -111,6 +111,7 @@ hipError_t launch_attn_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, hip
     const int64_t grid = a.total_q_rows * a.H;
     if (grid == 0) return hipSuccess;
     if (grid > 0x7fffffff || a.max_hist_len > kMaxKeysF32) return hipErrorInvalidValue;
+    if (attn_tile_f32_takes(a)) return launch_attn_tile_f32(a, sumi, cache_rows, false, s);
     const size_t shmem = (size_t)(a.max_hist_len + 1) * sizeof(float);
     if (sumi)
         hipLaunchKernelGGL(attn_f32_kernel<true>, dim3((unsigned)grid), dim3(64), shmem, s, a, cache_rows);

@@ -136,15 +136,6 @@ int attn_history_strided(const climber_config *cfg, const float *tau_layer, cons
     // short subsequences, bf16: one kernel writes the cache and attends (K/V rows read once)
     const bool fused = cfg->dtype == CLIMBER_BF16 && o && !bias && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) &&
                        hist_fused_supported(cfg->sub_len, (cfg->flags & CLIMBER_HIST_CAUSAL) != 0);
-    if (fused) {
-    } else if (cfg->dtype == CLIMBER_BF16) {
-        int e = rt(launch_kv_write_bf16(cv, k, v, ld, cfg->n_heads, cache->max_pad, s));
-        if (e) return e;
-    } else {
-        int e = rt(launch_kv_write_f32(cv, k, v, ld, cfg->n_heads, cfg->d_head, cache->rows, s));
-        if (e) return e;
-    }
-    if (!o) return CLIMBER_OK;
     AttnArgs a = base_args(cfg, cache, layer, tau_layer);
     a.q = q;
     a.k_self = k;  // a history row's own key seeds its softmax reference
@@ -159,6 +150,20 @@ int attn_history_strided(const climber_config *cfg, const float *tau_layer, cons
     a.total_q_rows = cache->rows;
     if (bias) a.bias = BiasArgs{bias->pos_table, bias->time_table, bias->hist_pos, bias->hist_ts, bias->hist_pos,
                                 bias->hist_ts, bias->n_pos, bias->n_time};
+    // fp32: likewise, unless the output lies on the rows that other workgroups still read
+    const size_t row_bytes = (size_t)cache->rows * ld * 4, o_bytes = (size_t)cache->rows * ld_o * 4;
+    auto apart = [&](const void *x) { return (uintptr_t)x + row_bytes <= (uintptr_t)o || (uintptr_t)o + o_bytes <= (uintptr_t)x; };
+    const bool fused_f32 = cfg->dtype == CLIMBER_F32 && o && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) && attn_tile_f32_takes(a) && apart(k) && apart(v);
+    if (fused || fused_f32) {
+    } else if (cfg->dtype == CLIMBER_BF16) {
+        int e = rt(launch_kv_write_bf16(cv, k, v, ld, cfg->n_heads, cache->max_pad, s));
+        if (e) return e;
+    } else {
+        int e = rt(launch_kv_write_f32(cv, k, v, ld, cfg->n_heads, cfg->d_head, cache->rows, s));
+        if (e) return e;
+    }
+    if (!o) return CLIMBER_OK;
+    if (fused_f32) return rt(launch_attn_tile_f32(a, false, cache->rows, true, s));
     if (fused) return rt(launch_hist_fused_bf16(a, s));
     if (cfg->dtype == CLIMBER_BF16) return rt(launch_attn_hist_bf16(a, s));
     return rt(launch_attn_f32(a, false, cache->rows, s));

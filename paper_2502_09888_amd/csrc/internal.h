@@ -64,6 +64,10 @@ hipError_t launch_hist_fused_bf16(const AttnArgs &a, hipStream_t s);
 // fp32 reference-path attention (attn_f32.hip); the cache layer holds plain [rows][H][dh] K then V
 hipError_t launch_attn_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, hipStream_t s);
 size_t attn_f32_max_keys();
+// the same on the matrix cores for the widths it has (attn_tile_f32.hip); write_cache (history): keys and values come from
+// the rows a.k_self / a.v_self, which nothing in the launch may overwrite, and go into the cache as well
+bool attn_tile_f32_takes(const AttnArgs &a);
+hipError_t launch_attn_tile_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, bool write_cache, hipStream_t s);
 
 // cache writers (kv_cache.hip): k, v are [rows][ld] with head h at column h*d_head
 hipError_t launch_kv_write_bf16(const CacheView &c, const void *k, const void *v, int64_t ld, int H,

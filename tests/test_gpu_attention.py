@@ -49,6 +49,34 @@ def test_fp32_subsequences_causal_ragged():
     check_all(w, causal=True)
 
 
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("L,sub,M", [(1, 0, 1), (15, 0, 16), (16, 5, 17), (49, 17, 33), (65, 0, 15), (130, 48, 5), (300, 64, 31)])
+def test_fp32_tiles(dh, L, sub, M):
+    # 16 queries and 16 keys a tile, keys over four waves: fewer keys than waves, remainders of both tiles, subsequences
+    # that end inside one; ragged lengths (NaN in the padding), one- and two-kernel history pass.  TOL: see above.
+    spec = W.shrink(W.CONFIG1, name=f"f32-tiles-{dh}-{L}-{sub}", B=3, L=L, L_min=int(L == 1), M=M, M_min=1, sub_len=sub, pad_to=3,
+                    nan_padding=True, dh=dh, H=2, seed=300 + L)
+    w = W.make_attention(spec)
+    check_all(w)
+    check_all(w, causal=True)
+    check_all(w, flags=TWO_KERNEL)
+
+
+def test_fp32_causal_keeps_later_values_out():
+    # an infinite value (and NaN) of a later key reaches no query that does not see it
+    spec = W.shrink(W.CONFIG1, name="f32-later", B=1, L=40, sub_len=20, M=3, dh=32, H=1, seed=17)
+    w = W.make_attention(spec)
+    clean = GpuAttention(w, causal=True).history()
+    w["vh"] = w["vh"].copy()
+    w["vh"][7, 0, 3], w["vh"][30, 0, 5] = np.inf, np.nan
+    got = GpuAttention(w, causal=True).history()
+    touched = np.zeros(got.shape, bool)
+    touched[7:20, 3] = touched[30:40, 5] = True
+    # (the order of the additions may differ: a few roundings of 2^-24 on values of order 1)
+    assert max_abs(got[~touched], clean[~touched]) < 1e-5
+    assert not np.isfinite(got[touched]).any()
+
+
 def test_bf16_small_multi_tile_ragged_tail():
     # several key tiles, several query tiles, candidate count with a ragged tail
     spec = W.shrink(W.CONFIG2, name="bf16-small", B=3, L=384, sub_len=128, M=200, H=2, seed=21)
