@@ -76,10 +76,11 @@ __device__ __forceinline__ void wait_vm()
     else if (N == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
     else if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     else if (N == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+    else if (N == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
     else if (N == 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
     else if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     else if (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    else static_assert(N == 0 || N == 2 || N == 4 || N == 6 || N == 8 || N == 12 || N == 16, "unsupported vmcnt");
+    else static_assert(N == 0 || N == 2 || N == 3 || N == 4 || N == 6 || N == 8 || N == 12 || N == 16, "unsupported vmcnt");
 }
 
 // WM, WN: 32 x 32 blocks per wave along M and N.  Macro tile (2*WM*32) x (2*WN*32) x 32.
@@ -290,6 +291,10 @@ hipError_t dispatch(const GemmArgs &g, hipStream_t s)
     // macro tile 256 x 128 when that still gives every CU two workgroups, else 128 x 128
     const int64_t big_tiles = (int64_t)(g.N / 128) * ((g.M + 255) / 256);
     if (big_tiles >= 512) return launch<EPI, 4, 2, 3>(g, s);
+    // 64 x 128 where 128 x 128 would leave CUs without a tile.  us per call with / without: one
+    // request (1000 behaviours, 200 candidates, four layers) 271 / 285, 4 x 1500 behaviours with 300 candidates each 570 / 583,
+    // encode of 8 x 1024 308 / 336, score of 4352 rows 421 / 436; with all CUs taken (score of 8192 rows) 565 / 558
+    if ((int64_t)(g.N / 128) * ((g.M + 127) / 128) < 256) return launch<EPI, 1, 2, 4>(g, s);
     return launch<EPI, 2, 2, 4>(g, s);
 }
 

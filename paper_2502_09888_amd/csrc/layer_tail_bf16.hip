@@ -16,7 +16,8 @@
 // that they leave (32768 rows, d_model 512: 1.0 PFLOP/s, a large plain matrix product reaches 1.26) and, nearly as
 // much, by the weights' way through the vector cache (4.7 MB per workgroup at 64 bytes per clock).  32768 rows: d_model
 // 512 154 us against 230 as three launches, d_model 256 52 against 87.  32 rows (RB = 1, NW = 8) where 64 would leave
-// CUs without work: bound by the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 58 us against 69.  (Taller tiles
+// CUs without work: bound by the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 58 us against 69 with the weights
+// in L2, 76 between the other launches of a stack.  (Taller tiles
 // would need less of the caches, but 128 rows do not fit the registers; separate waves for the two products gave
 // the same times.)
 // Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
@@ -363,12 +364,13 @@ hipError_t launch_tail(const TailArgs &a, hipStream_t s)
 
 }  // namespace
 
-// A launch takes the time of one workgroup until every CU has one; the separate launches grow with the rows.  us, this /
-// separate: d_model 512: 3072 rows 49 / 49, 4096 49 / 52, 8192 58 / 69, with 64-row tiles 8192 69 / 69, 12288 75 / 97;
-// d_model 256: 2048 rows 23.4 / 21.1, 3072 23.6 / 26.5, 8192 24 / 40.
+// A launch takes the time of one workgroup until every CU has one; the separate launches grow with the rows.  Weights that
+// four layers and the cache between them have pushed out of L2 count here, so whole calls decide (score, four layers, with /
+// without, us): d_model 512: 4352 rows 470 / 430, 6144 500 / 474, 7168 508 / 507, 8192 552 / 558, with 64-row tiles 8704
+// 637 / 638, 10240 665 / 682, 16384 804 / 901; d_model 256: 2816 rows 177 / 181, 4096 180 / 187, 8192 250 / 313.
 bool layer_tail_takes(int M, int D, int F)
 {
-    return F % 128 == 0 && F > 0 && ((D == 512 && M > (F % 256 == 0 ? 4096 : 8192)) || (D == 256 && M > 2560));
+    return F % 128 == 0 && F > 0 && ((D == 512 && M > (F % 256 == 0 ? 7168 : 8192)) || (D == 256 && M > 2560));
 }
 
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)

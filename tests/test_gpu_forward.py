@@ -132,8 +132,8 @@ def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(m):
     assert np.array_equal(yc[:g.m_total], g.score())
 
 
-@pytest.mark.parametrize("d_model, d_ffn, users, m", [(512, 128, 22, 33), (512, 384, 22, 95), (512, 256, 11, 31),
-                                                         (512, 768, 11, 1), (256, 128, 7, 1), (256, 256, 7, 64)])
+@pytest.mark.parametrize("d_model, d_ffn, users, m", [(512, 128, 22, 33), (512, 384, 22, 95), (512, 256, 19, 31),
+                                                         (512, 768, 19, 1), (256, 128, 7, 1), (256, 256, 7, 64)])
 def test_layer_tail_in_one_launch_gives_the_bits_of_three(d_model, d_ffn, users, m):
     # users x 384 history rows and the candidates in one launch: more rows than the single-launch tail asks for, the
     # candidates alone fewer.  One, two and three chunks of the hidden; tiles of 64 and 32 rows, the last one with 1
