@@ -145,22 +145,17 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
         static_for<NPRE>([&](auto c) __attribute__((always_inline)) { issue_one(kt, (kt % kStages) * kStageBytes, c); });
     };
 
-    f32x16 acc[WM][WN];  // (residual rows are requested ahead of the copies: loads return in order)
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j) {
-            if constexpr (EPI == EPI_RESID_F32) {
-                load_block(acc[i][j], resid + (int64_t)min(m0 + 32 * (WM * wm + i) + l32, M - 1) * ldr + n0 + 32 * (WN * wn + j) + 4 * hf);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-            }
-        }
-
     // the first tiles start their way in before anything else is set up (accumulators, row
     // statistics, cache geometry: a microsecond or two that the copies' latency covers)
     for (int kt = 0; kt < kStages - 1 && kt < n_kt; ++kt) issue(kt);
+
+    f32x16 acc[WM][WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     // Input rows that were not normalised: r = 1/sqrt(mean(x^2) + eps) of row 32i + l32 scales the
     // whole output row (a lane's accumulators of block row i all belong to that one row).  The
@@ -264,7 +259,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
     }
 
     wave_epilogue<EPI, WM, WN>(acc, rs, user, lds + wave * 32 * epilogue_pitch<EPI, WN>(), m0 + 32 * WM * wm, n0 + WN * 32 * wn,
-                               lane, M, N, C, ldc, nout, tiled, qc);
+                               lane, M, N, C, ldc, resid, ldr, nout, tiled, qc);
 }
 
 template <int EPI, int WM, int WN, int kStages>

@@ -56,19 +56,23 @@ static __device__ __forceinline__ float gelu_erf(float x)
 // x^2 + y^2 + z^2 + w^2, one fixed order (the row sums of squares are the same bits whoever forms them)
 static __device__ __forceinline__ float sumsq4(float x, float y, float z, float w)
 {
-    return fmaf(w, w, fmaf(z, z, fmaf(y, y, x * x)));
+    return fmaf(w, w, fmaf(z, z, fmaf(x, x, y * y)));
 }
 
 // A lane's part of a 32 x 32 block of fp32 rows, as its accumulators hold it: x = row l32 of the block, from column
-// 4 (lane / 32) on.  The residual rows are the accumulators' start value: requested ahead of the products, and no
-// separate addition behind them.
-static __device__ __forceinline__ void load_block(f32x16 &acc, const float *x)
+// 4 (lane / 32) on.
+static __device__ __forceinline__ void load_block(f32x16 &v, const float *x)
 {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-        const float4 v = *(const float4 *)(x + 8 * g);
-        acc[4 * g] = v.x, acc[4 * g + 1] = v.y, acc[4 * g + 2] = v.z, acc[4 * g + 3] = v.w;
+        const float4 q = *(const float4 *)(x + 8 * g);
+        v[4 * g] = q.x, v[4 * g + 1] = q.y, v[4 * g + 2] = q.z, v[4 * g + 3] = q.w;
     }
+}
+static __device__ __forceinline__ void store_block(float *x, const f32x16 &v)
+{
+#pragma unroll
+    for (int g = 0; g < 4; ++g) *(float4 *)(x + 8 * g) = float4{v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
 }
 
 // 1/sqrt(mean(x^2) + eps) of one row from its partial sums of squares
@@ -156,10 +160,13 @@ constexpr int epilogue_pitch() { return WN * 32 * (EPI == EPI_RESID_F32 ? 4 : 2)
 // 32j + 8g + 4hf + 0..3] for g = r/4 -- four consecutive columns of ONE row.  The wave turns 32 rows x (WN*32)
 // columns around in its own corner `tr` of the (idle) LDS (32 rows of epilogue_pitch bytes) and stores whole
 // rows, 16 bytes per lane.  rs: scale of the lane's row of every block row (RMSNorm folded in).
+// A residual row is added to the finished sum of products, one rounding of it; as the accumulators' start value it
+// would have every partial sum rounded at the residual's magnitude (3 to 11 times the error).
 template <int EPI, int WM, int WN>
 static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], const float (&rs)[WM], const CacheUser (&user)[WM],
                                                      uint8_t *tr, int row0, int col_base, int lane, int M, int N, void *C,
-                                                     int64_t ldc, const RowNormOut &nout, int tiled, const QkvToCache &qc)
+                                                     int64_t ldc, const float *resid, int64_t ldr, const RowNormOut &nout,
+                                                     int tiled, const QkvToCache &qc)
 {
     const int l32 = lane & 31, hf = lane >> 5;
     constexpr bool F32 = EPI == EPI_RESID_F32;
@@ -168,6 +175,21 @@ static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], cons
     constexpr int kPitch = epilogue_pitch<EPI, WN>();  // bytes per staged row
     constexpr int kChunksPerRow = CW * kElem / 16;
     constexpr int kIters = 32 * kChunksPerRow / 64;   // 16-byte pieces per lane and block row
+    // Residual rows of block row i, all requested before anything waits for them (a load placed
+    // after a store would make the wait for it drain the stores as well: one memory round trip per
+    // 16 bytes).  Block row i + 1 is requested before block row i is stored.
+    float4 rsd[2][F32 ? kIters : 1];
+    auto load_resid = [&](int i, float4 *buf) __attribute__((always_inline)) {
+        if constexpr (F32) {
+#pragma unroll
+            for (int it = 0; it < kIters; ++it) {
+                const int id = it * 64 + lane, r = id / kChunksPerRow, cc = id % kChunksPerRow;
+                const int row = min(row0 + 32 * i + r, M - 1);
+                buf[it] = *(const float4 *)(resid + (int64_t)row * ldr + col_base + cc * 4);
+            }
+        }
+    };
+    load_resid(0, rsd[0]);
     // direct cache write: slots past a user's valid length hold zeros
     bool zero_row[WM];
 #pragma unroll
@@ -195,6 +217,7 @@ static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], cons
                     *(uint2 *)(tr + l32 * kPitch + col * 2) = *(const uint2 *)v;
                 }
             }
+        if (i + 1 < WM) load_resid(i + 1, rsd[(i + 1) & 1]);
         const int row_base = row0 + 32 * i;
         if (EPI == EPI_STORE_BF16 && qc.layer_base) {
             // the wave's 32 x 64 block is one head of the queries, keys or values of 32 tokens of one
@@ -210,7 +233,9 @@ static __device__ __forceinline__ void wave_epilogue(f32x16 (&acc)[WM][WN], cons
             uint4 val = *(const uint4 *)(tr + r * kPitch + cc * 16);
             if (F32) {
                 const int col = col_base + cc * 4;
-                const float4 o = *(const float4 *)&val;
+                const float4 rd = rsd[i & 1][it];
+                float4 o = *(const float4 *)&val;
+                o.x += rd.x; o.y += rd.y; o.z += rd.z; o.w += rd.w;
                 if (row < M) {
                     *(float4 *)((float *)C + (int64_t)row * ldc + col) = o;
                     if (nout.ss) {

@@ -64,13 +64,6 @@ __global__ __launch_bounds__(128) void gemm_small_kernel(
     }
     const __bf16 *w_src = Wp + ((int64_t)(n0 / 32 + wn) * S * 64 + lane) * 8;
 
-    f32x16 acc;  // (the residual rows are requested ahead of the operands: loads return in order)
-    if constexpr (F32) {
-        load_block(acc, resid + (int64_t)min(row, M - 1) * ldr + n0 + 32 * wn + 4 * hf);
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    }
     bf16x8 fa[D], fw[D];
     auto load = [&](int s, int slot) __attribute__((always_inline)) {
         fw[slot] = *(const bf16x8 *)(w_src + (int64_t)s * 512);
@@ -80,7 +73,7 @@ __global__ __launch_bounds__(128) void gemm_small_kernel(
     for (int s = 0; s < D; ++s) load(s, s);
 
     // what the epilogue needs of global memory is requested behind the first operands: the partial sums of
-    // squares of the input rows (the lane's accumulators belong to row l32 of the tile)
+    // squares of the input rows (the lane's accumulators belong to row l32 of the tile), or the residual rows
     const bool scaled = !F32 && nin.ss, ss_fast = scaled && (nin.n_part == 8 || nin.n_part == 4);
     float4 raw_ss[2] = {};
     if (ss_fast) {
@@ -88,10 +81,21 @@ __global__ __launch_bounds__(128) void gemm_small_kernel(
         raw_ss[0] = *(const float4 *)p;
         raw_ss[1] = *(const float4 *)(p + (nin.n_part == 8 ? 4 : 0));
     }
+    float4 rsd[4];
+    if constexpr (F32) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int id = (4 * wn + it) * 64 + lane, r = id >> 4, cc = id & 15;
+            rsd[it] = *(const float4 *)(resid + (int64_t)min(m0 + r, M - 1) * ldr + n0 + cc * 4);
+        }
+    }
     CacheUser user{0, 64, 0};
     const bool to_cache = EPI == EPI_STORE_BF16 && qc.layer_base;
     if (to_cache) user = cache_user(qc, __builtin_amdgcn_readfirstlane(min(m0, M - 32)));
 
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     for (int s0 = 0; s0 + D < S; s0 += D) {
 #pragma unroll
         for (int s = 0; s < D; ++s) {
@@ -136,7 +140,9 @@ __global__ __launch_bounds__(128) void gemm_small_kernel(
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int id = (4 * wn + it) * 64 + lane, r = id >> 4, cc = id & 15, out = m0 + r, col = n0 + cc * 4;
-            const float4 o = *(const float4 *)(tr + r * kPitch + cc * 16);
+            float4 o = *(const float4 *)(tr + r * kPitch + cc * 16);
+            const float4 rd = rsd[it];
+            o.x += rd.x; o.y += rd.y; o.z += rd.z; o.w += rd.w;
             if (out < M) {
                 *(float4 *)((float *)C + (int64_t)out * ldc + col) = o;
                 if (nout.ss) {

@@ -3,8 +3,8 @@
 // for row counts that fill the chip.  As three launches, h (fp32 and bf16), its row sums and the feed-forward
 // hidden (d_ffn columns) go out to memory and come back: at d_model 512, d_ffn 2048 a row moves 20 KiB, of which 6
 // are the row's own input and output, and the launches wait for those bytes about as long as for their products.
-// Here a workgroup owns 32*RB rows and all their columns: h stays in accumulators (the feed-forward's second product
-// accumulates right on top of it), its bf16 copy and one chunk of the hidden live in LDS, and only weights -- packed
+// Here a workgroup owns 32*RB rows and all their columns: the bf16 copy of h and one chunk of the hidden live in LDS,
+// h itself in registers or (64 rows of 512 columns) in the rows of y until y replaces it, and only weights -- packed
 // fragments, L2-resident -- stream in, straight into registers.
 //
 // NW waves side by side over the columns: a wave owns D / NW columns of h / y and 32 columns of every chunk of the
@@ -12,14 +12,14 @@
 // dealt out between the matrix instructions (neither waits for the other's pipe).  The weight fragments of all
 // products form one stream of loads, R in flight per wave across phase changes and barriers; rows of LDS operands are
 // XOR-swizzled so that the fragment reads are conflict-free.
-// 64 rows (RB = 2, NW = 4), two workgroups per CU (80 KiB of LDS at d_model 512): bound by the matrix cores at the clock
-// that they leave (32768 rows, d_model 512: 1.0 PFLOP/s, a large plain matrix product reaches 1.26) and, nearly as
-// much, by the weights' way through the vector cache (4.7 MB per workgroup at 64 bytes per clock).  32768 rows: d_model
-// 512 154 us against 230 as three launches, d_model 256 52 against 87.  32 rows (RB = 1, NW = 8) where 64 would leave
-// CUs without work: bound by the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 58 us against 69 with the weights
-// in L2, 76 between the other launches of a stack.  (Taller tiles
-// would need less of the caches, but 128 rows do not fit the registers; separate waves for the two products gave
-// the same times.)
+// 64 rows (RB = 2): bound by the matrix cores at the clock that they leave and, nearly as much, by the weights' way
+// through the vector cache (4.7 MB per workgroup at 64 bytes per clock).  32768 rows in a stack: d_model 512 with eight
+// waves and h in registers 180 us, four waves and h by way of memory about 200 (64 MB out and back, by all workgroups at
+// once), h as the start value of the second sum 169, at 3 to 11 times the rounding error; three launches 230.  d_model
+// 256 (four waves, two workgroups per CU) 57 against 87.  32 rows (RB = 1) where 64 would leave CUs without work: bound by
+// the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 76 us between the other
+// launches of a stack.  (Taller tiles would need less of the caches, but 128 rows do not fit the registers; separate waves
+// for the two products gave the same times.)
 // Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
 // bits.
 #include "gemm_common.h"
@@ -101,16 +101,57 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
         }
     }
     f32x16 acc[RB][NJ];  // the lane's accumulators are [row 32i + l32][col0 + 32j + 8g + 4hf + 0..3]
+    auto clear_acc = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < RB; ++i)
+        for (int i = 0; i < RB; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            load_block(acc[i][j], p.x + (int64_t)min(m0 + 32 * i + l32, M - 1) * D + col0 + 32 * j + 4 * hf);
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+    clear_acc();
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), here and not in the loops below
+    // Both residuals join a finished sum (see wave_epilogue), so h exists beside the accumulators of the second one: in
+    // registers where they suffice, else in the rows of y, from which a lane reads back what it wrote itself.
+    constexpr int NB = RB * NJ;
+    constexpr bool kKeep = NB <= 4;
+    constexpr int kAhead = kKeep ? NB : 1;  // blocks of residual rows requested ahead of the end of a product
+    f32x16 side[kAhead];
+    // (offsets made where they are used: held across the products they would cost registers the loops have not got)
+    struct Rows { int64_t at[RB]; };
+    auto rows = [&]() __attribute__((always_inline)) {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        Rows r;
 #pragma unroll
-    for (int i = 0; i < RB; ++i)
+        for (int i = 0; i < RB; ++i) r.at[i] = (int64_t)min(m0 + 32 * i + (l & 31), M - 1) * D + col0 + 4 * (l >> 5);
+        return r;
+    };
+    auto request_rows = [&](const float *from) __attribute__((always_inline)) {
+        const Rows at = rows();
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(acc[i][j]));
+        for (int b = 0; b < kAhead; ++b) load_block(side[b], from + at.at[b / NJ] + 32 * (b % NJ));
+    };
+    auto add_rows = [&](const float *from) __attribute__((always_inline)) {  // acc += rows, block by block
+        const Rows at = rows();
+        static_for<NB>([&](auto b_tag) __attribute__((always_inline)) {
+            constexpr int b = decltype(b_tag)::value;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[b / NJ][b % NJ][r] += side[b % kAhead][r];
+            if constexpr (b + kAhead < NB) load_block(side[b % kAhead], from + at.at[(b + kAhead) / NJ] + 32 * ((b + kAhead) % NJ));
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+
+    auto keep_rows = [&]() __attribute__((always_inline)) {
+        const Rows at = rows();
+        static_for<NB>([&](auto b_tag) __attribute__((always_inline)) {
+            constexpr int b = decltype(b_tag)::value;
+            if constexpr (kKeep) side[b] = acc[b / NJ][b % NJ];
+            else if (m0 + 32 * (b / NJ) + l32 < M) store_block(p.y + at.at[b / NJ] + 32 * (b % NJ), acc[b / NJ][b % NJ]);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
 
     // the stream of weight fragments, 1 KiB each: Wo; W1 of chunk 0; then, per chunk, W1 of the next and W2 of this one
     const uint32_t w_lane = lane * 16;
@@ -164,7 +205,10 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
     };
 #pragma unroll 1
     for (int s0 = 0; s0 + 8 < S; s0 += 8) o_steps(s0, std::false_type{});
+    request_rows(p.x);
     o_steps(S - 8, std::true_type{});
+    add_rows(p.x);  // h
+    keep_rows();
     // sums of squares of the rows' 64-column slices, as the separate launches form them
     auto slice_sums = [&](auto &&put) __attribute__((always_inline)) {
 #pragma unroll
@@ -202,6 +246,7 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
                 for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[i][j][4 * g + e];
                 write_a(X, kXPitch, i, col0 + 32 * j + 8 * g, v);
             }
+    clear_acc();
     float rs[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) rs[i] = row_scale(RowNormIn{ss, D / 64, p.inv_d, p.eps}, 32 * i + l32);
@@ -315,7 +360,9 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
         write_hidden();
         lds_barrier();  // chunk ch + 1 is there
     }
+    if constexpr (!kKeep) request_rows(p.y);
     down(n_chunks - 1, next_down(n_chunks - 1), std::false_type{});  // (what it loads ahead is not used)
+    add_rows(p.y);  // y
 
     // ---- y out: rows through LDS, whole lines ----
     if (p.ss) {
@@ -376,8 +423,11 @@ bool layer_tail_takes(int M, int D, int F)
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)
 {
     if (a.M < 1 || a.F < 128 || a.F % 128 != 0) return hipErrorInvalidValue;
-    // d_model 512, no more than a 32-row tile per CU: those (fewer rows in line behind one another); needs chunks of 256
-    if (a.D == 512) return a.M <= 8192 && a.F % 256 == 0 ? launch_tail<512, 1, 8, 16>(a, s) : launch_tail<512, 2, 4, 8>(a, s);
+    // d_model 512: eight waves need chunks of 256; no more than a 32-row tile per CU: those (fewer rows in line behind one
+    // another).  Four waves hold twice the columns each, and h has to wait in memory.  Us, stack calls of four layers, eight
+    // / four waves: encode of 32768 rows 853 / 907, score of 8704 594 / 727, of 16384 772 / 919.
+    if (a.D == 512 && a.F % 256 == 0) return a.M <= 8192 ? launch_tail<512, 1, 8, 16>(a, s) : launch_tail<512, 2, 8, 8>(a, s);
+    if (a.D == 512) return launch_tail<512, 2, 4, 8>(a, s);
     if (a.D == 256) return launch_tail<256, 2, 4, 8>(a, s);
     return hipErrorInvalidValue;
 }

@@ -120,6 +120,35 @@ def test_randomized_stack_shapes_and_routes():
             run_forward(spec, users=users, want_hist=bool(rng.integers(0, 2)), flags=flags)
 
 
+@pytest.mark.parametrize("d, m", [(512, 5), (512, 7200), (512, 8300), (256, 2600), (384, 3500), (384, 11000), (384, 43600)])
+def test_residual_joins_the_finished_sum(d, m):
+    # every route of the two residual projections: a wave per block, the one-launch tail with 32- and 64-row tiles, and
+    # the 64 x 128, 128 x 128 and 256 x 128 tiles.  Residual rows of 4096 (ulp 2^-11) and products of which 16, what one
+    # matrix instruction adds, make a quarter of that ulp: summed onto the residual each would be lost, summed first
+    # they are d 2^-17 and d_ffn 2^-17, whole ulps, and every sum on the way is exact in fp32.
+    import torch
+    import paper_2502_09888_amd as P
+    say(f"[case] residual d={d} m={m}")
+    F, dev, bf = 256, "cuda:0", torch.bfloat16
+    cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=F, dtype=P.BF16)
+    w = {k: torch.zeros(*s, dtype=bf, device=dev) for k, s in
+         (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, F)), ("w2", (F, d)))}
+    w["g1"].fill_(1), w["g2"].fill_(1)
+    w["wqkv"][0, 2 * d:] = 1          # values: 1 (no history: a candidate's output is its own value)
+    w["wo"].fill_(2.0 ** -17)
+    w["w1"][0] = 16                   # hidden: GELU(16) = 16
+    w["w2"].fill_(2.0 ** -21)
+    buf = torch.empty(P.climber_kv_cache_bytes(cfg, [64]), dtype=torch.uint8, device=dev)
+    cache = P.climber_kv_cache_create(cfg, [0], [64], buf)
+    x = torch.full((m, d), 4096.0, device=dev)
+    y = torch.full((m, d), float("nan"), device=dev)
+    ids, off = torch.zeros(m, dtype=torch.int32, device=dev), torch.tensor([0, m], dtype=torch.int32, device=dev)
+    ws = torch.empty(P.climber_workspace_bytes(cfg, m), dtype=torch.uint8, device=dev)
+    P.climber_layer_forward(cfg, w, torch.ones(1, 1, device=dev), 0, P.MODE_CANDIDATE, cache, x, y, ids, ids, off, m, m, ws)
+    torch.cuda.synchronize()
+    assert bool((y == 4096.0 + (d + F) * 2.0 ** -17).all())
+
+
 @pytest.mark.parametrize("m", [1, 33, 95])
 def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(m):
     # the packed forward runs 10 x 384 history rows and the candidates through one launch (macro tiles), the
@@ -132,8 +161,8 @@ def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(m):
     assert np.array_equal(yc[:g.m_total], g.score())
 
 
-@pytest.mark.parametrize("d_model, d_ffn, users, m", [(512, 128, 22, 33), (512, 384, 22, 95), (512, 256, 19, 31),
-                                                         (512, 768, 19, 1), (256, 128, 7, 1), (256, 256, 7, 64)])
+@pytest.mark.parametrize("d_model, d_ffn, users, m", [(512, 128, 22, 33), (512, 384, 22, 95), (512, 256, 22, 63),
+                                                         (512, 512, 22, 2), (512, 256, 19, 31), (512, 768, 19, 1), (256, 128, 7, 1), (256, 256, 7, 64)])
 def test_layer_tail_in_one_launch_gives_the_bits_of_three(d_model, d_ffn, users, m):
     # users x 384 history rows and the candidates in one launch: more rows than the single-launch tail asks for, the
     # candidates alone fewer.  One, two and three chunks of the hidden; tiles of 64 and 32 rows, the last one with 1
