@@ -26,30 +26,35 @@ static __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
-// exact-erf GELU.  With a = |x| and h = Phi(-a) (the normal tail),
-//   GELU(x) = x Phi(x) = max(x, 0) - a h        (x >= 0: x - x h;  x < 0: x h),
-// which needs no sign select.  log2 Phi(-a) is smooth and falls like -a^2: a polynomial of degree 7 in a (least squares
-// against double-precision values of the normal tail, reweighted towards equal absolute error of a h among the
-// polynomials that fall throughout) gives h = exp2(poly) with a h to 6e-8, below the rounding of fp32 at 1, and h
-// goes to 0 for any large a.  9 instructions and one exponential; the rational form (Abramowitz & Stegun 7.1.26) takes
-// 11 and a reciprocal as well, and this epilogue is bound by the vector unit (up-projection at 32768 rows 115 us
-// against 123).  Evaluated in fp32, error of GELU(x) for x normal, root mean square / largest: 4.6e-8 / 2.9e-7, the
-// rational form 5.4e-8 / 3.3e-7.
-// In stages, for a kernel that deals them out between its matrix instructions (x, p: carried from stage to stage).
+// exact-erf GELU, erf by the rational/exponential formula 7.1.26 of Abramowitz & Stegun
+// (|error| <= 1.5e-7, far below the bf16 rounding of the result).  With a = |x|, z = a/sqrt(2),
+// t = 1/(1 + p z) and h = (1 - erf z)/2 = (poly(t)/2) t exp(-z^2):
+//   GELU(x) = x (1 + erf(x/sqrt 2))/2 = max(x, 0) - a h        (x >= 0: x - x h;  x < 0: x h)
+// which needs no sign select; the constants carry the factors 1/2, 1/sqrt(2) and log2(e)/2.
+// (A polynomial for log2 of the normal tail would take two instructions and the reciprocal less, and
+// the same absolute error; but its relative error is ten times as large where x < -4, above the bf16 rounding:
+// 2e-2 against 3.6e-3 in (-6, -5).)
+// In stages, for a kernel that deals them out between its matrix instructions (x, t, p: carried from stage to stage).
+constexpr int kGeluStages = 11;
 template <int STAGE>
-static __device__ __forceinline__ void gelu_stage(float &x, float &p)
+static __device__ __forceinline__ void gelu_stage(float &x, float &t, float &p)
 {
-    constexpr float c[8] = {-8.00000000e-07f, 4.17465955e-05f, -8.05730658e-04f, 8.15741547e-03f,
-                            -5.34969446e-02f, -4.58723035e-01f, -1.15121392e+00f, -9.99992063e-01f};
-    if constexpr (STAGE == 0) p = fmaf(__builtin_fabsf(x), c[0], c[1]);
-    else if constexpr (STAGE < 7) p = fmaf(p, __builtin_fabsf(x), c[STAGE + 1]);
-    else if constexpr (STAGE == 7) p = __builtin_amdgcn_exp2f(p);
+    if constexpr (STAGE == 0) t = fmaf(__builtin_fabsf(x), 0.3275911f * 0.70710678118654752f, 1.f);
+    else if constexpr (STAGE == 1) t = __builtin_amdgcn_rcpf(t);
+    else if constexpr (STAGE == 2) p = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+    else if constexpr (STAGE == 3) p = fmaf(p, t, 0.5f * 1.421413741f);
+    else if constexpr (STAGE == 4) p = fmaf(p, t, 0.5f * -0.284496736f);
+    else if constexpr (STAGE == 5) p = fmaf(p, t, 0.5f * 0.254829592f);
+    else if constexpr (STAGE == 6) p = p * t;
+    else if constexpr (STAGE == 7) t = (x * x) * -0.72134752044448170f;
+    else if constexpr (STAGE == 8) t = __builtin_amdgcn_exp2f(t);
+    else if constexpr (STAGE == 9) p = p * t;
     else x = fmaf(-__builtin_fabsf(x), p, fmaxf(x, 0.f));
 }
 static __device__ __forceinline__ float gelu_erf(float x)
 {
-    float p;
-    static_for<9>([&](auto s) __attribute__((always_inline)) { gelu_stage<decltype(s)::value>(x, p); });
+    float t, p;
+    static_for<kGeluStages>([&](auto s) __attribute__((always_inline)) { gelu_stage<decltype(s)::value>(x, t, p); });
     return x;
 }
 

@@ -13,11 +13,12 @@
 // products form one stream of loads, R in flight per wave across phase changes and barriers; rows of LDS operands are
 // XOR-swizzled so that the fragment reads are conflict-free.
 // 64 rows (RB = 2): bound by the matrix cores at the clock that they leave and, nearly as much, by the weights' way
-// through the vector cache (4.7 MB per workgroup at 64 bytes per clock).  32768 rows in a stack: d_model 512 with eight
-// waves and h in registers 180 us, four waves and h by way of memory about 200 (64 MB out and back, by all workgroups at
-// once), h as the start value of the second sum 169, at 3 to 11 times the rounding error; three launches 230.  d_model
-// 256 (four waves, two workgroups per CU) 57 against 87.  32 rows (RB = 1) where 64 would leave CUs without work: bound by
-// the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 76 us between the other
+// through the vector cache (4.7 MB per workgroup at 64 bytes per clock).  32768 rows in a stack: d_model 512, eight waves,
+// 193 us, against 230 as three launches; d_model 256, four waves and two workgroups per CU, 63 against 87.  Of the 193, 11
+// pay for the residuals' exact place (h as the start value of the second sum: 3 to 11 times the rounding error) and 12
+// for the GELU's relative error in the tail (see gelu_stage).  Four waves with h by way of memory (64 MB out and back,
+// by all workgroups at once) take about 20 us more.  32 rows (RB = 1) where 64 would leave CUs without work: bound by
+// the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 77 us between the other
 // launches of a stack.  (Taller tiles would need less of the caches, but 128 rows do not fit the registers; separate waves
 // for the two products gave the same times.)
 // Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
@@ -58,6 +59,9 @@ constexpr int tail_lds_bytes()
     constexpr int operands = 32 * RB * (D + 32 * NW) * 2, rows = 32 * D * 4;
     return operands > rows ? operands : rows;
 }
+
+template <int N>
+using At = std::integral_constant<int, N>;
 
 // The next fragments of the stream of weights: fragment e at base + (e % NJ) * a + (e / NJ) * b.
 struct Next { int base, a, b; };
@@ -288,26 +292,40 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
         for (int s0 = 0; s0 + R < S; s0 += R) steps(s0, std::false_type{});
         steps(S - R, std::true_type{});
     };
-    // values 4g .. 4g + 3 of hid[i] through the scale and the GELU, in eight pieces of about 32 clocks
-    float gx[4], gp[4];
+    // values 4g .. 4g + 3 of hid[i] through the scale and the GELU, in eight pieces of about 40 clocks
+    float gx[4], gt[4], gp[4];
     auto gelu_piece = [&](auto piece_tag, auto group_tag) __attribute__((always_inline)) {
         constexpr int piece = decltype(piece_tag)::value, i = decltype(group_tag)::value / 4, g = decltype(group_tag)::value % 4;
-        auto each = [&](auto stage, int e0, int e1) __attribute__((always_inline)) {
+        auto each = [&](auto from, auto to, int e0, int e1) __attribute__((always_inline)) {  // stages [from, to) of values [e0, e1)
+            constexpr int s0 = decltype(from)::value;
+            static_for<decltype(to)::value - s0>([&](auto s) __attribute__((always_inline)) {
 #pragma unroll
-            for (int e = e0; e < e1; ++e) gelu_stage<decltype(stage)::value>(gx[e], gp[e]);
+                for (int e = e0; e < e1; ++e) gelu_stage<s0 + decltype(s)::value>(gx[e], gt[e], gp[e]);
+            });
         };
         if constexpr (piece == 0) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) gx[e] = hid[i][4 * g + e] * rs[i];
-            each(std::integral_constant<int, 0>{}, 0, 4);
-        } else if constexpr (piece < 4) {
-            each(std::integral_constant<int, 2 * piece - 1>{}, 0, 4);
-            each(std::integral_constant<int, 2 * piece>{}, 0, 4);
-        } else if constexpr (piece < 6) {
-            each(std::integral_constant<int, 7>{}, 2 * (piece - 4), 2 * (piece - 4) + 2);
+            each(At<0>{}, At<1>{}, 0, 4);
+        } else if constexpr (piece == 1) {
+            each(At<1>{}, At<2>{}, 0, 3);   // a reciprocal or an exponential takes as long as four other instructions
+        } else if constexpr (piece == 2) {
+            each(At<1>{}, At<2>{}, 3, 4);
+            each(At<2>{}, At<4>{}, 0, 4);
+        } else if constexpr (piece == 3) {
+            each(At<4>{}, At<6>{}, 0, 4);
+            each(At<6>{}, At<7>{}, 0, 2);
+        } else if constexpr (piece == 4) {
+            each(At<6>{}, At<7>{}, 2, 4);
+            each(At<7>{}, At<8>{}, 0, 4);
+        } else if constexpr (piece == 5) {
+            each(At<8>{}, At<9>{}, 0, 2);
+            each(At<9>{}, At<10>{}, 0, 2);
         } else if constexpr (piece == 6) {
-            each(std::integral_constant<int, 8>{}, 0, 4);
+            each(At<8>{}, At<9>{}, 2, 4);
+            each(At<9>{}, At<10>{}, 2, 4);
         } else {
+            each(At<10>{}, At<11>{}, 0, 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) hb[i][g][e] = (__bf16)gx[e];
         }

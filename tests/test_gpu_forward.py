@@ -149,6 +149,41 @@ def test_residual_joins_the_finished_sum(d, m):
     assert bool((y == 4096.0 + (d + F) * 2.0 ** -17).all())
 
 
+@pytest.mark.parametrize("d, m", [(512, 5), (512, 7200), (512, 8300), (256, 2600), (384, 4000), (384, 8000), (384, 44000)])
+def test_gelu_keeps_its_relative_error_in_the_tail(d, m):
+    # every route of the up-projection (as above): hidden unit j gets the pre-activation z_j in every row and w2 hands it
+    # out as column j, 2^24 times.  Against formula 7.1.26 of Abramowitz & Stegun in double precision: the bf16 rounding
+    # of the hidden (eight bits: 2^-8) and 1e-5 for its evaluation in fp32 (the exponent of up to 26 to half an ulp: 1e-6 of the
+    # value; a reciprocal, an exponential and ten more operations: 1.5e-6), the rounding of 1 + 2^24 u (2^-24 / 0.1).
+    import torch
+    import paper_2502_09888_amd as P
+    say(f"[case] gelu d={d} m={m}")
+    dev, bf = "cuda:0", torch.bfloat16
+    cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=d, dtype=P.BF16, rms_eps=1e-12)
+    z = torch.linspace(-6, 2, d, dtype=torch.float64).to(bf)
+    w = {k: torch.zeros(*s, dtype=bf, device=dev) for k, s in
+         (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, d)), ("w2", (d, d)))}
+    w["g1"].fill_(1), w["g2"].fill_(1)
+    w["w1"][0] = z.to(dev)
+    w["w2"].fill_diagonal_(2.0 ** 24)
+    buf = torch.empty(P.climber_kv_cache_bytes(cfg, [64]), dtype=torch.uint8, device=dev)
+    cache = P.climber_kv_cache_create(cfg, [0], [64], buf)
+    x, y = torch.ones(m, d, device=dev), torch.full((m, d), float("nan"), device=dev)
+    ids, off = torch.zeros(m, dtype=torch.int32, device=dev), torch.tensor([0, m], dtype=torch.int32, device=dev)
+    ws = torch.empty(P.climber_workspace_bytes(cfg, m), dtype=torch.uint8, device=dev)
+    P.climber_layer_forward(cfg, w, torch.ones(1, 1, device=dev), 0, P.MODE_CANDIDATE, cache, x, y, ids, ids, off, m, m, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y[:1].expand_as(y))
+    a, zz = z.double().abs().numpy(), z.double().numpy()
+    t = 1 / (1 + 0.3275911 * a / np.sqrt(2))
+    poly = t * (0.254829592 + t * (-0.284496736 + t * (1.421413741 + t * (-1.453152027 + t * 1.061405429))))
+    want = np.maximum(zz, 0) - a * 0.5 * poly * np.exp(-a * a / 2)
+    got = (y[0].double().cpu().numpy() - 1) / 2.0 ** 24
+    err = np.abs(got - want) / np.abs(want).clip(1e-12)
+    say(f"largest relative error {err.max():.2e} at z = {zz[err.argmax()]:.3f}")
+    assert err.max() < 2.0 ** -8 + 1e-5
+
+
 @pytest.mark.parametrize("m", [1, 33, 95])
 def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(m):
     # the packed forward runs 10 x 384 history rows and the candidates through one launch (macro tiles), the
