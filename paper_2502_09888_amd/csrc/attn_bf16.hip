@@ -272,8 +272,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     };
     // FAST, SUMI: the candidate's own key/value.  Their rows travel through the same landing
     // buffer while the history loop runs (keys first, values once the keys are consumed), so no
-    // wave ever waits for them: weight w = exp2(<q', k_own>), then O += w * v_own
-    // (behind the seventh block of 32 keys; behind the last one against at most 256 keys) and, at the end, l += w.
+    // wave ever waits for them: weight w = exp2(<q', k_own>), l += w (behind the third block of 32 keys; behind the last
+    // one against at most 128 keys), then O += w * v_own (behind the seventh; behind the last against at most 256).
     float w_own[QB];
     bool fold = false;  // the wave runs the pass with the scale folded into a bf16 query (decided below)
     auto own_k = [&]() __attribute__((always_inline)) {
@@ -293,6 +293,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                 for (int e = 0; e < 8; ++e) dot += (float)qq[e] * (float)kk[e];
             }
             w_own[qb] = __builtin_amdgcn_exp2f((dot + xhalf(dot)) * (fold ? 1.f : st.c[qb]));
+            st.l[qb] += hf == 0 ? w_own[qb] : 0.f;
         }
     };
     auto own_v = [&]() __attribute__((always_inline)) {
@@ -519,8 +520,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             wait_tiles<NPRE>(0);
             own_v();
         }
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) st.l[qb] += hf == 0 ? w_own[qb] : 0.f;
     }
 
     // ---- SAFE pass (rare): whole workgroup redoes its rows with a running maximum -----------

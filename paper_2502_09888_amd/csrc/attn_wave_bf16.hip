@@ -231,21 +231,22 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
             const std::true_type tail;
             const std::false_type whole;
             int blk = 0;
-            auto groups = [&](int end) __attribute__((always_inline)) {  // whole groups of four, a further block exists
+            auto groups = [&](int end, auto own_tag) __attribute__((always_inline)) {  // whole groups of four, a further block exists
                 for (; blk + 4 < end; blk += 4) {
                     step(blk, S0, S1, P0, P1, u0, whole);
                     step(blk + 1, S1, S0, P1, P0, u1, whole);
                     step(blk + 2, S0, S1, P0, P1, u2, whole);
+                    if constexpr (decltype(own_tag)::value) st.l[0] += blk == 0 && hf == 0 ? w_own : 0.f;
                     step(blk + 3, S1, S0, P1, P0, u3, whole);
                 }
             };
             if (SUMI) {
                 own_weight();
                 fetch_own_v();
-                groups(min(n_blk, 9));
+                groups(min(n_blk, 9), std::true_type{});
                 if (n_blk > 8) own_v(w_own);  // behind the products of blocks 0 .. 6
             }
-            groups(n_blk);
+            groups(n_blk, std::false_type{});
             step(blk, S0, S1, P0, P1, u0, tail);  // one to four blocks are left
             step(blk + 1, S1, S0, P1, P0, u1, tail);
             if (blk + 2 < n_blk) {
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
             fetch_own_v();
         }
         if (n_blk <= 8) own_v(w_own);
-        st.l[0] += hf == 0 ? w_own : 0.f;
+        if (n_blk <= 4) st.l[0] += hf == 0 ? w_own : 0.f;
     }
     float lt = st.l[0] + xhalf(st.l[0]);
     const bool bad = fold ? !(lt > kDenomLo && lt < kDenomHi) : !(lt > kDenomLoExact && lt < kDenomHiExact);
