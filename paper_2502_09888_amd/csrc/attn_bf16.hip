@@ -620,8 +620,8 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
 // a head's K/V from L2 half as often and reuses every LDS fragment for two MFMAs; QB = 1 (128
 // queries) keeps two waves per SIMD busy when a head has few queries.
 // Launches of at most one wave of 32 queries per SIMD (1024) go to attn_wave_bf16.hip: us per launch there / here
-// for 8 heads and a history of 1000: 200 candidates of one user (56 waves) 11.4 / 19.5, of 16 users (896) 17.6 / 23.4, 256 of
-// 32 users (2048) 31 / 27; history pass over one user's 4096 behaviours (1024) 54 / 73, over 8 x 1024 (2048) 24.5 / 22.5.
+// for 8 heads and a history of 1000: 200 candidates of one user (56 waves) 11.8 / 19.4, of 16 users (896) 16.8 / 20.6, 256 of
+// 32 users (2048) 31 / 27; history pass over one user's 4096 behaviours (1024) 48 / 73, over 8 x 1024 (2048) 24.5 / 22.5.
 bool few_queries(const AttnArgs &a) { return (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 31) / 32) <= 1024; }
 }  // namespace
 

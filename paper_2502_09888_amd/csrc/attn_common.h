@@ -49,6 +49,7 @@ struct KParams {
     int B, H, n_scen, n_beh, sub_len, n_qtiles;
     int uni_len, uni_pad;  // >= 0: every user has this valid / padded history length
     int uni_cand;          // >= 0: every user has this many candidates (SUMI)
+    int pilot_pairs;       // attn_wave_bf16.hip: the choice of the softmax form is made for 64 queries
     float scale_log2e, inv_qk_scale;
     BiasArgs bias;  // relative attention bias (attn_bias_bf16.hip)
     int bias_H;
@@ -85,6 +86,7 @@ static inline KParams make_params(const AttnArgs &a, int n_qtiles)
     p.uni_len = a.uni_len;
     p.uni_pad = a.uni_pad;
     p.uni_cand = a.uni_cand;
+    p.pilot_pairs = 0;
     return p;
 }
 

@@ -10,8 +10,10 @@
 //
 // The steps and their order are those of attn_bf16.hip's FAST pass -- logits, exponentials, sums and products of
 // a block in the same order, the candidate's own key and value joining at the same place -- and so are the
-// bits: a candidate's result does not depend on how many others are scored with it.  Forms of the softmax (folded,
-// exact scale, SAFE) as described there; the decision is the wave's.
+// bits, within one form of the softmax.  Forms (folded, exact scale, SAFE) as described there.  Whether to fold is decided
+// for the same queries as there: the wave's 32, or the 64 that a wave of the 256-query tiles holds (a second product
+// against the first block of keys, 0.1 us); a SAFE pass is the wave's alone, where the tiled kernel repeats a
+// whole tile.
 #include "attn_common.h"
 
 #include <type_traits>
@@ -23,6 +25,8 @@ using namespace attn;
 
 constexpr int kRing = 2;  // blocks of 32 keys (and as many of 32 values) in flight or in use
 
+// (Two waves per SIMD in the bounds, although a launch has at most one: with all the registers to itself the candidate pass
+// uses no scratch memory and takes 13.3 us instead of 11.7 for 200 candidates, the history pass of 4096 rows 50 instead of 47.)
 template <bool SUMI, bool CAUSAL>
 __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
 {
@@ -48,7 +52,7 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
     }
     const int q0 = qt * 32;
     int64_t row0;
-    int nq, k_lo, k_hi;
+    int nq, k_lo, k_hi, nq_mate = 0;  // (nq_mate: queries of the 32 that share this wave's pilot)
     if (SUMI) {
         int c0, Mb;
         if (p.uni_cand >= 0) {
@@ -61,6 +65,7 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
         if (q0 >= Mb) return;
         row0 = (int64_t)c0 + q0;
         nq = min(32, Mb - q0);
+        if (p.pilot_pairs) nq_mate = min(32, Mb - (q0 ^ 32));
         k_lo = 0;
         k_hi = Lb;
     } else {
@@ -152,6 +157,14 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
     };
 
     load_q();
+    QState<1> mate;
+    int mate_scen = 0, mate_beh = 0;
+    if (SUMI && nq_mate > 0) {
+        const int64_t r = row0 + ((q0 ^ 32) - q0) + min(l32, nq_mate - 1);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) mate.qf[0][s] = *(const bf16x8 *)(p.q + r * p.ld_q + h * kDHead + 8 * hf + 16 * s);
+        mate_scen = p.scen[r], mate_beh = p.beh[r];
+    }
     if (n_blk > 0) {
 #pragma unroll
         for (int i = 0; i < kRing; ++i) {
@@ -178,6 +191,8 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
         load_block_v(0, vf[0]);
         vf[1] = VFrags{};
         qk_block(st, kf[0], S0);
+        f32x16 S_mate[1];
+        if (SUMI && nq_mate > 0) qk_block(mate, kf[0], S_mate);
         load_block_k(kRing, kf[0]);
         // fold the row scale into a bf16 query?  (the pilot of attn_bf16.hip)
         {
@@ -185,7 +200,15 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
 #pragma unroll
             for (int r = 0; r < 16; ++r) ss = fmaf(S0[0][r], S0[0][r], ss);
             ss += xhalf(ss);
-            const bool big = k_hi - k_lo < kFoldMinKeys || !(ss * st.c[0] * st.c[0] < kBlockKeys * kPilotSpread * kPilotSpread);
+            bool big = k_hi - k_lo < kFoldMinKeys || !(ss * st.c[0] * st.c[0] < kBlockKeys * kPilotSpread * kPilotSpread);
+            if (SUMI && nq_mate > 0) {  // the tiled kernel's waves have 64 queries here and fold for all of them or none
+                ss = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) ss = fmaf(S_mate[0][r], S_mate[0][r], ss);
+                ss += xhalf(ss);
+                const float c = p.scale_log2e / p.tau[min(max(mate_scen, 0), p.n_scen - 1) * p.n_beh + min(max(mate_beh, 0), p.n_beh - 1)];
+                big |= !(ss * c * c < kBlockKeys * kPilotSpread * kPilotSpread);
+            }
             fold = SUMI && __builtin_amdgcn_ballot_w64(big) == 0;
             if (fold) {
 #pragma unroll
@@ -303,7 +326,8 @@ hipError_t launch_attn_wave_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
     const int n_qtiles = (a.max_rows_per_user + 31) / 32;
     const int64_t grid = (int64_t)8 * n_qtiles * ((a.cache.B * a.H + 7) / 8);
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-    const KParams p = make_params(a, n_qtiles);
+    KParams p = make_params(a, n_qtiles);
+    p.pilot_pairs = sumi && a.max_rows_per_user > 128;
     const dim3 g((unsigned)grid), t(64);
     if (sumi) hipLaunchKernelGGL((attn_wave_kernel<true, false>), g, t, 0, s, p);
     else if (a.causal) hipLaunchKernelGGL((attn_wave_kernel<false, true>), g, t, 0, s, p);

@@ -215,6 +215,23 @@ def test_few_and_many_queries_give_the_same_bits(L, sub):
             assert max_abs(part, oracle_sumi(w)[7:7 + n]) < 2e-2
 
 
+def test_few_and_many_queries_choose_the_same_form_of_the_softmax():
+    # two rows whose temperature wants the scale in fp32 (exponents of 7 in the mean) among rows that fold it into
+    # the query: one in the second half of 64 queries, one in the first half of the next.  The choice is made for 64
+    # queries at a time, however many are in the launch.
+    spec = W.shrink(W.CONFIG2, name="bf16-mixed-forms", B=1, L=700, sub_len=0, M=8400, H=4, pad_to=64, seed=717)
+    w = W.make_attention(spec)
+    w["tau"] = np.full_like(w["tau"], 2.0)
+    w["tau"].flat[0] = 0.2
+    w["cscen"] = np.ones_like(w["cscen"])
+    w["cscen"][[40, 70]] = w["cbeh"][[40, 70]] = 0
+    g = GpuAttention(w)
+    g.history()
+    full, part = g.sumi(), g.sumi(sel=(0, 192))
+    assert np.array_equal(part, full[:192])
+    assert max_abs(part, oracle_sumi(w)[:192]) < 2e-2
+
+
 @pytest.mark.parametrize("L", [31, 64, 130, 385])
 def test_few_queries_causal_history(L):
     spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=2, L=L, sub_len=0, M=4, H=2, pad_to=64, L_min=max(1, L - 20),
