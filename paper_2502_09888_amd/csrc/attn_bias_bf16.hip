@@ -186,7 +186,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
     // Classes of 64 blocks: do a wave's 32 queries of a query block share one position and one time bucket with all
     // keys of the block, and which.  Distances are monotonic in both ends, so the buckets of the extreme pairs decide.
     // Eight lanes per block, four keys each.
-    constexpr int kMixed = 0x7fffffff;
+    // A class holds the clipped distance above eight bits of time bucket: blocks with a distance that does not fit there
+    // (tables of more than 2^23 entries a row) are looked up per logit.
+    constexpr int kMixed = 0x7fffffff, kClassPos = 1 << 22;
     int qp_min[QB], qp_max[QB];
     uint32_t qt_min[QB], qt_max[QB];
 #pragma unroll
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
                     else if (kt_min >= qt_max[qb]) d_min = kt_min - qt_max[qb], d_max = kt_max - qt_min[qb];
                     else d_max = max(qt_max[qb] - kt_min, kt_max - qt_min[qb]);
                     const int it = clip_zeros(d_min);
-                    const int cls = ip == ip2 && it == clip_zeros(d_max) ? (ip << 8) + it : kMixed;
+                    const int cls = ip == ip2 && abs(ip) < kClassPos && it == clip_zeros(d_max) ? (ip << 8) + it : kMixed;
                     if ((lane & 7) == 0) my_class[qb * 64 + 8 * (g0 + k) + (lane >> 3)] = cls;
                 }
             }

@@ -218,3 +218,15 @@ def test_bf16_bias_uniform_and_mixed_blocks(n_pos, n_time, L, sub, causal, shuff
 def test_bf16_bias_running_maximum_over_two_turns_of_blocks():
     spec = W.shrink(W.CONFIG2, name="bias-safe-long", B=1, L=2200, sub_len=0, M=140, H=2, qk_scale=12.0, seed=941)
     check_bias(W.add_bias_inputs(W.make_attention(spec)))
+
+
+@pytest.mark.parametrize("half", [2 ** 22 - 1, 2 ** 22, 2 ** 23, 2 ** 24])
+def test_bf16_bias_position_tables_of_any_length(half):
+    # every query at the positive clip of a long table, whose last entry puts all weight on the history and whose first
+    # would take it away: distances at and beyond what a block's class holds
+    spec = W.shrink(W.CONFIG2, name=f"bias-long-table-{half}", B=1, L=97, sub_len=0, M=40, H=1, n_scen=1, n_beh=1, seed=960)
+    w = W.add_bias_inputs(W.make_attention(spec), n_pos=3, n_time=12)
+    w["pos_table"] = np.zeros((1, 1, 1, 2 * half + 1), np.float32)
+    w["pos_table"][..., -1], w["pos_table"][..., 0] = 4.0, -4.0
+    w["cand_pos"] = np.full_like(w["cand_pos"], 2 ** 30)
+    check_bias(w)
