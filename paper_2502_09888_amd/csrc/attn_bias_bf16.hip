@@ -314,13 +314,18 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
         }
     };
     const int whole_hi = CAUSAL ? min(q0 + wave * WQ, k_hi) : k_hi;  // keys below it are visible to every query of the wave
-    auto mask = [&](f32x16 (&S)[QB], int blk) __attribute__((always_inline)) {
+    // A block with keys that not every query sees: the bias is applied here, then those keys are taken out.  (The other
+    // way round a table entry that only they select, be it infinite or NaN, would reach the rows.)
+    auto mask = [&](int qb, f32x16 (&S)[QB], int blk, float &scale, float &add) __attribute__((always_inline)) {
         const int lo = k_lo + blk * kBlockKeys;
         if (lo + kBlockKeys > whole_hi) {
-            int lim[QB];
+            const int lim[1] = {CAUSAL ? min(q0 + wave * WQ + qb * 32 + l32 + 1, k_hi) : k_hi};
+            f32x16 T[1];
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) lim[qb] = CAUSAL ? min(q0 + wave * WQ + qb * 32 + l32 + 1, k_hi) : k_hi;
-            mask_causal(S, hf, lo, lim);
+            for (int r = 0; r < 16; ++r) T[0][r] = fmaf(S[qb][r], scale, add);
+            scale = 1.f, add = 0.f;
+            mask_causal(T, hf, lo, lim);
+            S[qb] = T[0];
         }
     };
 
@@ -328,12 +333,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
     if (n_tiles > 0) {
         f32x16 S0[QB], S1[QB];
         bf16x8 P[QB][2];
-        auto soft = [&](f32x16 (&S)[QB], int blk, const uint8_t *stage) __attribute__((always_inline)) {
-            mask(S, blk);
+        // (without the causal flag only the last tile has keys that are not visible)
+        auto soft = [&](f32x16 (&S)[QB], int blk, const uint8_t *stage, auto last_tag) __attribute__((always_inline)) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 float scale, add;
                 bias_block(qb, S, blk, stage, scale, add);
+                if constexpr (CAUSAL || decltype(last_tag)::value) mask(qb, S, blk, scale, add);
                 st.l[qb] += exp_pack<true>(S[qb], scale, -add, P[qb]);
             }
         };
@@ -347,7 +353,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
                 const VFrags v0 = load_v(cur, lane);
                 __builtin_amdgcn_sched_barrier(0);
                 qk_block(st, k1, S1);
-                soft(S0, 2 * t, cur);
+                soft(S0, 2 * t, cur, std::false_type{});
                 pv_block(st, v0, P);
             }
             wait_copies();  // tile t + 1 has landed; nobody reads tile t - 1 any more
@@ -358,7 +364,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
                 const VFrags v1 = load_v(cur + kBlockBytes, lane);
                 __builtin_amdgcn_sched_barrier(0);
                 qk_block(st, k0, S0);
-                soft(S1, 2 * t + 1, cur);
+                soft(S1, 2 * t + 1, cur, std::false_type{});
                 pv_block(st, v1, P);
             }
             const int so = so_cur;
@@ -371,11 +377,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
             const bool two = k_lo + (blk + 1) * kBlockKeys < k_hi;
             if (two) qk_block(st, load_k(cur + kBlockBytes, lane), S1);
             const VFrags v0 = load_v(cur, lane);
-            soft(S0, blk, cur);
+            soft(S0, blk, cur, std::true_type{});
             pv_block(st, v0, P);
             if (two) {
                 const VFrags v1 = load_v(cur + kBlockBytes, lane);
-                soft(S1, blk + 1, cur);
+                soft(S1, blk + 1, cur, std::true_type{});
                 pv_block(st, v1, P);
             }
         }
@@ -455,11 +461,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
                 f32x16 S[QB];
                 bf16x8 P[QB][2];
                 qk_block(st, load_k(lds + k * kBlockBytes, lane), S);
-                mask(S, blk);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
                     float scale, add;
                     bias_block(qb, S, blk, lds, scale, add);
+                    mask(qb, S, blk, scale, add);
 #pragma unroll
                     for (int r = 0; r < 16; ++r) S[qb][r] = fmaf(S[qb][r], scale, add);
                 }

@@ -230,3 +230,26 @@ def test_bf16_bias_position_tables_of_any_length(half):
     w["pos_table"][..., -1], w["pos_table"][..., 0] = 4.0, -4.0
     w["cand_pos"] = np.full_like(w["cand_pos"], 2 ** 30)
     check_bias(w)
+
+
+@pytest.mark.parametrize("qk_scale", [0.125, 12.0])  # (12: the running-maximum pass)
+@pytest.mark.parametrize("L,sub,causal", [(97, 0, False), (161, 128, True), (300, 256, True)])
+@pytest.mark.parametrize("n_pos", [3, 65])           # (3: blocks of later keys fall into one bucket; 65: they do not)
+def test_bf16_bias_entries_of_unseen_keys_do_not_matter(L, sub, causal, qk_scale, n_pos):
+    # the entries for negative distances are selected by keys that no row sees: later behaviours under the causal
+    # flag, slots past a history's end.  Whatever they hold, the outputs are the same bits.
+    spec = W.shrink(W.CONFIG2, name=f"bias-unseen-{L}-{n_pos}", B=2, L=L, L_min=L - 30, sub_len=sub, M=40, H=2, nan_padding=True,
+                    qk_scale=qk_scale, seed=970 + L)
+    w = W.add_bias_inputs(W.make_attention(spec), n_pos=n_pos, n_time=12)
+    for b in range(2):
+        w["hist_pos"][w["tok_off"][b] + w["hist_len"][b]:w["tok_off"][b + 1]] = 2 ** 30
+    outs = []
+    for fill in (0.0, np.nan, np.inf):
+        w["pos_table"] = w["pos_table"].copy()
+        w["pos_table"][..., :(n_pos - 1) // 2] = fill
+        g = GpuBias(w, causal=causal)
+        outs.append(((g.history_bias() if causal else None), (g.history(want_output=False), g.sumi_bias())[1]))
+    for oh, oc in outs[1:]:
+        assert np.array_equal(oc, outs[0][1])
+        assert oh is None or np.array_equal(oh, outs[0][0])
+    assert np.isfinite(outs[0][1]).all()
