@@ -232,6 +232,22 @@ def test_few_and_many_queries_choose_the_same_form_of_the_softmax():
     assert max_abs(part, oracle_sumi(w)[:192]) < 2e-2
 
 
+@pytest.mark.parametrize("L", [20, 40, 70, 100, 130, 257])
+def test_few_queries_keep_an_infinite_value_infinite(L):
+    # one to nine blocks of 32 keys, odd and even: a value of the last one that every row sees, by the wave per 32
+    # queries and by the tiles
+    spec = W.shrink(W.CONFIG2, name=f"bf16-inf-{L}", B=1, L=L, sub_len=0, M=8400, H=4, pad_to=64, nan_padding=True, seed=760 + L)
+    w = W.make_attention(spec)
+    w["vh"] = w["vh"].copy()
+    w["vh"][L - 1, 2, 5] = np.inf
+    g = GpuAttention(w)
+    oh, ok = g.history(), valid_rows(w)
+    full, part = g.sumi(), g.sumi(sel=(0, 192))
+    at = 2 * 64 + 5
+    assert np.all(oh[ok][:, at] == np.inf) and np.all(part[:, at] == np.inf)
+    assert np.array_equal(part, full[:192]) and np.isfinite(np.delete(oh[ok], at, 1)).all()
+
+
 @pytest.mark.parametrize("L", [31, 64, 130, 385])
 def test_few_queries_causal_history(L):
     spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=2, L=L, sub_len=0, M=4, H=2, pad_to=64, L_min=max(1, L - 20),
