@@ -111,7 +111,7 @@ hipError_t launch_attn_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, hip
     const int64_t grid = a.total_q_rows * a.H;
     if (grid == 0) return hipSuccess;
     if (grid > 0x7fffffff || a.max_hist_len > kMaxKeysF32) return hipErrorInvalidValue;
-    if (attn_tile_f32_takes(a)) return launch_attn_tile_f32(a, sumi, cache_rows, false, s);
+    if (attn_tile_f32_takes(a, sumi)) return launch_attn_tile_f32(a, sumi, cache_rows, false, s);
     const size_t shmem = (size_t)(a.max_hist_len + 1) * sizeof(float);
     if (sumi)
         hipLaunchKernelGGL(attn_f32_kernel<true>, dim3((unsigned)grid), dim3(64), shmem, s, a, cache_rows);

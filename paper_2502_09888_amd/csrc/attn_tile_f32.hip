@@ -24,7 +24,7 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRows = 16, kKeys = 16, kWaves = 4;
+constexpr int kRows = kTileRowsF32, kKeys = 16, kWaves = 4;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // the four lanes that hold logits of one query
@@ -300,11 +300,42 @@ hipError_t launch_tile(const TileArgs &p, bool sumi, unsigned grid, hipStream_t 
 
 }  // namespace
 
-// (whole 16-byte pieces of rows; other widths and the relative bias take the kernel of attn_f32.hip)
-bool attn_tile_f32_takes(const AttnArgs &a)
+// Grid: every head of every user gets the tiles of the longest one.  Where lengths differ much most of them are empty.
+struct TileGrid { int sub, tiles_per_sub; int64_t heads, tiles; };
+static TileGrid tile_grid(const AttnArgs &a, bool sumi)
 {
-    return (a.d_head == 32 || a.d_head == 64 || a.d_head == 128) && !a.bias.pos_table && a.ld_q % 4 == 0 && a.ld_kv % 4 == 0 &&
-           a.ld_o % 4 == 0;
+    TileGrid g;
+    g.sub = !sumi && a.sub_len > 0 ? std::min(a.sub_len, a.max_rows_per_user) : a.max_rows_per_user;
+    g.tiles_per_sub = (g.sub + kRows - 1) / kRows;
+    g.heads = (int64_t)a.cache.B * a.H;
+    g.tiles = (int64_t)((a.max_rows_per_user + g.sub - 1) / g.sub) * g.tiles_per_sub;
+    return g;
+}
+
+// Whole 16-byte pieces of rows; other widths and the relative bias take the kernel of attn_f32.hip, a wave per row.  So do
+// launches that it is the faster way for, by what either costs in ns (d_head 64; the ratio is alike for 32 and 128):
+//   a wave per row   2.3 a row and 0.2 a key it sees; 4000 for the cache writer that the history pass then needs
+//   tiles            1.2 (history) or 4.5 (candidates) a workgroup, empty or not, and for a tile with rows 3.3 (history)
+//                    and 0.07 a key
+// Us, there / here, 8 heads: 4096 rows in subsequences of 1 76 / 108, of 2 80 / 58; one candidate for each of 4096
+// users with histories of 4 78 / 141, of 64 1680 / 250; 16000 histories of 2 and one of 1024, subsequences of 16, 471 /
+// 10388; 1024 of 16 and one of 2048, whole, 7567 / 1687; 1 candidate each for 4096 users and 512 for one 1247 / 4392.
+// A grid has less than 2^32 threads; beyond that the launch would leave rows out.
+bool attn_tile_f32_takes(const AttnArgs &a, bool sumi)
+{
+    if ((a.d_head != 32 && a.d_head != 64 && a.d_head != 128) || a.bias.pos_table || a.ld_q % 4 != 0 || a.ld_kv % 4 != 0 || a.ld_o % 4 != 0)
+        return false;
+    const TileGrid g = tile_grid(a, sumi);
+    const double grid = (double)g.heads * g.tiles, rows = (double)a.total_q_rows, users = a.cache.B;
+    if (grid * (kWaves * 64) >= 4294967296.0) return false;
+    if (grid <= 2048) return true;  // all of them at once: the length of one wave's chain counts
+    if (!sumi) {
+        const double keys = a.hist_pairs / rows;
+        return 1.2 * grid + a.hist_tiles * a.H * (3.3 + 0.07 * keys) < 4000 + rows * a.H * (2.3 + 0.2 * keys);
+    }
+    // (who has how many candidates is not known here: the longest history the most, the rest alike)
+    const double most = a.max_rows_per_user, keys = (most * a.max_hist_len + (rows - most) * (a.valid_rows / users)) / rows;
+    return 4.5 * grid + std::min(rows, users + rows / kRows) * a.H * 0.07 * keys < rows * a.H * (2.3 + 0.2 * keys);
 }
 
 hipError_t launch_attn_tile_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, bool write_cache, hipStream_t s)
@@ -314,13 +345,12 @@ hipError_t launch_attn_tile_f32(const AttnArgs &a, bool sumi, int64_t cache_rows
     p.cache_k = (float *)a.cache.layer_base;
     p.cache_v = p.cache_k + cache_rows * a.H * a.d_head;
     p.from_rows = write_cache;
-    p.sub = !sumi && a.sub_len > 0 ? std::min(a.sub_len, a.max_rows_per_user) : a.max_rows_per_user;
-    p.tiles_per_sub = (p.sub + kRows - 1) / kRows;
-    const int64_t heads = (int64_t)a.cache.B * a.H, tiles = (int64_t)((a.max_rows_per_user + p.sub - 1) / p.sub) * p.tiles_per_sub;
-    if (heads <= 0 || heads > 0x7fffffff) return hipErrorInvalidValue;
-    if (!sumi && heads * tiles > 0x7fffffff) return hipErrorInvalidValue;
-    p.n_tiles = (int)std::min<int64_t>(tiles, 0x7fffffff / heads);
-    const unsigned grid = (unsigned)(heads * p.n_tiles);
+    const TileGrid tg = tile_grid(a, sumi);
+    p.sub = tg.sub;
+    p.tiles_per_sub = tg.tiles_per_sub;
+    p.n_tiles = (int)tg.tiles;
+    if (tg.heads <= 0 || tg.heads * tg.tiles > 0xffffffffll / (kWaves * 64)) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)(tg.heads * tg.tiles);
     switch (a.d_head) {
     case 32: return launch_tile<32>(p, sumi, grid, s);
     case 64: return launch_tile<64>(p, sumi, grid, s);

@@ -24,6 +24,7 @@ struct climber_kv_cache {
     int32_t max_pad, max_len;
     int32_t uni_len, uni_pad;  // >= 0 when all users share one valid / padded length
     int64_t rows;
+    int64_t valid_rows, hist_tiles, hist_pairs;  // see AttnArgs
 };
 
 namespace {
@@ -110,6 +111,9 @@ AttnArgs base_args(const climber_config *cfg, const climber_kv_cache *cache, int
     a.uni_len = cache->uni_len;
     a.uni_pad = cache->uni_pad;
     a.uni_cand = -1;
+    a.valid_rows = cache->valid_rows;
+    a.hist_tiles = cache->hist_tiles;
+    a.hist_pairs = cache->hist_pairs;
     return a;
 }
 
@@ -153,7 +157,7 @@ int attn_history_strided(const climber_config *cfg, const float *tau_layer, cons
     // fp32: likewise, unless the output lies on the rows that other workgroups still read
     const size_t row_bytes = (size_t)cache->rows * ld * 4, o_bytes = (size_t)cache->rows * ld_o * 4;
     auto apart = [&](const void *x) { return (uintptr_t)x + row_bytes <= (uintptr_t)o || (uintptr_t)o + o_bytes <= (uintptr_t)x; };
-    const bool fused_f32 = cfg->dtype == CLIMBER_F32 && o && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) && attn_tile_f32_takes(a) && apart(k) && apart(v);
+    const bool fused_f32 = cfg->dtype == CLIMBER_F32 && o && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) && attn_tile_f32_takes(a, false) && apart(k) && apart(v);
     if (fused || fused_f32) {
     } else if (cfg->dtype == CLIMBER_BF16) {
         int e = rt(launch_kv_write_bf16(cv, k, v, ld, cfg->n_heads, cache->max_pad, s));
@@ -330,6 +334,14 @@ int climber_kv_cache_create(const climber_config *cfg, int32_t B, const int32_t 
     k->uni_len = uni ? hist_len[0] : -1;
     k->uni_pad = uni ? hist_len_padded[0] : -1;
     k->rows = rows;
+    for (int b = 0; b < B; ++b) {
+        const int64_t len = hist_len[b], pad = hist_len_padded[b], sub = cfg->sub_len > 0 && cfg->sub_len < pad ? cfg->sub_len : pad;
+        if (pad == 0) continue;
+        const int64_t tiles = (sub + kTileRowsF32 - 1) / kTileRowsF32, rest = (pad % sub + kTileRowsF32 - 1) / kTileRowsF32;
+        k->valid_rows += len;
+        k->hist_tiles += pad / sub * tiles + rest;
+        k->hist_pairs += len / sub * sub * sub + (len % sub) * (len % sub);
+    }
 
     std::vector<int32_t> hd;
     hd.insert(hd.end(), k->hist_len.begin(), k->hist_len.end());

@@ -46,6 +46,8 @@ struct AttnArgs {
     int max_hist_len;                // longest valid history of the batch
     int uni_len, uni_pad;            // >= 0: all users share this valid / padded history length
     int uni_cand;                    // >= 0: all users have this many candidates (SUMI)
+    int64_t valid_rows;              // valid history rows of the batch
+    int64_t hist_tiles, hist_pairs;  // fp32 history pass: tiles of 16 rows of a subsequence; (row, visible key) pairs
     float qk_scale;
     BiasArgs bias;                   // relative attention bias; bias.pos_table == nullptr: none
 };
@@ -64,9 +66,11 @@ hipError_t launch_hist_fused_bf16(const AttnArgs &a, hipStream_t s);
 // fp32 reference-path attention (attn_f32.hip); the cache layer holds plain [rows][H][dh] K then V
 hipError_t launch_attn_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, hipStream_t s);
 size_t attn_f32_max_keys();
-// the same on the matrix cores for the widths it has (attn_tile_f32.hip); write_cache (history): keys and values come from
-// the rows a.k_self / a.v_self, which nothing in the launch may overwrite, and go into the cache as well
-bool attn_tile_f32_takes(const AttnArgs &a);
+// the same on the matrix cores for the widths it has and where it is the faster way (attn_tile_f32.hip); write_cache
+// (history): keys and values come from the rows a.k_self / a.v_self, which nothing in the launch may overwrite, and go into
+// the cache as well
+constexpr int kTileRowsF32 = 16;
+bool attn_tile_f32_takes(const AttnArgs &a, bool sumi);
 hipError_t launch_attn_tile_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, bool write_cache, hipStream_t s);
 
 // cache writers (kv_cache.hip): k, v are [rows][ld] with head h at column h*d_head

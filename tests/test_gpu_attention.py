@@ -62,6 +62,53 @@ def test_fp32_tiles(dh, L, sub, M):
     check_all(w, flags=TWO_KERNEL)
 
 
+@pytest.mark.parametrize("n_short,long,sub,causal", [(16000, 4096, 16, False), (20000, 15000, 1, False), (1500, 700, 0, True)])
+def test_fp32_one_long_history_among_many_short_ones(n_short, long, sub, causal):
+    # histories of one behaviour (the output is its value) and a long one, a candidate for each of the former and 40 for
+    # the latter: what a grid of every user's tiles as many as the longest one's would be too large for (2^32 threads
+    # and 2^31 workgroups), and a batch that stays below; both passes against sums in 64 bits.  TOL: see above.
+    import torch
+    import paper_2502_09888_amd as P
+    say(f"[case] fp32 {n_short} histories of 1 and one of {long}, sub={sub}")
+    H, dh, B = 8, 32, n_short + 1
+    lens, cand = [1] * n_short + [long], [1] * n_short + [40]
+    rows, m = sum(lens), sum(cand)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(1000 + long)
+    q, k, v = (torch.randn(rows, H, dh, generator=gen, device="cuda:0") for _ in range(3))
+    qc, kc, vc = (torch.randn(m, H, dh, generator=gen, device="cuda:0") for _ in range(3))
+    cfg = P.Config(n_heads=H, d_head=dh, sub_len=sub, dtype=P.F32, qk_scale=dh ** -0.5, flags=P.HIST_CAUSAL if causal else 0)
+    buf = torch.empty(P.climber_kv_cache_bytes(cfg, lens), dtype=torch.uint8, device="cuda:0")
+    cache = P.climber_kv_cache_create(cfg, lens, lens, buf)
+    ids, tau = torch.zeros(max(rows, m), dtype=torch.int32, device="cuda:0"), torch.full((1, 1), 0.7, device="cuda:0")
+    off = torch.tensor(np.concatenate([[0], np.cumsum(cand)]), dtype=torch.int32, device="cuda:0")
+    o, oc = torch.full((rows, H * dh), float("nan"), device="cuda:0"), torch.full((m, H * dh), float("nan"), device="cuda:0")
+    P.climber_attn_history(cfg, tau, q, k, v, ids, ids, cache, 0, o)
+    P.climber_attn_sumi(cfg, tau, cache, 0, qc, kc, vc, off, m, 40, ids, ids, oc)
+    torch.cuda.synchronize()
+
+    def attend(q, k, v, visible):  # [rows][H][dh] in 64 bits, on the CPU
+        s = torch.einsum("qhd,khd->hqk", q, k) * (dh ** -0.5 / 0.7)
+        return torch.einsum("hqk,khd->qhd", s.masked_fill(~visible, -np.inf).softmax(-1), v)
+
+    q, k, v, qc, kc, vc, o, oc = (x.double().cpu() for x in (q, k, v, qc, kc, vc, o.view(rows, H, dh), oc.view(m, H, dh)))
+    n = n_short
+    assert (o[:n] - v[:n]).abs().max() < TOL["f32"]
+    own = torch.stack([(qc[:n] * k[:n]).sum(-1), (qc[:n] * kc[:n]).sum(-1)]) * (dh ** -0.5 / 0.7)
+    w = own.softmax(0)[..., None]
+    assert (oc[:n] - w[0] * v[:n] - w[1] * vc[:n]).abs().max() < TOL["f32"]
+    step = sub or long
+    for lo in {0, (long - 1) // step * step}:   # first and last subsequence of the long one
+        hi = min(lo + step, long)
+        vis = torch.ones(hi - lo, hi - lo, dtype=torch.bool)
+        want = attend(q[n + lo:n + hi], k[n + lo:n + hi], v[n + lo:n + hi], vis.tril() if causal else vis)
+        assert (o[n + lo:n + hi] - want).abs().max() < TOL["f32"]
+    for c in (0, 39):
+        one = slice(n + c, n + c + 1)
+        want = attend(qc[one], torch.cat([k[n:], kc[one]]), torch.cat([v[n:], vc[one]]), torch.ones(1, long + 1, dtype=torch.bool))
+        assert (oc[one] - want).abs().max() < TOL["f32"]
+
+
 def test_fp32_causal_keeps_later_values_out():
     # an infinite value (and NaN) of a later key reaches no query that does not see it
     spec = W.shrink(W.CONFIG1, name="f32-later", B=1, L=40, sub_len=20, M=3, dh=32, H=1, seed=17)
