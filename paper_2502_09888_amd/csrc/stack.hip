@@ -123,7 +123,10 @@ int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x,
     float *ss = ws.ss + (size_t)r0 * (d / 64);
     const RowNormIn nin{ss, d / 64, 1.f / (float)d, cfg->rms_eps}, no_in{nullptr, 0, 0.f, 0.f};
     const RowNormOut nout{ss, xb, d}, no_out{nullptr, nullptr, 0};
-    if (layer_tail_takes(M, d, F))
+    // (one launch reads and writes rows as its workgroups come to them: y is x itself or lies apart from it)
+    const size_t bytes = (size_t)M * d * 4;
+    const bool in_place = x == y, apart = (uintptr_t)x + bytes <= (uintptr_t)y || (uintptr_t)y + bytes <= (uintptr_t)x;
+    if ((in_place || apart) && layer_tail_takes(M, d, F))
         return rt(layer_tail_bf16(TailArgs{o, x, pw.wo, (int)(pw.w1 - pw.wo), (int)(pw.w2 - pw.wo), (int)(pw.w2 - pw.wo) + d * F * 2, y,
                                            norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F, nin.inv_d, nin.eps}, s));
     float *h = ws.h32 + (size_t)r0 * d;

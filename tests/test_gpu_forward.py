@@ -184,6 +184,34 @@ def test_gelu_keeps_its_relative_error_in_the_tail(d, m):
     assert err.max() < 2.0 ** -8 + 1e-5
 
 
+@pytest.mark.parametrize("d, m", [(256, 2600), (512, 7200), (512, 8300)])
+def test_layer_output_over_its_own_input(d, m):
+    # x_out apart from x_in, the same rows, and rows shifted by less than their number in either direction: the same bits
+    import torch
+    import paper_2502_09888_amd as P
+    say(f"[case] in and out d={d} m={m}")
+    F, dev, bf = 256, "cuda:0", torch.bfloat16
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(m)
+    cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=F, dtype=P.BF16)
+    w = {k: (torch.randn(*s, generator=gen, device=dev) * 0.05).to(bf) for k, s in
+         (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, F)), ("w2", (F, d)))}
+    buf = torch.empty(P.climber_kv_cache_bytes(cfg, [64]), dtype=torch.uint8, device=dev)
+    cache = P.climber_kv_cache_create(cfg, [0], [64], buf)
+    ids, off = torch.zeros(m, dtype=torch.int32, device=dev), torch.tensor([0, m], dtype=torch.int32, device=dev)
+    ws = torch.empty(P.climber_workspace_bytes(cfg, m), dtype=torch.uint8, device=dev)
+    x = torch.randn(m, d, generator=gen, device=dev)
+    outs = []
+    for at_in, at_out in ((0, 2 * m), (0, 0), (0, 100), (100, 0), (0, m)):
+        rows = torch.zeros(3 * m, d, device=dev)
+        rows[at_in:at_in + m] = x
+        P.climber_layer_forward(cfg, w, torch.ones(1, 1, device=dev), 0, P.MODE_CANDIDATE, cache, rows[at_in:], rows[at_out:], ids,
+                                ids, off, m, m, ws)
+        outs.append(rows[at_out:at_out + m].clone())
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, outs[0]) for o in outs[1:])
+
+
 @pytest.mark.parametrize("m", [1, 33, 95])
 def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(m):
     # the packed forward runs 10 x 384 history rows and the candidates through one launch (macro tiles), the
