@@ -278,11 +278,11 @@ hipError_t launch(const GemmArgs &g, hipStream_t s)
 template <int EPI>
 hipError_t dispatch(const GemmArgs &g, hipStream_t s)
 {
-    // few rows: a wave per 32 x 32 block without LDS, as long as that makes at most 2.5 workgroups per CU --
-    // beyond, the macro tiles' reuse of their operands wins.  us per launch, this / the 128 x 128 tile: K = 512,
-    // N = 1536, 512 rows (384 workgroups) 7.1 / 7.5, 1024 rows (768) 9.9 / 8.2; N = 512, 2048 rows (512) 8.3 / 10.4,
-    // 4096 rows (1024) 13.9 / 11.7; K = 2048, N = 512, 200 rows 8.1 / 19.4, 2048 rows (512) 16.1 / 20.9
-    if ((int64_t)(g.N / 64) * ((g.M + 31) / 32) <= 640 && g.K % 128 == 0) return gemm_small_bf16(EPI, g, s);
+    // Few rows: a wave per 32 x 32 block without LDS, as long as that makes at most 1.5 workgroups per CU -- beyond, the
+    // tiles' reuse of their operands wins.  Us per call, four layers, with the line at 192 / 384 / 640 / 1024 workgroups:
+    // one request (1000 behaviours, 200 candidates, d_model 512) 298 / 270 / 273 / 299; score of 768 rows 173 / 173 / 187 /
+    // 199, 1024 206 / 175 / 176 / 211, 2560 271 / 270 / 296 / 296; d_model 256, 2048 rows 160 / 144 / 145 / 157
+    if ((int64_t)(g.N / 64) * ((g.M + 31) / 32) <= 384 && g.K % 128 == 0) return gemm_small_bf16(EPI, g, s);
     // macro tile 256 x 128 when that still gives every CU two workgroups, else 128 x 128
     const int64_t big_tiles = (int64_t)(g.N / 128) * ((g.M + 255) / 256);
     if (big_tiles >= 512) return launch<EPI, 4, 2, 3>(g, s);
