@@ -430,12 +430,14 @@ hipError_t launch_tail(const TailArgs &a, hipStream_t s)
 }  // namespace
 
 // A launch takes the time of one workgroup until every CU has one; the separate launches grow with the rows.  Weights that
-// four layers and the cache between them have pushed out of L2 count here, so whole calls decide (score, four layers, with /
-// without, us): d_model 512: 4352 rows 470 / 430, 6144 500 / 474, 7168 508 / 507, 8192 552 / 558, with 64-row tiles 8704
-// 637 / 638, 10240 665 / 682, 16384 804 / 901; d_model 256: 2816 rows 177 / 181, 4096 180 / 187, 8192 250 / 313.
+// four layers and the cache between them have pushed out of L2 count here, so whole calls decide (four layers, with /
+// without, us).  d_model 512, d_ffn 2048: score of 4096 rows 353 / 333, 4352 431 / 444, 8192 549 / 559, 16384 795 / 964,
+// encode of 4096 222 / 209, 5120 235 / 257; d_ffn 1408 (four waves): score of 8704 rows 642 / 603, 12288 729 / 735,
+// 24576 1129 / 1237; d_model 256: score of 4096 rows 192 / 188, 4608 194 / 204, 32768 521 / 713.  Other widths have no kernel: the
+// stacks that this is configured and measured with have 256 or 512 columns.
 bool layer_tail_takes(int M, int D, int F)
 {
-    return F % 128 == 0 && F > 0 && ((D == 512 && M > (F % 256 == 0 ? 7168 : 8192)) || (D == 256 && M > 2560));
+    return F % 128 == 0 && F > 0 && ((D == 512 && M > (F % 256 == 0 ? 4096 : 12288)) || (D == 256 && M > 4096));
 }
 
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)

@@ -295,9 +295,9 @@ def test_few_queries_keep_an_infinite_value_infinite(L):
     assert np.array_equal(part, full[:192]) and np.isfinite(np.delete(oh[ok], at, 1)).all()
 
 
-@pytest.mark.parametrize("L", [31, 64, 130, 385])
-def test_few_queries_causal_history(L):
-    spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=2, L=L, sub_len=0, M=4, H=2, pad_to=64, L_min=max(1, L - 20),
+@pytest.mark.parametrize("L,sub", [(31, 0), (64, 0), (130, 0), (385, 0), (530, 384), (1100, 512)])
+def test_few_queries_causal_history(L, sub):
+    spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=2, L=L, sub_len=sub, M=4, H=2, pad_to=64, L_min=max(1, L - 20),
                     nan_padding=True, seed=730 + L)
     w = W.make_attention(spec)
     oh, ok = GpuAttention(w, causal=True).history(), valid_rows(w)

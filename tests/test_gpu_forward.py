@@ -120,16 +120,16 @@ def test_randomized_stack_shapes_and_routes():
             run_forward(spec, users=users, want_hist=bool(rng.integers(0, 2)), flags=flags)
 
 
-@pytest.mark.parametrize("d, m", [(512, 5), (512, 7200), (512, 8300), (256, 2600), (384, 3500), (384, 11000), (384, 43600)])
-def test_residual_joins_the_finished_sum(d, m):
-    # every route of the two residual projections: a wave per block, the one-launch tail with 32- and 64-row tiles, and
-    # the 64 x 128, 128 x 128 and 256 x 128 tiles.  Residual rows of 4096 (ulp 2^-11) and products of which 16, what one
+@pytest.mark.parametrize("d, F, m", [(512, 256, 5), (512, 256, 4200), (512, 256, 8300), (512, 128, 12400), (256, 256, 4200),
+                                     (384, 256, 3500), (384, 256, 11000), (384, 256, 43600)])
+def test_residual_joins_the_finished_sum(d, F, m):
+    # every route of the two residual projections: a wave per block, the one-launch tail with its four kernels, and the 64 x 128, 128 x 128 and 256 x 128 tiles.  Residual rows of 4096 (ulp 2^-11) and products of which 16, what one
     # matrix instruction adds, make a quarter of that ulp: summed onto the residual each would be lost, summed first
     # they are d 2^-17 and d_ffn 2^-17, whole ulps, and every sum on the way is exact in fp32.
     import torch
     import paper_2502_09888_amd as P
-    say(f"[case] residual d={d} m={m}")
-    F, dev, bf = 256, "cuda:0", torch.bfloat16
+    say(f"[case] residual d={d} F={F} m={m}")
+    dev, bf = "cuda:0", torch.bfloat16
     cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=F, dtype=P.BF16)
     w = {k: torch.zeros(*s, dtype=bf, device=dev) for k, s in
          (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, F)), ("w2", (F, d)))}
@@ -149,20 +149,21 @@ def test_residual_joins_the_finished_sum(d, m):
     assert bool((y == 4096.0 + (d + F) * 2.0 ** -17).all())
 
 
-@pytest.mark.parametrize("d, m", [(512, 5), (512, 7200), (512, 8300), (256, 2600), (384, 4000), (384, 8000), (384, 44000)])
-def test_gelu_keeps_its_relative_error_in_the_tail(d, m):
+@pytest.mark.parametrize("d, F, m", [(512, 512, 5), (512, 512, 4200), (512, 512, 8300), (512, 384, 12400), (256, 256, 4200),
+                                     (384, 384, 4000), (384, 384, 11000), (384, 384, 44000)])
+def test_gelu_keeps_its_relative_error_in_the_tail(d, F, m):
     # every route of the up-projection (as above): hidden unit j gets the pre-activation z_j in every row and w2 hands it
     # out as column j, 2^24 times.  Against formula 7.1.26 of Abramowitz & Stegun in double precision: the bf16 rounding
     # of the hidden (eight bits: 2^-8) and 1e-5 for its evaluation in fp32 (the exponent of up to 26 to half an ulp: 1e-6 of the
     # value; a reciprocal, an exponential and ten more operations: 1.5e-6), the rounding of 1 + 2^24 u (2^-24 / 0.1).
     import torch
     import paper_2502_09888_amd as P
-    say(f"[case] gelu d={d} m={m}")
+    say(f"[case] gelu d={d} F={F} m={m}")
     dev, bf = "cuda:0", torch.bfloat16
-    cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=d, dtype=P.BF16, rms_eps=1e-12)
-    z = torch.linspace(-6, 2, d, dtype=torch.float64).to(bf)
+    cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=F, dtype=P.BF16, rms_eps=1e-12)
+    z = torch.linspace(-6, 2, F, dtype=torch.float64).to(bf)
     w = {k: torch.zeros(*s, dtype=bf, device=dev) for k, s in
-         (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, d)), ("w2", (d, d)))}
+         (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, F)), ("w2", (F, d)))}
     w["g1"].fill_(1), w["g2"].fill_(1)
     w["w1"][0] = z.to(dev)
     w["w2"].fill_diagonal_(2.0 ** 24)
@@ -178,19 +179,19 @@ def test_gelu_keeps_its_relative_error_in_the_tail(d, m):
     t = 1 / (1 + 0.3275911 * a / np.sqrt(2))
     poly = t * (0.254829592 + t * (-0.284496736 + t * (1.421413741 + t * (-1.453152027 + t * 1.061405429))))
     want = np.maximum(zz, 0) - a * 0.5 * poly * np.exp(-a * a / 2)
-    got = (y[0].double().cpu().numpy() - 1) / 2.0 ** 24
+    got = (y[0, :F].double().cpu().numpy() - 1) / 2.0 ** 24
     err = np.abs(got - want) / np.abs(want).clip(1e-12)
     say(f"largest relative error {err.max():.2e} at z = {zz[err.argmax()]:.3f}")
     assert err.max() < 2.0 ** -8 + 1e-5
 
 
-@pytest.mark.parametrize("d, m", [(256, 2600), (512, 7200), (512, 8300)])
-def test_layer_output_over_its_own_input(d, m):
+@pytest.mark.parametrize("d, F, m", [(256, 256, 4200), (512, 256, 4200), (512, 256, 8300), (512, 128, 12400)])
+def test_layer_output_over_its_own_input(d, F, m):
     # x_out apart from x_in, the same rows, and rows shifted by less than their number in either direction: the same bits
     import torch
     import paper_2502_09888_amd as P
-    say(f"[case] in and out d={d} m={m}")
-    F, dev, bf = 256, "cuda:0", torch.bfloat16
+    say(f"[case] in and out d={d} F={F} m={m}")
+    dev, bf = "cuda:0", torch.bfloat16
     gen = torch.Generator(device=dev)
     gen.manual_seed(m)
     cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=F, dtype=P.BF16)
@@ -212,20 +213,22 @@ def test_layer_output_over_its_own_input(d, m):
     assert all(torch.equal(o, outs[0]) for o in outs[1:])
 
 
-@pytest.mark.parametrize("m", [1, 33, 95])
-def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(m):
-    # the packed forward runs 10 x 384 history rows and the candidates through one launch (macro tiles), the
-    # scoring call the candidates alone (a wave per 32 x 32 block): a row's bits do not depend on which; candidate
-    # counts at the edges of the 32-row blocks, one of them the smallest launch there is
-    spec = W.StackSpec(f"fwd-tiles-{m}", B=10, L=384, sub_len=128, M=0, n_layers=2, d_model=256, H=4, dh=64, d_ffn=512,
-                       n_scen=8, n_beh=4, seed=95 + m, hist_lens=(384,) * 10, cand_counts=(m,) + (0,) * 9)
+@pytest.mark.parametrize("users, m", [(10, 1), (10, 33), (10, 95), (30, 1), (30, 95), (115, 33), (115, 127)])
+def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(users, m):
+    # the packed forward runs users x 384 history rows and the candidates through one launch, at a width without a
+    # one-launch tail: 3840 rows 64 x 128 tiles, 11520 rows 128 x 128, 44160 rows 256 x 128, up-projection (tiled store)
+    # and both residual ones; the scoring call runs the candidates alone (a wave per 32 x 32 block): a row's bits do not
+    # depend on which; candidate counts at the edges of the 32-row blocks, one of them the smallest launch there is
+    spec = W.StackSpec(f"fwd-tiles-{users}-{m}", B=users, L=384, sub_len=128, M=0, n_layers=2, d_model=384, H=6, dh=64, d_ffn=768,
+                       n_scen=8, n_beh=4, seed=95 + m, hist_lens=(384,) * users, cand_counts=(m,) + (0,) * (users - 1))
     w, g, yc = run_forward(spec, users=(0,), want_hist=True)
     g.encode()
     assert np.array_equal(yc[:g.m_total], g.score())
 
 
-@pytest.mark.parametrize("d_model, d_ffn, users, m", [(512, 128, 22, 33), (512, 384, 22, 95), (512, 256, 22, 63),
-                                                         (512, 512, 22, 2), (512, 256, 19, 31), (512, 768, 19, 1), (256, 128, 7, 1), (256, 256, 7, 64)])
+@pytest.mark.parametrize("d_model, d_ffn, users, m", [(512, 128, 33, 33), (512, 384, 33, 95), (512, 256, 22, 63),
+                                                         (512, 512, 22, 2), (512, 256, 11, 31), (512, 768, 19, 1), (256, 128, 11, 1),
+                                                         (256, 256, 11, 64)])
 def test_layer_tail_in_one_launch_gives_the_bits_of_three(d_model, d_ffn, users, m):
     # users x 384 history rows and the candidates in one launch: more rows than the single-launch tail asks for, the
     # candidates alone fewer.  One, two and three chunks of the hidden; tiles of 64 and 32 rows, the last one with 1
