@@ -535,8 +535,14 @@ hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
 
 hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
 {
-    // candidates: 256-query tiles when a head has more than 128
-    if (sumi) return a.max_rows_per_user > 128 ? launch_bias<2, true, false>(a, s) : launch_bias<1, true, false>(a, s);
+    // Candidates: 256-query tiles once 128-query tiles make more than two workgroups per CU.  Us, 256 / 128, 8 heads,
+    // histories of 1024: 200 candidates of one user (16 workgroups of 128) 35 / 22, 512 of 16 (512) 36 / 31, of 24 (768)
+    // 49 / 46, of 32 (1024) 53 / 58, 128 of 64 (512) 49 / 33; histories of 215, 692 of 5 users, 2 heads (60) 15.7 / 10.5, of
+    // 16, 8 heads (768) 21.9 / 24.9.  Same bits.
+    if (sumi) {
+        const bool few = (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 127) / 128) <= 512;
+        return few || a.max_rows_per_user <= 128 ? launch_bias<1, true, false>(a, s) : launch_bias<2, true, false>(a, s);
+    }
     return a.causal ? launch_bias<1, false, true>(a, s) : launch_bias<1, false, false>(a, s);
 }
 

@@ -253,3 +253,22 @@ def test_bf16_bias_entries_of_unseen_keys_do_not_matter(L, sub, causal, qk_scale
         assert np.array_equal(oc, outs[0][1])
         assert oh is None or np.array_equal(oh, outs[0][0])
     assert np.isfinite(outs[0][1]).all()
+
+
+@pytest.mark.parametrize("L", [40, 300])
+def test_bf16_bias_few_and_many_candidates_give_the_same_bits(L):
+    # 128-query tiles up to 512 workgroups, 256-query tiles beyond: 33000 candidates of two heads in one call, 700 of them
+    spec = W.shrink(W.CONFIG2, name=f"bias-tiles-{L}", B=1, L=L, sub_len=0, M=33000, H=2, pad_to=64, nan_padding=True, seed=980 + L)
+    w = W.add_bias_inputs(W.make_attention(spec), n_pos=33, n_time=12)
+    g = GpuBias(w)
+    g.history(want_output=False)
+    full = g.sumi_bias()
+    part = dict(w)
+    for n in ("qc", "kc", "vc", "cscen", "cbeh", "cand_pos", "cand_ts"):
+        part[n] = np.ascontiguousarray(w[n][:700])
+    part["cand_off"] = np.array([0, 700], np.int32)
+    g = GpuBias(part)
+    g.history(want_output=False)
+    got = g.sumi_bias()
+    assert np.array_equal(got, full[:700])
+    assert max_abs(got, oracle_sumi_bias(part)) < TOL["bf16"]
