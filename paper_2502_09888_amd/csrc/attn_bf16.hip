@@ -619,16 +619,28 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
 // Query-tile shape: 4 waves x QB blocks of 32 queries per workgroup.  QB = 2 (256 queries) re-reads
 // a head's K/V from L2 half as often and reuses every LDS fragment for two MFMAs; QB = 1 (128
 // queries) keeps two waves per SIMD busy when a head has few queries.
-// Launches of at most one wave of 32 queries per SIMD (1024) go to attn_wave_bf16.hip: us per launch there / here
-// for 8 heads and a history of 1000: 200 candidates of one user (56 waves) 11.8 / 19.4, of 16 users (896) 16.8 / 20.6, 256 of
-// 32 users (2048) 31 / 27; history pass over one user's 4096 behaviours (1024) 48 / 73, over 8 x 1024 (2048) 24.5 / 22.5.
-bool few_queries(const AttnArgs &a) { return (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 31) / 32) <= 1024; }
+// Launches of few queries go to attn_wave_bf16.hip: at most one wave of 32 per SIMD (1024), fewer where the tiles are well
+// filled or the walk is too short to hide a launch's ends.  Us per call there / here, 8 heads.
+//   candidates, more than 128 or up to 64 a user: 200 of one user against 1000 (56 waves) 11.8 / 19.4, 256 of 16 (1024)
+//     against 1024 17.8 / 20.9, against 256 9.0 / 9.0, against 128 9.0 / 8.0; 64 of 64 (1024) against 512 14.8 / 15.8,
+//     against 128 9.2 / 7.6; 256 of 32 (2048) 31 / 27
+//   65 to 128 (128-query tiles, full ones): 128 of 8 (256) against 1024 11.5 / 12.8, of 16 (512) 13.4 / 14.0, against 512
+//     9.5 / 9.3, 96 of 32, 4 heads (384) against 512 9.4 / 9.0, 128 of 32 (1024) against 1024 18.0 / 16.5
+//   history pass: one user's 4096 (1024) 48 / 73, 16 of 256 13.7 / 14.7, 8 of 1024 (2048) 24.5 / 22.5; subsequences of 384
+//     (128-query tiles) of 2 x 1024 (512) 11.3 / 11.3, of 4 x 1024 (1024) 15.1 / 14.3
+bool few_queries(const AttnArgs &a, bool sumi)
+{
+    const int64_t waves = (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 31) / 32);
+    if (!sumi) return waves <= (a.sub_len % 256 == 0 || a.sub_len == 128 ? 1024 : 512);
+    if (a.max_rows_per_user > 64 && a.max_rows_per_user <= 128) return waves <= (a.max_hist_len > 640 ? 512 : 256);
+    return waves <= (a.max_hist_len >= 256 ? 1024 : 512);
+}
 }  // namespace
 
 hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 {
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, true, s);
-    if (few_queries(a)) return launch_attn_wave_bf16(a, true, s);
+    if (few_queries(a, true)) return launch_attn_wave_bf16(a, true, s);
     return a.max_rows_per_user > 128 ? launch<4, 2, true>(a, s) : launch<4, 1, true>(a, s);
 }
 
@@ -636,7 +648,7 @@ hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s)
 {
     // a query tile must lie inside one subsequence (sub_len is 0 or a multiple of 128)
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, false, s);
-    if (few_queries(a)) return launch_attn_wave_bf16(a, false, s);
+    if (few_queries(a, false)) return launch_attn_wave_bf16(a, false, s);
     const bool wide = a.sub_len % 256 == 0;
     if (a.causal) return wide ? launch<4, 2, false, true>(a, s) : launch<4, 1, false, true>(a, s);
     return wide ? launch<4, 2, false>(a, s) : launch<4, 1, false>(a, s);
