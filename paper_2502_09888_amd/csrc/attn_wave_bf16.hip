@@ -226,8 +226,7 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
             // Step `blk` (slot U of the group): the logits of block blk + 1, the exponentials of block blk (whose logits
             // are in Sc) and the value product of block blk - 1 (whose probabilities are in Pp) -- three chains that
             // do not depend on each other.  TAIL: the last group; keys past the end of the range (the whole block,
-            // where it lies beyond) get the logit -inf, i.e. add zeros -- to values of zero, where an infinite one of the
-            // last block would make them NaN -- and nothing is requested that is not used.
+            // where it lies beyond) get the logit -inf, i.e. add zeros, and nothing is requested that is not used.
             auto step = [&](int blk, f32x16 (&Sc)[1], f32x16 (&Sn)[1], bf16x8 (&Pc)[1][2], const bf16x8 (&Pp)[1][2], auto u_tag,
                             auto tail_tag) __attribute__((always_inline)) {
                 constexpr int U = decltype(u_tag)::value;
@@ -238,12 +237,7 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
                 if constexpr (FOLD) softmax_fast(st, Sc, Pc);
                 else st.l[0] += exp_pack<true>(Sc[0], st.c[0], 0.f, Pc[0]);
                 pv_block(st, vf[(U + 1) % kRing], Pp);
-                if constexpr (!TAIL) {
-                    load_block_v(blk + 1, vf[(U + 1) % kRing]);
-                } else if constexpr (U < 3) {
-                    if (blk + 1 < n_blk) load_block_v(blk + 1, vf[(U + 1) % kRing]);
-                    else vf[(U + 1) % kRing] = VFrags{};
-                }
+                if constexpr (!TAIL || U < 3) load_block_v(blk + 1, vf[(U + 1) % kRing]);
                 // the wave issues in order: a product, then exponentials while it runs
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
@@ -282,7 +276,9 @@ __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
                 step(blk + 2, S0, S1, P0, P1, u2, tail);
                 step(blk + 3, S1, S0, P1, P0, u3, tail);
             }
-            pv_block(st, vf[1], P1);
+            // (of an odd number the last one is missing: zeros times the values of the one before, which an infinite one among
+            // them would make NaN)
+            if ((n_blk & 1) == 0) pv_block(st, vf[1], P1);
         };
         if (fold) run(std::true_type{});
         else run(std::false_type{});
