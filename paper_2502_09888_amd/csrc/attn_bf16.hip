@@ -623,7 +623,7 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
 // filled or the walk is too short to hide a launch's ends.  Us per call there / here, 8 heads.
 //   candidates, more than 128 or up to 64 a user: 200 of one user against 1000 (56 waves) 11.8 / 19.4, 256 of 16 (1024)
 //     against 1024 17.8 / 20.9, against 256 9.0 / 9.0, against 128 9.0 / 8.0; 64 of 64 (1024) against 512 14.8 / 15.8,
-//     against 128 9.2 / 7.6; 256 of 32 (2048) 31 / 27
+//     against 128 9.2 / 7.6; 10 of 66 (528) against 193, the history pass with it, 40.7 / 44.9; 256 of 32 (2048) 31 / 27
 //   65 to 128 (128-query tiles, full ones): 128 of 8 (256) against 1024 11.5 / 12.8, of 16 (512) 13.4 / 14.0, against 512
 //     9.5 / 9.3, 96 of 32, 4 heads (384) against 512 9.4 / 9.0, 128 of 32 (1024) against 1024 18.0 / 16.5
 //   history pass: one user's 4096 (1024) 48 / 73, 16 of 256 13.7 / 14.7, 8 of 1024 (2048) 24.5 / 22.5; subsequences of 384
@@ -633,7 +633,7 @@ bool few_queries(const AttnArgs &a, bool sumi)
     const int64_t waves = (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 31) / 32);
     if (!sumi) return waves <= (a.sub_len % 256 == 0 || a.sub_len == 128 ? 1024 : 512);
     if (a.max_rows_per_user > 64 && a.max_rows_per_user <= 128) return waves <= (a.max_hist_len > 640 ? 512 : 256);
-    return waves <= (a.max_hist_len >= 256 ? 1024 : 512);
+    return waves <= (a.max_hist_len >= 256 || a.max_rows_per_user <= 32 ? 1024 : 512);
 }
 }  // namespace
 
