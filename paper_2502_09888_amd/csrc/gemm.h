@@ -87,7 +87,7 @@ hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s);
 
 // layer_tail_bf16.hip: y = h + GELU(RMSNorm(h) W1) W2 with h = x + o Wo, one launch.  Rows of D columns: o bf16,
 // x / y fp32, yb (nullable) bf16; ss (nullable) [M][D / 64] sums of squares of y; wo [D][D], w1 [D][F] (gains
-// multiplied in), w2 [F][D] packed.  y may be x.
+// multiplied in), w2 [F][D] packed.  y may be x, or lies apart from it; its rows may hold h for a while.
 struct TailArgs {
     const void *o;
     const float *x;

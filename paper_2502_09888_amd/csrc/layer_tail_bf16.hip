@@ -4,7 +4,7 @@
 // hidden (d_ffn columns) go out to memory and come back: at d_model 512, d_ffn 2048 a row moves 20 KiB, of which 6
 // are the row's own input and output, and the launches wait for those bytes about as long as for their products.
 // Here a workgroup owns 32*RB rows and all their columns: the bf16 copy of h and one chunk of the hidden live in LDS,
-// h itself in registers or (64 rows of 512 columns) in the rows of y until y replaces it, and only weights -- packed
+// h itself in registers or (64 rows of 512 columns, four waves) in the rows of y until y replaces it, and only weights -- packed
 // fragments, L2-resident -- stream in, straight into registers.
 //
 // NW waves side by side over the columns: a wave owns D / NW columns of h / y and 32 columns of every chunk of the
