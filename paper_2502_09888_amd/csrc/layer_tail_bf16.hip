@@ -18,8 +18,8 @@
 // pay for the residuals' exact place (h as the start value of the second sum: 3 to 11 times the rounding error) and 12
 // for the GELU's relative error in the tail (see gelu_stage).  Four waves with h by way of memory (64 MB out and back,
 // by all workgroups at once) take about 20 us more.  32 rows (RB = 1) where 64 would leave CUs without work: bound by
-// the weights out of L2 (20 TB/s over the chip), 16 fragments in flight per wave; 8192 rows 77 us between the other
-// launches of a stack.  (Taller tiles would need less of the caches, but 128 rows do not fit the registers; separate waves
+// the weights' way through the vector cache (the same bytes for half the products); 8192 rows 62 us between the other
+// launches of a stack, 76 without the weights requested ahead (PRE below).  (Taller tiles would need less of the caches, but 128 rows do not fit the registers; separate waves
 // for the two products gave the same times.)
 // Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
 // bits.
@@ -66,8 +66,16 @@ using At = std::integral_constant<int, N>;
 // The next fragments of the stream of weights: fragment e at base + (e % NJ) * a + (e / NJ) * b.
 struct Next { int base, a, b; };
 
-template <int D, int RB, int NW, int R>
-__global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p)
+// PRE = 1: one more wave, which requests the weights for the L2 of its XCD ahead of their use.  A workgroup of its own has to
+// itself a CU, and the 32 of an XCD walk over the same weights at the same time: what is not in L2 (kernels' boundaries
+// and four layers with the cache between them see to that) costs all of them a trip to memory every 8 or 16 fragments.
+// So every workgroup requests its share of them, one 8 KiB piece per load (a lane per 128-byte line; four bytes of each land
+// in a corner of LDS that nobody reads), a chunk of the hidden ahead.  By one of the other waves those loads would delay
+// its own, which return in order.  Us, four layers scored, 8192 rows: 484 with a 268 MB cache between (539 without), 379
+// with a short one (389); by the computing waves at their start 493 and 393.  With it eight fragments in flight do what
+// 16 did, and the registers hold a third wave per SIMD.  64-row tiles do not gain (and have no registers for it).
+template <int D, int RB, int NW, int R, int PRE>
+__global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(const TailArgs p)
 {
     constexpr int ROWS = 32 * RB, CW = D / NW, NJ = CW / 32;   // rows of the tile; columns and column blocks of a wave
     constexpr int kChunk = 32 * NW;                            // hidden columns of a chunk
@@ -92,6 +100,40 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
         const int c = col / 8;
         *(bf16x4 *)(op + (32 * i + l32) * pitch + (((c & ~15) | ((c & 15) ^ r15)) * 16) + 8 * hf) = v;
     };
+
+    if (PRE && wave == NW) {  // pieces in the order of use: Wo, W1 of chunk 0; per chunk W1 of the next, W2 of this one
+        constexpr int PO = D * D * 2 / 8192, P1 = NW * S / 8, P2 = (D / 32) * (T / 8);
+        static_assert(S % 8 == 0 && T % 8 == 0, "whole pieces");
+        const int n_pieces = PO + n_chunks * (P1 + P2), sharers = ((int)gridDim.x + 7) / 8;
+        int k = blockIdx.x / 8;  // (workgroups go round the eight XCDs)
+        auto request = [&](int end) __attribute__((always_inline)) {
+            for (; k < min(end, n_pieces); k += sharers) {
+                int at = k * 8192, r = k - PO - P1;
+                if (r >= 0) {
+                    const int ch = r / (P1 + P2);
+                    r %= P1 + P2;
+                    const int c = r - (ch + 1 < n_chunks ? P1 : 0);
+                    at = c < 0 ? p.w1 + (ch + 1) * (NW * S * 1024) + r * 8192
+                               : p.w2 + (c / (T / 8)) * ((F / 16) * 1024) + ch * T * 1024 + (c % (T / 8)) * 8192;
+                } else if (k >= PO) {
+                    at = p.w1 + (k - PO) * 8192;
+                }
+                __builtin_amdgcn_global_load_lds((glb_u8 *)((const uint8_t *)p.wo + at + lane * 128),
+                                                 (lds_u8 *)lds + tail_lds_bytes<D, RB, NW>(), 4, 0, 0);
+            }
+        };
+        int ahead = PO + P1 + (P1 + P2);
+        request(ahead);
+        for (int i = 0; i < 4; ++i) __builtin_amdgcn_s_barrier();  // the barriers below, one for one
+        for (int ch = 0; ch + 1 < n_chunks; ++ch) {
+            request(ahead += P1 + P2);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_s_barrier();
+        }
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): nothing may land in LDS that is no longer the workgroup's
+        return;
+    }
 
     // the attention output rows -> X, whole rows
     {
@@ -416,14 +458,14 @@ __global__ __launch_bounds__(NW * 64, 2) void layer_tail_kernel(const TailArgs p
     }
 }
 
-template <int D, int RB, int NW, int R>
+template <int D, int RB, int NW, int R, int PRE>
 hipError_t launch_tail(const TailArgs &a, hipStream_t s)
 {
-    constexpr size_t lds = tail_lds_bytes<D, RB, NW>();
-    constexpr auto kernel = layer_tail_kernel<D, RB, NW, R>;
+    constexpr size_t lds = tail_lds_bytes<D, RB, NW>() + PRE * 256;
+    constexpr auto kernel = layer_tail_kernel<D, RB, NW, R, PRE>;
     const hipError_t e = raise_lds_limit<kernel>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((a.M + 32 * RB - 1) / (32 * RB))), dim3(NW * 64), lds, s, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((a.M + 32 * RB - 1) / (32 * RB))), dim3((NW + PRE) * 64), lds, s, a);
     return hipGetLastError();
 }
 
@@ -432,7 +474,8 @@ hipError_t launch_tail(const TailArgs &a, hipStream_t s)
 // A launch takes the time of one workgroup until every CU has one; the separate launches grow with the rows.  Weights that
 // four layers and the cache between them have pushed out of L2 count here, so whole calls decide (four layers, with /
 // without, us).  d_model 512, d_ffn 2048: score of 4096 rows 353 / 333, 4352 431 / 444, 8192 549 / 559, 16384 795 / 964,
-// encode of 4096 222 / 209, 5120 235 / 257; d_ffn 1408 (four waves): score of 8704 rows 642 / 603, 12288 729 / 735,
+// encode of 4096 222 / 209, 5120 235 / 257 (without weights requested ahead; with them score of 4096 rows 298 / 282 and 362 / 361
+// with a short and a long history, 3072 280 / 255 and 321 / 304); d_ffn 1408 (four waves): score of 8704 rows 642 / 603, 12288 729 / 735,
 // 24576 1129 / 1237; d_model 256: score of 4096 rows 192 / 188, 4608 194 / 204, 32768 521 / 713.  Other widths have no kernel: the
 // stacks that this is configured and measured with have 256 or 512 columns.
 bool layer_tail_takes(int M, int D, int F)
@@ -446,9 +489,9 @@ hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)
     // d_model 512: eight waves need chunks of 256; no more than a 32-row tile per CU: those (fewer rows in line behind one
     // another).  Four waves hold twice the columns each, and h has to wait in memory.  Us, stack calls of four layers, eight
     // / four waves: encode of 32768 rows 853 / 907, score of 8704 594 / 727, of 16384 772 / 919.
-    if (a.D == 512 && a.F % 256 == 0) return a.M <= 8192 ? launch_tail<512, 1, 8, 16>(a, s) : launch_tail<512, 2, 8, 8>(a, s);
-    if (a.D == 512) return launch_tail<512, 2, 4, 8>(a, s);
-    if (a.D == 256) return launch_tail<256, 2, 4, 8>(a, s);
+    if (a.D == 512 && a.F % 256 == 0) return a.M <= 8192 ? launch_tail<512, 1, 8, 8, 1>(a, s) : launch_tail<512, 2, 8, 8, 0>(a, s);
+    if (a.D == 512) return launch_tail<512, 2, 4, 8, 0>(a, s);
+    if (a.D == 256) return launch_tail<256, 2, 4, 8, 0>(a, s);
     return hipErrorInvalidValue;
 }
 

@@ -239,3 +239,14 @@ def test_layer_tail_in_one_launch_gives_the_bits_of_three(d_model, d_ffn, users,
     w, g, yc = run_forward(spec, users=(0,), want_hist=True)
     g.encode()
     assert np.array_equal(yc[:g.m_total], g.score())
+
+
+@pytest.mark.parametrize("d_ffn, users, m", [(256, 11, 1), (512, 11, 32), (2048, 12, 33), (256, 16, 2048), (1024, 16, 2047)])
+def test_layer_tail_with_weights_requested_ahead_gives_the_bits_of_three(d_ffn, users, m):
+    # 32-row tiles at d_model 512, from 4097 to 8192 rows: one to eight chunks of the hidden, the fewest and the most
+    # workgroups that share out the requests; the candidates alone by separate launches
+    spec = W.StackSpec(f"fwd-ahead-{d_ffn}-{m}", B=users, L=384, sub_len=128, M=0, n_layers=2, d_model=512, H=8, dh=64, d_ffn=d_ffn,
+                       n_scen=8, n_beh=4, seed=240 + m, hist_lens=(384,) * users, cand_counts=(m,) + (0,) * (users - 1))
+    w, g, yc = run_forward(spec, users=(1,), want_hist=True)
+    g.encode()
+    assert np.array_equal(yc[:g.m_total], g.score())
