@@ -476,3 +476,12 @@ def test_device_side_input_check():
     w["cscen"][7] = spec.n_scen - 1
     g.history(want_output=False)
     assert max_abs(g.sumi(), oracle_sumi(w)) < 2e-2
+
+
+@pytest.mark.parametrize("n_scen,n_beh", [(1, 1), (255, 1), (257, 1), (1792, 2), (3585, 1)])
+def test_bf16_tiles_find_their_temperature_in_tables_of_any_size(n_scen, n_beh):
+    # one copy of 256 entries or less, more than one, the most that are staged in LDS and one more than that; query tiles
+    # of 256, the last of them nearly empty, both passes.  TOL: see above.
+    spec = W.shrink(W.CONFIG2, name=f"bf16-tau-{n_scen * n_beh}", B=16, L=700, sub_len=512, M=530, H=4, pad_to=64, n_scen=n_scen,
+                    n_beh=n_beh, seed=820)
+    check_all(W.make_attention(spec))
