@@ -485,3 +485,29 @@ def test_bf16_tiles_find_their_temperature_in_tables_of_any_size(n_scen, n_beh):
     spec = W.shrink(W.CONFIG2, name=f"bf16-tau-{n_scen * n_beh}", B=16, L=700, sub_len=512, M=530, H=4, pad_to=64, n_scen=n_scen,
                     n_beh=n_beh, seed=820)
     check_all(W.make_attention(spec))
+
+
+@pytest.mark.parametrize("B,M", [(16, 530), (36, 100)])
+@pytest.mark.parametrize("rows", [(5,), (70, 40), (5, 40, 70, 99)])
+def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
+    # Queries along one key, 2^24 above the others for candidates (folded form: window 2^20), 2^115 for history rows (exact
+    # scale: 2^100); keys in every wave's share, in the last block, and the candidate's own.  One and two times 32 queries of
+    # a 256- or 128-query tile redone by themselves, or the tile as a whole.  TOL: see above (an output is nearly one value row,
+    # below 4: its own rounding is 2^-7).
+    spec = W.shrink(W.CONFIG2, name=f"bf16-redo-{M}-{len(rows)}", B=B, L=700, sub_len=512, M=M, H=4, pad_to=64, seed=830)
+    w = W.make_attention(spec)
+    w["tau"] = np.ones_like(w["tau"])
+    for n in ("qh", "qc", "kc", "vh", "vc"):
+        w[n] = w[n].copy()
+    w["vh"], w["vc"] = w["vh"].clip(-3.9375, 3.9375), w["vc"].clip(-3.9375, 3.9375)
+    for b in range(B):
+        t0, c0 = int(w["tok_off"][b]), int(w["cand_off"][b])
+        for i, r in enumerate(rows):
+            key = (699, 40, 200, 600)[(b + i) % 4]
+            w["qc"][c0 + r] = W.round_bf16(w["kh"][t0 + key] * (16.6 / (w["kh"][t0 + key] ** 2).sum(-1, keepdims=True) * 8))
+            if (b + i) % 5 == 4:
+                w["kc"][c0 + r] = W.round_bf16(w["qc"][c0 + r] * (17.5 / (w["qc"][c0 + r] ** 2).sum(-1, keepdims=True) * 8))
+            key = (3, 2, r // 2, r)[(b + i) % 4]
+            w["qh"][t0 + r] = W.round_bf16(w["kh"][t0 + key] * (80 / (w["kh"][t0 + key] ** 2).sum(-1, keepdims=True) * 8))
+    check_all(w)
+    check_all(w, causal=True, flags=TWO_KERNEL)
