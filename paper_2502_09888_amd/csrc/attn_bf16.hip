@@ -386,6 +386,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                 ss += xhalf(ss);  // the 32 keys of the block
                 big |= !(ss * st.c[qb] * st.c[qb] < kBlockKeys * kPilotSpread * kPilotSpread);
             }
+            if (SUMI && QB == 1 && p.pilot_pairs && k_hi - k_lo >= kFoldMinKeys) {
+                // users with more than 128 candidates: the choice is made for 64 queries, as by the waves of the 256-query tiles.
+                // (Through the landing slices, whose query rows are in registers; own rows come into them after the next barrier.)
+                const bool any = __builtin_amdgcn_ballot_w64(big) != 0;
+                if (lane == 0) *(volatile int *)rows_lds = any;
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                const int mate = *(volatile int *)(lds + kStages * kTileBytes + (wave ^ 1) * (WQ * 128));
+                big |= mate != 0;
+            }
             // Only the candidate pass folds, and only against a history of some length: its rows then have
             // many comparable keys to average the per-logit error over.  History rows
             // see one subsequence (a few keys only under the causal flag) and can be sharply peaked, where
@@ -722,14 +732,35 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
     const int groups = (a.cache.B * a.H + 7) / 8;
     const int64_t grid = (int64_t)8 * n_qtiles * groups;
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-    const KParams p = make_params(a, n_qtiles);
+    KParams p = make_params(a, n_qtiles);
+    p.pilot_pairs = SUMI && QB == 1 && a.max_rows_per_user > 128;
     hipLaunchKernelGGL((attn_bf16_kernel<NW, QB, SUMI, CAUSAL>), dim3((unsigned)grid), dim3(NW * 64), 0, s, p);
     return hipGetLastError();
 }
 
 // Query-tile shape: 4 waves x QB blocks of 32 queries per workgroup.  QB = 2 (256 queries) re-reads
 // a head's K/V from L2 half as often and reuses every LDS fragment for two MFMAs; QB = 1 (128
-// queries) keeps two waves per SIMD busy when a head has few queries.
+// queries) keeps two waves per SIMD busy when a head has few queries, pads a user's candidates by less, and deals
+// the work out in smaller pieces where there are few workgroups or users of very different lengths.  Scoring, us, 256 / 128
+// queries, 8 heads:
+//   all users alike, as many rows with either: 32 x 256 against 1024 (256 workgroups of 256) 24.5 / 23.1, 24 x 512 (384) 34.1 / 31.9,
+//     28 x 512 against 512 (448) 22.3 / 24.2, 64 x 256 (512) 41.2 / 43.2, 64 x 512 (1024) 76.0 / 83.3
+//   fewer rows: 64 x 257 (384 rows instead of 512) 66.8 / 58.3, 40 x 300 against 600 33.9 / 26.9, 60 x 640 against 512 (640, 768) 59.1 /
+//     57.7, 30 x 896 (896, 1024) 67.0 / 67.6
+//   users that differ (a quarter of the longest at least), up to 256 candidates of 24 users against 2000 (about 220) 32.1 / 22.8, 900 of 12 against
+//     4000 (260) 59.7 / 46.7, 1024 of 16 against 4096 (380) 82.2 / 77.9, of 24 (580) 107.4 / 103.4, 512 of 48 against 1500 (670)
+//     51.5 / 53.7, 1024 of 64 against 2048 (1540) 154 / 157
+bool small_tiles(const AttnArgs &a)
+{
+    const int64_t m = a.max_rows_per_user, heads = (int64_t)a.cache.B * a.H;
+    if (m <= 128) return true;
+    if (a.uni_cand >= 0) {
+        const int64_t r1 = (m + 127) / 128 * 128, r2 = (m + 255) / 256 * 256;
+        return 6 * r1 <= 5 * r2 || heads * (r2 / 256) <= (a.uni_len >= 0 ? 384 : 576);
+    }
+    return a.total_q_rows * a.H / 256 + heads / 2 <= 576;  // (half a tile per head is padding)
+}
+
 // Launches of few queries go to attn_wave_bf16.hip: at most one wave of 32 per SIMD (1024), fewer where the tiles are well
 // filled or the walk is too short to hide a launch's ends.  Us per call there / here, 8 heads.
 //   candidates, more than 128 or up to 64 a user: 200 of one user against 1000 (56 waves) 11.8 / 19.4, 256 of 16 (1024)
@@ -752,7 +783,7 @@ hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 {
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, true, s);
     if (few_queries(a, true)) return launch_attn_wave_bf16(a, true, s);
-    return a.max_rows_per_user > 128 ? launch<4, 2, true>(a, s) : launch<4, 1, true>(a, s);
+    return small_tiles(a) ? launch<4, 1, true>(a, s) : launch<4, 2, true>(a, s);
 }
 
 hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s)
