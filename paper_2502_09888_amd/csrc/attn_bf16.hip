@@ -41,6 +41,7 @@
 //     mask.
 #include "attn_common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace climber {
@@ -70,10 +71,17 @@ __device__ __forceinline__ void wait_tiles(int tiles_in_flight)
     }
 }
 
-template <int NW, int QB, bool SUMI, bool CAUSAL = false>
+// RAW (history pass): the keys and values are rows, as the projection wrote them, and this launch writes them into the cache
+// as well.  Key and value tiles travel into the ring as whole 128-byte rows (16-byte chunk c of row r at slot c ^ (r / 2) % 8); key
+// fragments are row pieces, value fragments come out of the rows by LDS transpose reads (as in hist_fused_bf16.hip).  Every
+// wave writes the cache blocks of its own rows, which come by the landing buffer while it attends, as a candidate's own rows
+// do: nothing of it is in the loop.
+template <int NW, int QB, bool SUMI, bool CAUSAL = false, bool RAW = false>
 __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
 {
     static_assert(!(SUMI && CAUSAL), "the causal flag concerns the history pass");
+    static_assert(!(SUMI && RAW) && (!RAW || NW == 4), "rows: the history pass, two slabs of 32 rows");
+    constexpr bool OWN = SUMI || RAW;  // the tile's own key and value rows come by the landing buffer
     static_assert(kStages == 3, "tile t+1 is read while tile t is computed and one more is in flight; "
                                 "every wait in the FAST loop drains all copies");
     constexpr int NT = NW * 64;
@@ -130,7 +138,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         if (q0 >= Lpad) return;
         row0 = (int64_t)t0 + q0;
         nq = max(0, min(TQ, Lb - q0));
-        if (nq == 0) {  // a tile of padding rows only: defined output, zeros
+        if (nq == 0) {  // a tile of padding rows only: defined output, zeros (and zeros in the cache)
+            if (RAW) {
+                uint8_t *dst = const_cast<uint8_t *>(p.layer_base) + ((size_t)t0 * p.H + (size_t)h * Lpad) * (kDHead * 4) +
+                               (size_t)(q0 / kBlockKeys) * kBlockBytes;
+                for (int i = tid; i < min(TQ, Lpad - q0) * (kDHead * 4 / 16); i += NT) ((uint4 *)dst)[i] = uint4{0, 0, 0, 0};
+            }
             for (int idx = tid; idx < TQ * (kDHead / 8); idx += NT) {
                 const int r = idx / (kDHead / 8), cc = idx % (kDHead / 8);
                 if (q0 + r < Lpad)
@@ -159,7 +172,29 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     // K/V tiles go HBM -> LDS directly (no register staging): every wave copies NPRE slabs of
     // 1 KiB (64 lanes x 16 B) per tile; the LDS image equals the HBM image.
     // tile t into the ring stage at byte offset `stage` (= (t % kStages) * kTileBytes)
+    const uint8_t *raw_k = nullptr, *raw_v = nullptr;
+    uint32_t raw_lane = 0, k_lane[4] = {}, v_lane = 0;
+    if constexpr (RAW) {
+        raw_k = uniform_ptr((const uint8_t *)(p.k_self + ((int64_t)t0 + k_lo) * p.ld_kv + h * kDHead));
+        raw_v = uniform_ptr((const uint8_t *)(p.v_self + ((int64_t)t0 + k_lo) * p.ld_kv + h * kDHead));
+        const int r = tid >> 3;
+        raw_lane = (uint32_t)r * (uint32_t)p.ld_kv * 2u + (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) k_lane[s] = (uint32_t)(l32 * 128 + (((2 * s + hf) ^ ((l32 >> 1) & 7)) * 16));
+        // lane 4 j + a of a group of 16 names four columns of a row and receives four rows of one column: see hist_fused_bf16.hip
+        const int G = lane >> 4, i16 = lane & 15, x = 2 * (G & 1) + ((i16 >> 1) & 1), y = 2 * (G >> 1) + (i16 >> 3);
+        v_lane = (uint32_t)(8192 + (4 * (G >> 1) + (i16 >> 2)) * 128 + (x ^ y) * 16 + 8 * (i16 & 1));
+    }
     auto issue_tile_at = [&](int t, int stage) __attribute__((always_inline)) {
+        if constexpr (RAW) {  // (the 64 rows of a tile exist: padded lengths are multiples of 64)
+            const int64_t at = (int64_t)t * kTileKeys * p.ld_kv * 2, half = (int64_t)32 * p.ld_kv * 2;
+            lds_u8 *to = (lds_u8 *)lds + stage + wave * 1024;
+            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_k + at) + raw_lane, to, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_k + at + half) + raw_lane, to + 4096, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_v + at) + raw_lane, to + 8192, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_v + at + half) + raw_lane, to + 12288, 16, 0, 0);
+            return;
+        }
         glb_u8 *src = (glb_u8 *)(kv + (size_t)t * kTileBytes + (size_t)tid * 16);
         lds_u8 *dst = (lds_u8 *)lds + stage + wave * 1024;
 #pragma unroll
@@ -167,6 +202,48 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             __builtin_amdgcn_global_load_lds(src + i * NT * 16, dst + i * NT * 16, 16, 0, 0);
     };
     auto issue_tile = [&](int t) __attribute__((always_inline)) { issue_tile_at(t, (t % kStages) * kTileBytes); };
+    // fragments of block blk of the tile in the ring stage at byte offset `so`
+    auto tile_k = [&](int so, int blk) __attribute__((always_inline)) {
+        if constexpr (!RAW) return load_k(lds + so + blk * kBlockBytes, lane);
+        KFrags f;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) f.a[s] = *(const bf16x8 *)(lds + so + k_lane[s] + blk * 4096);
+        return f;
+    };
+    auto transpose_read = [&](uint32_t at) __attribute__((always_inline)) {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));  // (for a wave's own rows: no copy is in flight there)
+        return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)((lds_u8 *)lds + at));
+    };
+    auto tile_v = [&](int so, int blk) __attribute__((always_inline)) {
+        if constexpr (!RAW) return load_v(lds + so + blk * kBlockBytes, lane);
+        // (One block of inline assembly with its wait: for the builtin, with copies in flight, the compiler waits until all of
+        // them have landed.  In the loop it stands behind the MFMAs of the next logits, which run meanwhile.)
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        s16x4 x[8];
+        asm volatile("ds_read_b64_tr_b16 %0, %8 offset:0\n\tds_read_b64_tr_b16 %1, %8 offset:1088\n\t"
+                     "ds_read_b64_tr_b16 %2, %8 offset:64\n\tds_read_b64_tr_b16 %3, %8 offset:1024\n\t"
+                     "ds_read_b64_tr_b16 %4, %8 offset:2048\n\tds_read_b64_tr_b16 %5, %8 offset:3136\n\t"
+                     "ds_read_b64_tr_b16 %6, %8 offset:2112\n\tds_read_b64_tr_b16 %7, %8 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+                     : "v"((uint32_t)(uintptr_t)(lds_u8 *)lds + (uint32_t)so + v_lane + (uint32_t)blk * 4096u)
+                     : "memory");
+        VFrags f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            f.a[i >> 1][i & 1] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x[2 * i], x[2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+        return f;
+    };
+    // RAW: the value rows of the last tile beyond the range may hold anything: zeros, before they meet probabilities of 0
+    auto clear_tail = [&](int so, int tile_lo) __attribute__((always_inline)) {
+        if constexpr (RAW) {
+            if (tile_lo + kTileKeys > k_hi) {
+                const int first = k_hi - tile_lo;
+                for (int i = tid; i < (kTileKeys - first) * 8; i += NT) *(uint4 *)(lds + so + 8192 + first * 128 + i * 16) = uint4{0, 0, 0, 0};
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+            }
+        }
+    };
     QState<QB> st;
     // FAST start: the raw query rows stay in st.qf and the row scale in st.c until the first block's
     // logits have shown which form of the pass the wave takes; empty state (the candidate's own
@@ -283,7 +360,27 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     // one against at most 128 keys), then O += w * v_own (behind the seventh; behind the last against at most 256).
     float w_own[QB];
     bool fold = false;  // the wave runs the pass with the scale folded into a bf16 query (decided below)
+    // RAW: the cache blocks of the wave's rows, zeros where a slot has no row
+    auto own_block = [&](int qb) __attribute__((always_inline)) {
+        return const_cast<uint8_t *>(p.layer_base) + ((size_t)t0 * p.H + (size_t)h * Lpad) * (kDHead * 4) +
+               (size_t)((q0 + wave * WQ) / kBlockKeys + qb) * kBlockBytes + lane * 16;
+    };
     auto own_k = [&]() __attribute__((always_inline)) {
+        if constexpr (RAW) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                if (q0 + wave * WQ + qb * 32 >= Lpad) break;
+                const int r = qb * 32 + l32;
+                uint8_t *dst = own_block(qb);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    u32x4 x = *(const u32x4 *)(rows_lds + r * 128 + (((2 * s + hf) ^ (r & 7)) * 16));
+                    if (wave * WQ + r >= nq) x = u32x4{0, 0, 0, 0};
+                    *(u32x4 *)(dst + s * 1024) = x;
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const int r = qb * 32 + l32;
@@ -304,6 +401,31 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         }
     };
     auto own_v = [&]() __attribute__((always_inline)) {
+        if constexpr (RAW) {
+            const int G = lane >> 4, i16 = lane & 15;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                if (q0 + wave * WQ + qb * 32 >= Lpad) break;
+                uint8_t *dst = own_block(qb) + 4096;
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+#pragma unroll
+                    for (int db = 0; db < 2; ++db) {
+                        bf16x8 x;
+#pragma unroll
+                        for (int hh = 0; hh < 2; ++hh) {
+                            const int r = qb * 32 + 16 * g + 8 * hh + 4 * (G >> 1) + (i16 >> 2), c = 4 * db + 2 * (G & 1) + ((i16 >> 1) & 1);
+                            const bf16x4 part = __builtin_bit_cast(
+                                bf16x4, transpose_read((uint32_t)(rows_lds - lds) + r * 128 + ((c ^ (r & 7)) * 16) + 8 * (i16 & 1)));
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                x[4 * hh + e] = wave * WQ + qb * 32 + 16 * g + 8 * hh + 4 * hf + e < nq ? part[e] : (__bf16)0.f;
+                        }
+                        *(u32x4 *)(dst + (g * 2 + db) * 1024) = __builtin_bit_cast(u32x4, x);
+                    }
+            }
+            return;
+        }
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const int r = qb * 32 + l32;
@@ -367,7 +489,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         {
-            const KFrags k0 = load_k(lds, lane);
+            const KFrags k0 = tile_k(0, 0);
             qk_block(st, k0, S0);
             // Which form of the FAST pass?  Folding the row scale c = qk_scale*log2(e)/tau into the bf16
             // query saves a multiplication per logit but rounds q*c to 8 bits, an error of 2^-9 of every
@@ -437,13 +559,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         // additions and its own address register instead of an immediate.
         auto tile_step = [&](int t, int so_cur, int so_nxt, int so_fill, auto ev_tag) __attribute__((always_inline)) {
             constexpr int EV = decltype(ev_tag)::value;
-            const uint8_t *cur = lds + so_cur;
-            const uint8_t *nxt = lds + so_nxt;
             {   // block 0 of tile t: its logits are in S0; start block 1's logits
-                const KFrags k1 = load_k(cur + kBlockBytes, lane);
-                const VFrags v0 = load_v(cur, lane);
+                const KFrags k1 = tile_k(so_cur, 1);
+                VFrags v0;
+                if (!RAW) v0 = tile_v(so_cur, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 qk_block(st, k1, S1);
+                if (RAW) v0 = tile_v(so_cur, 0);
                 causal(S1, k_lo + t * kTileKeys + kBlockKeys);
                 soft(S0);
                 pv_block(st, v0, P);
@@ -453,17 +575,19 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             wait_tiles<NPRE>(0);
             __builtin_amdgcn_s_barrier();
             // the landing slice is overwritten: this wave's earlier reads of it must have returned
-            if (SUMI && (EV == 1 || EV == 3)) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (SUMI && EV == 1) issue_rows(p.k_self, p.ld_kv);
-            if (SUMI && EV == 3) issue_rows(p.v_self, p.ld_kv);
+            if (OWN && (EV == 1 || EV == 3)) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (OWN && EV == 1) issue_rows(p.k_self, p.ld_kv);
+            if (OWN && EV == 3) issue_rows(p.v_self, p.ld_kv);
             if (t + 2 < n_tiles) issue_tile_at(t + 2, so_fill);
-            if (SUMI && EV == 2) own_k();
-            if (SUMI && EV == 4) own_v();
+            if (OWN && EV == 2) own_k();
+            if (OWN && EV == 4) own_v();
             {   // block 1 of tile t; start block 0 of tile t+1
-                const KFrags k0 = load_k(nxt, lane);
-                const VFrags v1 = load_v(cur + kBlockBytes, lane);
+                const KFrags k0 = tile_k(so_nxt, 0);
+                VFrags v1;
+                if (!RAW) v1 = tile_v(so_cur, 1);
                 __builtin_amdgcn_sched_barrier(0);
                 qk_block(st, k0, S0);
+                if (RAW) v1 = tile_v(so_cur, 1);
                 causal(S0, k_lo + (t + 1) * kTileKeys);
                 soft(S1);
                 pv_block(st, v1, P);
@@ -491,23 +615,24 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         }
         {   // last tile: 1..64 keys, S0 holds its first block
             const int t = n_tiles - 1;
-            const uint8_t *cur = lds + (t % kStages) * kTileBytes;
+            const int so_cur = (t % kStages) * kTileBytes;
             const int tile_lo = k_lo + t * kTileKeys;
+            clear_tail(so_cur, tile_lo);
             const bool two = tile_lo + kBlockKeys < k_hi;
             if (two) {
-                const KFrags k1 = load_k(cur + kBlockBytes, lane);
+                const KFrags k1 = tile_k(so_cur, 1);
                 qk_block(st, k1, S1);
                 causal(S1, tile_lo + kBlockKeys);
             }
             if (tile_lo + kBlockKeys > k_hi) mask_block(S0, hf, tile_lo, k_hi);
             {
-                const VFrags v0 = load_v(cur, lane);
+                const VFrags v0 = tile_v(so_cur, 0);
                 soft(S0);
                 pv_block(st, v0, P);
             }
             if (two) {
                 if (tile_lo + kTileKeys > k_hi) mask_block(S1, hf, tile_lo + kBlockKeys, k_hi);
-                const VFrags v1 = load_v(cur + kBlockBytes, lane);
+                const VFrags v1 = tile_v(so_cur, 1);
                 soft(S1);
                 pv_block(st, v1, P);
             }
@@ -522,7 +647,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     // lane % 32 again, opaquely: otherwise the compiler carries the old copy across the loop (in
     // scratch memory, which would be this kernel's only use of it)
     asm volatile("v_and_b32 %0, 31, %1" : "=v"(l32) : "v"(tid));
-    if (SUMI) {  // whatever part of the own-row schedule a short history left undone
+    if (OWN) {  // whatever part of the own-row schedule a short history left undone
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (n_tiles < 2) issue_rows(p.k_self, p.ld_kv);
         if (n_tiles < 3) {
@@ -558,27 +683,28 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
 #pragma unroll
     for (int w = 0; w < NW; ++w) redo |= flag_lds[w * (WQ * 32)] << (w * QB);
     redo = __builtin_amdgcn_readfirstlane(redo);
-    if (__builtin_popcount(redo) > NW * QB / 4) {  // many: the whole tile in one walk, through the ring
+    if (__builtin_popcount(redo) > (RAW ? 0 : NW * QB / 4)) {  // many (RAW: any): the whole tile in one walk, through the ring
         prologue();
         init_safe();
         for (int t = 0; t < n_tiles; ++t) {
             wait_tiles<NPRE>(min(t + kStages - 1, n_tiles) - (t + 1));
             __builtin_amdgcn_s_barrier();
             if (t + kStages - 1 < n_tiles) issue_tile(t + kStages - 1);
-            const uint8_t *cur = lds + (t % kStages) * kTileBytes;
+            const int so_cur = (t % kStages) * kTileBytes;
             const int tile_lo = k_lo + t * kTileKeys;
+            clear_tail(so_cur, tile_lo);
 #pragma unroll
             for (int blk = 0; blk < 2; ++blk) {
                 const int blk_lo = tile_lo + blk * kBlockKeys;
                 if (blk_lo < k_hi) {
                     f32x16 S[QB];
                     bf16x8 P[QB][2];
-                    const KFrags kf = load_k(cur + blk * kBlockBytes, lane);
+                    const KFrags kf = tile_k(so_cur, blk);
                     qk_block(st, kf, S);
                     if (blk_lo + kBlockKeys > k_hi) mask_block(S, hf, blk_lo, k_hi);
                     causal(S, blk_lo);
                     softmax_safe(st, S, P);
-                    const VFrags vf = load_v(cur + blk * kBlockBytes, lane);
+                    const VFrags vf = tile_v(so_cur, blk);
                     pv_block(st, vf, P);
                 }
             }
@@ -592,6 +718,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     // parts.  (As a rule it is one row with one key far above the others.  Redoing the whole tile for it took a launch with one
     // workgroup per CU twice its time, 66 us against 34 for 8192 candidates of a stack; 32 rows this way take 9 us, a tile in one walk
     // 30.)  q unscaled; the own key / value is the first member of wave 0's part.
+    if constexpr (!RAW)
     for (; redo != 0; redo &= redo - 1) {
         const int id = __builtin_ctz(redo), own = id / QB, first = own * WQ + (id % QB) * 32;
         int ln;  // the lane once more (of what this needs, nothing is held in registers across the FAST pass)
@@ -724,7 +851,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     }
 }
 
-template <int NW, int QB, bool SUMI, bool CAUSAL = false>
+template <int NW, int QB, bool SUMI, bool CAUSAL = false, bool RAW = false>
 hipError_t launch(const AttnArgs &a, hipStream_t s)
 {
     constexpr int TQ = NW * 32 * QB;
@@ -734,7 +861,7 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
     KParams p = make_params(a, n_qtiles);
     p.pilot_pairs = SUMI && QB == 1 && a.max_rows_per_user > 128;
-    hipLaunchKernelGGL((attn_bf16_kernel<NW, QB, SUMI, CAUSAL>), dim3((unsigned)grid), dim3(NW * 64), 0, s, p);
+    hipLaunchKernelGGL((attn_bf16_kernel<NW, QB, SUMI, CAUSAL, RAW>), dim3((unsigned)grid), dim3(NW * 64), 0, s, p);
     return hipGetLastError();
 }
 
@@ -761,6 +888,19 @@ bool small_tiles(const AttnArgs &a)
     return a.total_q_rows * a.H / 256 + heads / 2 <= 576;  // (half a tile per head is padding)
 }
 
+// The history pass: a query tile lies inside one subsequence (sub_len is 0 or a multiple of 128); 256 queries where that allows them
+// and they are neither few nor poorly filled.  Us, 256 / 128 queries, from rows: 12 users x 300, 8 heads (192 workgroups of 256)
+// 12.2 / 11.3, 20 x 2000, 4 heads (640) 102.7 / 100.0, 128 x 500, 4 heads (1024) 50.6 / 54.9, 64 x 1024 in one subsequence (2048) 173 / 197; up to 333
+// of 128 (users of 40 to 384 rows) 45.7 / 35.0, 300 x 65 26.4 / 21.4.
+bool hist_wide_tiles(const AttnArgs &a)
+{
+    if (a.sub_len % 256 != 0) return false;
+    const int64_t B = a.cache.B, most = a.max_rows_per_user, total = a.total_q_rows;
+    // rows that the tiles cover; of users that differ, about half a tile each is padding
+    const int64_t r1 = a.uni_pad >= 0 ? B * ((most + 127) / 128 * 128) : total + B * 32, r2 = a.uni_pad >= 0 ? B * ((most + 255) / 256 * 256) : total + B * 96;
+    return 6 * r1 > 5 * r2 && r2 / 256 * a.H > 640;
+}
+
 // Launches of few queries go to attn_wave_bf16.hip: at most one wave of 32 per SIMD (1024), fewer where the tiles are well
 // filled or the walk is too short to hide a launch's ends.  Us per call there / here, 8 heads.
 //   candidates, more than 128 or up to 64 a user: 200 of one user against 1000 (56 waves) 11.8 / 19.4, 256 of 16 (1024)
@@ -779,6 +919,23 @@ bool few_queries(const AttnArgs &a, bool sumi)
 }
 }  // namespace
 
+// From rows, one launch, or the cache writer and a launch that reads the cache: two launches only where a wave per 32 queries
+// (attn_wave_bf16.hip) has a long walk to make, which tiles make more slowly.  Us from rows / as two, 8 heads: 4 users x 1024 behaviours in one
+// subsequence 16.8 / 22.3, in two 11.2 / 16.9, one user's 1000 in two 10.4 / 10.9, 2000 in one 28.1 / 23.9, 4096 in one 53.5 / 47.9; where two would
+// be the tiled kernel: 16 x up to 4096 in subsequences of 512 77.8 / 93.1, 64 x 1024 in one 167.6 / 187.9, causal 64 x 1000 in two 113 / 124.
+bool attn_hist_rows_bf16_takes(const AttnArgs &a)
+{
+    const int walk = a.sub_len > 0 ? std::min(a.sub_len, a.max_hist_len) : a.max_hist_len;
+    return !a.bias.pos_table && (walk <= 1024 || !few_queries(a, false));
+}
+
+hipError_t launch_attn_hist_rows_bf16(const AttnArgs &a, hipStream_t s)
+{
+    const bool wide = hist_wide_tiles(a);
+    if (a.causal) return wide ? launch<4, 2, false, true, true>(a, s) : launch<4, 1, false, true, true>(a, s);
+    return wide ? launch<4, 2, false, false, true>(a, s) : launch<4, 1, false, false, true>(a, s);
+}
+
 hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 {
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, true, s);
@@ -788,10 +945,9 @@ hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 
 hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s)
 {
-    // a query tile must lie inside one subsequence (sub_len is 0 or a multiple of 128)
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, false, s);
     if (few_queries(a, false)) return launch_attn_wave_bf16(a, false, s);
-    const bool wide = a.sub_len % 256 == 0;
+    const bool wide = hist_wide_tiles(a);
     if (a.causal) return wide ? launch<4, 2, false, true>(a, s) : launch<4, 1, false, true>(a, s);
     return wide ? launch<4, 2, false>(a, s) : launch<4, 1, false>(a, s);
 }

@@ -154,11 +154,14 @@ int attn_history_strided(const climber_config *cfg, const float *tau_layer, cons
     a.total_q_rows = cache->rows;
     if (bias) a.bias = BiasArgs{bias->pos_table, bias->time_table, bias->hist_pos, bias->hist_ts, bias->hist_pos,
                                 bias->hist_ts, bias->n_pos, bias->n_time};
-    // fp32: likewise, unless the output lies on the rows that other workgroups still read
-    const size_t row_bytes = (size_t)cache->rows * ld * 4, o_bytes = (size_t)cache->rows * ld_o * 4;
+    // other subsequences, and fp32: likewise, unless the output lies on the rows that other workgroups still read
+    const size_t elem = cfg->dtype == CLIMBER_F32 ? 4 : 2;
+    const size_t row_bytes = (size_t)cache->rows * ld * elem, o_bytes = (size_t)cache->rows * ld_o * elem;
     auto apart = [&](const void *x) { return (uintptr_t)x + row_bytes <= (uintptr_t)o || (uintptr_t)o + o_bytes <= (uintptr_t)x; };
-    const bool fused_f32 = cfg->dtype == CLIMBER_F32 && o && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) && attn_tile_f32_takes(a, false) && apart(k) && apart(v);
-    if (fused || fused_f32) {
+    const bool one_launch = !fused && o && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) && apart(k) && apart(v);
+    const bool fused_f32 = one_launch && cfg->dtype == CLIMBER_F32 && attn_tile_f32_takes(a, false);
+    const bool fused_rows = one_launch && cfg->dtype == CLIMBER_BF16 && attn_hist_rows_bf16_takes(a);
+    if (fused || fused_f32 || fused_rows) {
     } else if (cfg->dtype == CLIMBER_BF16) {
         int e = rt(launch_kv_write_bf16(cv, k, v, ld, cfg->n_heads, cache->max_pad, s));
         if (e) return e;
@@ -169,6 +172,7 @@ int attn_history_strided(const climber_config *cfg, const float *tau_layer, cons
     if (!o) return CLIMBER_OK;
     if (fused_f32) return rt(launch_attn_tile_f32(a, false, cache->rows, true, s));
     if (fused) return rt(launch_hist_fused_bf16(a, s));
+    if (fused_rows) return rt(launch_attn_hist_rows_bf16(a, s));
     if (cfg->dtype == CLIMBER_BF16) return rt(launch_attn_hist_bf16(a, s));
     return rt(launch_attn_f32(a, false, cache->rows, s));
 }

@@ -55,6 +55,10 @@ struct AttnArgs {
 // bf16 MFMA flash attention (attn_bf16.hip)
 hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s);
+// the history pass from the key / value rows a.k_self / a.v_self, which nothing in the launch may overwrite, into outputs and
+// cache at once: where it is the faster way
+bool attn_hist_rows_bf16_takes(const AttnArgs &a);
+hipError_t launch_attn_hist_rows_bf16(const AttnArgs &a, hipStream_t s);
 // the same for launches of few queries, a wave per 32 of them (attn_wave_bf16.hip); no bias
 hipError_t launch_attn_wave_bf16(const AttnArgs &a, bool sumi, hipStream_t s);
 // the same with the relative attention bias (attn_bias_bf16.hip)

@@ -511,3 +511,49 @@ def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
             w["qh"][t0 + r] = W.round_bf16(w["kh"][t0 + key] * (80 / (w["kh"][t0 + key] ** 2).sum(-1, keepdims=True) * 8))
     check_all(w)
     check_all(w, causal=True, flags=TWO_KERNEL)
+
+
+@pytest.mark.parametrize("B,L,L_min,sub,H,pad", [(1, 1, 1, 0, 1, 64), (3, 63, 0, 384, 2, 64), (3, 65, 64, 0, 1, 64), (4, 129, 0, 512, 2, 64),
+                                                 (5, 300, 1, 0, 4, 64), (2, 448, 256, 0, 2, 128), (6, 700, 0, 640, 3, 64), (2, 1024, 900, 512, 8, 64),
+                                                 (30, 1100, 400, 512, 8, 64), (25, 1500, None, 0, 8, 128), (40, 830, None, 384, 8, 64)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_history_from_rows_writes_the_bits_of_two_launches(B, L, L_min, sub, H, pad, causal):
+    # outputs and the whole cache, over what was in both before: tiles of 128 queries (few of them, subsequences of odd multiples of 128)
+    # and of 256 (the last three), histories down to none, at the edges of blocks and tiles, tiles of padding only; NaN in the padding
+    import torch
+    spec = W.shrink(W.CONFIG2, name=f"bf16-rows-{L}-{sub}", B=B, L=L, L_min=L_min, sub_len=sub, M=1, H=H, pad_to=pad, nan_padding=True, seed=840 + L)
+    w = W.make_attention(spec)
+    say(f"[case] {spec.name} causal={causal}")
+    out = []
+    for flags in (0, TWO_KERNEL):
+        g = GpuAttention(w, causal=causal, flags=flags)
+        payload = int(w["tok_off"][-1]) * H * 256
+        g.buf[-payload:].fill_(77)
+        oh, ok = g.history(), valid_rows(w)
+        assert np.isfinite(oh[ok]).all() and np.all(oh[~ok] == 0)
+        out.append((oh, g.buf[-payload:].clone()))
+    assert np.array_equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    # outputs over the key or the value rows
+    for name in ("kh", "vh"):
+        g = GpuAttention(w, causal=causal)
+        rows = getattr(g, name)
+        g.P.climber_attn_history(g.cfg, g.tau, g.qh, g.kh, g.vh, g.scen, g.beh, g.cache, 0, rows)
+        torch.cuda.synchronize()
+        assert np.array_equal(rows.float().cpu().numpy().reshape(out[0][0].shape), out[0][0])
+        assert torch.equal(g.buf[-payload:], out[0][1])
+
+
+@pytest.mark.parametrize("B,H", [(2, 2), (30, 8)])
+def test_history_from_rows_redoes_a_tile_that_one_key_outgrows(B, H):
+    # 2^115 above the other keys of the row (window 2^100): the whole tile walks once more over the rows, up to a last tile of
+    # keys that ends in NaN.  TOL: see above.
+    spec = W.shrink(W.CONFIG2, name=f"bf16-rows-redo-{B}", B=B, L=1000, sub_len=512, M=1, H=H, pad_to=64, nan_padding=True, seed=850)
+    w = W.make_attention(spec)
+    w["tau"], w["qh"] = np.ones_like(w["tau"]), w["qh"].copy()
+    for b in range(B):
+        t0 = int(w["tok_off"][b])
+        for r, key in ((5, 3), (600, 520), (999, 999)):
+            w["qh"][t0 + r] = W.round_bf16(w["kh"][t0 + key] * (80 / (w["kh"][t0 + key] ** 2).sum(-1, keepdims=True) * 8))
+    w["vh"] = w["vh"].clip(-3.9375, 3.9375)
+    check_all(w)
+    check_all(w, causal=True)
