@@ -72,8 +72,7 @@ __device__ __forceinline__ void wait_tiles(int tiles_in_flight)
 }
 
 // RAW (history pass): the keys and values are rows, as the projection wrote them, and this launch writes them into the cache
-// as well.  Key and value tiles travel into the ring as whole 128-byte rows (16-byte chunk c of row r at slot c ^ (r / 2) % 8); key
-// fragments are row pieces, value fragments come out of the rows by LDS transpose reads (as in hist_fused_bf16.hip).  Every
+// as well.  Key and value tiles travel into the ring as rows (RawTiles, attn_common.h).  Every
 // wave writes the cache blocks of its own rows, which come by the landing buffer while it attends, as a candidate's own rows
 // do: nothing of it is in the loop.
 template <int NW, int QB, bool SUMI, bool CAUSAL = false, bool RAW = false>
@@ -172,29 +171,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     // K/V tiles go HBM -> LDS directly (no register staging): every wave copies NPRE slabs of
     // 1 KiB (64 lanes x 16 B) per tile; the LDS image equals the HBM image.
     // tile t into the ring stage at byte offset `stage` (= (t % kStages) * kTileBytes)
-    const uint8_t *raw_k = nullptr, *raw_v = nullptr;
-    uint32_t raw_lane = 0, k_lane[4] = {}, v_lane = 0;
-    if constexpr (RAW) {
-        raw_k = uniform_ptr((const uint8_t *)(p.k_self + ((int64_t)t0 + k_lo) * p.ld_kv + h * kDHead));
-        raw_v = uniform_ptr((const uint8_t *)(p.v_self + ((int64_t)t0 + k_lo) * p.ld_kv + h * kDHead));
-        const int r = tid >> 3;
-        raw_lane = (uint32_t)r * (uint32_t)p.ld_kv * 2u + (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) k_lane[s] = (uint32_t)(l32 * 128 + (((2 * s + hf) ^ ((l32 >> 1) & 7)) * 16));
-        // lane 4 j + a of a group of 16 names four columns of a row and receives four rows of one column: see hist_fused_bf16.hip
-        const int G = lane >> 4, i16 = lane & 15, x = 2 * (G & 1) + ((i16 >> 1) & 1), y = 2 * (G >> 1) + (i16 >> 3);
-        v_lane = (uint32_t)(8192 + (4 * (G >> 1) + (i16 >> 2)) * 128 + (x ^ y) * 16 + 8 * (i16 & 1));
-    }
+    RawTiles raw;
+    if constexpr (RAW) raw = raw_tiles(p, (int64_t)t0 + k_lo, h, tid);
     auto issue_tile_at = [&](int t, int stage) __attribute__((always_inline)) {
-        if constexpr (RAW) {  // (the 64 rows of a tile exist: padded lengths are multiples of 64)
-            const int64_t at = (int64_t)t * kTileKeys * p.ld_kv * 2, half = (int64_t)32 * p.ld_kv * 2;
-            lds_u8 *to = (lds_u8 *)lds + stage + wave * 1024;
-            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_k + at) + raw_lane, to, 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_k + at + half) + raw_lane, to + 4096, 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_v + at) + raw_lane, to + 8192, 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((glb_u8 *)(raw_v + at + half) + raw_lane, to + 12288, 16, 0, 0);
-            return;
-        }
+        if constexpr (RAW) return raw_issue(raw, t, (lds_u8 *)lds + stage + wave * 1024);
         glb_u8 *src = (glb_u8 *)(kv + (size_t)t * kTileBytes + (size_t)tid * 16);
         lds_u8 *dst = (lds_u8 *)lds + stage + wave * 1024;
 #pragma unroll
@@ -204,45 +184,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     auto issue_tile = [&](int t) __attribute__((always_inline)) { issue_tile_at(t, (t % kStages) * kTileBytes); };
     // fragments of block blk of the tile in the ring stage at byte offset `so`
     auto tile_k = [&](int so, int blk) __attribute__((always_inline)) {
-        if constexpr (!RAW) return load_k(lds + so + blk * kBlockBytes, lane);
-        KFrags f;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) f.a[s] = *(const bf16x8 *)(lds + so + k_lane[s] + blk * 4096);
-        return f;
-    };
-    auto transpose_read = [&](uint32_t at) __attribute__((always_inline)) {
-        typedef short s16x4 __attribute__((ext_vector_type(4)));  // (for a wave's own rows: no copy is in flight there)
-        return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)((lds_u8 *)lds + at));
+        if constexpr (RAW) return raw_k(raw, lds + so, blk);
+        else return load_k(lds + so + blk * kBlockBytes, lane);
     };
     auto tile_v = [&](int so, int blk) __attribute__((always_inline)) {
-        if constexpr (!RAW) return load_v(lds + so + blk * kBlockBytes, lane);
-        // (One block of inline assembly with its wait: for the builtin, with copies in flight, the compiler waits until all of
-        // them have landed.  In the loop it stands behind the MFMAs of the next logits, which run meanwhile.)
-        typedef short s16x4 __attribute__((ext_vector_type(4)));
-        s16x4 x[8];
-        asm volatile("ds_read_b64_tr_b16 %0, %8 offset:0\n\tds_read_b64_tr_b16 %1, %8 offset:1088\n\t"
-                     "ds_read_b64_tr_b16 %2, %8 offset:64\n\tds_read_b64_tr_b16 %3, %8 offset:1024\n\t"
-                     "ds_read_b64_tr_b16 %4, %8 offset:2048\n\tds_read_b64_tr_b16 %5, %8 offset:3136\n\t"
-                     "ds_read_b64_tr_b16 %6, %8 offset:2112\n\tds_read_b64_tr_b16 %7, %8 offset:3072\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
-                     : "v"((uint32_t)(uintptr_t)(lds_u8 *)lds + (uint32_t)so + v_lane + (uint32_t)blk * 4096u)
-                     : "memory");
-        VFrags f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            f.a[i >> 1][i & 1] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x[2 * i], x[2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7));
-        return f;
+        if constexpr (RAW) return raw_v(raw, lds + so, blk);
+        else return load_v(lds + so + blk * kBlockBytes, lane);
     };
-    // RAW: the value rows of the last tile beyond the range may hold anything: zeros, before they meet probabilities of 0
     auto clear_tail = [&](int so, int tile_lo) __attribute__((always_inline)) {
-        if constexpr (RAW) {
-            if (tile_lo + kTileKeys > k_hi) {
-                const int first = k_hi - tile_lo;
-                for (int i = tid; i < (kTileKeys - first) * 8; i += NT) *(uint4 *)(lds + so + 8192 + first * 128 + i * 16) = uint4{0, 0, 0, 0};
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-            }
-        }
+        if constexpr (RAW)
+            if (tile_lo + kTileKeys > k_hi) raw_clear(lds + so, k_hi - tile_lo, tid);
     };
     QState<QB> st;
     // FAST start: the raw query rows stay in st.qf and the row scale in st.c until the first block's
@@ -363,22 +314,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     // RAW: the cache blocks of the wave's rows, zeros where a slot has no row
     auto own_block = [&](int qb) __attribute__((always_inline)) {
         return const_cast<uint8_t *>(p.layer_base) + ((size_t)t0 * p.H + (size_t)h * Lpad) * (kDHead * 4) +
-               (size_t)((q0 + wave * WQ) / kBlockKeys + qb) * kBlockBytes + lane * 16;
+               (size_t)((q0 + wave * WQ) / kBlockKeys + qb) * kBlockBytes;
     };
     auto own_k = [&]() __attribute__((always_inline)) {
         if constexpr (RAW) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                if (q0 + wave * WQ + qb * 32 >= Lpad) break;
-                const int r = qb * 32 + l32;
-                uint8_t *dst = own_block(qb);
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    u32x4 x = *(const u32x4 *)(rows_lds + r * 128 + (((2 * s + hf) ^ (r & 7)) * 16));
-                    if (wave * WQ + r >= nq) x = u32x4{0, 0, 0, 0};
-                    *(u32x4 *)(dst + s * 1024) = x;
-                }
-            }
+            for (int qb = 0; qb < QB; ++qb)
+                if (q0 + wave * WQ + qb * 32 < Lpad) own_block_k(own_block(qb), rows_lds + qb * 4096, nq - wave * WQ - qb * 32, lane);
             return;
         }
 #pragma unroll
@@ -402,28 +344,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     };
     auto own_v = [&]() __attribute__((always_inline)) {
         if constexpr (RAW) {
-            const int G = lane >> 4, i16 = lane & 15;
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                if (q0 + wave * WQ + qb * 32 >= Lpad) break;
-                uint8_t *dst = own_block(qb) + 4096;
-#pragma unroll
-                for (int g = 0; g < 2; ++g)
-#pragma unroll
-                    for (int db = 0; db < 2; ++db) {
-                        bf16x8 x;
-#pragma unroll
-                        for (int hh = 0; hh < 2; ++hh) {
-                            const int r = qb * 32 + 16 * g + 8 * hh + 4 * (G >> 1) + (i16 >> 2), c = 4 * db + 2 * (G & 1) + ((i16 >> 1) & 1);
-                            const bf16x4 part = __builtin_bit_cast(
-                                bf16x4, transpose_read((uint32_t)(rows_lds - lds) + r * 128 + ((c ^ (r & 7)) * 16) + 8 * (i16 & 1)));
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                x[4 * hh + e] = wave * WQ + qb * 32 + 16 * g + 8 * hh + 4 * hf + e < nq ? part[e] : (__bf16)0.f;
-                        }
-                        *(u32x4 *)(dst + (g * 2 + db) * 1024) = __builtin_bit_cast(u32x4, x);
-                    }
-            }
+            for (int qb = 0; qb < QB; ++qb)
+                if (q0 + wave * WQ + qb * 32 < Lpad) own_block_v(own_block(qb), rows_lds + qb * 4096, nq - wave * WQ - qb * 32, lane);
             return;
         }
 #pragma unroll
@@ -926,11 +849,12 @@ bool few_queries(const AttnArgs &a, bool sumi)
 bool attn_hist_rows_bf16_takes(const AttnArgs &a)
 {
     const int walk = a.sub_len > 0 ? std::min(a.sub_len, a.max_hist_len) : a.max_hist_len;
-    return !a.bias.pos_table && (walk <= 1024 || !few_queries(a, false));
+    return a.bias.pos_table || walk <= 1024 || !few_queries(a, false);
 }
 
 hipError_t launch_attn_hist_rows_bf16(const AttnArgs &a, hipStream_t s)
 {
+    if (a.bias.pos_table) return launch_attn_hist_rows_bias_bf16(a, s);
     const bool wide = hist_wide_tiles(a);
     if (a.causal) return wide ? launch<4, 2, false, true, true>(a, s) : launch<4, 1, false, true, true>(a, s);
     return wide ? launch<4, 2, false, false, true>(a, s) : launch<4, 1, false, false, true>(a, s);

@@ -41,11 +41,14 @@ __device__ __forceinline__ int half_wave_reduce(int x, F &&f)
 template <int QB>
 constexpr int kClassBytes = NW * QB * 64 * 4;
 
-// IN_LDS: the head's rows of the tables are copied into LDS (else looked up in global memory)
-template <int QB, bool SUMI, bool CAUSAL, bool IN_LDS>
+// IN_LDS: the head's rows of the tables are copied into LDS (else looked up in global memory).
+// RAW (history pass): keys and values are rows, and this launch writes them into the cache as well (RawTiles, attn_common.h);
+// every wave the blocks of its own rows, which it fetches once more behind its last tile.
+template <int QB, bool SUMI, bool CAUSAL, bool IN_LDS, bool RAW>
 __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
 {
     static_assert(!(SUMI && CAUSAL), "the causal flag concerns the history pass");
+    static_assert(!RAW || (!SUMI && QB == 1), "rows: the history pass");
     constexpr int NT = NW * 64, WQ = 32 * QB, TQ = NW * WQ, NPRE = kTileBytes / 16 / NT;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     int *flag_lds = (int *)(lds + kStages * kStageBytes), *class_lds = flag_lds + NW;
@@ -91,7 +94,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
         if (q0 >= Lpad) return;
         row0 = (int64_t)t0 + q0;
         nq = max(0, min(TQ, Lb - q0));
-        if (nq == 0) {  // a tile of padding rows only: defined output, zeros
+        if (nq == 0) {  // a tile of padding rows only: defined output, zeros (and zeros in the cache)
+            if (RAW) {
+                uint8_t *dst = const_cast<uint8_t *>(p.layer_base) + ((size_t)t0 * p.H + (size_t)h * Lpad) * (kDHead * 4) +
+                               (size_t)(q0 / kBlockKeys) * kBlockBytes;
+                for (int i = tid; i < min(TQ, Lpad - q0) * (kDHead * 4 / 16); i += NT) ((uint4 *)dst)[i] = uint4{0, 0, 0, 0};
+            }
             for (int idx = tid; idx < TQ * (kDHead / 8); idx += NT) {
                 const int r = idx / (kDHead / 8), cc = idx % (kDHead / 8);
                 if (q0 + r < Lpad) *(uint4 *)(p.o + (row0 + r) * p.ld_o + h * kDHead + cc * 8) = uint4{0, 0, 0, 0};
@@ -105,14 +113,32 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
     const int n_tiles = (k_hi - k_lo + kTileKeys - 1) / kTileKeys;
     const uint8_t *kv = p.layer_base + ((size_t)t0 * p.H + (size_t)h * Lpad) * (kDHead * 4) +
                         (size_t)(k_lo / kBlockKeys) * kBlockBytes;
+    RawTiles raw;
+    if constexpr (RAW) raw = raw_tiles(p, (int64_t)t0 + k_lo, h, tid);
     auto issue_tile = [&](int t, int stage) __attribute__((always_inline)) {
-        glb_u8 *src = (glb_u8 *)(kv + (size_t)t * kTileBytes + (size_t)tid * 16);
-        lds_u8 *dst = (lds_u8 *)lds + stage + wave * 1024;
+        if constexpr (RAW) {
+            raw_issue(raw, t, (lds_u8 *)lds + stage + wave * 1024);
+        } else {
+            glb_u8 *src = (glb_u8 *)(kv + (size_t)t * kTileBytes + (size_t)tid * 16);
+            lds_u8 *dst = (lds_u8 *)lds + stage + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < NPRE; ++i) __builtin_amdgcn_global_load_lds(src + i * NT * 16, dst + i * NT * 16, 16, 0, 0);
+            for (int i = 0; i < NPRE; ++i) __builtin_amdgcn_global_load_lds(src + i * NT * 16, dst + i * NT * 16, 16, 0, 0);
+        }
         if (wave < 2)  // wave 0: positions, wave 1: time stamps of the tile's keys, 4 bytes per lane
             __builtin_amdgcn_global_load_lds((glb_u8 *)((wave ? p.bias.key_ts : p.bias.key_pos) + t0 + k_lo + t * kTileKeys + lane),
                                              (lds_u8 *)lds + stage + kTileBytes + wave * (kTileKeys * 4), 4, 0, 0);
+    };
+    auto tile_k = [&](const uint8_t *tile, int blk) __attribute__((always_inline)) {
+        if constexpr (RAW) return raw_k(raw, tile, blk);
+        else return load_k(tile + blk * kBlockBytes, lane);
+    };
+    auto tile_v = [&](const uint8_t *tile, int blk) __attribute__((always_inline)) {
+        if constexpr (RAW) return raw_v(raw, tile, blk);
+        else return load_v(tile + blk * kBlockBytes, lane);
+    };
+    auto clear_tail = [&](uint8_t *tile, int t) __attribute__((always_inline)) {
+        if constexpr (RAW)
+            if (k_lo + (t + 1) * kTileKeys > k_hi) raw_clear(tile, k_hi - k_lo - t * kTileKeys, tid);
     };
     auto wait_copies = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
     if (n_tiles > 0) issue_tile(0, 0);
@@ -356,16 +382,18 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
                 st.l[qb] += exp_pack<true>(S[qb], scale, -add, P[qb]);
             }
         };
-        qk_block(st, load_k(lds, lane), S0);
+        qk_block(st, tile_k(lds, 0), S0);
         int so_cur = 0, so_nxt = kStageBytes, so_fill = 2 * kStageBytes;
         for (int t = 0; t + 1 < n_tiles; ++t) {
             const uint8_t *cur = lds + so_cur, *nxt = lds + so_nxt;
             if (t > 0 && (t & 31) == 0) classes_from(2 * t);
             {   // block 0 of tile t: its logits are in S0; start block 1's
-                const KFrags k1 = load_k(cur + kBlockBytes, lane);
-                const VFrags v0 = load_v(cur, lane);
+                const KFrags k1 = tile_k(cur, 1);
+                VFrags v0;
+                if (!RAW) v0 = tile_v(cur, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 qk_block(st, k1, S1);
+                if (RAW) v0 = tile_v(cur, 0);
                 soft(S0, 2 * t, cur, std::false_type{});
                 pv_block(st, v0, P);
             }
@@ -373,10 +401,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
             __builtin_amdgcn_s_barrier();
             if (t + 2 < n_tiles) issue_tile(t + 2, so_fill);
             {   // block 1 of tile t; start block 0 of tile t + 1
-                const KFrags k0 = load_k(nxt, lane);
-                const VFrags v1 = load_v(cur + kBlockBytes, lane);
+                const KFrags k0 = tile_k(nxt, 0);
+                VFrags v1;
+                if (!RAW) v1 = tile_v(cur, 1);
                 __builtin_amdgcn_sched_barrier(0);
                 qk_block(st, k0, S0);
+                if (RAW) v1 = tile_v(cur, 1);
                 soft(S1, 2 * t + 1, cur, std::false_type{});
                 pv_block(st, v1, P);
             }
@@ -385,15 +415,16 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
         }
         {   // last tile: 1..64 keys
             const int blk = 2 * (n_tiles - 1);
-            const uint8_t *cur = lds + so_cur;
+            uint8_t *cur = lds + so_cur;
+            clear_tail(cur, n_tiles - 1);
             if (blk > 0 && (blk & 63) == 0) classes_from(blk);
             const bool two = k_lo + (blk + 1) * kBlockKeys < k_hi;
-            if (two) qk_block(st, load_k(cur + kBlockBytes, lane), S1);
-            const VFrags v0 = load_v(cur, lane);
+            if (two) qk_block(st, tile_k(cur, 1), S1);
+            const VFrags v0 = tile_v(cur, 0);
             soft(S0, blk, cur, std::true_type{});
             pv_block(st, v0, P);
             if (two) {
-                const VFrags v1 = load_v(cur + kBlockBytes, lane);
+                const VFrags v1 = tile_v(cur, 1);
                 soft(S1, blk + 1, cur, std::true_type{});
                 pv_block(st, v1, P);
             }
@@ -467,13 +498,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
             issue_tile(t, 0);
             wait_copies();
             __syncthreads();
+            clear_tail(lds, t);
             for (int k = 0; k < 2; ++k) {
                 const int blk = 2 * t + k;
                 if (k_lo + blk * kBlockKeys >= k_hi) break;
                 if ((blk & 63) == 0) classes_from(blk);
                 f32x16 S[QB];
                 bf16x8 P[QB][2];
-                qk_block(st, load_k(lds + k * kBlockBytes, lane), S);
+                qk_block(st, tile_k(lds, k), S);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
                     float scale, add;
@@ -488,7 +520,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
                 softmax_safe(st, S, P);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) st.c[qb] = c_keep[qb];
-                pv_block(st, load_v(lds + k * kBlockBytes, lane), P);
+                pv_block(st, tile_v(lds, k), P);
             }
         }
 #pragma unroll
@@ -496,9 +528,20 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
         __syncthreads();
     }
 
-    // normalise and store: each wave turns its 32 x 64 blocks around in its corner of the idle ring
-    constexpr int kRowPitch = 144;
-    uint8_t *tr = lds + wave * (32 * kRowPitch);
+    // normalise and store: each wave turns its 32 x 64 blocks around in its corner of the idle ring (chunk c of row r at
+    // slot c ^ r % 8); behind it in the corner, RAW: its own key and value rows, on their way into the cache
+    constexpr int kCorner = 12288;
+    static_assert(NW * kCorner <= kStages * kStageBytes, "");
+    uint8_t *tr = lds + wave * kCorner;
+    if constexpr (RAW) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int pos = i * 64 + lane, r = pos >> 3, c = (pos & 7) ^ (r & 7);
+            const int64_t at = (row0 + min(wave * WQ + r, nq - 1)) * p.ld_kv + h * kDHead + c * 8;
+            __builtin_amdgcn_global_load_lds((glb_u8 *)(p.k_self + at), (lds_u8 *)tr + 4096 + i * 1024, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((glb_u8 *)(p.v_self + at), (lds_u8 *)tr + 8192 + i * 1024, 16, 0, 0);
+        }
+    }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const float inv = 1.f / lt[qb];
@@ -509,21 +552,30 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
                 bf16x4 ov;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(st.O[db][qb][4 * g + e] * inv);
-                *(bf16x4 *)(tr + l32 * kRowPitch + (32 * db + 8 * g + 4 * hf) * 2) = ov;
+                *(bf16x4 *)(tr + l32 * 128 + (((4 * db + g) ^ (l32 & 7)) * 16) + 8 * hf) = ov;
             }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int id = i * 64 + lane, r = id >> 3, cc = id & 7;
             const int wq = wave * WQ + qb * 32 + r;
-            const u32x4 val = *(const u32x4 *)(tr + r * kRowPitch + cc * 16);
+            const u32x4 val = *(const u32x4 *)(tr + r * 128 + ((cc ^ (r & 7)) * 16));
             __bf16 *op = p.o + (row0 + wq) * p.ld_o + h * kDHead + cc * 8;
             if (wq < nq) __builtin_nontemporal_store(val, (u32x4 *)op);
             else if (!SUMI && q0 + wq < Lpad) *(uint4 *)op = uint4{0, 0, 0, 0};
         }
     }
+    if constexpr (RAW) {
+        wait_copies();
+        if (q0 + wave * WQ < Lpad) {
+            uint8_t *block = const_cast<uint8_t *>(p.layer_base) + ((size_t)t0 * p.H + (size_t)h * Lpad) * (kDHead * 4) +
+                             (size_t)((q0 + wave * WQ) / kBlockKeys) * kBlockBytes;
+            own_block_k(block, tr + 4096, nq - wave * WQ, lane);
+            own_block_v(block, tr + 8192, nq - wave * WQ, lane);
+        }
+    }
 }
 
-template <int QB, bool SUMI, bool CAUSAL>
+template <int QB, bool SUMI, bool CAUSAL, bool RAW = false>
 hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
 {
     constexpr int TQ = NW * 32 * QB;
@@ -535,7 +587,7 @@ hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
     const bool in_lds = entries <= kBiasLdsFloats;
     const size_t lds = kStages * kStageBytes + NW * 4 + kClassBytes<QB> + (in_lds ? (size_t)entries * 4 : 0);
     auto go = [&](auto in_lds_tag) {
-        constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value>;
+        constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value, RAW>;
         const hipError_t e = raise_lds_limit<kernel>(kStages * kStageBytes + NW * 4 + kClassBytes<QB> + kBiasLdsFloats * 4);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NW * 64), lds, s, p);
@@ -557,6 +609,11 @@ hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
         return few || a.max_rows_per_user <= 128 ? launch_bias<1, true, false>(a, s) : launch_bias<2, true, false>(a, s);
     }
     return a.causal ? launch_bias<1, false, true>(a, s) : launch_bias<1, false, false>(a, s);
+}
+
+hipError_t launch_attn_hist_rows_bias_bf16(const AttnArgs &a, hipStream_t s)
+{
+    return a.causal ? launch_bias<1, false, true, true>(a, s) : launch_bias<1, false, false, true>(a, s);
 }
 
 }  // namespace climber

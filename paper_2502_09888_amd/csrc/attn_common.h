@@ -276,6 +276,109 @@ static __device__ __forceinline__ void softmax_safe(QState<QB> &st, const f32x16
         st.l[qb] += exp_pack<true>(S[qb], st.c[qb], st.m_ref[qb] * st.c[qb], P[qb]);
 }
 
+// ---- keys and values as rows (history pass that writes the cache itself) --------------------------
+// A tile of 64 keys in LDS: 64 key rows of 128 bytes, then 64 value rows, 16-byte chunk c of row r at slot c ^ (r / 2) % 8.  Key
+// fragments are row pieces; value fragments come out of the rows by LDS transpose reads (addresses as derived in
+// hist_fused_bf16.hip).  256 threads.
+struct RawTiles {
+    const uint8_t *k, *v;  // first row of the range, the head's columns
+    int64_t row_bytes;
+    uint32_t row_at, k_at[4], v_at;
+};
+
+static __device__ __forceinline__ RawTiles raw_tiles(const KParams &p, int64_t row, int h, int tid)
+{
+    const int lane = tid & 63, l32 = lane & 31, hf = lane >> 5, r = tid >> 3;
+    RawTiles t;
+    t.k = uniform_ptr((const uint8_t *)(p.k_self + row * p.ld_kv + h * kDHead));
+    t.v = uniform_ptr((const uint8_t *)(p.v_self + row * p.ld_kv + h * kDHead));
+    t.row_bytes = p.ld_kv * 2;
+    t.row_at = (uint32_t)r * (uint32_t)p.ld_kv * 2u + (uint32_t)((tid & 7) ^ ((r >> 1) & 7)) * 16u;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) t.k_at[s] = (uint32_t)(l32 * 128 + (((2 * s + hf) ^ ((l32 >> 1) & 7)) * 16));
+    const int G = lane >> 4, i16 = lane & 15, x = 2 * (G & 1) + ((i16 >> 1) & 1), y = 2 * (G >> 1) + (i16 >> 3);
+    t.v_at = (uint32_t)(8192 + (4 * (G >> 1) + (i16 >> 2)) * 128 + (x ^ y) * 16 + 8 * (i16 & 1));
+    return t;
+}
+
+// rows 64 n .. 64 n + 63 of the range (they exist: padded lengths are multiples of 64); `to`: the wave's first KiB of the tile
+static __device__ __forceinline__ void raw_issue(const RawTiles &t, int n, lds_u8 *to)
+{
+    const int64_t at = (int64_t)n * 64 * t.row_bytes, half = 32 * t.row_bytes;
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.k + at) + t.row_at, to, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.k + at + half) + t.row_at, to + 4096, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.v + at) + t.row_at, to + 8192, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.v + at + half) + t.row_at, to + 12288, 16, 0, 0);
+}
+
+static __device__ __forceinline__ KFrags raw_k(const RawTiles &t, const uint8_t *tile, int blk)
+{
+    KFrags f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) f.a[s] = *(const bf16x8 *)(tile + t.k_at[s] + blk * 4096);
+    return f;
+}
+
+// (One block of inline assembly with its wait: for the builtin, with copies in flight, the compiler waits until all of
+// them have landed.  In a loop it belongs behind the MFMAs of the next logits, which run meanwhile.)
+static __device__ __forceinline__ VFrags raw_v(const RawTiles &t, const uint8_t *tile, int blk)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    s16x4 x[8];
+    asm volatile("ds_read_b64_tr_b16 %0, %8 offset:0\n\tds_read_b64_tr_b16 %1, %8 offset:1088\n\t"
+                 "ds_read_b64_tr_b16 %2, %8 offset:64\n\tds_read_b64_tr_b16 %3, %8 offset:1024\n\t"
+                 "ds_read_b64_tr_b16 %4, %8 offset:2048\n\tds_read_b64_tr_b16 %5, %8 offset:3136\n\t"
+                 "ds_read_b64_tr_b16 %6, %8 offset:2112\n\tds_read_b64_tr_b16 %7, %8 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+                 : "v"((uint32_t)(uintptr_t)(lds_u8 *)tile + t.v_at + (uint32_t)blk * 4096u)
+                 : "memory");
+    VFrags f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        f.a[i >> 1][i & 1] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(x[2 * i], x[2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+    return f;
+}
+
+// the value rows of a tile from row `first` on, which may hold anything: zeros, before they meet probabilities of 0
+static __device__ __forceinline__ void raw_clear(uint8_t *tile, int first, int tid)
+{
+    for (int i = tid; i < (64 - first) * 8; i += 256) *(uint4 *)(tile + 8192 + first * 128 + i * 16) = uint4{0, 0, 0, 0};
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+}
+
+// The cache block of 32 rows that lie in LDS (chunk c of row r at slot c ^ r % 8; no copy in flight), of which `n` count: key
+// and value fragments as laid out in internal.h, zeros in the slots beyond.
+static __device__ __forceinline__ void own_block_k(uint8_t *block, const uint8_t *rows, int n, int lane)
+{
+    const int r = lane & 31, hf = lane >> 5;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        u32x4 x = *(const u32x4 *)(rows + r * 128 + (((2 * s + hf) ^ (r & 7)) * 16));
+        if (r >= n) x = u32x4{0, 0, 0, 0};
+        *(u32x4 *)(block + (s * 64 + lane) * 16) = x;
+    }
+}
+static __device__ __forceinline__ void own_block_v(uint8_t *block, const uint8_t *rows, int n, int lane)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    const int G = lane >> 4, i16 = lane & 15, hf = lane >> 5;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+            bf16x8 x;
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                const int r = 16 * g + 8 * hh + 4 * (G >> 1) + (i16 >> 2), c = 4 * db + 2 * (G & 1) + ((i16 >> 1) & 1);
+                const bf16x4 part = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(
+                                                                   (lds_u8 *)const_cast<uint8_t *>(rows) + r * 128 + ((c ^ (r & 7)) * 16) + 8 * (i16 & 1))));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[4 * hh + e] = 16 * g + 8 * hh + 4 * hf + e < n ? part[e] : (__bf16)0.f;
+            }
+            *(u32x4 *)(block + 4096 + ((g * 2 + db) * 64 + lane) * 16) = __builtin_bit_cast(u32x4, x);
+        }
+}
 
 }  // namespace attn
 }  // namespace climber
