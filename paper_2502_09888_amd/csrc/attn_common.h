@@ -35,7 +35,10 @@ constexpr float kDenomLoExact = 1.0e-30f;
 constexpr float kPilotSpread = 4.25f;
 constexpr int kFoldMinKeys = 256;
 constexpr float kSafeNoRef = -1.0e30f;       // SAFE: "no reference yet", below any finite logit
-constexpr int kBiasLdsFloats = 4096;         // LDS floats for one head's rows of the bias tables
+// LDS floats for one head's rows of the bias tables: what two workgroups per CU leave beside the rings (80 KiB each).  Beyond it
+// they are looked up in global memory, behind the tiles in flight.  Us that way / from LDS, 32 rows of 129 + 12 or 129 + 20 entries: history
+// of 64 x 1024 in subsequences of 256 261 / 185, causal of 20 x 2000 171 / 121, scoring 512 of 64 136 / 109, 128 of 32 27.5 / 28.8.
+constexpr int kBiasLdsFloats = 6656;
 
 // What the attention kernels are given.
 struct KParams {
