@@ -792,23 +792,23 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
 // a head's K/V from L2 half as often and reuses every LDS fragment for two MFMAs; QB = 1 (128
 // queries) keeps two waves per SIMD busy when a head has few queries, pads a user's candidates by less, and deals
 // the work out in smaller pieces where there are few workgroups or users of very different lengths.  Scoring, us, 256 / 128
-// queries, 8 heads:
-//   all users alike, as many rows with either: 32 x 256 against 1024 (256 workgroups of 256) 24.5 / 23.1, 24 x 512 (384) 34.1 / 31.9,
-//     28 x 512 against 512 (448) 22.3 / 24.2, 64 x 256 (512) 41.2 / 43.2, 64 x 512 (1024) 76.0 / 83.3
-//   fewer rows: 64 x 257 (384 rows instead of 512) 66.8 / 58.3, 40 x 300 against 600 33.9 / 26.9, 60 x 640 against 512 (640, 768) 59.1 /
-//     57.7, 30 x 896 (896, 1024) 67.0 / 67.6
-//   users that differ (a quarter of the longest at least), up to 256 candidates of 24 users against 2000 (about 220) 32.1 / 22.8, 900 of 12 against
-//     4000 (260) 59.7 / 46.7, 1024 of 16 against 4096 (380) 82.2 / 77.9, of 24 (580) 107.4 / 103.4, 512 of 48 against 1500 (670)
-//     51.5 / 53.7, 1024 of 64 against 2048 (1540) 154 / 157
+// queries, 8 heads, caches and rows that no earlier call left in the last-level cache:
+//   all users alike, as many rows with either: 20 x 512 against 2048 (320 workgroups of 256) 64.8 / 63.2, 24 x 512 against 1024 (384) 39.1 / 38.8,
+//     48 x 256 (384) 40.9 / 43.8; in that cache 64 x 256 (512) 41.2 / 43.2, 64 x 512 (1024) 76.0 / 83.3
+//   fewer rows: 64 x 257 (384 rows instead of 512) 75.7 / 68.3, 40 x 300 against 600 40.5 / 33.0, 60 x 640 against 512 (640, 768) 69.7 / 68.4,
+//     30 x 896 (896, 1024) 74.9 / 74.8
+//   users that differ (a quarter of the longest at least), up to 256 candidates of 24 users against 2000 (about 220) 33.1 / 27.5, 900 of 12
+//     against 4000 (260) 63.3 / 50.3, 1024 of 16 against 4096 (410) 85.2 / 84.2, 500 of 32 against 2000 (440) 46.2 / 46.6, 400 of 40
+//     (470) 59.1 / 61.5
 bool small_tiles(const AttnArgs &a)
 {
     const int64_t m = a.max_rows_per_user, heads = (int64_t)a.cache.B * a.H;
     if (m <= 128) return true;
     if (a.uni_cand >= 0) {
         const int64_t r1 = (m + 127) / 128 * 128, r2 = (m + 255) / 256 * 256;
-        return 6 * r1 <= 5 * r2 || heads * (r2 / 256) <= (a.uni_len >= 0 ? 384 : 576);
+        return 6 * r1 <= 5 * r2 || heads * (r2 / 256) <= 300;
     }
-    return a.total_q_rows * a.H / 256 + heads / 2 <= 576;  // (half a tile per head is padding)
+    return a.total_q_rows * a.H / 256 + heads / 2 <= 420;  // (half a tile per head is padding)
 }
 
 // The history pass: a query tile lies inside one subsequence (sub_len is 0 or a multiple of 128); 256 queries where that allows them

@@ -137,9 +137,6 @@ int attn_history_strided(const climber_config *cfg, const float *tau_layer, cons
 {
     const CacheView cv = view_of(cache, layer);
     if (cache->rows == 0) return CLIMBER_OK;
-    // short subsequences, bf16: one kernel writes the cache and attends (K/V rows read once)
-    const bool fused = cfg->dtype == CLIMBER_BF16 && o && !bias && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) &&
-                       hist_fused_supported(cfg->sub_len, (cfg->flags & CLIMBER_HIST_CAUSAL) != 0);
     AttnArgs a = base_args(cfg, cache, layer, tau_layer);
     a.q = q;
     a.k_self = k;  // a history row's own key seeds its softmax reference
@@ -154,6 +151,8 @@ int attn_history_strided(const climber_config *cfg, const float *tau_layer, cons
     a.total_q_rows = cache->rows;
     if (bias) a.bias = BiasArgs{bias->pos_table, bias->time_table, bias->hist_pos, bias->hist_ts, bias->hist_pos,
                                 bias->hist_ts, bias->n_pos, bias->n_time};
+    // short subsequences, bf16: one kernel writes the cache and attends (K/V rows read once)
+    const bool fused = cfg->dtype == CLIMBER_BF16 && o && !bias && !(cfg->flags & CLIMBER_HIST_TWO_KERNEL) && hist_fused_takes(a);
     // other subsequences, and fp32: likewise, unless the output lies on the rows that other workgroups still read
     const size_t elem = cfg->dtype == CLIMBER_F32 ? 4 : 2;
     const size_t row_bytes = (size_t)cache->rows * ld * elem, o_bytes = (size_t)cache->rows * ld_o * elem;

@@ -445,7 +445,14 @@ __global__ __launch_bounds__(SUB * 2, 256 / SUB) void hist_fused_kernel(const HP
 
 }  // namespace
 
-bool hist_fused_supported(int sub_len, int causal) { (void)causal; return sub_len == 128 || sub_len == 256; }
+// Up to 320 subsequences of 256 are less than two per workgroup, with nothing to prefetch behind: there the tiled kernel, which takes
+// rows as well, is the faster way.  Us there / here, 8 heads: 8 users x 256 (64 subsequences) 7.9 / 10.5, 16 x 256 (128) 8.7 / 11.2, 8 x 1000 (256)
+// 13.4 / 14.2, 32 x 200 (256) 12.8 / 13.0, causal 13.4 / 12.9, 10 x 800 (320) 17.8 / 22.5, 20 x 700 (480) 29.0 / 24.3, 16 x 1024 (512) 29.9 / 28.1;
+// of 128: 2 x 300, 4 heads 7.5 / 7.6, 32 x 512, 4 heads 12.4 / 11.6.
+bool hist_fused_takes(const AttnArgs &a)
+{
+    return a.sub_len == 128 || (a.sub_len == 256 && (int64_t)((a.max_rows_per_user + 255) / 256) * a.cache.B * a.H > 320);
+}
 
 hipError_t launch_hist_fused_bf16(const AttnArgs &a, hipStream_t s)
 {

@@ -66,7 +66,7 @@ hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s);
 hipError_t launch_attn_hist_rows_bias_bf16(const AttnArgs &a, hipStream_t s);  // by launch_attn_hist_rows_bf16
 // fused cache write + attention inside short subsequences (hist_fused_bf16.hip): a.k_self / a.v_self
 // are the history key / value rows (same row stride as the queries)
-bool hist_fused_supported(int sub_len, int causal);
+bool hist_fused_takes(const AttnArgs &a);
 hipError_t launch_hist_fused_bf16(const AttnArgs &a, hipStream_t s);
 // fp32 reference-path attention (attn_f32.hip); the cache layer holds plain [rows][H][dh] K then V
 hipError_t launch_attn_f32(const AttnArgs &a, bool sumi, int64_t cache_rows, hipStream_t s);
