@@ -24,8 +24,6 @@ struct RowNormOut {         // producer side; ss == nullptr: fp32 rows only
 };
 
 // W [K][N] bf16 row-major -> MFMA B-operand fragments (same byte size).  K % 16 == 0, N % 32 == 0.
-hipError_t pack_weight(const void *w, void *packed, int K, int N, hipStream_t s);
-
 // Several weights in one launch (n <= kMaxPackJobs): job i packs w[i] [K[i]][N[i]] into packed[i].
 constexpr int kMaxPackJobs = 16;
 struct PackJobs {
@@ -60,7 +58,7 @@ struct QkvToCache {         // layer_base == nullptr: plain store
     int64_t rows;
 };
 
-// C = A W (+ epilogue).  A: bf16 [M][lda], or tiled (kTiledA; lda unused); w_packed from pack_weight;
+// C = A W (+ epilogue).  A: bf16 [M][lda], or tiled (kTiledA; lda unused); w_packed from pack_weights;
 // N % 128 == 0, K % 64 == 0.  EPI_STORE_BF16 / EPI_GELU_BF16 / EPI_RELU_BF16: C is bf16 [M][ldc] (EPI_GELU_BF16 with
 // kTiledC: tiled, ldc unused).  EPI_RESID_F32: C is fp32, C = acc + resid.
 hipError_t gemm_bf16(int epi, const void *A, int64_t lda, const void *w_packed, int M, int N, int K,

@@ -2,7 +2,7 @@
 // arXiv 2502.09888): C[M][N] = A[M][K] * W[K][N] with fp32 accumulation and a fused epilogue
 // (plain bf16 store, residual add into the fp32 stream, erf-GELU).
 //
-// W is first repacked (pack_weight) into B-operand fragments of v_mfma_f32_32x32x16_bf16:
+// W is first repacked (pack_weights) into B-operand fragments of v_mfma_f32_32x32x16_bf16:
 //   chunk (nb, ks, lane), 16 B: W[16ks + 8(lane/32) + 0..7][32nb + lane%32]
 // so that a k-tile of a 32-column block is contiguous and is copied HBM -> LDS linearly.
 // A is row-major (its tile is copied row by row, 64 B per row and k-tile, with the 16-byte chunks
@@ -36,37 +36,44 @@ typedef const __attribute__((address_space(1))) uint8_t glb_u8;
 
 constexpr int BK = 32;      // k-tile
 
-__device__ __forceinline__ void pack_chunk(const __bf16 *w, const __bf16 *gain, __bf16 *out, int K, int N,
-                                           int64_t chunk)
-{
-    // one thread per 16-byte chunk (nb, ks, lane)
-    const int lane = (int)(chunk & 63);
-    const int64_t t = chunk >> 6;
-    const int ks = (int)(t % (K / 16)), nb = (int)(t / (K / 16));
-    const int n = 32 * nb + (lane & 31), k0 = 16 * ks + 8 * (lane >> 5);
-    bf16x8 v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const __bf16 x = w[(int64_t)(k0 + e) * N + n];
-        v[e] = gain ? (__bf16)((float)x * (float)gain[k0 + e]) : x;
-    }
-    ((bf16x8 *)out)[chunk] = v;
-}
-
-__global__ __launch_bounds__(256) void pack_weight_kernel(const __bf16 *w, __bf16 *out, int K, int N)
-{
-    const int64_t chunk = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (chunk < (int64_t)(N / 32) * (K / 16) * 64) pack_chunk(w, nullptr, out, K, N, chunk);
-}
-
-// blockIdx.y = job
+// blockIdx.y = job.  A lane packs 16 rows of two columns, i.e. four 16-byte chunks of a fragment (nb, ks): 64 lanes read whole
+// lines of a row with one load, all 16 loads are in flight at once, and 16 lanes write the whole fragment.  Bound by memory.
+// (A lane per chunk, eight 2-byte loads of half a line each: 25 MB of four layers 18.2 us that way, 13.7 this way; the fusion module 13.9 in two launches, 7.2 in one.)  Weights and gains are 16-byte aligned.
 __global__ __launch_bounds__(256) void pack_weights_kernel(const PackJobs jobs)
 {
     const int j = blockIdx.y, K = jobs.K[j], N = jobs.N[j];
-    const int64_t n_chunks = (int64_t)(N / 32) * (K / 16) * 64;
-    for (int64_t chunk = (int64_t)blockIdx.x * 256 + threadIdx.x; chunk < n_chunks;
-         chunk += (int64_t)gridDim.x * 256)
-        pack_chunk((const __bf16 *)jobs.w[j], (const __bf16 *)jobs.gain[j], (__bf16 *)jobs.packed[j], K, N, chunk);
+    const uint32_t pairs = (uint32_t)N / 2, n_items = (uint32_t)K / 16 * pairs;
+    const __bf16 *w = (const __bf16 *)jobs.w[j], *gain = (const __bf16 *)jobs.gain[j];
+    for (uint32_t item = blockIdx.x * 256 + threadIdx.x; item < n_items; item += gridDim.x * 256) {
+        const uint32_t ks = item / pairs, n = item % pairs * 2;
+        uint32_t x[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = *(const uint32_t *)(w + (int64_t)(16 * ks + e) * N + n);
+        __bf16 v[2][16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            v[0][e] = __builtin_bit_cast(__bf16, (uint16_t)x[e]);
+            v[1][e] = __builtin_bit_cast(__bf16, (uint16_t)(x[e] >> 16));
+        }
+        if (gain) {
+            const bf16x8 g[2] = {*(const bf16x8 *)(gain + 16 * ks), *(const bf16x8 *)(gain + 16 * ks + 8)};
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                v[0][e] = (__bf16)((float)v[0][e] * (float)g[e / 8][e % 8]);
+                v[1][e] = (__bf16)((float)v[1][e] * (float)g[e / 8][e % 8]);
+            }
+        }
+        bf16x8 *out = (bf16x8 *)jobs.packed[j] + ((int64_t)(n / 32) * (K / 16) + ks) * 64 + n % 32;
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                bf16x8 y;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) y[e] = v[c][8 * half + e];
+                out[32 * half + c] = y;
+            }
+    }
 }
 
 template <int N>
@@ -295,21 +302,13 @@ hipError_t dispatch(const GemmArgs &g, hipStream_t s)
 
 }  // namespace
 
-hipError_t pack_weight(const void *w, void *packed, int K, int N, hipStream_t s)
-{
-    const int64_t n_chunks = (int64_t)(N / 32) * (K / 16) * 64;
-    hipLaunchKernelGGL(pack_weight_kernel, dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, s,
-                       (const __bf16 *)w, (__bf16 *)packed, K, N);
-    return hipGetLastError();
-}
-
 hipError_t pack_weights(const PackJobs &jobs, hipStream_t s)
 {
     if (jobs.n <= 0) return hipSuccess;
     if (jobs.n > kMaxPackJobs) return hipErrorInvalidValue;
     int64_t most = 0;
     for (int j = 0; j < jobs.n; ++j)
-        most = std::max<int64_t>(most, (int64_t)(jobs.N[j] / 32) * (jobs.K[j] / 16) * 64);
+        most = std::max<int64_t>(most, (int64_t)(jobs.N[j] / 2) * (jobs.K[j] / 16));
     const unsigned gx = (unsigned)std::min<int64_t>((most + 255) / 256, 1024);
     hipLaunchKernelGGL(pack_weights_kernel, dim3(gx, (unsigned)jobs.n), dim3(256), 0, s, jobs);
     return hipGetLastError();

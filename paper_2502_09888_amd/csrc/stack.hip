@@ -82,29 +82,27 @@ int rt(hipError_t e) { return e == hipSuccess ? CLIMBER_OK : CLIMBER_ERR_RUNTIME
         if (e_) return e_; \
     } while (0)
 
+void add_job(PackJobs &jobs, const void *w, const void *gain, const uint8_t *packed, int K, int N)
+{
+    jobs.w[jobs.n] = w, jobs.gain[jobs.n] = gain, jobs.packed[jobs.n] = const_cast<uint8_t *>(packed);
+    jobs.K[jobs.n] = K, jobs.N[jobs.n] = N;
+    ++jobs.n;
+}
+
 // MFMA fragment order for the weights of layers [0, n) into slots [0, n) of the workspace: one
-// launch per four layers
+// launch per four layers (`jobs`: what else the first of them packs)
 int pack_layers(const climber_config *cfg, const climber_layer_weights *layers, int n,
-                const Workspace &ws, hipStream_t s)
+                const Workspace &ws, hipStream_t s, PackJobs jobs = PackJobs{})
 {
     const int d = cfg->d_model, F = cfg->d_ffn;
-    PackJobs jobs;
-    jobs.n = 0;
     for (int l = 0; l < n; ++l) {
         const PackedLayer pl = packed_layer(cfg, ws, l);
         const void *src[4] = {layers[l].wqkv, layers[l].wo, layers[l].w1, layers[l].w2};
         const void *gain[4] = {layers[l].g1, nullptr, layers[l].g2, nullptr};
         const uint8_t *dst[4] = {pl.wqkv, pl.wo, pl.w1, pl.w2};
         const int K[4] = {d, d, d, F}, N[4] = {3 * d, d, F, d};
-        for (int i = 0; i < 4; ++i) {
-            jobs.w[jobs.n] = src[i];
-            jobs.gain[jobs.n] = gain[i];
-            jobs.packed[jobs.n] = const_cast<uint8_t *>(dst[i]);
-            jobs.K[jobs.n] = K[i];
-            jobs.N[jobs.n] = N[i];
-            ++jobs.n;
-        }
-        if (jobs.n == kMaxPackJobs || l + 1 == n) {
+        for (int i = 0; i < 4; ++i) add_job(jobs, src[i], gain[i], dst[i], K[i], N[i]);
+        if (jobs.n + 4 > kMaxPackJobs || l + 1 == n) {
             TRY(rt(pack_weights(jobs, s)));
             jobs.n = 0;
         }
@@ -423,15 +421,11 @@ int climber_bgf_score(const climber_config *cfg, const climber_bgf_weights *w, c
     if (m_total == 0) return CLIMBER_OK;
     hipStream_t s = (hipStream_t)stream;
     // operand order for the fusion layer's weights (gains folded in) and the two gate projections
-    TRY(pack_layers(&one, &w->atl, 1, ws, s));
     uint8_t *down_p = gate_pack, *up_p = gate_pack + (size_t)nd * dg * 2;
-    {
-        PackJobs jobs;
-        jobs.n = 2;
-        jobs.w[0] = w->w_down, jobs.gain[0] = nullptr, jobs.packed[0] = down_p, jobs.K[0] = nd, jobs.N[0] = dg;
-        jobs.w[1] = w->w_up, jobs.gain[1] = nullptr, jobs.packed[1] = up_p, jobs.K[1] = dg, jobs.N[1] = nd;
-        TRY(rt(pack_weights(jobs, s)));
-    }
+    PackJobs gate{};
+    add_job(gate, w->w_down, nullptr, down_p, nd, dg);
+    add_job(gate, w->w_up, nullptr, up_p, dg, nd);
+    TRY(pack_layers(&one, &w->atl, 1, ws, s, gate));
     const PackedLayer pw = packed_layer(&one, ws, 0);
     const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps};
     const RowNormOut no_out{nullptr, nullptr, 0};

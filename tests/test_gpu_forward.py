@@ -250,3 +250,30 @@ def test_layer_tail_with_weights_requested_ahead_gives_the_bits_of_three(d_ffn, 
     w, g, yc = run_forward(spec, users=(1,), want_hist=True)
     g.encode()
     assert np.array_equal(yc[:g.m_total], g.score())
+
+
+@pytest.mark.parametrize("d, F, layers", [(128, 128, 1), (256, 384, 5), (384, 128, 4), (512, 2048, 2)])
+def test_packed_weights_are_the_operand_fragments(d, F, layers):
+    # 16 bytes (column block nb, k step ks, lane): rows 16 ks + 8 (lane / 32) + 0..7 of column 32 nb + lane % 32, the gains of the
+    # two projections behind a norm multiplied in and rounded once; the five-layer stack takes two launches
+    import torch
+    import paper_2502_09888_amd as P
+    say(f"[case] packed weights d={d} F={F} layers={layers}")
+    dev, bf = "cuda:0", torch.bfloat16
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d + F)
+    cfg = P.Config(n_layers=layers, d_model=d, n_heads=d // 64, d_head=64, d_ffn=F, dtype=P.BF16)
+    ws = [{k: torch.randn(*s, generator=gen, device=dev).to(bf) for k, s in
+           (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, F)), ("w2", (F, d)))} for _ in range(layers)]
+    packed = torch.full((P.climber_packed_weights_bytes(cfg) // 2,), float("nan"), dtype=bf, device=dev)
+    P.climber_pack_weights(cfg, ws, packed)
+    torch.cuda.synchronize()
+    got = packed.view(layers, -1)
+    for l, w in enumerate(ws):
+        at = 0
+        for k, gain in (("wqkv", "g1"), ("wo", None), ("w1", "g2"), ("w2", None)):
+            x = w[k].float() * w[gain].float()[:, None] if gain else w[k].float()
+            K, N = x.shape
+            want = x.to(bf).view(K // 16, 2, 8, N // 32, 32).permute(3, 0, 1, 4, 2).reshape(-1)
+            assert torch.equal(got[l, at:at + K * N], want), (l, k)
+            at += K * N
