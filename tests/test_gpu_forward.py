@@ -277,3 +277,14 @@ def test_packed_weights_are_the_operand_fragments(d, F, layers):
             want = x.to(bf).view(K // 16, 2, 8, N // 32, 32).permute(3, 0, 1, 4, 2).reshape(-1)
             assert torch.equal(got[l, at:at + K * N], want), (l, k)
             at += K * N
+
+
+@pytest.mark.parametrize("layers, flags", [(1, 0), (3, 0), (1, 4), (2, 4)])
+def test_packed_forward_candidates_with_and_without_history_outputs(layers, flags):
+    # the first layer's inputs where they are (flags 0) or copied behind one another (CLIMBER_QKV_VIA_ROWS); the candidates'
+    # rows written by the last layer, or copied out behind the history's: the same bits
+    spec = W.StackSpec(f"fwd-outputs-{layers}-{flags}", B=2, L=0, sub_len=128, M=0, n_layers=layers, d_model=256, H=4, dh=64, d_ffn=256,
+                       n_scen=8, n_beh=4, seed=300 + layers, pad_to=64, hist_lens=(130, 63), cand_counts=(33, 7), nan_padding=True)
+    a = run_forward(spec, users=(0, 1), want_hist=False, flags=flags)[2]
+    b = run_forward(spec, users=(0, 1), want_hist=True, flags=flags)[2]
+    assert np.array_equal(a[:40], b[:40])
