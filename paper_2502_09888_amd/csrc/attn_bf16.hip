@@ -634,7 +634,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         }
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) lt[qb] = st.l[qb] + xhalf(st.l[qb]);
-            redo = 0;
+        redo = 0;
         __syncthreads();  // every wave is done reading K/V tiles
     }
     // Few: every wave takes a share of the keys, fragments straight from global memory, and the wave that owns the rows adds up the

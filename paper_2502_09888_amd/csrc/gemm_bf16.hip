@@ -38,7 +38,8 @@ constexpr int BK = 32;      // k-tile
 
 // blockIdx.y = job.  A lane packs 16 rows of two columns, i.e. four 16-byte chunks of a fragment (nb, ks): 64 lanes read whole
 // lines of a row with one load, all 16 loads are in flight at once, and 16 lanes write the whole fragment.  Bound by memory.
-// (A lane per chunk, eight 2-byte loads of half a line each: 25 MB of four layers 18.2 us that way, 13.7 this way; the fusion module 13.9 in two launches, 7.2 in one.)  Weights and gains are 16-byte aligned.
+// (A lane per chunk, eight 2-byte loads of half a line each: 25 MB of four layers 18.2 us that way, 13.7 this way; the fusion
+// module 13.9 in two launches, 7.2 in one.)  Weights and gains are 16-byte aligned.
 __global__ __launch_bounds__(256) void pack_weights_kernel(const PackJobs jobs)
 {
     const int j = blockIdx.y, K = jobs.K[j], N = jobs.N[j];
