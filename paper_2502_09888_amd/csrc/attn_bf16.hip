@@ -29,12 +29,11 @@
 //     exact form.  The loop is software pipelined
 //     over 32-key blocks: the S^T MFMAs of block i+1 are issued before the exponentials of block
 //     i, so matrix and vector pipes overlap inside one wave.
-//   - SAFE pass.  A row whose denominator leaves its window (or is not finite) is redone with the
-//     classical online softmax: unscaled q, fp32 scale p = exp2(s*c - m*c), running row maximum
-//     (moved when exceeded by 2^8, O and l rescaled).  This covers logits of any size.  A few such
-//     rows are redone 32 queries at a time, the keys split over the waves; many with their whole
-//     tile.  The choice of form is per wave and the redo per 32 queries or tile, so a row's
-//     rounding depends on whether a neighbour of its tile has large logits: results
+//   - SAFE pass.  If any row's denominator leaves its window (or is not finite) the workgroup
+//     redoes its work with the classical online softmax: unscaled q, fp32 scale
+//     p = exp2(s*c - m*c), running row maximum (moved when exceeded by 2^8, O and l rescaled).
+//     This covers logits of any size.  The choice of form is per wave and the redo per workgroup,
+//     so a row's rounding depends on whether a neighbour of its tile has large logits: results
 //     are bitwise independent of the other rows only within one form.
 //   - SUMI: the candidate's own key / value join the softmax as one more member (FAST: between
 //     two tiles, from the landing buffer; SAFE: as the initial state): the "+ itself" term of the
@@ -587,26 +586,27 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         }
     }
 
-    // ---- SAFE pass (rare): rows that left their window, 32 queries at a time ----------------
+    // ---- SAFE pass (rare): whole workgroup redoes its rows with a running maximum -----------
     float lt[QB];
-    int wave_bad = 0;
+    bool bad = false;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         lt[qb] = st.l[qb] + xhalf(st.l[qb]);
-        const bool bad = fold ? !(lt[qb] > kDenomLo && lt[qb] < kDenomHi) : !(lt[qb] > kDenomLoExact && lt[qb] < kDenomHiExact);
-        // (the ballot is taken by the whole wave: inside a branch it would see part of the lanes)
-        wave_bad |= (__builtin_amdgcn_ballot_w64(bad) != 0) << qb;
+        bad |= fold ? !(lt[qb] > kDenomLo && lt[qb] < kDenomHi) : !(lt[qb] > kDenomLoExact && lt[qb] < kDenomHiExact);
     }
-    // One flag per 32 queries, through the (idle) landing buffer, a wave's in its own slice; the barrier also orders
-    // the reuse of the LDS ring below.
+    // Workgroup-wide OR of `bad` through the (idle) landing buffer: one flag per wave in its own
+    // slice, one barrier; the barrier also orders the reuse of the LDS ring below.
+    // (Redoing 32 queries at a time is faster, but leaves the rest of the tile in the folded form: 2.3e-3 -> 2.8e-3 off the
+    // results in 64 bits.  With the keys split over the waves, a causal row may see none in some wave's share.)
     int *flag_lds = (int *)(lds + kStages * kTileBytes);
+    // (the ballot is taken by the whole wave: inside the branch it would see lane 0 only)
+    const int wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
     if (lane == 0) flag_lds[wave * (WQ * 32)] = wave_bad;
     __syncthreads();
-    int redo = 0;
+    int any_bad = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) redo |= flag_lds[w * (WQ * 32)] << (w * QB);
-    redo = __builtin_amdgcn_readfirstlane(redo);
-    if (__builtin_popcount(redo) > (RAW ? 0 : NW * QB / 4)) {  // many (RAW: any): the whole tile in one walk, through the ring
+    for (int w = 0; w < NW; ++w) any_bad |= flag_lds[w * (WQ * 32)];
+    if (any_bad) {
         prologue();
         init_safe();
         for (int t = 0; t < n_tiles; ++t) {
@@ -634,117 +634,13 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         }
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) lt[qb] = st.l[qb] + xhalf(st.l[qb]);
-        redo = 0;
-        __syncthreads();  // every wave is done reading K/V tiles
-    }
-    // Few: every wave takes a share of the keys, fragments straight from global memory, and the wave that owns the rows adds up the
-    // parts.  (As a rule it is one row with one key far above the others.  Redoing the whole tile for it took a launch with one
-    // workgroup per CU twice its time, 66 us against 34 for 8192 candidates of a stack; 32 rows this way take 9 us, a tile in one walk
-    // 30.)  q unscaled; the own key / value is the first member of wave 0's part.
-    if constexpr (!RAW)
-    for (; redo != 0; redo &= redo - 1) {
-        const int id = __builtin_ctz(redo), own = id / QB, first = own * WQ + (id % QB) * 32;
-        int ln;  // the lane once more (of what this needs, nothing is held in registers across the FAST pass)
-        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(ln));
-        const int l32 = ln & 31, hf = ln >> 5, lane = ln;
-        const int64_t row = row0 + min(first + l32, nq - 1);
-        const int sc = min(max(p.scen[row], 0), p.n_scen - 1), bhv = min(max(p.beh[row], 0), p.n_beh - 1);
-        QState<1> part;
-        part.c[0] = p.scale_log2e / p.tau[sc * p.n_beh + bhv];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) part.qf[0][s] = *(const bf16x8 *)(p.q + row * p.ld_q + h * kDHead + 8 * hf + 16 * s);
-        // no member of the row is known yet: a reference far below any logit makes the first block's maximum the
-        // reference (0 would leave rows whose logits are all very negative with an empty sum)
-        part.m_ref[0] = kSafeNoRef;
-        part.l[0] = 0.f;
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part.O[db][0][r] = 0.f;
-        if (SUMI && wave == 0) {
-            float dot = 0.f;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const bf16x8 kk = *(const bf16x8 *)(p.k_self + row * p.ld_kv + h * kDHead + 8 * hf + 16 * s);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) dot += (float)part.qf[0][s][e] * (float)kk[e];
-            }
-            part.m_ref[0] = dot + xhalf(dot);  // (both halves add the same two numbers)
-            part.l[0] = hf == 0 ? 1.f : 0.f;
-            const __bf16 *vp = p.v_self + row * p.ld_kv + h * kDHead + 4 * hf;
-#pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const bf16x4 vv = *(const bf16x4 *)(vp + 32 * db + 8 * g);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) part.O[db][0][4 * g + e] = (float)vv[e];
-                }
-        }
-        const int n_blk = (k_hi - k_lo + kBlockKeys - 1) / kBlockKeys, share = (n_blk + NW - 1) / NW;
-        const int end = min(n_blk, (wave + 1) * share);
-        int blk = wave * share;
-        if (blk < end) {
-            KFrags kf = load_k(kv + (size_t)blk * kBlockBytes, lane);
-            VFrags vf = load_v(kv + (size_t)blk * kBlockBytes, lane);
-            for (; blk < end; ++blk) {
-                f32x16 S[1];
-                bf16x8 P[1][2];
-                const uint8_t *next = kv + (size_t)min(blk + 1, end - 1) * kBlockBytes;
-                qk_block(part, kf, S);
-                kf = load_k(next, lane);
-                const int blk_lo = k_lo + blk * kBlockKeys;
-                if (blk_lo + kBlockKeys > k_hi) mask_block(S, hf, blk_lo, k_hi);
-                if (CAUSAL && blk_lo + kBlockKeys > q0 + first) {
-                    const int lim1[1] = {q0 + first + l32 + 1};
-                    mask_causal(S, hf, blk_lo, lim1);
-                }
-                softmax_safe(part, S, P);
-                pv_block(part, vf, P);
-                vf = load_v(next, lane);
-            }
-        }
-        // parts of O, of the denominators and their references: [wave][32 values][lane] in the ring, [wave][m, l][32 queries]
-        float *part_O = (float *)lds, *part_ml = (float *)(lds + NW * 8192);
-        static_assert(NW * (8192 + 256) <= kStages * kTileBytes, "the parts fit into the ring");
-        const float l_sum = part.l[0] + xhalf(part.l[0]);
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part_O[(wave * 32 + db * 16 + r) * 64 + lane] = part.O[db][0][r];
-        part_ml[wave * 64 + lane] = hf == 0 ? part.m_ref[0] : l_sum;
-        __syncthreads();
-        if (wave == own) {
-            float m = part_ml[l32], w[NW], l = 0.f;
-#pragma unroll
-            for (int i = 1; i < NW; ++i) m = fmaxf(m, part_ml[i * 64 + l32]);
-#pragma unroll
-            for (int i = 0; i < NW; ++i) {
-                w[i] = __builtin_amdgcn_exp2f((part_ml[i * 64 + l32] - m) * part.c[0]);
-                l += w[i] * part_ml[i * 64 + 32 + l32];
-            }
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-                if (qb == id % QB) {
-                    lt[qb] = l;
-#pragma unroll
-                    for (int db = 0; db < 2; ++db)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            float o = 0.f;
-#pragma unroll
-                            for (int i = 0; i < NW; ++i) o += w[i] * part_O[(i * 32 + db * 16 + r) * 64 + lane];
-                            st.O[db][qb][r] = o;
-                        }
-                }
-        }
-        __syncthreads();  // the parts have been read
     }
 
     // ---- normalise and store ----------------------------------------------------------------
     // A lane holds O^T[32db + 8g + 4hf + 0..3][query]: 8-byte pieces of 32 different rows.  Each
     // wave turns its 32 x 64 block around in its own corner of the (now idle) LDS ring so that
     // the global stores are whole 128-byte rows, 16 bytes per lane.
+    if (any_bad) __syncthreads();  // SAFE pass: every wave is done reading K/V tiles
     constexpr int kRowPitch = 144;  // 128 B of a row + 16 B pad, keeps 16-byte alignment
     uint8_t *tr = lds + wave * (32 * kRowPitch);
 #pragma unroll

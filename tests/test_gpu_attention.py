@@ -491,8 +491,8 @@ def test_bf16_tiles_find_their_temperature_in_tables_of_any_size(n_scen, n_beh):
 @pytest.mark.parametrize("rows", [(5,), (70, 40), (5, 40, 70, 99)])
 def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
     # Queries along one key, 2^24 above the others for candidates (folded form: window 2^20), 2^115 for history rows (exact
-    # scale: 2^100); keys in every wave's share, in the last block, and the candidate's own.  One and two times 32 queries of
-    # a 256- or 128-query tile redone by themselves, or the tile as a whole.  TOL: see above (an output is nearly one value row,
+    # scale: 2^100); keys early and late, in the last block, and the candidate's own.  One, two and four times 32 queries of a
+    # tile call for the running maximum, which the whole tile then takes.  TOL: see above (an output is nearly one value row,
     # below 4: its own rounding is 2^-7).
     spec = W.shrink(W.CONFIG2, name=f"bf16-redo-{M}-{len(rows)}", B=B, L=700, sub_len=512, M=M, H=4, pad_to=64, seed=830)
     w = W.make_attention(spec)
@@ -559,3 +559,46 @@ def test_history_from_rows_redoes_a_tile_that_one_key_outgrows(B, H):
     w["vh"] = w["vh"].clip(-3.9375, 3.9375)
     check_all(w)
     check_all(w, causal=True)
+
+
+@pytest.mark.parametrize("B", [2, 36])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("flags", [0, TWO_KERNEL])
+def test_bf16_history_row_of_a_tiny_temperature_among_ordinary_ones(B, causal, flags):
+    # a temperature of 1e-10 (exponents of 2e7: the row is its best key's value) in one row of a tile, the others as usual: a wave
+    # per 32 queries, tiles from rows and from the cache.  Under the causal flag the row sees keys of its tile's first block
+    # only.  TOL: see above (an output is one value row, below 4: its own rounding is 2^-7).
+    spec = W.shrink(W.CONFIG2, name=f"bf16-tiny-tau-{B}", B=B, L=700, sub_len=512, M=4, H=4, pad_to=64, nan_padding=True, seed=860)
+    w = W.make_attention(spec)
+    w["tau"], w["qh"] = w["tau"].copy(), w["qh"].copy()
+    w["tau"][1] = 1e-10
+    w["vh"] = w["vh"].clip(-3.9375, 3.9375)
+    w["scen"], w["cscen"] = np.zeros_like(w["scen"]), np.zeros_like(w["cscen"])
+    for b in range(B):
+        for r, key in ((5, 3), (520, 515)):
+            at = int(w["tok_off"][b]) + r
+            k = w["kh"][int(w["tok_off"][b]) + key]
+            w["scen"][at] = 1
+            w["qh"][at] = W.round_bf16(k * (0.01 / (k ** 2).sum(-1, keepdims=True)))
+    check_all(w, causal=causal, flags=flags)
+
+
+@pytest.mark.parametrize("B,M,H", [(36, 100, 4)])
+def test_bf16_one_outgrown_row_redoes_its_whole_tile(B, M, H):
+    # The other candidates of its query tile are held in unrounded queries and an fp32 scale too, however few rows leave the
+    # window: one of a tile, or one of every 32, leaves the same bits in the rest, which are not those of the folded form.
+    spec = W.shrink(W.CONFIG2, name=f"bf16-outgrown-{M}", B=B, L=700, sub_len=512, M=M, H=H, pad_to=64, seed=870)
+    w = W.make_attention(spec)
+    w["tau"] = np.ones_like(w["tau"])
+    qc, every, out = w["qc"], range(5, M, 32), []
+    for rows in ((), range(5, M, 256), every):
+        w["qc"] = qc.copy()
+        for b in range(B):
+            for r in rows:
+                k = w["kh"][int(w["tok_off"][b]) + (r * 7) % 700]
+                w["qc"][int(w["cand_off"][b]) + r] = W.round_bf16(k * (16.6 / (k ** 2).sum(-1, keepdims=True) * 8))
+        g = GpuAttention(w)
+        g.history(want_output=False)
+        out.append(np.delete(g.sumi().reshape(B, M, -1), list(every), 1))
+    assert np.array_equal(out[1], out[2])
+    assert not np.array_equal(out[0], out[1])
