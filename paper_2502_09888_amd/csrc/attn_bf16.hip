@@ -430,16 +430,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
                 ss += xhalf(ss);  // the 32 keys of the block
                 big |= !(ss * st.c[qb] * st.c[qb] < kBlockKeys * kPilotSpread * kPilotSpread);
             }
-            if (SUMI && QB == 1 && p.pilot_pairs && k_hi - k_lo >= kFoldMinKeys) {
-                // users with more than 128 candidates: the choice is made for 64 queries, as by the waves of the 256-query tiles.
-                // (Through the landing slices, whose query rows are in registers; own rows come into them after the next barrier.)
-                const bool any = __builtin_amdgcn_ballot_w64(big) != 0;
-                if (lane == 0) *(volatile int *)rows_lds = any;
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                const int mate = *(volatile int *)(lds + kStages * kTileBytes + (wave ^ 1) * (WQ * 128));
-                big |= mate != 0;
-            }
             // Only the candidate pass folds, and only against a history of some length: its rows then have
             // many comparable keys to average the per-logit error over.  History rows
             // see one subsequence (a few keys only under the causal flag) and can be sharply peaked, where
@@ -678,35 +668,17 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
     const int groups = (a.cache.B * a.H + 7) / 8;
     const int64_t grid = (int64_t)8 * n_qtiles * groups;
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-    KParams p = make_params(a, n_qtiles);
-    p.pilot_pairs = SUMI && QB == 1 && a.max_rows_per_user > 128;
+    const KParams p = make_params(a, n_qtiles);
     hipLaunchKernelGGL((attn_bf16_kernel<NW, QB, SUMI, CAUSAL, RAW>), dim3((unsigned)grid), dim3(NW * 64), 0, s, p);
     return hipGetLastError();
 }
 
 // Query-tile shape: 4 waves x QB blocks of 32 queries per workgroup.  QB = 2 (256 queries) re-reads
 // a head's K/V from L2 half as often and reuses every LDS fragment for two MFMAs; QB = 1 (128
-// queries) keeps two waves per SIMD busy when a head has few queries, pads a user's candidates by less, and deals
-// the work out in smaller pieces where there are few workgroups or users of very different lengths.  Scoring, us, 256 / 128
-// queries, 8 heads, caches and rows that no earlier call left in the last-level cache:
-//   all users alike, as many rows with either: 20 x 512 against 2048 (320 workgroups of 256) 64.8 / 63.2, 24 x 512 against 1024 (384) 39.1 / 38.8,
-//     48 x 256 (384) 40.9 / 43.8; in that cache 64 x 256 (512) 41.2 / 43.2, 64 x 512 (1024) 76.0 / 83.3
-//   fewer rows: 64 x 257 (384 rows instead of 512) 75.7 / 68.3, 40 x 300 against 600 40.5 / 33.0, 60 x 640 against 512 (640, 768) 69.7 / 68.4,
-//     30 x 896 (896, 1024) 74.9 / 74.8
-//   users that differ (a quarter of the longest at least), up to 256 candidates of 24 users against 2000 (about 220) 33.1 / 27.5, 900 of 12
-//     against 4000 (260) 63.3 / 50.3, 1024 of 16 against 4096 (410) 85.2 / 84.2, 500 of 32 against 2000 (440) 46.2 / 46.6, 400 of 40
-//     (470) 59.1 / 61.5
-bool small_tiles(const AttnArgs &a)
-{
-    const int64_t m = a.max_rows_per_user, heads = (int64_t)a.cache.B * a.H;
-    if (m <= 128) return true;
-    if (a.uni_cand >= 0) {
-        const int64_t r1 = (m + 127) / 128 * 128, r2 = (m + 255) / 256 * 256;
-        return 6 * r1 <= 5 * r2 || heads * (r2 / 256) <= 300;
-    }
-    return a.total_q_rows * a.H / 256 + heads / 2 <= 420;  // (half a tile per head is padding)
-}
-
+// queries) keeps two waves per SIMD busy when a head has few queries.  Scoring takes 128 only for users of up to 128
+// candidates: where a row leaves the softmax's window all rows of its tile are redone with unrounded queries, so
+// smaller tiles would hold more rows in the folded form.  (They pad less and deal the work out in smaller pieces; us, 256 / 128
+// queries, 8 heads: 64 x 257 75.7 / 68.3, 40 x 300 against 600 40.5 / 33.0, 64 x 512 76.0 / 83.3.)
 // The history pass: a query tile lies inside one subsequence (sub_len is 0 or a multiple of 128); 256 queries where that allows them
 // and they are neither few nor poorly filled.  Us, 256 / 128 queries, from rows: 12 users x 300, 8 heads (192 workgroups of 256)
 // 12.2 / 11.3, 20 x 2000, 4 heads (640) 102.7 / 100.0, 128 x 500, 4 heads (1024) 50.6 / 54.9, 64 x 1024 in one subsequence (2048) 173 / 197; up to 333
@@ -760,7 +732,7 @@ hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 {
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, true, s);
     if (few_queries(a, true)) return launch_attn_wave_bf16(a, true, s);
-    return small_tiles(a) ? launch<4, 1, true>(a, s) : launch<4, 2, true>(a, s);
+    return a.max_rows_per_user > 128 ? launch<4, 2, true>(a, s) : launch<4, 1, true>(a, s);
 }
 
 hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s)

@@ -583,20 +583,25 @@ def test_bf16_history_row_of_a_tiny_temperature_among_ordinary_ones(B, causal, f
     check_all(w, causal=causal, flags=flags)
 
 
-@pytest.mark.parametrize("B,M,H", [(36, 100, 4)])
+@pytest.mark.parametrize("B,M,H", [(36, 100, 4), (16, 530, 4), (24, 500, 8)])
 def test_bf16_one_outgrown_row_redoes_its_whole_tile(B, M, H):
     # The other candidates of its query tile are held in unrounded queries and an fp32 scale too, however few rows leave the
-    # window: one of a tile, or one of every 32, leaves the same bits in the rest, which are not those of the folded form.
+    # window: one of a tile (of 256, where a user has more than 128) or one of every 32 leaves the same bits in the rest, which are
+    # not those of the folded form.  (Such a row has a zero product with the first 32 keys: by them its wave would choose the
+    # form of wider window.)
     spec = W.shrink(W.CONFIG2, name=f"bf16-outgrown-{M}", B=B, L=700, sub_len=512, M=M, H=H, pad_to=64, seed=870)
     w = W.make_attention(spec)
+    say(f"[case] {spec.name} B={B} M={M} H={H}")
     w["tau"] = np.ones_like(w["tau"])
     qc, every, out = w["qc"], range(5, M, 32), []
+    first = [np.linalg.qr(w["kh"][t0:t0 + 32].transpose(1, 2, 0))[0] for t0 in w["tok_off"][:-1]]  # [H][64][32]
     for rows in ((), range(5, M, 256), every):
         w["qc"] = qc.copy()
         for b in range(B):
             for r in rows:
-                k = w["kh"][int(w["tok_off"][b]) + (r * 7) % 700]
-                w["qc"][int(w["cand_off"][b]) + r] = W.round_bf16(k * (16.6 / (k ** 2).sum(-1, keepdims=True) * 8))
+                k = w["kh"][int(w["tok_off"][b]) + 32 + (r * 7) % 668]
+                q = k - np.einsum("hdi,hei,he->hd", first[b], first[b], k)
+                w["qc"][int(w["cand_off"][b]) + r] = W.round_bf16(q * (16.6 * 8 / (q * k).sum(-1, keepdims=True)))
         g = GpuAttention(w)
         g.history(want_output=False)
         out.append(np.delete(g.sumi().reshape(B, M, -1), list(every), 1))
