@@ -679,17 +679,21 @@ hipError_t launch(const AttnArgs &a, hipStream_t s)
 // candidates: where a row leaves the softmax's window all rows of its tile are redone with unrounded queries, so
 // smaller tiles would hold more rows in the folded form.  (They pad less and deal the work out in smaller pieces; us, 256 / 128
 // queries, 8 heads: 64 x 257 75.7 / 68.3, 40 x 300 against 600 40.5 / 33.0, 64 x 512 76.0 / 83.3.)
-// The history pass: a query tile lies inside one subsequence (sub_len is 0 or a multiple of 128); 256 queries where that allows them
-// and they are neither few nor poorly filled.  Us, 256 / 128 queries, from rows: 12 users x 300, 8 heads (192 workgroups of 256)
-// 12.2 / 11.3, 20 x 2000, 4 heads (640) 102.7 / 100.0, 128 x 500, 4 heads (1024) 50.6 / 54.9, 64 x 1024 in one subsequence (2048) 173 / 197; up to 333
-// of 128 (users of 40 to 384 rows) 45.7 / 35.0, 300 x 65 26.4 / 21.4.
+// The history pass: a query tile lies inside one subsequence (sub_len is 0 or a multiple of 128); 256 queries where that allows them,
+// they are well filled, and there are many of them or just enough for the 512 workgroups that the chip holds at a time: with a few
+// more a nearly empty second turn costs more than the tiles' economy gives, and under the causal flag half-empty tiles balance
+// badly.  Us, 256 / 128 queries, rows and caches that no earlier call left in the last-level cache, 8 heads:
+//   from the cache, writer's launch included: 12 users x 1000 in subsequences of 512 (384 workgroups of 256) 33.0 / 31.6, 16 (512) 38.4 / 39.9,
+//     18 (576) 46.4 / 45.3, 32 (1024) 67.1 / 71.5; in one subsequence 16 52.8 / 57.3, 18 68.7 / 65.7; causal, 512 each, 16 38.7 / 38.5, 18
+//     48.5 / 44.6, 32 69.1 / 69.7; of 256 to 1024 behaviours 16 (512 launched) 6 % for 256, 18 (576) 8 % for 128; poorly filled: 32 x 600 50.2 / 47.4, 36 x 300 34.7 / 31.0
+//   from rows: 12 x 1000 in 512 29.8 / 28.5, 16 32.0 / 35.9, 18 42.9 / 42.5, 32 60.0 / 65.3; causal 16 33.0 / 36.9 (but 16 of 256 to 1024
+//     8 % the other way), 18 45.8 / 43.8; 32 x 600 46.5 / 42.7, 36 x 300 30.6 / 27.4
 bool hist_wide_tiles(const AttnArgs &a)
 {
     if (a.sub_len % 256 != 0) return false;
-    const int64_t B = a.cache.B, most = a.max_rows_per_user, total = a.total_q_rows;
-    // rows that the tiles cover; of users that differ, about half a tile each is padding
-    const int64_t r1 = a.uni_pad >= 0 ? B * ((most + 127) / 128 * 128) : total + B * 32, r2 = a.uni_pad >= 0 ? B * ((most + 255) / 256 * 256) : total + B * 96;
-    return 6 * r1 > 5 * r2 && r2 / 256 * a.H > 640;
+    const int64_t r1 = hist_tile_rows(a, 128), r2 = hist_tile_rows(a, 256), tiles = r2 / 256 * a.H;
+    const int64_t launched = (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 255) / 256);  // those beyond a user's end, too
+    return 6 * r1 > 5 * r2 && (tiles > 640 || (!a.causal && tiles > 384 && launched <= 512));
 }
 
 // Launches of few queries go to attn_wave_bf16.hip: at most one wave of 32 per SIMD (1024), fewer where the tiles are well

@@ -52,6 +52,14 @@ struct AttnArgs {
     BiasArgs bias;                   // relative attention bias; bias.pos_table == nullptr: none
 };
 
+// Rows that query tiles of 128 or 256 cover in the history pass; of users that differ (padded to multiples of 64), about half a tile
+// each is padding.
+static inline int64_t hist_tile_rows(const AttnArgs &a, int tile)
+{
+    const int64_t B = a.cache.B;
+    return a.uni_pad >= 0 ? B * ((a.max_rows_per_user + tile - 1) / tile * tile) : a.total_q_rows + B * (tile / 2 - 32);
+}
+
 // bf16 MFMA flash attention (attn_bf16.hip)
 hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s);

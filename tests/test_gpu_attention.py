@@ -515,12 +515,12 @@ def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
 
 @pytest.mark.parametrize("B,L,L_min,sub,H,pad", [(1, 1, 1, 0, 1, 64), (3, 63, 0, 384, 2, 64), (3, 65, 64, 0, 1, 64), (4, 129, 0, 512, 2, 64),
                                                  (5, 300, 1, 0, 4, 64), (2, 448, 256, 0, 2, 128), (6, 700, 0, 640, 3, 64), (2, 1024, 900, 512, 8, 64),
-                                                 (30, 1100, 400, 512, 8, 64), (25, 1500, None, 0, 8, 128), (40, 830, None, 384, 8, 64),
+                                                 (30, 1100, 400, 512, 8, 64), (25, 1500, None, 0, 8, 128), (40, 830, None, 384, 8, 64), (16, 1000, None, 512, 8, 64),
                                                  (3, 500, 1, 256, 4, 64), (14, 1000, 100, 256, 8, 64), (5, 300, 0, 128, 4, 64)])
 @pytest.mark.parametrize("causal", [False, True])
 def test_history_from_rows_writes_the_bits_of_two_launches(B, L, L_min, sub, H, pad, causal):
     # outputs and the whole cache, over what was in both before: tiles of 128 queries (few of them, subsequences of odd multiples of 128)
-    # and of 256 (three), histories down to none, at the edges of blocks and tiles, tiles of padding only; NaN in the padding; subsequences
+    # and of 256 (four), histories down to none, at the edges of blocks and tiles, tiles of padding only; NaN in the padding; subsequences
     # of 256 and 128, few of them and many
     import torch
     spec = W.shrink(W.CONFIG2, name=f"bf16-rows-{L}-{sub}", B=B, L=L, L_min=L_min, sub_len=sub, M=1, H=H, pad_to=pad, nan_padding=True, seed=840 + L)
