@@ -445,13 +445,21 @@ __global__ __launch_bounds__(SUB * 2, 256 / SUB) void hist_fused_kernel(const HP
 
 }  // namespace
 
-// Up to 320 subsequences of 256 are less than two per workgroup, with nothing to prefetch behind: there the tiled kernel, which takes
-// rows as well, is the faster way.  Us there / here, 8 heads: 8 users x 256 (64 subsequences) 7.9 / 10.5, 16 x 256 (128) 8.7 / 11.2, 8 x 1000 (256)
-// 13.4 / 14.2, 32 x 200 (256) 12.8 / 13.0, causal 13.4 / 12.9, 10 x 800 (320) 17.8 / 22.5, 20 x 700 (480) 29.0 / 24.3, 16 x 1024 (512) 29.9 / 28.1;
-// of 128: 2 x 300, 4 heads 7.5 / 7.6, 32 x 512, 4 heads 12.4 / 11.6.
+// Subsequences of 256: a persistent workgroup per CU takes as long for its first item as a nearly empty chip, and twice as long
+// where some have a second one.  The tiled kernel, which takes rows as well, is the faster way with up to one 128-query tile per CU, and
+// where a few CUs would have a second item, or most items were half empty; a causal walk shares less between its tiles.  Us
+// there / here, cold inputs, full / causal, 8 heads:
+//   up to a tile per CU: 8 users x 256 (64 items, 128 tiles) 8.9 / 11.0, 9.4 / 10.9, 4 x 1024 (128, 256) 10.3 / 11.9, 10.5 / 11.6
+//   one item: 24 x 256 (192, 384) 13.4 / 13.2, 15.2 / 12.8, 8 x 1024 (256, 512) 15.1 / 14.2, 16.2 / 13.6; 21 x 700, 4 heads (252, 504)
+//     19.1 / 14.4, 17.7 / 13.7
+//   a second one: 10 x 1024 (320, 640) 21.5 / 22.9, 23.6 / 21.4, 20 x 300 (320, 480) 13.7 / 21.0, 13.9 / 19.8, 24 x 300 (384, 576)
+//     19.0 / 21.9, 19.1 / 20.3, 12 x 1000 (384, 768) 22.6 / 23.2, 25.1 / 23.0, 16 x 1024 (512, 1024) 29.8 / 24.6, 31.1 / 23.7
+// Of 128: 2 x 300, 4 heads 7.5 / 7.6, 32 x 512, 4 heads 12.4 / 11.6.
 bool hist_fused_takes(const AttnArgs &a)
 {
-    return a.sub_len == 128 || (a.sub_len == 256 && (int64_t)((a.max_rows_per_user + 255) / 256) * a.cache.B * a.H > 320);
+    if (a.sub_len != 256) return a.sub_len == 128;
+    const int64_t items = (int64_t)((a.max_rows_per_user + 255) / 256) * a.cache.B * a.H, tiles = hist_tile_rows(a, 128) / 128 * a.H;
+    return tiles > 256 && (items <= 256 || tiles > (a.causal ? 576 : 640));
 }
 
 hipError_t launch_hist_fused_bf16(const AttnArgs &a, hipStream_t s)
