@@ -138,10 +138,10 @@ def test_bf16_ragged_lengths_nan_padding():
 
 
 def test_bf16_causal_history():
-    # history token i sees j <= i of its subsequence.  Subsequences of 128 and 256 (the one-kernel pass:
-    # wave w stops after key block w; and, under the two-kernel flag, the tiled kernel, whose query
-    # tile of 256 rows holds two resp. one subsequence), one undivided sequence spanning several query
-    # tiles, ragged lengths with NaN padding, large logits (the running-maximum pass of both
+    # history token i sees j <= i of its subsequence.  Subsequences of 128 (the one-kernel pass: wave w
+    # stops after key block w) and 256 (so few of them: tiles from rows), under the two-kernel flag a wave
+    # per 32 queries, one undivided sequence spanning several query
+    # tiles, ragged lengths with NaN padding, large logits (the running-maximum pass of these
     # kernels); the candidate pass on the cache that the causal history call wrote.
     for name, kw in (("bf16-causal-sub128", dict(B=3, L=384, sub_len=128, M=40, H=2, seed=41)),
                      ("bf16-causal-sub256", dict(B=2, L=512, sub_len=256, M=40, H=2, seed=42)),
@@ -160,8 +160,8 @@ def test_bf16_causal_history():
 
 
 def test_bf16_large_temperature_table():
-    # more (scenario, behaviour) pairs than a wavefront has lanes: the one-kernel history pass keeps
-    # small tables in a register and reads larger ones from memory
+    # more (scenario, behaviour) pairs than a wavefront has lanes: the one-kernel history pass (subsequences of 128
+    # here) keeps small tables in a register and reads larger ones from memory
     spec = W.shrink(W.CONFIG2, name="bf16-tau-128", B=2, L=256, sub_len=128, M=40, H=2, n_scen=16,
                     n_beh=8, seed=45)
     check_all(W.make_attention(spec))
@@ -170,9 +170,30 @@ def test_bf16_large_temperature_table():
     check_all(W.make_attention(spec))
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("kind", ["ragged", "large logits", "one user's large logits", "large table"])
+def test_bf16_one_kernel_history_pass_of_subsequences_of_256(kind, causal):
+    # 192 subsequences in more than 256 query tiles of 128 (fewer take the tiles from rows): ragged lengths with NaN padding;
+    # rows that need the running maximum, in every wave and in a few; more temperatures than a wavefront has lanes (read
+    # from memory).  Outputs against the oracle, the cache against the cache writer's.  TOL: see above.
+    import torch
+    spec = W.shrink(W.CONFIG2, name=f"bf16-one-kernel-256-{kind}", B=12, L=500, L_min=300 if kind == "ragged" else None, sub_len=256, M=4,
+                    H=8, pad_to=64, nan_padding=True, seed=880, qk_scale=12.0 if kind == "large logits" else 0.125,
+                    n_scen=16 if kind == "large table" else 8, n_beh=8 if kind == "large table" else 4)
+    w = W.make_attention(spec)
+    if kind == "one user's large logits":
+        w["qh"] = w["qh"].copy()
+        w["qh"][5:w["tok_off"][1]:40] *= 64.0  # power of two: still exactly representable
+    g, _ = check_all(w, causal=causal)
+    two = GpuAttention(w, causal=causal, flags=TWO_KERNEL)
+    two.history(want_output=False)
+    payload = int(w["tok_off"][-1]) * spec.H * 256
+    assert torch.equal(g.buf[-payload:], two.buf[-payload:])
+
+
 def test_bf16_shape_sweep():
     # seeded sweep over shapes the API admits: paddings of 64 and 128, subsequence lengths that are
-    # any multiple of 128 (384 takes the tiled kernel with 128-query tiles), 1..3 heads, ragged
+    # any multiple of 128, 1..3 heads, ragged
     # histories down to no history at all, candidate counts around the 128 / 256 query tiles and
     # down to none, both masks, NaN padding
     rng = np.random.Generator(np.random.Philox(20250209))
@@ -295,12 +316,14 @@ def test_few_queries_keep_an_infinite_value_infinite(L):
     assert np.array_equal(part, full[:192]) and np.isfinite(np.delete(oh[ok], at, 1)).all()
 
 
-@pytest.mark.parametrize("L,sub", [(31, 0), (64, 0), (130, 0), (385, 0), (530, 384), (1100, 512)])
-def test_few_queries_causal_history(L, sub):
+@pytest.mark.parametrize("L,sub", [(31, 0), (64, 0), (130, 0), (385, 0), (530, 384), (1100, 512), (1100, 0)])
+@pytest.mark.parametrize("flags", [0, TWO_KERNEL])
+def test_few_queries_causal_history(L, sub, flags):
+    # tiles from rows (but for 1100 in one subsequence), and a wave per 32 queries from the cache
     spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=2, L=L, sub_len=sub, M=4, H=2, pad_to=64, L_min=max(1, L - 20),
                     nan_padding=True, seed=730 + L)
     w = W.make_attention(spec)
-    oh, ok = GpuAttention(w, causal=True).history(), valid_rows(w)
+    oh, ok = GpuAttention(w, causal=True, flags=flags).history(), valid_rows(w)
     assert max_abs(oh[ok], oracle_history(w, causal=True)[ok]) < 2e-2 and np.all(oh[~ok] == 0)
 
 
@@ -367,8 +390,8 @@ def test_bf16_long_histories():
 
 
 def test_two_kernel_history_path():
-    # Subsequences of 128 / 256 tokens take the one-kernel pass (cache blocks + attention) by
-    # default; the same cases must also hold on the other route (cache writer, then tiled attention)
+    # Subsequences of 128 / 256 tokens take one launch (cache blocks + attention) by
+    # default; the same cases must also hold on the other route (cache writer, then attention from the cache)
     for name, kw in (("bf16-small-2k", dict(B=3, L=384, sub_len=128, M=200, H=2, seed=21)),
                      ("bf16-sub256-2k", dict(B=2, L=512, sub_len=256, M=40, H=2, seed=27)),
                      ("bf16-biglogits-2k", dict(B=1, L=256, sub_len=128, M=64, H=2, qk_scale=12.0, seed=25))):
@@ -385,13 +408,14 @@ def sigma_t(spec, w):
 
 
 @pytest.mark.parametrize("qk_scale", [0.25, 0.5, 1.0, 2.0])
-@pytest.mark.parametrize("M", [40, 300])
-def test_bf16_logit_scale_sweep(qk_scale, M):
+@pytest.mark.parametrize("M,B,H", [(40, 2, 2), (300, 2, 2), (100, 36, 4), (300, 14, 8)])
+def test_bf16_logit_scale_sweep(qk_scale, M, B, H):
     # N(0,1) inputs with logit scales between the unit-scale benchmark (0.125) and the overflow case:
     # the regime in which the pass that folds the temperature into a bf16 query is still accepted for
-    # some rows while its rounding error (relative 2^-9 of a logit) grows with the logits.  M = 40
-    # takes the 128-query tile, M = 300 the 256-query tile; history on both routes.
-    spec = W.shrink(W.CONFIG2, name=f"bf16-logits-{qk_scale}-M{M}", B=2, L=512, sub_len=128, M=M, H=2,
+    # some rows while its rounding error (relative 2^-9 of a logit) grows with the logits.  Two users
+    # take a wave per 32 candidates, 36 of 100 the 128-query tile (576 waves would be more than 512),
+    # 14 of 300 the 256-query tile (1120, 1024); history on both routes.
+    spec = W.shrink(W.CONFIG2, name=f"bf16-logits-{qk_scale}-M{M}-B{B}", B=B, L=512, sub_len=128, M=M, H=H,
                     qk_scale=qk_scale, seed=50 + M)
     w = W.make_attention(spec)
     say(f"  logit std at the smallest temperature: {sigma_t(spec, w):.1f} (log2 units)")
@@ -399,14 +423,16 @@ def test_bf16_logit_scale_sweep(qk_scale, M):
     check_all(w, flags=TWO_KERNEL)
 
 
-def test_bf16_large_logits_in_wide_tile_and_mixed_batch():
-    # logits in the hundreds with M > 128 (the 256-query tile redoes its rows with a running maximum),
+@pytest.mark.parametrize("B,H", [(3, 2), (14, 8)])
+def test_bf16_large_logits_in_wide_tile_and_mixed_batch(B, H):
+    # logits in the hundreds with M > 128 (a wave per 32 candidates; and, with 14 users of 8 heads, the 256-query
+    # tile: both redo their rows with a running maximum),
     # then a batch in which only user 0 has large logits: some workgroups of the launch fall back,
     # the others do not
-    spec = W.shrink(W.CONFIG2, name="bf16-biglogits-wide", B=2, L=384, sub_len=128, M=300, H=2,
+    spec = W.shrink(W.CONFIG2, name="bf16-biglogits-wide", B=B - 1 if B == 3 else B, L=384, sub_len=128, M=300, H=H,
                     qk_scale=12.0, seed=28)
     check_all(W.make_attention(spec))
-    spec = W.shrink(W.CONFIG2, name="bf16-mixed-logits", B=3, L=384, sub_len=128, M=300, H=2, seed=29)
+    spec = W.shrink(W.CONFIG2, name="bf16-mixed-logits", B=B, L=384, sub_len=128, M=300, H=H, seed=29)
     w = W.make_attention(spec)
     c0, c1 = w["cand_off"][0], w["cand_off"][1]
     w["qc"][c0:c1] *= 64.0             # power of two: still exactly representable
@@ -480,8 +506,8 @@ def test_device_side_input_check():
 
 @pytest.mark.parametrize("n_scen,n_beh", [(1, 1), (255, 1), (257, 1), (1792, 2), (3585, 1)])
 def test_bf16_tiles_find_their_temperature_in_tables_of_any_size(n_scen, n_beh):
-    # one copy of 256 entries or less, more than one, the most that are staged in LDS and one more than that; query tiles
-    # of 256, the last of them nearly empty, both passes.  TOL: see above.
+    # one copy of 256 entries or less, more than one, the most that are staged in LDS and one more than that; candidates in
+    # query tiles of 256 (1088 waves of 32), the last of them nearly empty, history in tiles of 128.  TOL: see above.
     spec = W.shrink(W.CONFIG2, name=f"bf16-tau-{n_scen * n_beh}", B=16, L=700, sub_len=512, M=530, H=4, pad_to=64, n_scen=n_scen,
                     n_beh=n_beh, seed=820)
     check_all(W.make_attention(spec))
@@ -492,8 +518,8 @@ def test_bf16_tiles_find_their_temperature_in_tables_of_any_size(n_scen, n_beh):
 def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
     # Queries along one key, 2^24 above the others for candidates (folded form: window 2^20), 2^115 for history rows (exact
     # scale: 2^100); keys early and late, in the last block, and the candidate's own.  One, two and four times 32 queries of a
-    # tile call for the running maximum, which the whole tile then takes.  TOL: see above (an output is nearly one value row,
-    # below 4: its own rounding is 2^-7).
+    # tile (of 256 where M is 530, else 128; history rows 128) call for the running maximum, which the whole tile then takes.
+    # TOL: see above (an output is nearly one value row, below 4: its own rounding is 2^-7).
     spec = W.shrink(W.CONFIG2, name=f"bf16-redo-{M}-{len(rows)}", B=B, L=700, sub_len=512, M=M, H=4, pad_to=64, seed=830)
     w = W.make_attention(spec)
     w["tau"] = np.ones_like(w["tau"])
@@ -510,6 +536,7 @@ def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
             key = (3, 2, r // 2, r)[(b + i) % 4]
             w["qh"][t0 + r] = W.round_bf16(w["kh"][t0 + key] * (80 / (w["kh"][t0 + key] ** 2).sum(-1, keepdims=True) * 8))
     check_all(w)
+    check_all(w, flags=TWO_KERNEL)
     check_all(w, causal=True, flags=TWO_KERNEL)
 
 
@@ -547,8 +574,9 @@ def test_history_from_rows_writes_the_bits_of_two_launches(B, L, L_min, sub, H, 
 
 @pytest.mark.parametrize("B,H", [(2, 2), (30, 8)])
 def test_history_from_rows_redoes_a_tile_that_one_key_outgrows(B, H):
-    # 2^115 above the other keys of the row (window 2^100): the whole tile walks once more over the rows, up to a last tile of
-    # keys that ends in NaN.  TOL: see above.
+    # 2^115 above the other keys of the row (window 2^100): the whole tile (of 128 queries; with 30 users, 960 tiles of 256)
+    # walks once more over the rows, up to a last tile of keys that ends in NaN; and over the cache (two users: a wave per 32
+    # queries).  TOL: see above.
     spec = W.shrink(W.CONFIG2, name=f"bf16-rows-redo-{B}", B=B, L=1000, sub_len=512, M=1, H=H, pad_to=64, nan_padding=True, seed=850)
     w = W.make_attention(spec)
     w["tau"], w["qh"] = np.ones_like(w["tau"]), w["qh"].copy()
@@ -557,8 +585,9 @@ def test_history_from_rows_redoes_a_tile_that_one_key_outgrows(B, H):
         for r, key in ((5, 3), (600, 520), (999, 999)):
             w["qh"][t0 + r] = W.round_bf16(w["kh"][t0 + key] * (80 / (w["kh"][t0 + key] ** 2).sum(-1, keepdims=True) * 8))
     w["vh"] = w["vh"].clip(-3.9375, 3.9375)
-    check_all(w)
-    check_all(w, causal=True)
+    for flags in (0, TWO_KERNEL):
+        check_all(w, flags=flags)
+        check_all(w, causal=True, flags=flags)
 
 
 @pytest.mark.parametrize("B", [2, 36])
