@@ -556,8 +556,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
             run(std::false_type{});
     }
 
-    // lane % 32 again, opaquely: otherwise the compiler carries the old copy across the loop (in
-    // scratch memory, which would be this kernel's only use of it)
+    // lane % 32 again, opaquely: otherwise the compiler carries the old copy across the loop, in
+    // scratch memory (where the 256-query scoring kernel already keeps 12 registers)
     asm volatile("v_and_b32 %0, 31, %1" : "=v"(l32) : "v"(tid));
     if (OWN) {  // whatever part of the own-row schedule a short history left undone
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -720,8 +720,9 @@ bool few_queries(const AttnArgs &a, bool sumi)
 // be the tiled kernel: 16 x up to 4096 in subsequences of 512 77.8 / 93.1, 64 x 1024 in one 167.6 / 187.9, causal 64 x 1000 in two 113 / 124.
 bool attn_hist_rows_bf16_takes(const AttnArgs &a)
 {
+    if (a.bias.pos_table) return attn_hist_rows_bias_bf16_takes(a);
     const int walk = a.sub_len > 0 ? std::min(a.sub_len, a.max_hist_len) : a.max_hist_len;
-    return a.bias.pos_table || walk <= 1024 || !few_queries(a, false);
+    return walk <= 1024 || !few_queries(a, false);
 }
 
 hipError_t launch_attn_hist_rows_bf16(const AttnArgs &a, hipStream_t s)

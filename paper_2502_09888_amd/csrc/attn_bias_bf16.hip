@@ -575,6 +575,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
     }
 }
 
+// one head's rows of the tables
+int64_t bias_entries(const AttnArgs &a)
+{
+    return (int64_t)a.n_scen * a.n_beh * ((int64_t)a.bias.n_pos + a.bias.n_time);
+}
+
 template <int QB, bool SUMI, bool CAUSAL, bool RAW = false>
 hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
 {
@@ -583,7 +589,7 @@ hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
     const int64_t grid = (int64_t)8 * n_qtiles * ((a.cache.B * a.H + 7) / 8);
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
     const KParams p = make_params(a, n_qtiles);
-    const int64_t entries = (int64_t)a.n_scen * a.n_beh * ((int64_t)a.bias.n_pos + a.bias.n_time);
+    const int64_t entries = bias_entries(a);
     const bool in_lds = entries <= kBiasLdsFloats;
     const size_t lds = kStages * kStageBytes + NW * 4 + kClassBytes<QB> + (in_lds ? (size_t)entries * 4 : 0);
     auto go = [&](auto in_lds_tag) {
@@ -593,7 +599,8 @@ hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NW * 64), lds, s, p);
         return hipGetLastError();
     };
-    return in_lds ? go(std::true_type{}) : go(std::false_type{});
+    if constexpr (RAW && !CAUSAL) return in_lds ? go(std::true_type{}) : hipErrorInvalidValue;
+    else return in_lds ? go(std::true_type{}) : go(std::false_type{});
 }
 
 }  // namespace
@@ -610,6 +617,12 @@ hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
     }
     return a.causal ? launch_bias<1, false, true>(a, s) : launch_bias<1, false, false>(a, s);
 }
+
+// From rows with the tables in LDS.  With look-ups in global memory the cache writer and a launch that reads the cache are the faster
+// way but for causal passes: 32 rows of 257 + 20 entries, subsequences of 256, us from rows / as two, causal: one user's 1000 24.2 / 23.0,
+// 24.7 / 26.2; 30 x 1000 131.2 / 128.4, 131.7 / 123.5; 8 x 2000 70.1 / 70.6, 70.7 / 81.2; 64 x 1024 260 / 254, 259 / 245; 4 x 300 24.5 /
+// 23.4, 24.8 / 26.4.
+bool attn_hist_rows_bias_bf16_takes(const AttnArgs &a) { return a.causal || bias_entries(a) <= kBiasLdsFloats; }
 
 hipError_t launch_attn_hist_rows_bias_bf16(const AttnArgs &a, hipStream_t s)
 {

@@ -71,6 +71,7 @@ hipError_t launch_attn_hist_rows_bf16(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_wave_bf16(const AttnArgs &a, bool sumi, hipStream_t s);
 // the same with the relative attention bias (attn_bias_bf16.hip)
 hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s);
+bool attn_hist_rows_bias_bf16_takes(const AttnArgs &a);                        // by attn_hist_rows_bf16_takes
 hipError_t launch_attn_hist_rows_bias_bf16(const AttnArgs &a, hipStream_t s);  // by launch_attn_hist_rows_bf16
 // fused cache write + attention inside short subsequences (hist_fused_bf16.hip): a.k_self / a.v_self
 // are the history key / value rows (same row stride as the queries)
