@@ -44,8 +44,9 @@ constexpr int kClassBytes = NW * QB * 64 * 4;
 // IN_LDS: the head's rows of the tables are copied into LDS (else looked up in global memory).
 // RAW (history pass): keys and values are rows, and this launch writes them into the cache as well (RawTiles, attn_common.h);
 // every wave the blocks of its own rows, which it fetches once more behind its last tile.
-template <int QB, bool SUMI, bool CAUSAL, bool IN_LDS, bool RAW>
-__global__ __launch_bounds__(NW * 64, 2) void attn_bias_kernel(const KParams p)
+// PER_CU: workgroups per CU, which the registers have to leave room for (168 a lane for three).
+template <int QB, bool SUMI, bool CAUSAL, bool IN_LDS, bool RAW, int PER_CU>
+__global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParams p)
 {
     static_assert(!(SUMI && CAUSAL), "the causal flag concerns the history pass");
     static_assert(!RAW || (!SUMI && QB == 1), "rows: the history pass");
@@ -592,15 +593,29 @@ hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
     const int64_t entries = bias_entries(a);
     const bool in_lds = entries <= kBiasLdsFloats;
     const size_t lds = kStages * kStageBytes + NW * 4 + kClassBytes<QB> + (in_lds ? (size_t)entries * 4 : 0);
-    auto go = [&](auto in_lds_tag) {
-        constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value, RAW>;
+    auto go = [&](auto in_lds_tag, auto per_cu) {
+        constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value, RAW, decltype(per_cu)::value>;
         const hipError_t e = raise_lds_limit<kernel>(kStages * kStageBytes + NW * 4 + kClassBytes<QB> + kBiasLdsFloats * 4);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NW * 64), lds, s, p);
         return hipGetLastError();
     };
-    if constexpr (RAW && !CAUSAL) return in_lds ? go(std::true_type{}) : hipErrorInvalidValue;
-    else return in_lds ? go(std::true_type{}) : go(std::false_type{});
+    using Two = std::integral_constant<int, 2>;
+    using Three = std::integral_constant<int, 3>;
+    // The history pass: a third workgroup per CU where the tables leave it room in LDS (given out by 1280 bytes) and there are that
+    // many.  From rows it costs the compiler the order it likes best: us with two / three, subsequences of 256, one row of 33 + 20 entries,
+    // full and causal: 64 users x 1024 142 / 125, 146 / 126; 30 x 1000 74.3 / 67.4, 74.6 / 68.3; 8 x 2000 (1024 workgroups) 41.9 / 41.5, 42.3 /
+    // 41.6; 100 x 100 (800) 32.9 / 34.9, 33.6 / 36.4; 4 x 300 14.2 / 14.2, 14.4 / 15.2; 32 rows of it, 64 x 1024 145 / 145, 148 / 153.
+    constexpr size_t kLds = 160 * 1024, kLdsUnit = 1280;
+    const bool three = (lds + kLdsUnit - 1) / kLdsUnit * kLdsUnit * 3 <= kLds && grid >= 1024;
+    if constexpr (RAW) {
+        if (in_lds) return three ? go(std::true_type{}, Three{}) : go(std::true_type{}, Two{});
+        if constexpr (CAUSAL) return go(std::false_type{}, Two{});
+        return hipErrorInvalidValue;
+    } else {
+        using LdsHist = std::integral_constant<int, SUMI ? 2 : 3>;
+        return in_lds ? go(std::true_type{}, LdsHist{}) : go(std::false_type{}, Two{});
+    }
 }
 
 }  // namespace
