@@ -15,6 +15,7 @@
 #include "attn_common.h"
 #include "launch.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace climber {
@@ -610,8 +611,7 @@ hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
     const bool three = (lds + kLdsUnit - 1) / kLdsUnit * kLdsUnit * 3 <= kLds && grid >= 1024;
     if constexpr (RAW) {
         if (in_lds) return three ? go(std::true_type{}, Three{}) : go(std::true_type{}, Two{});
-        if constexpr (CAUSAL) return go(std::false_type{}, Two{});
-        return hipErrorInvalidValue;
+        return go(std::false_type{}, Two{});
     } else {
         using LdsHist = std::integral_constant<int, SUMI ? 2 : 3>;
         return in_lds ? go(std::true_type{}, LdsHist{}) : go(std::false_type{}, Two{});
@@ -634,10 +634,14 @@ hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
 }
 
 // From rows with the tables in LDS.  With look-ups in global memory the cache writer and a launch that reads the cache are the faster
-// way but for causal passes: 32 rows of 257 + 20 entries, subsequences of 256, us from rows / as two, causal: one user's 1000 24.2 / 23.0,
-// 24.7 / 26.2; 30 x 1000 131.2 / 128.4, 131.7 / 123.5; 8 x 2000 70.1 / 70.6, 70.7 / 81.2; 64 x 1024 260 / 254, 259 / 245; 4 x 300 24.5 /
-// 23.4, 24.8 / 26.4.
-bool attn_hist_rows_bias_bf16_takes(const AttnArgs &a) { return a.causal || bias_entries(a) <= kBiasLdsFloats; }
+// way but for causal passes and short walks: 32 rows of 257 + 20 entries, us from rows / as two, causal: subsequences of 256, one
+// user's 1000 24.2 / 23.0, 24.7 / 26.2; 4 x 300 24.5 / 23.4, 24.8 / 26.4; 30 x 1000 131 / 128, 132 / 124; 8 x 2000 70.1 / 70.6, 70.7 / 81.2;
+// 64 x 1024 260 / 254, 259 / 245; histories of 60 x 200 32.2 / 36.9, 31.6 / 34.7, 100 x 100 23.4 / 26.2, 23.7 / 26.9.
+bool attn_hist_rows_bias_bf16_takes(const AttnArgs &a)
+{
+    const int walk = a.sub_len > 0 ? std::min(a.sub_len, a.max_hist_len) : a.max_hist_len;
+    return a.causal || walk < 256 || bias_entries(a) <= kBiasLdsFloats;
+}
 
 hipError_t launch_attn_hist_rows_bias_bf16(const AttnArgs &a, hipStream_t s)
 {

@@ -274,28 +274,43 @@ def test_bf16_bias_few_and_many_candidates_give_the_same_bits(L):
     assert max_abs(got, oracle_sumi_bias(part)) < TOL["bf16"]
 
 
-@pytest.mark.parametrize("L,L_min,sub,H,qk_scale", [(1, 1, 0, 1, 0.125), (65, 0, 0, 2, 0.125), (129, 64, 384, 1, 0.125), (300, 1, 256, 3, 0.125),
-                                                    (700, 200, 128, 2, 0.125), (500, 300, 512, 2, 12.0), (2200, 1900, 0, 2, 0.125)])
-@pytest.mark.parametrize("causal", [False, True])
-def test_bf16_bias_history_from_rows_writes_the_bits_of_two_launches(L, L_min, sub, H, qk_scale, causal):
-    # outputs and the whole cache, over what was in both before; tiles of padding only, NaN in the padding, histories of more than the
-    # 64 blocks that are classified at a time; 12: the running-maximum pass
+def check_one_launch_writes_the_bits_of_two(spec, n_pos, n_time, causal):
+    """Outputs and the whole cache of the history pass, over what was in both before."""
     import torch
-    spec = W.shrink(W.CONFIG2, name=f"bias-rows-{L}-{sub}", B=3, L=L, L_min=L_min, sub_len=sub, M=1, H=H, pad_to=64, nan_padding=True,
-                    qk_scale=qk_scale, seed=990 + L)
-    w = W.add_bias_inputs(W.make_attention(spec), n_pos=33, n_time=12)
+    w = W.add_bias_inputs(W.make_attention(spec), n_pos=n_pos, n_time=n_time)
     say(f"[case] {spec.name} causal={causal}")
     out = []
     for flags in (0, 2):
         g = GpuBias(w, causal=causal)
         g.cfg.flags |= flags
-        payload = int(w["tok_off"][-1]) * H * 256
+        payload = int(w["tok_off"][-1]) * spec.H * 256
         g.buf[-payload:].fill_(77)
         oh, ok = g.history_bias(), valid_rows(w)
         assert np.isfinite(oh[ok]).all() and np.all(oh[~ok] == 0)
         out.append((oh, g.buf[-payload:].clone()))
     assert np.array_equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
     assert max_abs(out[0][0][ok], oracle_hist_bias(w, causal=causal)[ok]) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("L,L_min,sub,H,qk_scale", [(1, 1, 0, 1, 0.125), (65, 0, 0, 2, 0.125), (129, 64, 384, 1, 0.125), (300, 1, 256, 3, 0.125),
+                                                    (700, 200, 128, 2, 0.125), (500, 300, 512, 2, 12.0), (2200, 1900, 0, 2, 0.125)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_bf16_bias_history_from_rows_writes_the_bits_of_two_launches(L, L_min, sub, H, qk_scale, causal):
+    # tiles of padding only, NaN in the padding, histories of more than the 64 blocks that are classified at a time; 12: the
+    # running-maximum pass
+    spec = W.shrink(W.CONFIG2, name=f"bias-rows-{L}-{sub}", B=3, L=L, L_min=L_min, sub_len=sub, M=1, H=H, pad_to=64, nan_padding=True,
+                    qk_scale=qk_scale, seed=990 + L)
+    check_one_launch_writes_the_bits_of_two(spec, 33, 12, causal)
+
+
+@pytest.mark.parametrize("B,L,H,n_scen,n_beh,n_pos", [(44, 300, 8, 1, 1, 483), (44, 300, 8, 1, 1, 497), (5, 255, 2, 8, 4, 257), (5, 256, 2, 8, 4, 257)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_bf16_bias_history_from_rows_by_tables_and_workgroups(B, L, H, n_scen, n_beh, n_pos, causal):
+    # 1056 workgroups: three per CU with tables of 503 entries, two with 517; tables beyond LDS: from rows with walks below
+    # 256 keys or the causal flag, else two launches either way
+    spec = W.shrink(W.CONFIG2, name=f"bias-rows-by-{n_pos}-{L}", B=B, L=L, L_min=L - 60, sub_len=0, M=1, H=H, pad_to=64, nan_padding=True,
+                    n_scen=n_scen, n_beh=n_beh, seed=1100 + n_pos)
+    check_one_launch_writes_the_bits_of_two(spec, n_pos, 20, causal)
 
 
 @pytest.mark.parametrize("n_scen,n_beh,n_pos,n_time", [(8, 4, 195, 13), (1, 1, 6645, 12), (8, 4, 129, 20)])
