@@ -518,7 +518,8 @@ def test_bf16_tiles_find_their_temperature_in_tables_of_any_size(n_scen, n_beh):
 def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
     # Queries along one key, 2^24 above the others for candidates (folded form: window 2^20), 2^115 for history rows (exact
     # scale: 2^100); keys early and late, in the last block, and the candidate's own.  One, two and four times 32 queries of a
-    # tile (of 256 where M is 530, else 128; history rows 128) call for the running maximum, which the whole tile then takes.
+    # tile (candidates of 256 where M is 530, else 128; history rows of 256 where M is 100, but for causal ones, else 128) call for
+    # the running maximum, which the whole tile then takes.
     # TOL: see above (an output is nearly one value row, below 4: its own rounding is 2^-7).
     spec = W.shrink(W.CONFIG2, name=f"bf16-redo-{M}-{len(rows)}", B=B, L=700, sub_len=512, M=M, H=4, pad_to=64, seed=830)
     w = W.make_attention(spec)
