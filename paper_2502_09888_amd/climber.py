@@ -134,8 +134,10 @@ def _ptr(t) -> Optional[int]:
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        # The handle by itself: torch.cuda.current_stream() builds a Stream object around it, 2.9 of a small call's 7.9 us
+        # on the host (0.3 this way; two fp32 calls of one small user 15.6 us as a pass, 10.9 this way).
         import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None

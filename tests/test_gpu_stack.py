@@ -196,3 +196,21 @@ def test_projection_through_rows_path():
                          w_std=0.05), (0, 1))):
         run(spec, users, flags=VIA_ROWS)
         run(spec, users, flags=VIA_ROWS | TWO_KERNEL)
+
+
+def test_calls_without_a_stream_take_torchs_current_one():
+    # the default stream, another one inside a with block, and a thread, which has a current stream of its own
+    import threading
+    import torch
+    from paper_2502_09888_amd import climber
+    other = torch.cuda.Stream()
+    handle = lambda: (climber._stream(None) or 0, torch.cuda.current_stream().cuda_stream)
+    seen = [handle()]
+    with torch.cuda.stream(other):
+        seen.append(handle())
+        t = threading.Thread(target=lambda: seen.append(handle()))
+        t.start()
+        t.join()
+    seen.append(handle())
+    assert all(a == b for a, b in seen)
+    assert [a for a, _ in seen] == [0, other.cuda_stream, 0, 0]
