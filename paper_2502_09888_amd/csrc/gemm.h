@@ -83,6 +83,19 @@ struct GemmArgs {
 // gemm_small_bf16.hip: few rows.  N % 64 == 0, K % 128 == 0.
 hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s);
 
+// Where the fused QKV projection of a call's rows goes: rows [0, n_cached), the history's, keys and values into the cache and
+// queries to rows of q; the others as rows of `rows`, row n_cached first.  n_cached: none, or qc.rows.
+struct QkvOut {
+    QkvToCache qc;        // (qc.which0 = 1: no queries of the history)
+    int n_cached;
+    void *q, *rows;
+    int64_t ld_q, ld_rows;
+};
+
+// gemm_resident_bf16.hip: the fused QKV projection of many rows.  A: bf16 [M][K]; N = 3 K.
+bool gemm_resident_takes(int M, int K, bool cached);
+hipError_t gemm_resident_bf16(const void *A, const void *w_packed, int M, int K, const RowNormIn &in_norm, const QkvOut &out, hipStream_t s);
+
 // layer_tail_bf16.hip: y = h + GELU(RMSNorm(h) W1) W2 with h = x + o Wo, one launch.  Rows of D columns: o bf16,
 // x / y fp32, yb (nullable) bf16; ss (nullable) [M][D / 64] sums of squares of y; wo [D][D], w1 [D][F] (gains
 // multiplied in), w2 [F][D] packed.  y may be x, or lies apart from it; its rows may hold h for a while.
@@ -97,8 +110,13 @@ struct TailArgs {
     float *ss;
     int M, D, F;
     float inv_d, eps;
+    // The next layer's QKV projection behind it, on the rows as they leave (where layer_tail_projects; yb and ss are then not written):
+    int wq;           // its packed weights, so many bytes behind wo (within w_bytes); 0: no projection
+    int y_first;      // y is wanted from this row on (a multiple of 64)
+    QkvOut next;
 };
 bool layer_tail_takes(int M, int D, int F);  // shapes it has a kernel for and is the faster way
+bool layer_tail_projects(int M, int D, int F, int n_cached);  // where that is the faster way; n_cached of the rows go to a cache
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s);
 
 // What the first projection of a stack call needs of its input rows: the sum of squares of every

@@ -21,11 +21,17 @@
 // the weights' way through the vector cache (the same bytes for half the products); 8192 rows 62 us between the other
 // launches of a stack, 76 without the weights requested ahead (PRE below).  (Taller tiles would need less of the caches, but 128 rows do not fit the registers; separate waves
 // for the two products gave the same times.)
+// The rows that leave are the next layer's input: with QKV the workgroup goes on to that layer's fused QKV projection (qkv_units.h),
+// its rows' bf16 copy in LDS once more.  They and their row sums do not go out and come back (66 MB a layer at 32768 rows of 512), and
+// what the launch between two attentions starts and ends with goes away; y itself is left out where nobody reads it.  Encode of
+// 32 users x 1024, four layers: 847 -> 808 us with the projection of the first layer's rows by gemm_resident_bf16.hip, packed forward
+// 1010 -> 927; 0.9 PFLOP/s over the launch.
 // Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
 // bits.
 #include "gemm_common.h"
 #include "lanes.h"
 #include "launch.h"
+#include "qkv_units.h"
 
 #include <utility>
 
@@ -34,7 +40,6 @@ namespace {
 
 using namespace gemm;
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 typedef const __attribute__((address_space(1))) uint8_t glb_u8;
 
@@ -52,13 +57,15 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
-// rows of h, a chunk of the hidden (at the end: 32 rows of y, fp32)
+// rows of h, a chunk of the hidden (at the end: 32 rows of y, fp32); with a projection behind it: sums of squares and scales of y
 template <int D, int RB, int NW>
 constexpr int tail_lds_bytes()
 {
     constexpr int operands = 32 * RB * (D + 32 * NW) * 2, rows = 32 * D * 4;
     return operands > rows ? operands : rows;
 }
+template <int D, int RB>
+constexpr int tail_scale_bytes() { return 32 * RB * (D / 64 + 1) * 4; }
 
 template <int N>
 using At = std::integral_constant<int, N>;
@@ -74,9 +81,10 @@ struct Next { int base, a, b; };
 // its own, which return in order.  Us, four layers scored, 8192 rows: 484 with a 268 MB cache between (539 without), 379
 // with a short one (389); by the computing waves at their start 493 and 393.  With it eight fragments in flight do what
 // 16 did, and the registers hold a third wave per SIMD.  64-row tiles do not gain (and have no registers for it).
-template <int D, int RB, int NW, int R, int PRE>
+template <int D, int RB, int NW, int R, int PRE, bool QKV>
 __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(const TailArgs p)
 {
+    static_assert(!QKV || (D / NW == 64 && RB % 2 == 0 && !PRE), "");
     constexpr int ROWS = 32 * RB, CW = D / NW, NJ = CW / 32;   // rows of the tile; columns and column blocks of a wave
     constexpr int kChunk = 32 * NW;                            // hidden columns of a chunk
     constexpr int S = D / 16, T = kChunk / 16;                 // k-steps of the products over h and over a chunk
@@ -421,11 +429,18 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
         lds_barrier();  // chunk ch + 1 is there
     }
     if constexpr (!kKeep) request_rows(p.y);
-    down(n_chunks - 1, next_down(n_chunks - 1), std::false_type{});  // (what it loads ahead is not used)
+    const bool cached = QKV && m0 < p.next.n_cached;
+    const int u0 = (cached ? p.next.qc.which0 * (D / 64) : 0) + wave;  // the wave's first unit of the projection
+    down(n_chunks - 1, QKV ? Next{p.wq + 2 * u0 * (S * 1024), S * 1024, 1024} : next_down(n_chunks - 1), std::false_type{});  // (without it, what it loads ahead is not used)
     add_rows(p.y);  // y
 
     // ---- y out: rows through LDS, whole lines ----
-    if (p.ss) {
+    float *const y_ss = (float *)(lds + tail_lds_bytes<D, RB, NW>()), *const y_scale = y_ss + ROWS * (D / 64);
+    if constexpr (QKV) {
+        slice_sums([&](int i, int sl, float v) __attribute__((always_inline)) {
+            if (hf == 0) y_ss[(32 * i + l32) * (D / 64) + wave * (NJ / 2) + sl] = v;
+        });
+    } else if (p.ss) {
         slice_sums([&](int i, int sl, float v) __attribute__((always_inline)) {
             const int row = m0 + 32 * i + l32;
             if (hf == 0 && row < M) p.ss[(int64_t)row * (D / 64) + wave * (NJ / 2) + sl] = v;
@@ -436,6 +451,7 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
     uint8_t *tr = lds + wave * (32 * kRowB);
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
+        if (QKV && m0 < p.y_first) break;
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -448,7 +464,7 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
             const float4 v = *(const float4 *)(tr + r * kRowB + ((c ^ (r & 15)) * 16));
             if (row < M) {
                 *(float4 *)(p.y + (int64_t)row * D + col) = v;
-                if (p.yb) {
+                if (!QKV && p.yb) {
                     bf16x4 b;
                     b[0] = (__bf16)v.x, b[1] = (__bf16)v.y, b[2] = (__bf16)v.z, b[3] = (__bf16)v.w;
                     *(bf16x4 *)((__bf16 *)p.yb + (int64_t)row * D + col) = b;
@@ -456,13 +472,34 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
             }
         }
     }
+    if constexpr (QKV) {
+        lds_barrier();  // (everybody's corner of LDS is free; the sums are there)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    bf16x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = (__bf16)acc[i][j][4 * g + e];
+                    write_a(X, kXPitch, i, col0 + 32 * j + 8 * g, v);
+                }
+        if (tid < ROWS) y_scale[tid] = row_scale(RowNormIn{y_ss, D / 64, p.inv_d, p.eps}, tid);
+        CacheUser user[RB / 2];
+#pragma unroll
+        for (int b = 0; b < RB / 2; ++b) user[b] = cached ? cache_user(p.next.qc, min(m0 + 64 * b, p.next.n_cached - 64)) : CacheUser{0, 64, 0};
+        lds_barrier();  // y is there
+        if (cached) qkv_units<D, RB, R / 2, true>(X, y_scale, w, p.wq, ring, u0, NW, 3 * D / 64, p.next, user, m0, M, lane);
+        else qkv_units<D, RB, R / 2, false>(X, y_scale, w, p.wq, ring, u0, NW, 3 * D / 64, p.next, user, m0, M, lane);
+    }
 }
 
-template <int D, int RB, int NW, int R, int PRE>
+template <int D, int RB, int NW, int R, int PRE, bool QKV = false>
 hipError_t launch_tail(const TailArgs &a, hipStream_t s)
 {
-    constexpr size_t lds = tail_lds_bytes<D, RB, NW>() + PRE * 256;
-    constexpr auto kernel = layer_tail_kernel<D, RB, NW, R, PRE>;
+    constexpr size_t lds = tail_lds_bytes<D, RB, NW>() + PRE * 256 + (QKV ? tail_scale_bytes<D, RB>() : 0);
+    constexpr auto kernel = layer_tail_kernel<D, RB, NW, R, PRE, QKV>;
     const hipError_t e = raise_lds_limit<kernel>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((a.M + 32 * RB - 1) / (32 * RB))), dim3((NW + PRE) * 64), lds, s, a);
@@ -483,9 +520,27 @@ bool layer_tail_takes(int M, int D, int F)
     return F % 128 == 0 && F > 0 && ((D == 512 && M > (F % 256 == 0 ? 4096 : 12288)) || (D == 256 && M > 4096));
 }
 
+// With the next layer's projection in the same launch its input rows, their row sums and that launch's start and end are saved; without,
+// it is dealt out over all CUs whatever the tail leaves idle.  Us per call with / without, d_model 512: encode of 32 users x 1024 four layers
+// 827 / 852, two 313 / 328, of 28 753 / 783, of 24 (384 tiles) 707 / 721, of 20 672 / 678 and, elsewhere, 673 / 666, of 17 672 / 654, of 16 (256 tiles, one per CU) 454 / 468, of 14 433 / 431, of 10 390 / 376;
+// packed forward (candidates' rows besides: one launch instead of three) of 9 users 422 / 455, 13 506 / 551, 20 855 / 858, 32 928 / 1001; scoring
+// alone, against the 128 x 128 tiles, 9766 rows 554 / 530, 16448 944 / 896, 24672 1020 / 1015, 30840 1173 / 1204.  d_model 256 (tiles two
+// per CU): encode of 9 users 141 / 151, 32 286 / 324, 64 530 / 581, scoring of 8481 rows 206 / 213, 32896 517 / 539.
+bool layer_tail_projects(int M, int D, int F, int n_cached)
+{
+    if (!layer_tail_takes(M, D, F)) return false;
+    if (D == 256) return true;
+    const int tiles = (M + 63) / 64;
+    return F % 256 == 0 && M > 8192 && n_cached > 0 && (n_cached < M || tiles > 352 || (tiles > 240 && tiles <= 256));
+}
+
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)
 {
     if (a.M < 1 || a.F < 128 || a.F % 128 != 0) return hipErrorInvalidValue;
+    if (a.wq) {
+        if (!layer_tail_takes(a.M, a.D, a.F) || (a.D == 512 && (a.F % 256 != 0 || a.M <= 8192)) || a.next.n_cached % 64 != 0 || a.y_first % 64 != 0) return hipErrorInvalidValue;
+        return a.D == 512 ? launch_tail<512, 2, 8, 8, 0, true>(a, s) : launch_tail<256, 2, 4, 8, 0, true>(a, s);
+    }
     // d_model 512: eight waves need chunks of 256; no more than a 32-row tile per CU: those (fewer rows in line behind one
     // another).  Four waves hold twice the columns each, and h has to wait in memory.  Us, stack calls of four layers, eight
     // / four waves: encode of 32768 rows 853 / 907, score of 8704 594 / 727, of 16384 772 / 919.

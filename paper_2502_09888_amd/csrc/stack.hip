@@ -110,10 +110,19 @@ int pack_layers(const climber_config *cfg, const climber_layer_weights *layers, 
     return CLIMBER_OK;
 }
 
+// The QKV projection of the layer behind a tail, where the tail makes it: that layer's weights (in one block of memory with the
+// tail's own, further on), where its rows go, and from which row on the tail's own output is wanted besides.
+struct NextQkv {
+    const uint8_t *wqkv;
+    QkvOut out;
+    int64_t y_first;
+};
+
 // attention output rows -> y (f_FFN and the residual stream), `rows` rows from row r0 of the workspace's arrays.
-// x, y: fp32 rows of the residual stream; norm_out: also the bf16 copy and sums of squares of y.
+// x, y: fp32 rows of the residual stream; norm_out: also the bf16 copy and sums of squares of y; next (nullable): the next
+// layer's projection instead of those.
 int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x, float *y, bool norm_out,
-               int64_t r0, int64_t rows, const Workspace &ws, hipStream_t s)
+               int64_t r0, int64_t rows, const Workspace &ws, hipStream_t s, const NextQkv *next = nullptr)
 {
     const int d = cfg->d_model, F = cfg->d_ffn, M = (int)rows;
     const uint8_t *o = ws.o + (size_t)r0 * d * 2;
@@ -124,9 +133,17 @@ int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x,
     // (one launch reads and writes rows as its workgroups come to them: y is x itself or lies apart from it)
     const size_t bytes = (size_t)M * d * 4;
     const bool in_place = x == y, apart = (uintptr_t)x + bytes <= (uintptr_t)y || (uintptr_t)y + bytes <= (uintptr_t)x;
-    if ((in_place || apart) && layer_tail_takes(M, d, F))
-        return rt(layer_tail_bf16(TailArgs{o, x, pw.wo, (int)(pw.w1 - pw.wo), (int)(pw.w2 - pw.wo), (int)(pw.w2 - pw.wo) + d * F * 2, y,
-                                           norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F, nin.inv_d, nin.eps}, s));
+    if ((in_place || apart) && layer_tail_takes(M, d, F)) {
+        TailArgs a{o, x, pw.wo, (int)(pw.w1 - pw.wo), (int)(pw.w2 - pw.wo), (int)(pw.w2 - pw.wo) + d * F * 2, y,
+                   norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F, nin.inv_d, nin.eps, 0, 0, QkvOut{}};
+        if (next) {
+            a.yb = nullptr, a.ss = nullptr;
+            a.wq = (int)(next->wqkv - pw.wo), a.w_bytes = a.wq + 3 * d * d * 2;
+            a.next = next->out, a.y_first = (int)next->y_first;
+        }
+        return rt(layer_tail_bf16(a, s));
+    }
+    if (next) return CLIMBER_ERR_RUNTIME;  // (asked for by layer_tail_projects, and rows in place)
     float *h = ws.h32 + (size_t)r0 * d;
     uint8_t *u = ws.u + (size_t)r0 * F * 2;
     TRY(rt(gemm_bf16(EPI_RESID_F32, o, d, pw.wo, M, d, d, h, d, x, d, no_in, nout, 0, s)));
@@ -134,32 +151,43 @@ int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x,
     return rt(gemm_bf16(EPI_RESID_F32, u, F, pw.w2, M, d, F, y, d, h, d, no_in, norm_out ? nout : no_out, kTiledA, s));
 }
 
+// the fused QKV projection of all rows of a call that go the same way (in: bf16 rows of d; nin: their sums of squares)
+int project_qkv(const climber_config *cfg, const PackedLayer &pw, const void *in, int64_t rows, const RowNormIn &nin,
+                const QkvOut &out, hipStream_t s)
+{
+    const int d = cfg->d_model, M = (int)rows;
+    if (gemm_resident_takes(M, d, out.n_cached > 0)) return rt(gemm_resident_bf16(in, pw.wqkv, M, d, nin, out, s));
+    const RowNormOut no_out{nullptr, nullptr, 0};
+    if (!out.n_cached)
+        return rt(gemm_bf16(EPI_STORE_BF16, in, d, pw.wqkv, M, 3 * d, d, out.rows, out.ld_rows, nullptr, 0, nin, no_out, 0, s));
+    const int skip = out.qc.which0 * d;  // columns that nobody wants
+    return rt(gemm_bf16(EPI_STORE_BF16, in, d, pw.wqkv + (size_t)skip * d * 2, M, 3 * d - skip, d, out.q, out.ld_q, nullptr, 0, nin,
+                        no_out, 0, s, &out.qc));
+}
+
 // one layer on `rows` rows.  x_in: fp32 rows (the residual stream); xb_in / ws.ss: their bf16 copy and
 // row sums of squares (from the previous layer's last projection or from a row_prep kernel).
 // norm_out: also emit the bf16 copy and sums of squares of x_out (the next layer needs them).
+// projected: the layer's QKV projection is made already; next (nullable): make the next layer's.
 int run_layer(const climber_config *cfg, const PackedLayer &pw, const float *tau_layer, int32_t layer,
               int32_t mode, climber_kv_cache *cache, const float *x_in, const void *xb_in, float *x_out,
               bool norm_out, const int32_t *scen, const int32_t *beh, const int32_t *cand_off,
-              int32_t m_total, int32_t m_max, int64_t rows, const Workspace &ws, hipStream_t s)
+              int32_t m_total, int32_t m_max, int64_t rows, const Workspace &ws, hipStream_t s, bool projected = false,
+              const NextQkv *next = nullptr)
 {
-    const int d = cfg->d_model, M = (int)rows;
+    const int d = cfg->d_model;
     const RowNormIn nin{ws.ss, d / 64, 1.f / (float)d, cfg->rms_eps};
-    const RowNormOut no_out{nullptr, nullptr, 0};
-    QkvToCache qc;
-    if (mode == CLIMBER_MODE_HISTORY && cache_direct_target(cfg, cache, layer, &qc)) {
+    QkvOut to{};
+    if (mode == CLIMBER_MODE_HISTORY && cache_direct_target(cfg, cache, layer, &to.qc)) {
         // the projection's epilogue writes keys and values into the cache as operand fragments; only
         // the query rows exist as rows (the last layer needs none at all)
-        if (!x_out) {
-            qc.which0 = 1;
-            return rt(gemm_bf16(EPI_STORE_BF16, xb_in, d, pw.wqkv + (size_t)d * d * 2, M, 2 * d, d, ws.qkv, d,
-                                nullptr, 0, nin, no_out, 0, s, &qc));
-        }
-        TRY(rt(gemm_bf16(EPI_STORE_BF16, xb_in, d, pw.wqkv, M, 3 * d, d, ws.qkv, d, nullptr, 0, nin, no_out, 0,
-                         s, &qc)));
+        to.n_cached = (int)rows, to.q = ws.qkv, to.ld_q = d, to.qc.which0 = x_out ? 0 : 1;
+        if (!projected) TRY(project_qkv(cfg, pw, xb_in, rows, nin, to, s));
+        if (!x_out) return CLIMBER_OK;
         TRY(attn_history_cached(cfg, tau_layer, ws.qkv, d, scen, beh, cache, layer, ws.o, d, s));
     } else {
-        TRY(rt(gemm_bf16(EPI_STORE_BF16, xb_in, d, pw.wqkv, M, 3 * d, d, ws.qkv, 3 * d, nullptr, 0, nin,
-                         no_out, 0, s)));
+        to.rows = ws.qkv, to.ld_rows = 3 * d;
+        if (!projected) TRY(project_qkv(cfg, pw, xb_in, rows, nin, to, s));
         const uint8_t *q = ws.qkv, *k = ws.qkv + (size_t)d * 2, *v = ws.qkv + (size_t)2 * d * 2;
         if (mode == CLIMBER_MODE_HISTORY) {
             TRY(attn_history_strided(cfg, tau_layer, q, k, v, 3 * d, scen, beh, cache, layer,
@@ -170,7 +198,7 @@ int run_layer(const climber_config *cfg, const PackedLayer &pw, const float *tau
                                   scen, beh, ws.o, d, s));
         }
     }
-    return layer_tail(cfg, pw, x_in, x_out, norm_out, 0, rows, ws, s);
+    return layer_tail(cfg, pw, x_in, x_out, norm_out, 0, rows, ws, s, next);
 }
 
 int check_layer_weights(const climber_layer_weights *w)
@@ -239,13 +267,19 @@ int score_layers(const climber_config *cfg, const climber_weights *weights, cons
     TRY(stage_weights(cfg, weights, ws, s));
     TRY(rt(row_prep_bf16(x_cand, ws.x32, ws.ss, cfg->d_model / 64, m_total, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
+    const bool chain = layer_tail_projects(m_total, cfg->d_model, cfg->d_ffn, 0);
     for (int l = 0; l < cfg->n_layers; ++l) {
         const bool last = l + 1 == cfg->n_layers;
+        NextQkv next{};
+        if (chain && !last) {
+            next.wqkv = packed_layer(cfg, ws, l + 1).wqkv;
+            next.out.rows = ws.qkv, next.out.ld_rows = 3 * cfg->d_model;
+        }
         // the cache is only read in candidate mode
         TRY(run_layer(cfg, packed_layer(cfg, ws, l), tau + l * tl, l, CLIMBER_MODE_CANDIDATE,
                       const_cast<climber_kv_cache *>(cache), ws.x32, l == 0 ? x_cand : (const void *)ws.xb,
                       last ? y_cand : ws.x32, !last, cand_scen, cand_beh, cand_off, m_total, m_max,
-                      m_total, ws, s));
+                      m_total, ws, s, chain && l > 0, next.wqkv ? &next : nullptr));
     }
     return CLIMBER_OK;
 }
@@ -363,11 +397,22 @@ int climber_history_encode(const climber_config *cfg, const climber_weights *wei
     TRY(stage_weights(cfg, weights, ws, s));
     TRY(rt(row_prep_bf16(x_hist, ws.x32, ws.ss, cfg->d_model / 64, rows, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
+    const bool chain = layer_tail_projects((int)rows, cfg->d_model, cfg->d_ffn, cfg->flags & CLIMBER_QKV_VIA_ROWS ? 0 : (int)rows);
     for (int l = 0; l < cfg->n_layers; ++l) {
         const bool last = l + 1 == cfg->n_layers;  // nothing reads the last layer's history output
+        NextQkv next{};
+        if (chain && !last) {
+            next.wqkv = packed_layer(cfg, ws, l + 1).wqkv;
+            if (cache_direct_target(cfg, cache, l + 1, &next.out.qc)) {
+                next.out.n_cached = (int)rows, next.out.q = ws.qkv, next.out.ld_q = cfg->d_model;
+                if (l + 2 == cfg->n_layers) next.out.qc.which0 = 1, next.y_first = rows;  // (keys and values only)
+            } else {
+                next.out.rows = ws.qkv, next.out.ld_rows = 3 * cfg->d_model;
+            }
+        }
         TRY(run_layer(cfg, packed_layer(cfg, ws, l), tau + l * tl, l, CLIMBER_MODE_HISTORY, cache,
                       ws.x32, l == 0 ? x_hist : (const void *)ws.xb, last ? nullptr : ws.x32, !last, scen,
-                      beh, nullptr, 0, 0, rows, ws, s));
+                      beh, nullptr, 0, 0, rows, ws, s, chain && l > 0, next.wqkv ? &next : nullptr));
     }
     return CLIMBER_OK;
 }
@@ -478,8 +523,10 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
     if (m_total && !direct)
         TRY(rt(hipMemcpyAsync(ws.xb + (size_t)T * d * 2, x_cand, (size_t)m_total * d * 2, hipMemcpyDeviceToDevice, s)));
     const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps};
-    const RowNormOut no_out{nullptr, nullptr, 0};
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
+    // a tail over all rows makes the next layer's projection too, keys and values of the history into the cache that its
+    // attention has read by then (T is a multiple of 64)
+    const bool chain = direct && layer_tail_projects((int)R, d, cfg->d_ffn, (int)T);
     for (int l = 0; l < cfg->n_layers; ++l) {
         const bool last = l + 1 == cfg->n_layers;
         const PackedLayer pw = packed_layer(cfg, ws, l);
@@ -493,23 +540,24 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
             // history rows: the projection's epilogue writes keys and values into layer 0 of the scratch
             // cache as operand fragments and the queries as rows of d (none of them when nothing follows);
             // the candidates' rows get a projection launch of their own
-            if (hist_out) {
-                TRY(rt(gemm_bf16(EPI_STORE_BF16, xh, d, pw.wqkv, (int)T, 3 * d, d, ws.qkv, d, nullptr, 0, nin, no_out,
-                                 0, s, &qc)));
-                TRY(attn_history_cached(cfg, tau_l, ws.qkv, d, scen, beh, scratch_cache, 0, ws.o, d, s));
-            } else {
-                qc.which0 = 1;
-                TRY(rt(gemm_bf16(EPI_STORE_BF16, xh, d, pw.wqkv + (size_t)d * d * 2, (int)T, 2 * d, d, ws.qkv, d,
-                                 nullptr, 0, nin, no_out, 0, s, &qc)));
+            if (!chain || l == 0) {
+                QkvOut to{};
+                to.qc = qc, to.qc.which0 = hist_out ? 0 : 1, to.n_cached = (int)T, to.q = ws.qkv, to.ld_q = d;
+                TRY(project_qkv(cfg, pw, xh, T, nin, to, s));
             }
-            const RowNormIn nin_c{ws.ss + (size_t)T * np, np, 1.f / (float)d, cfg->rms_eps};
-            TRY(rt(gemm_bf16(EPI_STORE_BF16, xc, d, pw.wqkv, m_total, 3 * d, d, ws.qkv + crow,
-                             3 * d, nullptr, 0, nin_c, no_out, 0, s)));
+            if (hist_out) TRY(attn_history_cached(cfg, tau_l, ws.qkv, d, scen, beh, scratch_cache, 0, ws.o, d, s));
+            if (!chain || l == 0) {
+                const RowNormIn nin_c{ws.ss + (size_t)T * np, np, 1.f / (float)d, cfg->rms_eps};
+                QkvOut to{};
+                to.rows = ws.qkv + crow, to.ld_rows = 3 * d;
+                TRY(project_qkv(cfg, pw, xc, m_total, nin_c, to, s));
+            }
         } else {
             // one fused projection over both kinds of rows; keys / values of the history rows into layer 0
             // of the scratch cache through rows, attention inside the subsequences
-            TRY(rt(gemm_bf16(EPI_STORE_BF16, ws.xb, d, pw.wqkv, (int)R, 3 * d, d, ws.qkv, 3 * d, nullptr, 0, nin, no_out,
-                             0, s)));
+            QkvOut to{};
+            to.rows = ws.qkv, to.ld_rows = 3 * d;
+            TRY(project_qkv(cfg, pw, ws.xb, R, nin, to, s));
             TRY(attn_history_strided(cfg, tau_l, q, k, v, 3 * d, scen, beh, scratch_cache, 0, hist_out ? ws.o : nullptr,
                                      d, s));
         }
@@ -520,7 +568,14 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
         const int64_t r0 = hist_out ? 0 : T, nr = R - r0;
         if (nr == 0) continue;
         float *x = ws.x32 + (size_t)r0 * d;
-        TRY(layer_tail(cfg, pw, x, hist_out ? x : y_cand, !last, r0, nr, ws, s));
+        NextQkv next{};
+        if (chain && !last) {
+            const bool ends = l + 2 == cfg->n_layers && !y_hist;  // (the history: keys and values only)
+            next.wqkv = packed_layer(cfg, ws, l + 1).wqkv;
+            next.out.qc = qc, next.out.qc.which0 = ends, next.out.n_cached = (int)T, next.y_first = ends ? T : 0;
+            next.out.q = ws.qkv, next.out.ld_q = d, next.out.rows = ws.qkv + crow, next.out.ld_rows = 3 * d;
+        }
+        TRY(layer_tail(cfg, pw, x, hist_out ? x : y_cand, !last, r0, nr, ws, s, next.wqkv ? &next : nullptr));
     }
     if (y_hist && T) TRY(rt(hipMemcpyAsync(y_hist, ws.x32, (size_t)T * d * 4, hipMemcpyDeviceToDevice, s)));
     if (y_hist && m_total)

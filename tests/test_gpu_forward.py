@@ -288,3 +288,61 @@ def test_packed_forward_candidates_with_and_without_history_outputs(layers, flag
     a = run_forward(spec, users=(0, 1), want_hist=False, flags=flags)[2]
     b = run_forward(spec, users=(0, 1), want_hist=True, flags=flags)[2]
     assert np.array_equal(a[:40], b[:40])
+
+
+@pytest.mark.parametrize("d, F, layers, lens, cands, flags", [
+    (512, 256, 3, (384, 77, 300, 129, 512, 64, 1) * 6, 8200, 0),     # histories and candidates, each more than 8192 rows
+    (512, 768, 2, (448,) * 19, 127, 0),                              # a uniform batch, few candidates
+    (512, 384, 3, (500, 33) * 15, 33, 0),                            # no kernel with a projection at this d_ffn: launches of their own
+    (256, 128, 3, (200, 31, 0, 96, 130) * 9, 4161, 0), (256, 384, 2, (320,) * 14, 1, 1), (256, 256, 3, (320, 65) * 12, 31, 4)])
+def test_projection_behind_the_tail_gives_the_bits_of_separate_launches(d, F, layers, lens, cands, flags):
+    # a batch large enough for the tail that makes the next layer's projection (and for the projection of resident rows) against
+    # single users, which take the launches for few rows: caches of all layers, scores, packed forward with and without
+    # history outputs.  Lengths at and off the edges of blocks, NaN in the padding rows
+    import torch
+    import paper_2502_09888_amd as P
+    say(f"[case] chain d={d} F={F} users={len(lens)} cands={cands} flags={flags}")
+    dev, bf, H = "cuda:0", torch.bfloat16, d // 64
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d + F + cands)
+    cfg = P.Config(n_layers=layers, d_model=d, n_heads=H, d_head=64, d_ffn=F, n_scen=2, n_beh=2, sub_len=128, flags=flags, dtype=P.BF16,
+                   qk_scale=0.02)  # (every row stays in one form of the softmax)
+    w = [{k: (torch.randn(*s, generator=gen, device=dev) * 0.05 + (k[0] == "g")).to(bf) for k, s in
+          (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, F)), ("w2", (F, d)))} for _ in range(layers)]
+    tau = torch.rand(layers, 2, 2, generator=gen, device=dev) + 0.5
+    pads = [max(64, (n + 63) // 64 * 64) for n in lens]
+    t0 = [sum(pads[:i]) for i in range(len(lens) + 1)]
+    counts = [cands // len(lens) + (i < cands % len(lens)) for i in range(len(lens))]
+    c0 = [sum(counts[:i]) for i in range(len(lens) + 1)]
+    x = torch.randn(t0[-1], d, generator=gen, device=dev).to(bf)
+    for i, n in enumerate(lens):
+        x[t0[i] + n:t0[i + 1]] = float("nan")
+    xc = torch.randn(cands, d, generator=gen, device=dev).to(bf)
+    ids = torch.randint(0, 2, (2, t0[-1]), generator=gen, device=dev, dtype=torch.int32)
+    cids = torch.randint(0, 2, (2, cands), generator=gen, device=dev, dtype=torch.int32)
+
+    def run(users):
+        hist, pad, m = [lens[i] for i in users], [pads[i] for i in users], [counts[i] for i in users]
+        rows, a, b = sum(pad), t0[users[0]], c0[users[0]]
+        buf = torch.full((P.climber_kv_cache_bytes(cfg, pad),), 0x7f, dtype=torch.uint8, device=dev)
+        cache = P.climber_kv_cache_create(cfg, hist, pad, buf)
+        ws = torch.empty(P.climber_workspace_bytes(cfg, rows + sum(m)), dtype=torch.uint8, device=dev)
+        s, be, cs, cb = (t[k:k + n].clone() for t, k, n in ((ids[0], a, rows), (ids[1], a, rows), (cids[0], b, sum(m)), (cids[1], b, sum(m))))
+        xh, xq = x[a:a + rows].clone(), xc[b:b + sum(m)].clone()
+        off = torch.tensor([0] + [sum(m[:i + 1]) for i in range(len(m))], dtype=torch.int32, device=dev)
+        P.climber_history_encode(cfg, w, tau, xh, s, be, cache, ws)
+        ys = [torch.zeros(sum(m), d, device=dev) for _ in range(3)]
+        yh = torch.zeros(rows, d, device=dev)
+        P.climber_sumi_score(cfg, w, tau, cache, xq, off, sum(m), max(m), cs, cb, ys[0], ws)
+        kv = buf[-layers * rows * d * 4:].view(layers, rows, d * 4).clone()
+        for y, h in ((ys[1], None), (ys[2], yh)):
+            P.climber_sumi_forward(cfg, w, tau, xh, s, be, xq, off, sum(m), max(m), cs, cb, cache, h, y, ws)
+        torch.cuda.synchronize()
+        return kv, ys, yh
+
+    kv, ys, yh = run(list(range(len(lens))))
+    assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0], ys[2]) and not ys[0].isnan().any()
+    for i in (0, 1, len(lens) - 1):
+        kv1, ys1, yh1 = run([i])
+        assert torch.equal(kv1, kv[:, t0[i]:t0[i + 1]]) and torch.equal(ys1[0], ys[0][c0[i]:c0[i + 1]])
+        assert torch.equal(yh1[:lens[i]], yh[t0[i]:t0[i] + lens[i]])
