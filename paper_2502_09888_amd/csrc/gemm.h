@@ -92,16 +92,20 @@ struct QkvOut {
     int64_t ld_q, ld_rows;
 };
 
-// gemm_resident_bf16.hip: the fused QKV projection of many rows.  A: bf16 [M][K]; N = 3 K.
-bool gemm_resident_takes(int M, int K, bool cached);
-hipError_t gemm_resident_bf16(const void *A, const void *w_packed, int M, int K, const RowNormIn &in_norm, const QkvOut &out, hipStream_t s);
+// gemm_resident_bf16.hip: the fused QKV projection of many rows.  A: [M][K], bf16 with their sums of squares in in_norm.ss, or fp32
+// rows, whose sums it forms itself (row_prep_f32's bits; in_norm: inv_d and eps); N = 3 K.
+enum RowsIn { kRowsSummed, kRowsF32 };
+bool gemm_resident_takes(int M, int K, bool cached);   // rows with their sums
+bool gemm_resident_sums(int M, int K);                 // fp32 rows, instead of a launch for their sums before
+hipError_t gemm_resident_bf16(RowsIn in, const void *A, const void *w_packed, int M, int K, const RowNormIn &in_norm, const QkvOut &out,
+                              hipStream_t s);
 
 // layer_tail_bf16.hip: y = h + GELU(RMSNorm(h) W1) W2 with h = x + o Wo, one launch.  Rows of D columns: o bf16,
 // x / y fp32, yb (nullable) bf16; ss (nullable) [M][D / 64] sums of squares of y; wo [D][D], w1 [D][F] (gains
 // multiplied in), w2 [F][D] packed.  y may be x, or lies apart from it; its rows may hold h for a while.
 struct TailArgs {
     const void *o;
-    const float *x;
+    const float *x;   // or, where layer_tail_reads_bf16, bf16 rows: x16, from row x16_split on x16_b
     const void *wo;   // the three packed weights are one block of memory: wo here,
     int w1, w2;       // w1 and w2 that many bytes further on,
     int w_bytes;      // all of them in so many bytes (< 2^31)
@@ -114,14 +118,17 @@ struct TailArgs {
     int wq;           // its packed weights, so many bytes behind wo (within w_bytes); 0: no projection
     int y_first;      // y is wanted from this row on (a multiple of 64)
     QkvOut next;
+    const void *x16, *x16_b;
+    int x16_split;    // a multiple of 64
 };
 bool layer_tail_takes(int M, int D, int F);  // shapes it has a kernel for and is the faster way
 bool layer_tail_projects(int M, int D, int F, int n_cached);  // where that is the faster way; n_cached of the rows go to a cache
+bool layer_tail_reads_bf16(int M, int D, int F);
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s);
 
 // What the first projection of a stack call needs of its input rows: the sum of squares of every
 // row into ss[row][0] (ss[row][1 .. n_part-1] = 0) and
-//   from bf16 rows x (the embeddings): the fp32 copy x32 (the residual stream);
+//   from bf16 rows x (the embeddings): the fp32 copy x32 (the residual stream; nullable);
 //   from fp32 rows x: the bf16 copy xb.
 hipError_t row_prep_bf16(const void *x, float *x32, float *ss, int n_part, int64_t rows, int d, hipStream_t s);
 hipError_t row_prep_f32(const float *x, void *xb, float *ss, int n_part, int64_t rows, int d, hipStream_t s);

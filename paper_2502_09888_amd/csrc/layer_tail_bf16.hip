@@ -26,6 +26,8 @@
 // what the launch between two attentions starts and ends with goes away; y itself is left out where nobody reads it.  Encode of
 // 32 users x 1024, four layers: 847 -> 808 us with the projection of the first layer's rows by gemm_resident_bf16.hip, packed forward
 // 1010 -> 927; 0.9 PFLOP/s over the launch.
+// X16: the residual rows are the bf16 rows that a call was given, so that no fp32 copy of them is made (that launch 18.7 us at 32768 rows, the
+// sums alone 11; encode 823 -> 811, one layer of 32896 candidates and more 1 %).
 // Products, row sums and their order are those of the separate launches (gemm_bf16.hip, gemm_small_bf16.hip): same
 // bits.
 #include "gemm_common.h"
@@ -81,9 +83,10 @@ struct Next { int base, a, b; };
 // its own, which return in order.  Us, four layers scored, 8192 rows: 484 with a 268 MB cache between (539 without), 379
 // with a short one (389); by the computing waves at their start 493 and 393.  With it eight fragments in flight do what
 // 16 did, and the registers hold a third wave per SIMD.  64-row tiles do not gain (and have no registers for it).
-template <int D, int RB, int NW, int R, int PRE, bool QKV>
+template <int D, int RB, int NW, int R, int PRE, bool QKV, bool X16>
 __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(const TailArgs p)
 {
+    static_assert(!X16 || RB * (D / NW / 32) <= 4, "the residual's blocks are all requested ahead");
     static_assert(!QKV || (D / NW == 64 && RB % 2 == 0 && !PRE), "");
     constexpr int ROWS = 32 * RB, CW = D / NW, NJ = CW / 32;   // rows of the tile; columns and column blocks of a wave
     constexpr int kChunk = 32 * NW;                            // hidden columns of a chunk
@@ -186,6 +189,28 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
 #pragma unroll
         for (int b = 0; b < kAhead; ++b) load_block(side[b], from + at.at[b / NJ] + 32 * (b % NJ));
     };
+    auto request_rows16 = [&]() __attribute__((always_inline)) {  // as they are: two values in a register
+        const bool second = m0 >= p.x16_split;
+        const __bf16 *from = second ? (const __bf16 *)p.x16_b - (int64_t)p.x16_split * D : (const __bf16 *)p.x16;
+        const Rows at = rows();
+#pragma unroll
+        for (int b = 0; b < kAhead; ++b)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float2 q = *(const float2 *)(from + at.at[b / NJ] + 32 * (b % NJ) + 8 * g);
+                side[b][2 * g] = q.x, side[b][2 * g + 1] = q.y;
+            }
+    };
+    auto add_rows16 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                const uint32_t two = __float_as_uint(side[b % kAhead][r / 2]);
+                acc[b / NJ][b % NJ][r] += __uint_as_float(two << 16);
+                acc[b / NJ][b % NJ][r + 1] += __uint_as_float(two & 0xffff0000u);
+            }
+    };
     auto add_rows = [&](const float *from) __attribute__((always_inline)) {  // acc += rows, block by block
         const Rows at = rows();
         static_for<NB>([&](auto b_tag) __attribute__((always_inline)) {
@@ -259,9 +284,11 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
     };
 #pragma unroll 1
     for (int s0 = 0; s0 + 8 < S; s0 += 8) o_steps(s0, std::false_type{});
-    request_rows(p.x);
+    if constexpr (X16) request_rows16();
+    else request_rows(p.x);
     o_steps(S - 8, std::true_type{});
-    add_rows(p.x);  // h
+    if constexpr (X16) add_rows16();  // h
+    else add_rows(p.x);
     keep_rows();
     // sums of squares of the rows' 64-column slices, as the separate launches form them
     auto slice_sums = [&](auto &&put) __attribute__((always_inline)) {
@@ -495,11 +522,13 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
     }
 }
 
-template <int D, int RB, int NW, int R, int PRE, bool QKV = false>
+template <int D, int RB, int NW, int R, int PRE, bool QKV = false, bool X16 = false>
 hipError_t launch_tail(const TailArgs &a, hipStream_t s)
 {
+    if constexpr (!X16 && D / NW == 64)
+        if (a.x16) return launch_tail<D, RB, NW, R, PRE, QKV, true>(a, s);
     constexpr size_t lds = tail_lds_bytes<D, RB, NW>() + PRE * 256 + (QKV ? tail_scale_bytes<D, RB>() : 0);
-    constexpr auto kernel = layer_tail_kernel<D, RB, NW, R, PRE, QKV>;
+    constexpr auto kernel = layer_tail_kernel<D, RB, NW, R, PRE, QKV, X16>;
     const hipError_t e = raise_lds_limit<kernel>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)((a.M + 32 * RB - 1) / (32 * RB))), dim3((NW + PRE) * 64), lds, s, a);
@@ -534,9 +563,12 @@ bool layer_tail_projects(int M, int D, int F, int n_cached)
     return F % 256 == 0 && M > 8192 && n_cached > 0 && (n_cached < M || tiles > 352 || (tiles > 240 && tiles <= 256));
 }
 
+bool layer_tail_reads_bf16(int M, int D, int F) { return layer_tail_takes(M, D, F) && (D == 256 || F % 256 == 0); }
+
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)
 {
     if (a.M < 1 || a.F < 128 || a.F % 128 != 0) return hipErrorInvalidValue;
+    if (a.x16 && (!layer_tail_reads_bf16(a.M, a.D, a.F) || a.x16_split % 64 != 0)) return hipErrorInvalidValue;
     if (a.wq) {
         if (!layer_tail_takes(a.M, a.D, a.F) || (a.D == 512 && (a.F % 256 != 0 || a.M <= 8192)) || a.next.n_cached % 64 != 0 || a.y_first % 64 != 0) return hipErrorInvalidValue;
         return a.D == 512 ? launch_tail<512, 2, 8, 8, 0, true>(a, s) : launch_tail<256, 2, 4, 8, 0, true>(a, s);

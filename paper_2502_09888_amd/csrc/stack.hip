@@ -118,11 +118,23 @@ struct NextQkv {
     int64_t y_first;
 };
 
+// The rows that a call is given (bf16; from row `split` on: b), where the first layer's tail takes them for the residual
+// (layer_tail_reads_bf16) and no fp32 copy of them is made.
+struct GivenRows {
+    const void *a, *b;
+    int64_t split;
+};
+bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 // attention output rows -> y (f_FFN and the residual stream), `rows` rows from row r0 of the workspace's arrays.
 // x, y: fp32 rows of the residual stream; norm_out: also the bf16 copy and sums of squares of y; next (nullable): the next
-// layer's projection instead of those.
+// layer's projection instead of those; given (nullable): the residual rows instead of x, apart from y.
 int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x, float *y, bool norm_out,
-               int64_t r0, int64_t rows, const Workspace &ws, hipStream_t s, const NextQkv *next = nullptr)
+               int64_t r0, int64_t rows, const Workspace &ws, hipStream_t s, const NextQkv *next = nullptr,
+               const GivenRows *given = nullptr)
 {
     const int d = cfg->d_model, F = cfg->d_ffn, M = (int)rows;
     const uint8_t *o = ws.o + (size_t)r0 * d * 2;
@@ -132,10 +144,11 @@ int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x,
     const RowNormOut nout{ss, xb, d}, no_out{nullptr, nullptr, 0};
     // (one launch reads and writes rows as its workgroups come to them: y is x itself or lies apart from it)
     const size_t bytes = (size_t)M * d * 4;
-    const bool in_place = x == y, apart = (uintptr_t)x + bytes <= (uintptr_t)y || (uintptr_t)y + bytes <= (uintptr_t)x;
+    const bool in_place = x == y || given, apart = (uintptr_t)x + bytes <= (uintptr_t)y || (uintptr_t)y + bytes <= (uintptr_t)x;
     if ((in_place || apart) && layer_tail_takes(M, d, F)) {
         TailArgs a{o, x, pw.wo, (int)(pw.w1 - pw.wo), (int)(pw.w2 - pw.wo), (int)(pw.w2 - pw.wo) + d * F * 2, y,
-                   norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F, nin.inv_d, nin.eps, 0, 0, QkvOut{}};
+                   norm_out ? xb : nullptr, norm_out ? ss : nullptr, M, d, F, nin.inv_d, nin.eps, 0, 0, QkvOut{}, nullptr, nullptr, 0};
+        if (given) a.x16 = given->a, a.x16_b = given->b, a.x16_split = (int)given->split;
         if (next) {
             a.yb = nullptr, a.ss = nullptr;
             a.wq = (int)(next->wqkv - pw.wo), a.w_bytes = a.wq + 3 * d * d * 2;
@@ -143,7 +156,7 @@ int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x,
         }
         return rt(layer_tail_bf16(a, s));
     }
-    if (next) return CLIMBER_ERR_RUNTIME;  // (asked for by layer_tail_projects, and rows in place)
+    if (next || given) return CLIMBER_ERR_RUNTIME;  // (asked for where layer_tail_takes)
     float *h = ws.h32 + (size_t)r0 * d;
     uint8_t *u = ws.u + (size_t)r0 * F * 2;
     TRY(rt(gemm_bf16(EPI_RESID_F32, o, d, pw.wo, M, d, d, h, d, x, d, no_in, nout, 0, s)));
@@ -156,7 +169,7 @@ int project_qkv(const climber_config *cfg, const PackedLayer &pw, const void *in
                 const QkvOut &out, hipStream_t s)
 {
     const int d = cfg->d_model, M = (int)rows;
-    if (gemm_resident_takes(M, d, out.n_cached > 0)) return rt(gemm_resident_bf16(in, pw.wqkv, M, d, nin, out, s));
+    if (gemm_resident_takes(M, d, out.n_cached > 0)) return rt(gemm_resident_bf16(kRowsSummed, in, pw.wqkv, M, d, nin, out, s));
     const RowNormOut no_out{nullptr, nullptr, 0};
     if (!out.n_cached)
         return rt(gemm_bf16(EPI_STORE_BF16, in, d, pw.wqkv, M, 3 * d, d, out.rows, out.ld_rows, nullptr, 0, nin, no_out, 0, s));
@@ -168,12 +181,13 @@ int project_qkv(const climber_config *cfg, const PackedLayer &pw, const void *in
 // one layer on `rows` rows.  x_in: fp32 rows (the residual stream); xb_in / ws.ss: their bf16 copy and
 // row sums of squares (from the previous layer's last projection or from a row_prep kernel).
 // norm_out: also emit the bf16 copy and sums of squares of x_out (the next layer needs them).
-// projected: the layer's QKV projection is made already; next (nullable): make the next layer's.
+// projected: the layer's QKV projection is made already; next (nullable): make the next layer's; given (nullable): the
+// residual rows instead of x_in.
 int run_layer(const climber_config *cfg, const PackedLayer &pw, const float *tau_layer, int32_t layer,
               int32_t mode, climber_kv_cache *cache, const float *x_in, const void *xb_in, float *x_out,
               bool norm_out, const int32_t *scen, const int32_t *beh, const int32_t *cand_off,
               int32_t m_total, int32_t m_max, int64_t rows, const Workspace &ws, hipStream_t s, bool projected = false,
-              const NextQkv *next = nullptr)
+              const NextQkv *next = nullptr, const GivenRows *given = nullptr)
 {
     const int d = cfg->d_model;
     const RowNormIn nin{ws.ss, d / 64, 1.f / (float)d, cfg->rms_eps};
@@ -198,7 +212,7 @@ int run_layer(const climber_config *cfg, const PackedLayer &pw, const float *tau
                                   scen, beh, ws.o, d, s));
         }
     }
-    return layer_tail(cfg, pw, x_in, x_out, norm_out, 0, rows, ws, s, next);
+    return layer_tail(cfg, pw, x_in, x_out, norm_out, 0, rows, ws, s, next, given);
 }
 
 int check_layer_weights(const climber_layer_weights *w)
@@ -265,7 +279,11 @@ int score_layers(const climber_config *cfg, const climber_weights *weights, cons
 {
     if (m_total == 0) return CLIMBER_OK;
     TRY(stage_weights(cfg, weights, ws, s));
-    TRY(rt(row_prep_bf16(x_cand, ws.x32, ws.ss, cfg->d_model / 64, m_total, cfg->d_model, s)));
+    // (of one layer, the tail that reads the rows writes the outputs: the two lie apart)
+    const bool as_given = layer_tail_reads_bf16(m_total, cfg->d_model, cfg->d_ffn) &&
+                          (cfg->n_layers > 1 || !overlap(x_cand, (size_t)m_total * cfg->d_model * 2, y_cand, (size_t)m_total * cfg->d_model * 4));
+    const GivenRows given{x_cand, nullptr, (int64_t)(m_total + 63) / 64 * 64};
+    TRY(rt(row_prep_bf16(x_cand, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, m_total, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
     const bool chain = layer_tail_projects(m_total, cfg->d_model, cfg->d_ffn, 0);
     for (int l = 0; l < cfg->n_layers; ++l) {
@@ -279,7 +297,7 @@ int score_layers(const climber_config *cfg, const climber_weights *weights, cons
         TRY(run_layer(cfg, packed_layer(cfg, ws, l), tau + l * tl, l, CLIMBER_MODE_CANDIDATE,
                       const_cast<climber_kv_cache *>(cache), ws.x32, l == 0 ? x_cand : (const void *)ws.xb,
                       last ? y_cand : ws.x32, !last, cand_scen, cand_beh, cand_off, m_total, m_max,
-                      m_total, ws, s, chain && l > 0, next.wqkv ? &next : nullptr));
+                      m_total, ws, s, chain && l > 0, next.wqkv ? &next : nullptr, as_given && l == 0 ? &given : nullptr));
     }
     return CLIMBER_OK;
 }
@@ -395,7 +413,9 @@ int climber_history_encode(const climber_config *cfg, const climber_weights *wei
     if (rows == 0) return CLIMBER_OK;
     hipStream_t s = (hipStream_t)stream;
     TRY(stage_weights(cfg, weights, ws, s));
-    TRY(rt(row_prep_bf16(x_hist, ws.x32, ws.ss, cfg->d_model / 64, rows, cfg->d_model, s)));
+    const bool as_given = layer_tail_reads_bf16((int)rows, cfg->d_model, cfg->d_ffn);
+    const GivenRows given{x_hist, nullptr, rows};
+    TRY(rt(row_prep_bf16(x_hist, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, rows, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
     const bool chain = layer_tail_projects((int)rows, cfg->d_model, cfg->d_ffn, cfg->flags & CLIMBER_QKV_VIA_ROWS ? 0 : (int)rows);
     for (int l = 0; l < cfg->n_layers; ++l) {
@@ -412,7 +432,7 @@ int climber_history_encode(const climber_config *cfg, const climber_weights *wei
         }
         TRY(run_layer(cfg, packed_layer(cfg, ws, l), tau + l * tl, l, CLIMBER_MODE_HISTORY, cache,
                       ws.x32, l == 0 ? x_hist : (const void *)ws.xb, last ? nullptr : ws.x32, !last, scen,
-                      beh, nullptr, 0, 0, rows, ws, s, chain && l > 0, next.wqkv ? &next : nullptr));
+                      beh, nullptr, 0, 0, rows, ws, s, chain && l > 0, next.wqkv ? &next : nullptr, as_given && l == 0 ? &given : nullptr));
     }
     return CLIMBER_OK;
 }
@@ -475,8 +495,14 @@ int climber_bgf_score(const climber_config *cfg, const climber_bgf_weights *w, c
     const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps};
     const RowNormOut no_out{nullptr, nullptr, 0};
     // G = ATL(E) on the m * n_blocks rows: the layer of the stack with the fusion attention in the middle
-    TRY(rt(row_prep_f32(e, ws.xb, ws.ss, np, R, d, s)));
-    TRY(rt(gemm_bf16(EPI_STORE_BF16, ws.xb, d, pw.wqkv, (int)R, 3 * d, d, ws.qkv, 3 * d, nullptr, 0, nin, no_out, 0, s)));
+    QkvOut to{};
+    to.rows = ws.qkv, to.ld_rows = 3 * d;
+    if (gemm_resident_sums((int)R, d)) {
+        TRY(rt(gemm_resident_bf16(kRowsF32, e, pw.wqkv, (int)R, d, nin, to, s)));
+    } else {
+        TRY(rt(row_prep_f32(e, ws.xb, ws.ss, np, R, d, s)));
+        TRY(project_qkv(&one, pw, ws.xb, R, nin, to, s));
+    }
     TRY(rt(launch_bgf_attention(ws.qkv, ws.o, cand_scen, w->tau_scen, cfg->n_scen, m_total, nb, cfg->n_heads,
                                 cfg->qk_scale, s)));
     TRY(layer_tail(&one, pw, e, ws.x32, true, 0, R, ws, s));
@@ -512,13 +538,16 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
     const int d = cfg->d_model, np = d / 64;
     TRY(stage_weights(cfg, weights, ws, s));
     // rows [0, T): the padded history rows of the batch; rows [T, R): the candidates
-    TRY(rt(row_prep_bf16(x_hist, ws.x32, ws.ss, np, T, d, s)));
-    TRY(rt(row_prep_bf16(x_cand, ws.x32 + (size_t)T * d, ws.ss + (size_t)T * np, np, m_total, d, s)));
     // The first layer's projections read the inputs where they are; one projection over both kinds of rows needs them behind
     // one another.  (Copying them in, and the candidates' rows out of the residual stream at the end: three launches of 6 us for 24000
     // history and 4900 candidate rows; the call 998 us with them, 984 without.)
     QkvToCache qc;
     const bool direct = T > 0 && cache_direct_target(cfg, scratch_cache, 0, &qc);
+    // (the first tail takes all rows, into the workspace)
+    const bool as_given = direct && (cfg->n_layers > 1 || y_hist) && layer_tail_reads_bf16((int)R, d, cfg->d_ffn);
+    const GivenRows given{x_hist, x_cand, T};
+    TRY(rt(row_prep_bf16(x_hist, as_given ? nullptr : ws.x32, ws.ss, np, T, d, s)));
+    TRY(rt(row_prep_bf16(x_cand, as_given ? nullptr : ws.x32 + (size_t)T * d, ws.ss + (size_t)T * np, np, m_total, d, s)));
     if (T && !direct) TRY(rt(hipMemcpyAsync(ws.xb, x_hist, (size_t)T * d * 2, hipMemcpyDeviceToDevice, s)));
     if (m_total && !direct)
         TRY(rt(hipMemcpyAsync(ws.xb + (size_t)T * d * 2, x_cand, (size_t)m_total * d * 2, hipMemcpyDeviceToDevice, s)));
@@ -575,7 +604,8 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
             next.out.qc = qc, next.out.qc.which0 = ends, next.out.n_cached = (int)T, next.y_first = ends ? T : 0;
             next.out.q = ws.qkv, next.out.ld_q = d, next.out.rows = ws.qkv + crow, next.out.ld_rows = 3 * d;
         }
-        TRY(layer_tail(cfg, pw, x, hist_out ? x : y_cand, !last, r0, nr, ws, s, next.wqkv ? &next : nullptr));
+        TRY(layer_tail(cfg, pw, x, hist_out ? x : y_cand, !last, r0, nr, ws, s, next.wqkv ? &next : nullptr,
+                       as_given && l == 0 ? &given : nullptr));
     }
     if (y_hist && T) TRY(rt(hipMemcpyAsync(y_hist, ws.x32, (size_t)T * d * 4, hipMemcpyDeviceToDevice, s)));
     if (y_hist && m_total)

@@ -292,6 +292,7 @@ def test_packed_forward_candidates_with_and_without_history_outputs(layers, flag
 
 @pytest.mark.parametrize("d, F, layers, lens, cands, flags", [
     (512, 256, 3, (384, 77, 300, 129, 512, 64, 1) * 6, 8200, 0),     # histories and candidates, each more than 8192 rows
+    (512, 256, 1, (384, 130) * 17, 4133, 0), (256, 128, 1, (384,) * 11, 4097, 0),  # one layer: the inputs are its residual
     (512, 768, 2, (448,) * 19, 127, 0),                              # a uniform batch, few candidates
     (512, 384, 3, (500, 33) * 15, 33, 0),                            # no kernel with a projection at this d_ffn: launches of their own
     (256, 128, 3, (200, 31, 0, 96, 130) * 9, 4161, 0), (256, 384, 2, (320,) * 14, 1, 1), (256, 256, 3, (320, 65) * 12, 31, 4)])
@@ -346,3 +347,32 @@ def test_projection_behind_the_tail_gives_the_bits_of_separate_launches(d, F, la
         kv1, ys1, yh1 = run([i])
         assert torch.equal(kv1, kv[:, t0[i]:t0[i + 1]]) and torch.equal(ys1[0], ys[0][c0[i]:c0[i + 1]])
         assert torch.equal(yh1[:lens[i]], yh[t0[i]:t0[i] + lens[i]])
+
+
+@pytest.mark.parametrize("d, m", [(512, 4225), (256, 4225), (512, 200)])
+def test_one_layer_scores_written_over_its_inputs(d, m):
+    # outputs that begin inside the candidates' rows, before them, and apart from them: the same bits
+    import torch
+    import paper_2502_09888_amd as P
+    say(f"[case] outputs over inputs d={d} m={m}")
+    dev, bf = "cuda:0", torch.bfloat16
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d + m)
+    cfg = P.Config(n_layers=1, d_model=d, n_heads=d // 64, d_head=64, d_ffn=256, dtype=P.BF16, qk_scale=0.02)
+    w = [{k: (torch.randn(*s, generator=gen, device=dev) * 0.05).to(bf) for k, s in
+          (("g1", (d,)), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", (d,)), ("w1", (d, 256)), ("w2", (256, d)))}]
+    buf = torch.empty(P.climber_kv_cache_bytes(cfg, [64]), dtype=torch.uint8, device=dev)
+    cache = P.climber_kv_cache_create(cfg, [0], [64], buf)
+    ids, off = torch.zeros(m, dtype=torch.int32, device=dev), torch.tensor([0, m], dtype=torch.int32, device=dev)
+    ws = torch.empty(P.climber_workspace_bytes(cfg, m), dtype=torch.uint8, device=dev)
+    x = torch.randn(m, d, generator=gen, device=dev).to(bf)
+    outs = []
+    for at_y in (0, m // 2 * d, m * d, 3 * m * d):  # in bf16 values; the candidates' rows begin at m * d
+        mem = torch.zeros(5 * m * d, dtype=bf, device=dev)
+        mem[m * d:2 * m * d] = x.flatten()
+        at_y = at_y // 64 * 64
+        y = mem[at_y:at_y + 2 * m * d].view(torch.float32).view(m, d)
+        P.climber_sumi_score(cfg, w, torch.ones(1, 1, 1, device=dev), cache, mem[m * d:2 * m * d], off, m, m, ids, ids, y, ws)
+        outs.append(y.clone())
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, outs[-1]) for o in outs) and outs[-1].abs().max() > 0
