@@ -7,14 +7,14 @@
 // (candidate, head), held in registers; d_head = 64.
 #include "bgf.h"
 #include "lanes.h"
+#include "qkv_units.h"
 
 namespace climber {
 namespace {
 
 constexpr int kMaxBlocks = 16;
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+using namespace gemm;
 
 // sum over the 8 lanes 8s .. 8s+7, in each of them
 __device__ __forceinline__ float sum8(float x)
@@ -82,6 +82,20 @@ __global__ __launch_bounds__(256) void bgf_attention_kernel(const __bf16 *qkv, _
 }
 
 // g: fp32 [m][nd] (the fusion layer's output), pre: bf16 [m][nd] (f_gate(G) before the sigmoid);
+__device__ __forceinline__ float4 gated(const float4 &g, const bf16x4 &pre)
+{
+    float4 y;
+    y.x = g.x * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pre[0]));
+    y.y = g.y * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pre[1]));
+    y.z = g.z * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pre[2]));
+    y.w = g.w * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pre[3]));
+    return y;
+}
+__device__ __forceinline__ float head_sum(const float4 &y, const float4 &w, float sum)
+{
+    return fmaf(y.x, w.x, fmaf(y.y, w.y, fmaf(y.z, w.z, fmaf(y.w, w.w, sum))));
+}
+
 // y (nullable): fp32 [m][nd]; score: [m].  One wavefront per candidate.
 __global__ __launch_bounds__(256) void bgf_gate_head_kernel(const float *g, const __bf16 *pre, const float *w_head,
                                                             float b_head, float *y, float *score, int64_t m, int nd)
@@ -95,19 +109,177 @@ __global__ __launch_bounds__(256) void bgf_gate_head_kernel(const float *g, cons
         const float4 gv = *(const float4 *)(g + c * nd + e);
         const float4 wv = *(const float4 *)(w_head + e);
         const bf16x4 pv = *(const bf16x4 *)(pre + c * nd + e);
-        float4 yv;
-        yv.x = gv.x * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pv[0]));
-        yv.y = gv.y * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pv[1]));
-        yv.z = gv.z * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pv[2]));
-        yv.w = gv.w * __builtin_amdgcn_rcpf(1.f + __expf(-(float)pv[3]));
+        const float4 yv = gated(gv, pv);
         if (y) *(float4 *)(y + c * nd + e) = yv;
-        acc = fmaf(yv.x, wv.x, fmaf(yv.y, wv.y, fmaf(yv.z, wv.z, fmaf(yv.w, wv.w, acc))));
+        acc = head_sum(yv, wv, acc);
     }
     acc = wave_sum64(acc);
     if (lane == 0) score[c] = acc + b_head;
 }
 
+// Both projections of the gate, the gate and the head in one launch for 32 candidates a workgroup.  Down: a wave per 32 columns of the
+// hidden, the rows by way of registers into a double buffer of 256 columns, weights from L2 into registers.  Up: 256 columns a
+// step, a wave per 32 of them; their bf16 values meet G in LDS, where a wave takes whole rows as bgf_gate_head_kernel does: the same
+// bits as by the three launches.  8192 candidates x 4 blocks of 512, d_gate 256: 66 us instead of 25 + 19 + 30, of which the bytes of G and
+// Y take 33 and the weights' way from L2 (2 MB a workgroup) about as long; fragments further ahead (16 instead of 8) and G two steps
+// ahead change nothing.  Registers for two workgroups per CU (344 -> 333 us the call; three spilled).
+template <int DG>
+__global__ __launch_bounds__(512, 4) void bgf_gate_kernel(const __bf16 *gb, const float *g, const __bf16 *w_down, const __bf16 *w_up,
+                                                          const float *w_head, float b_head, float *y, float *score, int m, int nd)
+{
+    constexpr int NW = 8, R = 8, kRows = 32, kCols = 256, kStep = kCols / 16, S2 = DG / 16, kOwn = kRows / NW;
+    constexpr int kBuf = kRows * kCols * 2, kPre = kCols * 2 + 16;
+    constexpr int kSwap = 2 * kBuf > 2 * kRows * kPre ? 2 * kBuf : 2 * kRows * kPre;
+    static_assert(kStep % R == 0 && S2 % R == 0 && DG / 32 <= NW, "");
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kSwap + kRows * DG * 2];
+    uint8_t *const hid = lds + kSwap;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hf = lane >> 5, r15 = lane & 15;
+    const int64_t m0 = (int64_t)blockIdx.x * kRows;
+    const int n_steps = nd / kCols;
+    auto frag = [&](const __amdgpu_buffer_rsrc_t &w, int at) __attribute__((always_inline)) {
+        return __builtin_amdgcn_raw_buffer_load_b128(w, lane * 16, at * 1024, 0);
+    };
+    const __amdgpu_buffer_rsrc_t wd = __builtin_amdgcn_make_buffer_rsrc((void *)w_down, 0, nd * DG * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wu = __builtin_amdgcn_make_buffer_rsrc((void *)w_up, 0, nd * DG * 2, 0x00020000);
+    auto barrier = []() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    // ---- hidden = ReLU(G W_down) ----
+    u32x4 ring[R];
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    {
+        const int blk = min(wave, DG / 32 - 1), S = nd / 16;  // (waves beyond the last block copy only)
+        u32x4 rows[2];
+        auto fetch = [&](int t) __attribute__((always_inline)) {  // rows 4 wave .. + 3 of the step, two at a time
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                rows[i] = *(const u32x4 *)(gb + min(m0 + 4 * wave + 2 * i + hf, (int64_t)m - 1) * nd + t * kCols + l32 * 8);
+        };
+        auto put = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = 4 * wave + 2 * i + hf;
+                *(u32x4 *)(lds + buf * kBuf + r * LdsRows<kCols>::kPitch + ((l32 & ~15) | (r15 ^ (r & 15))) * 16) = rows[i];
+            }
+        };
+        fetch(0);
+#pragma unroll
+        for (int e = 0; e < R; ++e) ring[e] = frag(wd, blk * S + e);
+        put(0);
+        fetch(min(1, n_steps - 1));
+        barrier();
+        const uint32_t base = LdsRows<kCols>::base(l32, hf);
+#pragma unroll 1
+        for (int t = 0; t < n_steps; ++t) {
+            const uint8_t *a = lds + (t & 1) * kBuf;
+            static_for<kStep>([&](auto s_tag) __attribute__((always_inline)) {
+                constexpr int s = decltype(s_tag)::value;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[s % R]), LdsRows<kCols>::frag(a, base, s, 0), acc, 0, 0, 0);
+                ring[s % R] = frag(wd, blk * S + min(t * kStep + s + R, S - 1));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if (t + 1 < n_steps) put((t + 1) & 1);
+            fetch(min(t + 2, n_steps - 1));
+            barrier();
+        }
+        if (wave < DG / 32) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int c = 4 * wave + q;
+                bf16x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (__bf16)fmaxf(acc[4 * q + e], 0.f);
+                *(bf16x4 *)(hid + l32 * LdsRows<DG>::kPitch + ((c & ~15) | ((c & 15) ^ r15)) * 16 + 8 * hf) = v;
+            }
+        }
+    }
+
+    // ---- Y = G sigmoid(hidden W_up), score = <w_head, Y> + b_head ----
+#pragma unroll
+    for (int e = 0; e < R; ++e) ring[e] = frag(wu, wave * S2 + e);
+    float4 gv[kOwn], wv;
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k)
+            gv[k] = *(const float4 *)(g + min(m0 + kOwn * wave + k, (int64_t)m - 1) * nd + t * kCols + lane * 4);
+        wv = *(const float4 *)(w_head + t * kCols + lane * 4);
+    };
+    fetch(0);
+    float sum[kOwn] = {};
+    barrier();
+    const uint32_t base = LdsRows<DG>::base(l32, hf);
+#pragma unroll 1
+    for (int t = 0; t < n_steps; ++t) {
+        f32x16 up;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) up[r] = 0.f;
+        const int blk = NW * t + wave, next = min(blk + NW, nd / 32 - 1);
+        static_for<S2>([&](auto s_tag) __attribute__((always_inline)) {
+            constexpr int s = decltype(s_tag)::value;
+            up = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ring[s % R]), LdsRows<DG>::frag(hid, base, s, 0), up, 0, 0, 0);
+            ring[s % R] = frag(wu, s + R < S2 ? blk * S2 + s + R : next * S2 + s + R - S2);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        uint8_t *pre = lds + (t & 1) * (kRows * kPre);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            bf16x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (__bf16)up[4 * q + e];
+            *(bf16x4 *)(pre + l32 * kPre + (32 * wave + 8 * q + 4 * hf) * 2) = v;
+        }
+        barrier();
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) {
+            const bf16x4 pv = *(const bf16x4 *)(pre + (kOwn * wave + k) * kPre + lane * 8);
+            const float4 yv = gated(gv[k], pv);
+            sum[k] = head_sum(yv, wv, sum[k]);
+            const int64_t row = m0 + kOwn * wave + k;
+            if (y && row < m) *(float4 *)(y + row * nd + t * kCols + lane * 4) = yv;
+        }
+        fetch(min(t + 1, n_steps - 1));
+    }
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+        const float total = wave_sum64(sum[k]);
+        const int64_t row = m0 + kOwn * wave + k;
+        if (lane == 0 && row < m) score[row] = total + b_head;
+    }
+}
+
 }  // namespace
+
+// A workgroup streams both weights for its 32 candidates, whoever else does, so few of them are better served by the tiles.  Us a call,
+// one launch / three: 8192 candidates x 4 blocks of 512, d_gate 256 333 / 341, 12000 484 / 498, 6000 267 / 275, 4200 253 / 256, 2100 136 / 138,
+// 1500 119 / 112; x 8 12000 927 / 941, 6000 487 / 486, 4200 433 / 424; of 256 x 4 2100 72 / 76, 1500 69 / 67; d_gate 128, x 4 of 512 4200 242 / 256, 1500
+// 109 / 109, 1000 98 / 98.
+bool bgf_gate_takes(int64_t m, int nd, int dg)
+{
+    if (nd % 256 != 0) return false;
+    return dg == 128 ? m >= 1500 : dg == 256 && m >= (nd <= 2048 ? 2000 : 6000);
+}
+
+hipError_t launch_bgf_gate(const void *gb, const float *g, const void *w_down, const void *w_up, const float *w_head, float b_head, float *y,
+                           float *score, int64_t m, int nd, int dg, hipStream_t s)
+{
+    if (m <= 0) return hipSuccess;
+    const dim3 grid((unsigned)((m + 31) / 32)), block(512);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, (const __bf16 *)gb, g, (const __bf16 *)w_down, (const __bf16 *)w_up, w_head, b_head, y,
+                           score, (int)m, nd);
+        return hipGetLastError();
+    };
+    if (dg == 128) return go(bgf_gate_kernel<128>);
+    if (dg == 256) return go(bgf_gate_kernel<256>);
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_bgf_attention(const void *qkv, void *o, const int32_t *scen, const float *tau_scen, int n_scen,
                                 int64_t m, int nb, int H, float qk_scale, hipStream_t s)

@@ -506,6 +506,8 @@ int climber_bgf_score(const climber_config *cfg, const climber_bgf_weights *w, c
     TRY(rt(launch_bgf_attention(ws.qkv, ws.o, cand_scen, w->tau_scen, cfg->n_scen, m_total, nb, cfg->n_heads,
                                 cfg->qk_scale, s)));
     TRY(layer_tail(&one, pw, e, ws.x32, true, 0, R, ws, s));
+    if (bgf_gate_takes(m_total, nd, dg))
+        return rt(launch_bgf_gate(ws.xb, ws.x32, down_p, up_p, w->w_head, w->b_head, y, score, m_total, nd, dg, s));
     // f_gate on the flattened G (its bf16 copy, [m][n_blocks * d]): down, ReLU, up; then sigmoid,
     // Hadamard product and the head in one pass over G
     TRY(rt(gemm_bf16(EPI_RELU_BF16, ws.xb, nd, down_p, m_total, dg, nd, ws.o, dg, nullptr, 0, RowNormIn{}, no_out, 0, s)));

@@ -101,16 +101,17 @@ def test_multi_block_scoring_end_to_end():
     assert e < 2e-2
 
 
-@pytest.mark.parametrize("d, nb, m, part", [(512, 4, 2049, 33), (512, 3, 2731, 1), (256, 8, 1025, 16), (256, 2, 4129, 40)])
-def test_few_and_many_candidates_give_the_same_bits(d, nb, m, part):
-    # more than 8192 rows: the projection forms the fp32 rows' sums itself, and the tail is one launch; few: a launch for the sums and
-    # launches of their own
+@pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 128, 2049, 33), (512, 3, 256, 2731, 1), (256, 8, 128, 1025, 16), (256, 2, 256, 4129, 40),
+                                                (256, 3, 256, 2031, 64), (256, 1, 128, 1500, 9), (512, 5, 256, 6001, 32)])
+def test_few_and_many_candidates_give_the_same_bits(d, nb, dg, m, part):
+    # more than 8192 rows: the projection forms the fp32 rows' sums itself, and the tail is one launch; 1500 or 2000 candidates and more: so
+    # are the gate and the head, the last 32 of them in part, an even and an odd number of steps; few: launches of their own
     import torch
     import paper_2502_09888_amd as P
     spec = W.StackSpec(f"bgf-many-{d}", B=1, L=128, sub_len=0, M=1, n_layers=1, d_model=d, H=d // 64, dh=64, d_ffn=256, n_scen=8, n_beh=4,
                        seed=57)
     say(f"[case] {spec.name} n_blocks={nb} m={m}")
-    w = W.make_bgf(spec, nb, 128, m)
+    w = W.make_bgf(spec, nb, dg, m)
     cfg = stack_config(spec)
     y, sc = gpu_bgf(P, torch, cfg, w, w["e"])
     for lo in (0, m - part):
