@@ -173,7 +173,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
     RawTiles raw;
     if constexpr (RAW) raw = raw_tiles(p, (int64_t)t0 + k_lo, h, tid);
     auto issue_tile_at = [&](int t, int stage) __attribute__((always_inline)) {
-        if constexpr (RAW) return raw_issue(raw, t, (lds_u8 *)lds + stage + wave * 1024);
+        if constexpr (RAW) return raw_issue(raw, t, (lds_u8 *)lds + stage + wave * 1024, (lds_u8 *)lds + stage + 8192 + wave * 1024);
         glb_u8 *src = (glb_u8 *)(kv + (size_t)t * kTileBytes + (size_t)tid * 16);
         lds_u8 *dst = (lds_u8 *)lds + stage + wave * 1024;
 #pragma unroll
@@ -187,12 +187,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(const KParams p)
         else return load_k(lds + so + blk * kBlockBytes, lane);
     };
     auto tile_v = [&](int so, int blk) __attribute__((always_inline)) {
-        if constexpr (RAW) return raw_v(raw, lds + so, blk);
+        if constexpr (RAW) return raw_v(raw, lds + so + 8192, blk);
         else return load_v(lds + so + blk * kBlockBytes, lane);
     };
     auto clear_tail = [&](int so, int tile_lo) __attribute__((always_inline)) {
         if constexpr (RAW)
-            if (tile_lo + kTileKeys > k_hi) raw_clear(lds + so, k_hi - tile_lo, tid);
+            if (tile_lo + kTileKeys > k_hi) raw_clear(lds + so + 8192, k_hi - tile_lo, tid);
     };
     QState<QB> st;
     // FAST start: the raw query rows stay in st.qf and the row scale in st.c until the first block's

@@ -23,8 +23,18 @@ namespace {
 
 using namespace attn;
 
-// a ring stage: 64 keys and values as in the cache, their positions, their time stamps
-constexpr int kTileKeys = 64, kTileBytes = 2 * kBlockBytes, kStageBytes = kTileBytes + kTileKeys * 8, kStages = 3, NW = 4;
+constexpr int kTileKeys = 64, kTileBytes = 2 * kBlockBytes, kStages = 3, NW = 4;
+
+// Tiles of 64 keys in LDS: a ring of three stages of keys, values, positions and time stamps, or (SPLIT) two rings: the keys themselves,
+// two stages, as all of a tile have been read when the next one's first block is started; and what is read later, three.  The
+// latter takes 8 KiB less, which makes room for a third workgroup per CU (QB = 1), and a few per cent longer where it does not (QB = 2:
+// 512 candidates of 32 users against 4000 171 us, 162 with one ring).
+template <bool SPLIT>
+struct Ring {
+    static constexpr int kKeyStage = SPLIT ? kTileBytes / 2 : 0;                                  // stages of keys begin at 0
+    static constexpr int kRest = 2 * kKeyStage, kCoords = SPLIT ? kTileBytes / 2 : kTileBytes;  // those of the rest; coordinates in them
+    static constexpr int kStage = kCoords + kTileKeys * 8, kBytes = kRest + kStages * kStage;
+};
 
 // minimum over the 32 lanes of a half-wave, as a scalar (both halves hold the same 32 values)
 template <class F>
@@ -38,9 +48,16 @@ __device__ __forceinline__ int half_wave_reduce(int x, F &&f)
     return f(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16));
 }
 
-// LDS: ring, tables of the head, classes [wave][query block][64], one flag per wave
-template <int QB>
-constexpr int kClassBytes = NW * QB * 64 * 4;
+// LDS: rings, tables of the head, one flag per wave; at the end, over the first two, a wave's corner for 32 rows of outputs, and of keys
+// and values on their way to the cache.
+template <bool RAW>
+constexpr int kCorner = RAW ? 12288 : 4096;
+template <int QB, bool RAW>
+__host__ __device__ constexpr int bias_flags_at(int entries)
+{
+    const int used = Ring<QB == 1>::kBytes + entries * 4, corners = NW * kCorner<RAW>;
+    return used > corners ? used : corners;
+}
 
 // IN_LDS: the head's rows of the tables are copied into LDS (else looked up in global memory).
 // RAW (history pass): keys and values are rows, and this launch writes them into the cache as well (RawTiles, attn_common.h);
@@ -53,8 +70,11 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
     static_assert(!RAW || (!SUMI && QB == 1), "rows: the history pass");
     constexpr int NT = NW * 64, WQ = 32 * QB, TQ = NW * WQ, NPRE = kTileBytes / 16 / NT;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    int *flag_lds = (int *)(lds + kStages * kStageBytes), *class_lds = flag_lds + NW;
-    float *bias_lds = (float *)(class_lds + kClassBytes<QB> / 4);  // the head's table rows: [n_tau][n_pos], [n_tau][n_time]
+    constexpr bool SPLIT = QB == 1;
+    using LdsRing = Ring<SPLIT>;
+    float *bias_lds = (float *)(lds + LdsRing::kBytes);  // the head's table rows: [n_tau][n_pos], [n_tau][n_time]
+    // (behind everything: a wave's corner is in use while others may still read the flags)
+    int *flag_lds = (int *)(lds + bias_flags_at<QB, RAW>(IN_LDS ? p.n_scen * p.n_beh * (p.bias.n_pos + p.bias.n_time) : 0));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
@@ -117,33 +137,37 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
                         (size_t)(k_lo / kBlockKeys) * kBlockBytes;
     RawTiles raw;
     if constexpr (RAW) raw = raw_tiles(p, (int64_t)t0 + k_lo, h, tid);
-    auto issue_tile = [&](int t, int stage) __attribute__((always_inline)) {
+    // tile t: its keys to stage t % 2 of theirs (SPLIT; `keys`: byte offset), the rest to the stage of the ring at byte offset `stage`
+    auto issue_tile = [&](int t, int keys, int stage) __attribute__((always_inline)) {
+        lds_u8 *to = (lds_u8 *)lds + LdsRing::kRest + stage, *to_k = (lds_u8 *)lds + keys + wave * 1024, *to_v = to + wave * 1024;
         if constexpr (RAW) {
-            raw_issue(raw, t, (lds_u8 *)lds + stage + wave * 1024);
-        } else {
+            raw_issue(raw, t, to_k, to_v);
+        } else {  // a block of the cache is 4 KiB of keys and 4 KiB of values
             glb_u8 *src = (glb_u8 *)(kv + (size_t)t * kTileBytes + (size_t)tid * 16);
-            lds_u8 *dst = (lds_u8 *)lds + stage + wave * 1024;
-#pragma unroll
-            for (int i = 0; i < NPRE; ++i) __builtin_amdgcn_global_load_lds(src + i * NT * 16, dst + i * NT * 16, 16, 0, 0);
+            static_assert(NPRE == 4 && NT * 16 == kBlockBytes / 2, "");
+            __builtin_amdgcn_global_load_lds(src, SPLIT ? to_k : to_v, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(src + 4096, SPLIT ? to_v : to_v + 4096, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(src + 8192, SPLIT ? to_k + 4096 : to_v + 8192, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(src + 12288, SPLIT ? to_v + 4096 : to_v + 12288, 16, 0, 0);
         }
         if (wave < 2)  // wave 0: positions, wave 1: time stamps of the tile's keys, 4 bytes per lane
             __builtin_amdgcn_global_load_lds((glb_u8 *)((wave ? p.bias.key_ts : p.bias.key_pos) + t0 + k_lo + t * kTileKeys + lane),
-                                             (lds_u8 *)lds + stage + kTileBytes + wave * (kTileKeys * 4), 4, 0, 0);
+                                             to + LdsRing::kCoords + wave * (kTileKeys * 4), 4, 0, 0);
     };
-    auto tile_k = [&](const uint8_t *tile, int blk) __attribute__((always_inline)) {
-        if constexpr (RAW) return raw_k(raw, tile, blk);
-        else return load_k(tile + blk * kBlockBytes, lane);
+    auto tile_k = [&](int keys, int stage, int blk) __attribute__((always_inline)) {
+        if constexpr (RAW) return raw_k(raw, lds + keys, blk);
+        else return load_k(SPLIT ? lds + keys + blk * (kBlockBytes / 2) : lds + stage + blk * kBlockBytes, lane);
     };
-    auto tile_v = [&](const uint8_t *tile, int blk) __attribute__((always_inline)) {
-        if constexpr (RAW) return raw_v(raw, tile, blk);
-        else return load_v(tile + blk * kBlockBytes, lane);
+    auto tile_v = [&](const uint8_t *stage, int blk) __attribute__((always_inline)) {
+        if constexpr (RAW) return raw_v(raw, stage, blk);
+        else return load_v(SPLIT ? stage + blk * (kBlockBytes / 2) - kBlockBytes / 2 : stage + blk * kBlockBytes, lane);
     };
-    auto clear_tail = [&](uint8_t *tile, int t) __attribute__((always_inline)) {
+    auto clear_tail = [&](uint8_t *stage, int t) __attribute__((always_inline)) {
         if constexpr (RAW)
-            if (k_lo + (t + 1) * kTileKeys > k_hi) raw_clear(tile, k_hi - k_lo - t * kTileKeys, tid);
+            if (k_lo + (t + 1) * kTileKeys > k_hi) raw_clear(stage, k_hi - k_lo - t * kTileKeys, tid);
     };
     auto wait_copies = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-    if (n_tiles > 0) issue_tile(0, 0);
+    if (n_tiles > 0) issue_tile(0, 0, 0);
 
     // the lane's queries: rows, scales, bias coordinates
     QState<QB> st;
@@ -209,7 +233,7 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
 #pragma unroll
             for (int r = 0; r < 16; ++r) st.O[db][qb][r] = 0.f;
     }
-    if (n_tiles > 1) issue_tile(1, kStageBytes);
+    if (n_tiles > 1) issue_tile(1, LdsRing::kKeyStage, LdsRing::kStage);
 
     // Classes of 64 blocks: do a wave's 32 queries of a query block share one position and one time bucket with all
     // keys of the block, and which.  Distances are monotonic in both ends, so the buckets of the extreme pairs decide.
@@ -226,7 +250,13 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
         qt_min[qb] = half_wave_reduce((int)b_ts[qb], [](int x, int y) { return (int)min((uint32_t)x, (uint32_t)y); });
         qt_max[qb] = half_wave_reduce((int)b_ts[qb], [](int x, int y) { return (int)max((uint32_t)x, (uint32_t)y); });
     }
-    int *my_class = class_lds + wave * QB * 64;
+    // The classes of the wave's blocks, a lane per block, and what the last uniform class came to: neighbouring blocks mostly
+    // share it (everything clipped), and then a block costs no trip to LDS.  Scoring 512 of 64 users against 1024 97.9 -> 95.2 us,
+    // 128 of 32 28.1 -> 26.8, causal history pass of 20 x 2000 in subsequences of 512 191 -> 169.
+    int classes[QB] = {}, last_class[QB];
+    float last_add[QB] = {};
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) last_class[qb] = kMixed;
     // position distance clipped to the table; leading zeros of a time distance, from those of the last bucket (the
     // hardware's count of 0 is all ones, which the unsigned clamp takes to 31: bucket 0)
     int half_v = half, z_min_v = max(32 - n_time, 0);
@@ -247,7 +277,7 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
         asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(a), "v"(b));  // |a - b|
         return clip_zeros(d);
     };
-    auto classify = [&](int blk0) __attribute__((always_inline)) {
+    auto classes_from = [&](int blk0) __attribute__((always_inline)) {
         auto dpp = [](int v, auto ctrl) { return __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, 0xf, 0xf, false); };
         auto over8 = [&](int x, auto &&f) {  // over the eight lanes of a block
             x = f(x, dpp(x, std::integral_constant<int, 0xB1>{}));
@@ -289,22 +319,11 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
                     else d_max = max(qt_max[qb] - kt_min, kt_max - qt_min[qb]);
                     const int it = clip_zeros(d_min);
                     const int cls = ip == ip2 && abs(ip) < kClassPos && it == clip_zeros(d_max) ? (ip << 8) + it : kMixed;
-                    if ((lane & 7) == 0) my_class[qb * 64 + 8 * (g0 + k) + (lane >> 3)] = cls;
+                    const int mine = __builtin_amdgcn_ds_bpermute(32 * (lane & 7), cls);  // (the eight lanes of a block hold it)
+                    if (lane >> 3 == g0 + k) classes[qb] = mine;
                 }
             }
         }
-    };
-    // The classes of the wave's blocks, a lane per block, and what the last uniform class came to: neighbouring blocks mostly
-    // share it (everything clipped), and then a block costs no trip to LDS.  Scoring 512 of 64 users against 1024 97.9 -> 95.2 us,
-    // 128 of 32 28.1 -> 26.8, causal history pass of 20 x 2000 in subsequences of 512 191 -> 169.
-    int classes[QB] = {}, last_class[QB];
-    float last_add[QB] = {};
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) last_class[qb] = kMixed;
-    auto classes_from = [&](int blk0) __attribute__((always_inline)) {
-        classify(blk0);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) classes[qb] = my_class[qb * 64 + lane];
     };
     if (n_tiles > 0) classes_from(0);
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -349,7 +368,7 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
             scale = st.c[qb];
             add = last_add[qb];
         } else {
-            lookup_block(qb, S, stage + kTileBytes + (blk & 1) * (kBlockKeys * 4));
+            lookup_block(qb, S, stage + LdsRing::kCoords + (blk & 1) * (kBlockKeys * 4));
             scale = 1.f;
             add = 0.f;
         }
@@ -384,13 +403,13 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
                 st.l[qb] += exp_pack<true>(S[qb], scale, -add, P[qb]);
             }
         };
-        qk_block(st, tile_k(lds, 0), S0);
-        int so_cur = 0, so_nxt = kStageBytes, so_fill = 2 * kStageBytes;
+        qk_block(st, tile_k(0, 0, 0), S0);
+        int ko_cur = 0, so_cur = 0, so_nxt = LdsRing::kStage, so_fill = 2 * LdsRing::kStage;
         for (int t = 0; t + 1 < n_tiles; ++t) {
-            const uint8_t *cur = lds + so_cur, *nxt = lds + so_nxt;
+            const uint8_t *cur = lds + LdsRing::kRest + so_cur;
             if (t > 0 && (t & 31) == 0) classes_from(2 * t);
             {   // block 0 of tile t: its logits are in S0; start block 1's
-                const KFrags k1 = tile_k(cur, 1);
+                const KFrags k1 = tile_k(ko_cur, so_cur, 1);
                 VFrags v0;
                 if (!RAW) v0 = tile_v(cur, 0);
                 __builtin_amdgcn_sched_barrier(0);
@@ -399,11 +418,12 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
                 soft(S0, 2 * t, cur, std::false_type{});
                 pv_block(st, v0, P);
             }
-            wait_copies();  // tile t + 1 has landed; nobody reads tile t - 1 any more
+            wait_copies();  // tile t + 1 has landed; nobody reads tile t - 1 any more, nor the keys of tile t
             __builtin_amdgcn_s_barrier();
-            if (t + 2 < n_tiles) issue_tile(t + 2, so_fill);
+            if (t + 2 < n_tiles) issue_tile(t + 2, ko_cur, so_fill);
+            ko_cur ^= LdsRing::kKeyStage;
             {   // block 1 of tile t; start block 0 of tile t + 1
-                const KFrags k0 = tile_k(nxt, 0);
+                const KFrags k0 = tile_k(ko_cur, so_nxt, 0);
                 VFrags v1;
                 if (!RAW) v1 = tile_v(cur, 1);
                 __builtin_amdgcn_sched_barrier(0);
@@ -417,11 +437,11 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
         }
         {   // last tile: 1..64 keys
             const int blk = 2 * (n_tiles - 1);
-            uint8_t *cur = lds + so_cur;
+            uint8_t *cur = lds + LdsRing::kRest + so_cur;
             clear_tail(cur, n_tiles - 1);
             if (blk > 0 && (blk & 63) == 0) classes_from(blk);
             const bool two = k_lo + (blk + 1) * kBlockKeys < k_hi;
-            if (two) qk_block(st, tile_k(cur, 1), S1);
+            if (two) qk_block(st, tile_k(ko_cur, so_cur, 1), S1);
             const VFrags v0 = tile_v(cur, 0);
             soft(S0, blk, cur, std::true_type{});
             pv_block(st, v0, P);
@@ -497,21 +517,21 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
         }
         for (int t = 0; t < n_tiles; ++t) {
             __syncthreads();
-            issue_tile(t, 0);
+            issue_tile(t, 0, 0);
             wait_copies();
             __syncthreads();
-            clear_tail(lds, t);
+            clear_tail(lds + LdsRing::kRest, t);
             for (int k = 0; k < 2; ++k) {
                 const int blk = 2 * t + k;
                 if (k_lo + blk * kBlockKeys >= k_hi) break;
                 if ((blk & 63) == 0) classes_from(blk);
                 f32x16 S[QB];
                 bf16x8 P[QB][2];
-                qk_block(st, tile_k(lds, k), S);
+                qk_block(st, tile_k(0, 0, k), S);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
                     float scale, add;
-                    bias_block(qb, S, blk, lds, scale, add);
+                    bias_block(qb, S, blk, lds + LdsRing::kRest, scale, add);
                     mask(qb, S, blk, scale, add);
 #pragma unroll
                     for (int r = 0; r < 16; ++r) S[qb][r] = fmaf(S[qb][r], scale, add);
@@ -522,7 +542,7 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
                 softmax_safe(st, S, P);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) st.c[qb] = c_keep[qb];
-                pv_block(st, tile_v(lds, k), P);
+                pv_block(st, tile_v(lds + LdsRing::kRest, k), P);
             }
         }
 #pragma unroll
@@ -532,9 +552,7 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
 
     // normalise and store: each wave turns its 32 x 64 blocks around in its corner of the idle ring (chunk c of row r at
     // slot c ^ r % 8); behind it in the corner, RAW: its own key and value rows, on their way into the cache
-    constexpr int kCorner = 12288;
-    static_assert(NW * kCorner <= kStages * kStageBytes, "");
-    uint8_t *tr = lds + wave * kCorner;
+    uint8_t *tr = lds + wave * kCorner<RAW>;
     if constexpr (RAW) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -583,6 +601,20 @@ int64_t bias_entries(const AttnArgs &a)
     return (int64_t)a.n_scen * a.n_beh * ((int64_t)a.bias.n_pos + a.bias.n_time);
 }
 
+template <int QB, bool RAW>
+size_t bias_lds_bytes(const AttnArgs &a)
+{
+    const int64_t entries = bias_entries(a);
+    return (size_t)bias_flags_at<QB, RAW>(entries <= kBiasLdsFloats ? (int)entries : 0) + NW * 4;
+}
+
+// (LDS is given out by 1280 bytes)
+bool three_per_cu(size_t lds)
+{
+    constexpr size_t kLds = 160 * 1024, kUnit = 1280;
+    return (lds + kUnit - 1) / kUnit * kUnit * 3 <= kLds;
+}
+
 template <int QB, bool SUMI, bool CAUSAL, bool RAW = false>
 hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
 {
@@ -591,24 +623,22 @@ hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
     const int64_t grid = (int64_t)8 * n_qtiles * ((a.cache.B * a.H + 7) / 8);
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
     const KParams p = make_params(a, n_qtiles);
-    const int64_t entries = bias_entries(a);
-    const bool in_lds = entries <= kBiasLdsFloats;
-    const size_t lds = kStages * kStageBytes + NW * 4 + kClassBytes<QB> + (in_lds ? (size_t)entries * 4 : 0);
+    const bool in_lds = bias_entries(a) <= kBiasLdsFloats;
+    const size_t lds = bias_lds_bytes<QB, RAW>(a);
     auto go = [&](auto in_lds_tag, auto per_cu) {
         constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value, RAW, decltype(per_cu)::value>;
-        const hipError_t e = raise_lds_limit<kernel>(kStages * kStageBytes + NW * 4 + kClassBytes<QB> + kBiasLdsFloats * 4);
+        const hipError_t e = raise_lds_limit<kernel>(bias_flags_at<QB, RAW>(kBiasLdsFloats) + NW * 4);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NW * 64), lds, s, p);
         return hipGetLastError();
     };
     using Two = std::integral_constant<int, 2>;
     using Three = std::integral_constant<int, 3>;
-    // The history pass: a third workgroup per CU where the tables leave it room in LDS (given out by 1280 bytes) and there are that
+    // The history pass: a third workgroup per CU where the tables leave it room in LDS and there are that
     // many.  From rows it costs the compiler the order it likes best: us with two / three, subsequences of 256, one row of 33 + 20 entries,
     // full and causal: 64 users x 1024 142 / 125, 146 / 126; 30 x 1000 74.3 / 67.4, 74.6 / 68.3; 8 x 2000 (1024 workgroups) 41.9 / 41.5, 42.3 /
-    // 41.6; 100 x 100 (800) 32.9 / 34.9, 33.6 / 36.4; 4 x 300 14.2 / 14.2, 14.4 / 15.2; 32 rows of it, 64 x 1024 145 / 145, 148 / 153.
-    constexpr size_t kLds = 160 * 1024, kLdsUnit = 1280;
-    const bool three = (lds + kLdsUnit - 1) / kLdsUnit * kLdsUnit * 3 <= kLds && grid >= 1024;
+    // 41.6; 100 x 100 (800) 32.9 / 34.9, 33.6 / 36.4; 4 x 300 14.2 / 14.2, 14.4 / 15.2; 32 rows of 33 + 12, 64 x 1024 137 / 120, 139 / 119.
+    const bool three = three_per_cu(lds) && grid >= 1024;
     if constexpr (RAW) {
         if (in_lds) return three ? go(std::true_type{}, Three{}) : go(std::true_type{}, Two{});
         return go(std::false_type{}, Two{});
@@ -626,9 +656,19 @@ hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
     // histories of 1024: 200 candidates of one user (16 workgroups of 128) 35 / 22, 512 of 16 (512) 36 / 31, of 24 (768)
     // 49 / 46, of 32 (1024) 53 / 58, 128 of 64 (512) 49 / 33; histories of 215, 692 of 5 users, 2 heads (60) 15.7 / 10.5, of
     // 16, 8 heads (768) 21.9 / 24.9.  Same bits.
+    // Where three workgroups of 128 fit a CU (the tables), the busiest CU's share of queries decides: 512 of 24 users 49.9 / 40.9, 256 of 40 49.4 /
+    // 39.5, 300 of 64 104 / 79, 1000 of 20 against 4000 234 / 205; equal shares: 512 of 32 54.3 / 55.2, 200 of 64 54.4 / 58.5, 1024 of 16 51.6 / 52.7,
+    // 512 of 64 111 / 111, with 17 + 8 entries 101 / 105.  Where two do: poorly filled tiles only (512 of 64, 129 + 20
+    // entries, 118 / 137).
     if (sumi) {
-        const bool few = (int64_t)a.cache.B * a.H * ((a.max_rows_per_user + 127) / 128) <= 512;
-        return few || a.max_rows_per_user <= 128 ? launch_bias<1, true, false>(a, s) : launch_bias<2, true, false>(a, s);
+        const int64_t B = a.cache.B, H = a.H;
+        const bool few = B * H * ((a.max_rows_per_user + 127) / 128) <= 512;
+        auto rows = [&](int tile) {  // (of users that differ, about half a tile each is padding)
+            return a.uni_cand >= 0 ? B * ((a.uni_cand + tile - 1) / tile * tile) : a.total_q_rows + B * (tile / 2);
+        };
+        const int64_t narrow = H * rows(128) / 128, wide = H * rows(256) / 256;
+        const bool better = three_per_cu(bias_lds_bytes<1, false>(a)) ? (narrow + 255) / 256 < (wide + 255) / 256 * 2 : 6 * narrow <= 10 * wide;
+        return few || a.max_rows_per_user <= 128 || better ? launch_bias<1, true, false>(a, s) : launch_bias<2, true, false>(a, s);
     }
     return a.causal ? launch_bias<1, false, true>(a, s) : launch_bias<1, false, false>(a, s);
 }

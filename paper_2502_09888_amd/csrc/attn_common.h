@@ -280,7 +280,7 @@ static __device__ __forceinline__ void softmax_safe(QState<QB> &st, const f32x16
 }
 
 // ---- keys and values as rows (history pass that writes the cache itself) --------------------------
-// A tile of 64 keys in LDS: 64 key rows of 128 bytes, then 64 value rows, 16-byte chunk c of row r at slot c ^ (r / 2) % 8.  Key
+// A tile of 64 keys in LDS: 64 key rows of 128 bytes and 64 value rows, 16-byte chunk c of row r at slot c ^ (r / 2) % 8.  Key
 // fragments are row pieces; value fragments come out of the rows by LDS transpose reads (addresses as derived in
 // hist_fused_bf16.hip).  256 threads.
 struct RawTiles {
@@ -300,31 +300,33 @@ static __device__ __forceinline__ RawTiles raw_tiles(const KParams &p, int64_t r
 #pragma unroll
     for (int s = 0; s < 4; ++s) t.k_at[s] = (uint32_t)(l32 * 128 + (((2 * s + hf) ^ ((l32 >> 1) & 7)) * 16));
     const int G = lane >> 4, i16 = lane & 15, x = 2 * (G & 1) + ((i16 >> 1) & 1), y = 2 * (G >> 1) + (i16 >> 3);
-    t.v_at = (uint32_t)(8192 + (4 * (G >> 1) + (i16 >> 2)) * 128 + (x ^ y) * 16 + 8 * (i16 & 1));
+    t.v_at = (uint32_t)((4 * (G >> 1) + (i16 >> 2)) * 128 + (x ^ y) * 16 + 8 * (i16 & 1));
     return t;
 }
 
-// rows 64 n .. 64 n + 63 of the range (they exist: padded lengths are multiples of 64); `to`: the wave's first KiB of the tile
-static __device__ __forceinline__ void raw_issue(const RawTiles &t, int n, lds_u8 *to)
+// rows 64 n .. 64 n + 63 of the range (they exist: padded lengths are multiples of 64); to_k, to_v: the wave's first KiB of the key
+// and of the value rows
+static __device__ __forceinline__ void raw_issue(const RawTiles &t, int n, lds_u8 *to_k, lds_u8 *to_v)
 {
     const int64_t at = (int64_t)n * 64 * t.row_bytes, half = 32 * t.row_bytes;
-    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.k + at) + t.row_at, to, 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.k + at + half) + t.row_at, to + 4096, 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.v + at) + t.row_at, to + 8192, 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.v + at + half) + t.row_at, to + 12288, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.k + at) + t.row_at, to_k, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.k + at + half) + t.row_at, to_k + 4096, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.v + at) + t.row_at, to_v, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((glb_u8 *)(t.v + at + half) + t.row_at, to_v + 4096, 16, 0, 0);
 }
 
-static __device__ __forceinline__ KFrags raw_k(const RawTiles &t, const uint8_t *tile, int blk)
+// (keys, values: a tile's rows of either kind)
+static __device__ __forceinline__ KFrags raw_k(const RawTiles &t, const uint8_t *keys, int blk)
 {
     KFrags f;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) f.a[s] = *(const bf16x8 *)(tile + t.k_at[s] + blk * 4096);
+    for (int s = 0; s < 4; ++s) f.a[s] = *(const bf16x8 *)(keys + t.k_at[s] + blk * 4096);
     return f;
 }
 
 // (One block of inline assembly with its wait: for the builtin, with copies in flight, the compiler waits until all of
 // them have landed.  In a loop it belongs behind the MFMAs of the next logits, which run meanwhile.)
-static __device__ __forceinline__ VFrags raw_v(const RawTiles &t, const uint8_t *tile, int blk)
+static __device__ __forceinline__ VFrags raw_v(const RawTiles &t, const uint8_t *values, int blk)
 {
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     s16x4 x[8];
@@ -333,7 +335,7 @@ static __device__ __forceinline__ VFrags raw_v(const RawTiles &t, const uint8_t 
                  "ds_read_b64_tr_b16 %4, %8 offset:2048\n\tds_read_b64_tr_b16 %5, %8 offset:3136\n\t"
                  "ds_read_b64_tr_b16 %6, %8 offset:2112\n\tds_read_b64_tr_b16 %7, %8 offset:3072\n\ts_waitcnt lgkmcnt(0)"
                  : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
-                 : "v"((uint32_t)(uintptr_t)(lds_u8 *)tile + t.v_at + (uint32_t)blk * 4096u)
+                 : "v"((uint32_t)(uintptr_t)(lds_u8 *)values + t.v_at + (uint32_t)blk * 4096u)
                  : "memory");
     VFrags f;
 #pragma unroll
@@ -343,9 +345,9 @@ static __device__ __forceinline__ VFrags raw_v(const RawTiles &t, const uint8_t 
 }
 
 // the value rows of a tile from row `first` on, which may hold anything: zeros, before they meet probabilities of 0
-static __device__ __forceinline__ void raw_clear(uint8_t *tile, int first, int tid)
+static __device__ __forceinline__ void raw_clear(uint8_t *values, int first, int tid)
 {
-    for (int i = tid; i < (64 - first) * 8; i += 256) *(uint4 *)(tile + 8192 + first * 128 + i * 16) = uint4{0, 0, 0, 0};
+    for (int i = tid; i < (64 - first) * 8; i += 256) *(uint4 *)(values + first * 128 + i * 16) = uint4{0, 0, 0, 0};
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
 }

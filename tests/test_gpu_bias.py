@@ -321,3 +321,33 @@ def test_bf16_bias_tables_up_to_and_beyond_what_lds_holds(n_scen, n_beh, n_pos, 
         spec = W.shrink(W.CONFIG2, name=f"bias-lds-{n_pos}-{B}", B=B, L=300, L_min=200, sub_len=256, M=M, H=8, n_scen=n_scen, n_beh=n_beh,
                         pad_to=64, seed=1000 + n_pos)
         check_bias(W.add_bias_inputs(W.make_attention(spec), n_pos=n_pos, n_time=n_time))
+
+
+@pytest.mark.parametrize("n_pos", [2791, 2793])
+@pytest.mark.parametrize("causal", [False, True])
+def test_bf16_bias_history_with_tables_that_just_leave_room_for_three_workgroups(n_pos, causal):
+    # 1056 workgroups, two rings: 42496 bytes and the entries, and four flags behind them, in 53760 (a third of what LDS gives out), and 4 more
+    spec = W.shrink(W.CONFIG2, name=f"bias-rows-three-{n_pos}", B=44, L=300, L_min=240, sub_len=0, M=1, H=8, pad_to=64, nan_padding=True,
+                    n_scen=1, n_beh=1, seed=1200)
+    check_one_launch_writes_the_bits_of_two(spec, n_pos, 20, causal)
+
+
+@pytest.mark.parametrize("B,M,n_pos,n_time", [(33, 300, 65, 12), (24, 512, 65, 12), (32, 512, 33, 12), (33, 300, 97, 20), (33, 129, 33, 12)])
+def test_bf16_bias_candidate_tiles_by_the_share_of_the_busiest_cu(B, M, n_pos, n_time):
+    # tiles of 128 where they leave the busiest CU fewer queries or fill better (tables that leave room for three workgroups per CU, 65 + 12
+    # entries, and that do not, 97 + 20), of 256 else (512 of 32; 129 of 33), against single users, which take 128: the same bits.  Histories of
+    # one to five tiles of 64 keys: both rings' ends
+    spec = W.shrink(W.CONFIG2, name=f"bias-share-{B}-{M}", B=B, L=320, L_min=20, sub_len=128, M=M, H=8, pad_to=64, nan_padding=True, seed=1300 + M)
+    w = W.add_bias_inputs(W.make_attention(spec), n_pos=n_pos, n_time=n_time)
+    g = GpuBias(w)
+    g.history(want_output=False)
+    full = g.sumi_bias()
+    assert np.isfinite(full).all() and max_abs(full, oracle_sumi_bias(w)) < TOL["bf16"]
+    for b in (0, B // 2, B - 1):
+        part, c = dict(w), slice(int(w["cand_off"][b]), int(w["cand_off"][b + 1]))
+        for n in ("qc", "kc", "vc", "cscen", "cbeh", "cand_pos", "cand_ts"):
+            part[n] = np.ascontiguousarray(w[n][c])
+        part["cand_off"] = np.array([0] * (b + 1) + [c.stop - c.start] * (B - b), np.int32)
+        g = GpuBias(part)
+        g.history(want_output=False)
+        assert np.array_equal(g.sumi_bias(), full[c])
