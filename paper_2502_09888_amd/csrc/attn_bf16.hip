@@ -712,16 +712,30 @@ bool few_queries(const AttnArgs &a, bool sumi)
     if (a.max_rows_per_user > 64 && a.max_rows_per_user <= 128) return waves <= (a.max_hist_len > 640 ? 512 : 256);
     return waves <= (a.max_hist_len >= 256 || a.max_rows_per_user <= 32 ? 1024 : 512);
 }
+
+// Launches of at most a workgroup per CU of an XCD (the tiles of a head are on one) share a tile's keys out among waves
+// (attn_split_bf16.hip) but for the shortest walks.  Us there / with a wave per 32 queries, 8 heads: candidates of one user against 1000,
+// 10 to 256 of them 7.8 to 8.4 / 11.3 to 11.9, against 4000 18.2 / 31.4, against 256 5.9 / 6.8, against 64 5.8 / 5.8; the most workgroups (256):
+// 128 of 8 against 1024 9.6 / 12.8, 10 of 32 against 1000 13.1 / 14.5; one more per CU: 256 of 8 against 512 (512) 12.3 / 9.6, 128
+// of 10 against 1000 (320) 17.3 / 13.3; two heads of one user's 4000 in one subsequence (125 on each of two XCDs) 72 / 45.
+bool split_keys(const AttnArgs &a, bool sumi)
+{
+    const int64_t per_xcd = ((int64_t)a.cache.B * a.H + 7) / 8 * ((a.max_rows_per_user + 31) / 32);
+    const int walk = !sumi && a.sub_len > 0 ? std::min(a.sub_len, a.max_hist_len) : a.max_hist_len;
+    return per_xcd <= 32 && walk >= 128;
+}
 }  // namespace
 
 // From rows, one launch, or the cache writer and a launch that reads the cache: two launches only where a wave per 32 queries
-// (attn_wave_bf16.hip) has a long walk to make, which tiles make more slowly.  Us from rows / as two, 8 heads: 4 users x 1024 behaviours in one
-// subsequence 16.8 / 22.3, in two 11.2 / 16.9, one user's 1000 in two 10.4 / 10.9, 2000 in one 28.1 / 23.9, 4096 in one 53.5 / 47.9; where two would
-// be the tiled kernel: 16 x up to 4096 in subsequences of 512 77.8 / 93.1, 64 x 1024 in one 167.6 / 187.9, causal 64 x 1000 in two 113 / 124.
+// (attn_wave_bf16.hip) has a long walk to make, which tiles make more slowly, or where the walk is shared out among waves (split_keys).  Us from
+// rows / as two, 8 heads: 4 users x 1024 behaviours in one subsequence 16.8 / 22.3, in two 11.2 / 16.9, one user's 2000 in one 28.1 / 23.9, 4096 in
+// one 53.5 / 47.9; shared out: one user's 1000 in one 16.5 / 11.4, causal 16.7 / 10.8, in two 10.6 / 10.1, 2 x 500 in one 10.4 / 9.5, one user's
+// 300 8.0 / 8.7, 1000 in four 7.7 / 8.5; where two would be the tiled kernel: 16 x up to 4096 in subsequences of 512 77.8 / 93.1, 64 x 1024 in one 167.6 / 187.9, causal 64 x 1000 in two 113 / 124.
 bool attn_hist_rows_bf16_takes(const AttnArgs &a)
 {
     if (a.bias.pos_table) return attn_hist_rows_bias_bf16_takes(a);
     const int walk = a.sub_len > 0 ? std::min(a.sub_len, a.max_hist_len) : a.max_hist_len;
+    if (split_keys(a, false)) return walk <= 384;
     return walk <= 1024 || !few_queries(a, false);
 }
 
@@ -736,6 +750,7 @@ hipError_t launch_attn_hist_rows_bf16(const AttnArgs &a, hipStream_t s)
 hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 {
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, true, s);
+    if (split_keys(a, true)) return launch_attn_split_bf16(a, true, s);
     if (few_queries(a, true)) return launch_attn_wave_bf16(a, true, s);
     return a.max_rows_per_user > 128 ? launch<4, 2, true>(a, s) : launch<4, 1, true>(a, s);
 }
@@ -743,6 +758,7 @@ hipError_t launch_attn_sumi_bf16(const AttnArgs &a, hipStream_t s)
 hipError_t launch_attn_hist_bf16(const AttnArgs &a, hipStream_t s)
 {
     if (a.bias.pos_table) return launch_attn_bias_bf16(a, false, s);
+    if (split_keys(a, false)) return launch_attn_split_bf16(a, false, s);
     if (few_queries(a, false)) return launch_attn_wave_bf16(a, false, s);
     const bool wide = hist_wide_tiles(a);
     if (a.causal) return wide ? launch<4, 2, false, true>(a, s) : launch<4, 1, false, true>(a, s);

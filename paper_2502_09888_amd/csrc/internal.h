@@ -69,6 +69,8 @@ bool attn_hist_rows_bf16_takes(const AttnArgs &a);
 hipError_t launch_attn_hist_rows_bf16(const AttnArgs &a, hipStream_t s);
 // the same for launches of few queries, a wave per 32 of them (attn_wave_bf16.hip); no bias
 hipError_t launch_attn_wave_bf16(const AttnArgs &a, bool sumi, hipStream_t s);
+// of so few that most SIMDs would have none (attn_split_bf16.hip); no bias
+hipError_t launch_attn_split_bf16(const AttnArgs &a, bool sumi, hipStream_t s);
 // the same with the relative attention bias (attn_bias_bf16.hip)
 hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s);
 bool attn_hist_rows_bias_bf16_takes(const AttnArgs &a);                        // by attn_hist_rows_bf16_takes

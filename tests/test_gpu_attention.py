@@ -300,6 +300,40 @@ def test_few_and_many_queries_choose_the_same_form_of_the_softmax():
     assert max_abs(part, oracle_sumi(w)[:192]) < 2e-2
 
 
+@pytest.mark.parametrize("L,L_min,n_scen", [(128, 128, 8), (129, 129, 17), (160, 160, 8), (191, 0, 8), (255, 255, 8), (256, 256, 17), (257, 257, 8),
+                                            (290, 290, 8), (385, 33, 8), (1000, 1000, 8), (1030, 1, 17)])
+def test_keys_shared_out_among_waves_give_the_bits_of_other_launches(L, L_min, n_scen):
+    # up to 1024 candidates a user, histories from 128 on: four waves per 32 queries make the probabilities and two add them up; beyond, a wave
+    # per 32 queries (1100 candidates), and then tiles (5600).  Histories at the edges of blocks and of rounds of four blocks, before and behind those
+    # where the own key (the third block) and value (the seventh) join, none at all; temperatures in more entries (17 x 4) than a
+    # wavefront has lanes (and none so low that the form of the softmax depended on which queries are looked at together)
+    spec = W.shrink(W.CONFIG2, name=f"bf16-split-{L}", B=3, L=L, L_min=L_min, sub_len=0, M=5600, H=2, pad_to=64, nan_padding=True, n_scen=n_scen,
+                    n_beh=4, seed=1100 + L)
+    w = W.make_attention(spec)
+    w["tau"] = np.maximum(w["tau"], 1.0)
+    g = GpuAttention(w)
+    oh, ok = g.history(), valid_rows(w)
+    assert max_abs(oh[ok], oracle_history(w)[ok]) < 2e-2 and np.all(oh[~ok] == 0)
+    full = g.sumi()
+    for n in (1, 33, 200, 1100):
+        part = g.sumi(sel=(7, 7 + n))
+        assert np.array_equal(part, full[g.last_idx])
+
+
+@pytest.mark.parametrize("L", [150, 300])
+def test_keys_shared_out_among_waves_where_one_key_outgrows_the_rest(L):
+    # rows whose logits leave every window: the running-maximum pass, by both of the waves that add up, against a wave per 32 queries
+    spec = W.shrink(W.CONFIG2, name=f"bf16-split-safe-{L}", B=1, L=L, sub_len=0, M=1100, H=8, pad_to=64, nan_padding=True, seed=1170 + L)
+    w = W.make_attention(spec)
+    w["qc"] = w["qc"].copy()
+    w["qc"][5:40] *= 64  # (exactly: the inputs are bf16)
+    g = GpuAttention(w)
+    g.history()
+    full, part = g.sumi(), g.sumi(sel=(0, 70))
+    assert np.isfinite(full).all() and np.array_equal(part, full[:70])
+    assert max_abs(part, oracle_sumi(w)[:70]) < 2e-2
+
+
 @pytest.mark.parametrize("L", [20, 40, 70, 100, 130, 257])
 def test_few_queries_keep_an_infinite_value_infinite(L):
     # one to nine blocks of 32 keys, odd and even: a value of the last one that every row sees, by the wave per 32
