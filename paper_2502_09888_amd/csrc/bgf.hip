@@ -1,8 +1,9 @@
-// Bit-wise gating fusion of Climber (arXiv 2502.09888, Sec. 3.1.4, Eq. (4)): the two small kernels
+// Bit-wise gating fusion of Climber (arXiv 2502.09888, Sec. 3.1.4, Eq. (4)): what stands
 // around the projections of the fusion layer.
 //   fusion attention: G = ATL(E): every one of a candidate's N_b block outputs attends to all N_b of
 //     them, no relative attention bias, temperature from the candidate's scenario only;
-//   gate + head: Y = G (.) sigmoid(f_gate(G)), score = <w_head, vec(Y)> + b.
+//   gate + head: Y = G (.) sigmoid(f_gate(G)), score = <w_head, vec(Y)> + b;
+//     with f_gate's projections in one launch (bgf_gate_kernel) or behind two launches of gemm_bf16.
 // N_b is a handful (the number of extraction strategies), so the attention is N_b x N_b logits per
 // (candidate, head), held in registers; d_head = 64.
 #include "bgf.h"
