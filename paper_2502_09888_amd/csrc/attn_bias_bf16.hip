@@ -418,7 +418,11 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
                 soft(S0, 2 * t, cur, std::false_type{});
                 pv_block(st, v0, P);
             }
-            wait_copies();  // tile t + 1 has landed; nobody reads tile t - 1 any more, nor the keys of tile t
+            // Tile t + 1 has landed; nobody reads tile t - 1 any more, nor the keys of tile t, whose reads have returned before the copies
+            // behind the barrier overwrite them: raw_v has waited for all of a wave's reads, load_v leaves it to the compiler, whose waits may
+            // as well stand behind the barrier.
+            if constexpr (RAW) wait_copies();
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             if (t + 2 < n_tiles) issue_tile(t + 2, ko_cur, so_fill);
             ko_cur ^= LdsRing::kKeyStage;
