@@ -27,14 +27,18 @@ constexpr int kTileKeys = 64, kTileBytes = 2 * kBlockBytes, kStages = 3, NW = 4;
 
 // Tiles of 64 keys in LDS: a ring of three stages of keys, values, positions and time stamps, or (SPLIT) two rings: the keys themselves,
 // two stages, as all of a tile have been read when the next one's first block is started; and what is read later, three.  The
-// latter takes 8 KiB less, which makes room for a third workgroup per CU (QB = 1), and a few per cent longer where it does not (QB = 2:
-// 512 candidates of 32 users against 4000 171 us, 162 with one ring).
+// latter takes 8 KiB less, which makes room for a third workgroup per CU, and where there is none it gains nothing: us with one / two, QB = 2, 512
+// candidates of 32 users against 4000 162 / 171; QB = 1, tables of 129 + 20 entries, 300 of 64 users 101.5 / 102.6, 128 of 96 69.5 / 68.1, history of
+// 64 x 1024 in one, from the cache, 291.0 / 292.6, of 30 x 1000 in four 98.3 / 98.3.  From rows it is always two.
 template <bool SPLIT>
 struct Ring {
     static constexpr int kKeyStage = SPLIT ? kTileBytes / 2 : 0;                                  // stages of keys begin at 0
     static constexpr int kRest = 2 * kKeyStage, kCoords = SPLIT ? kTileBytes / 2 : kTileBytes;  // those of the rest; coordinates in them
     static constexpr int kStage = kCoords + kTileKeys * 8, kBytes = kRest + kStages * kStage;
 };
+
+template <bool RAW, int PER_CU>
+constexpr bool two_rings = RAW || PER_CU == 3;
 
 // minimum over the 32 lanes of a half-wave, as a scalar (both halves hold the same 32 values)
 template <class F>
@@ -52,10 +56,10 @@ __device__ __forceinline__ int half_wave_reduce(int x, F &&f)
 // and values on their way to the cache.
 template <bool RAW>
 constexpr int kCorner = RAW ? 12288 : 4096;
-template <int QB, bool RAW>
+template <bool SPLIT, bool RAW>
 __host__ __device__ constexpr int bias_flags_at(int entries)
 {
-    const int used = Ring<QB == 1>::kBytes + entries * 4, corners = NW * kCorner<RAW>;
+    const int used = Ring<SPLIT>::kBytes + entries * 4, corners = NW * kCorner<RAW>;
     return used > corners ? used : corners;
 }
 
@@ -70,11 +74,11 @@ __global__ __launch_bounds__(NW * 64, PER_CU) void attn_bias_kernel(const KParam
     static_assert(!RAW || (!SUMI && QB == 1), "rows: the history pass");
     constexpr int NT = NW * 64, WQ = 32 * QB, TQ = NW * WQ, NPRE = kTileBytes / 16 / NT;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    constexpr bool SPLIT = QB == 1;
+    constexpr bool SPLIT = two_rings<RAW, PER_CU>;
     using LdsRing = Ring<SPLIT>;
     float *bias_lds = (float *)(lds + LdsRing::kBytes);  // the head's table rows: [n_tau][n_pos], [n_tau][n_time]
     // (behind everything: a wave's corner is in use while others may still read the flags)
-    int *flag_lds = (int *)(lds + bias_flags_at<QB, RAW>(IN_LDS ? p.n_scen * p.n_beh * (p.bias.n_pos + p.bias.n_time) : 0));
+    int *flag_lds = (int *)(lds + bias_flags_at<SPLIT, RAW>(IN_LDS ? p.n_scen * p.n_beh * (p.bias.n_pos + p.bias.n_time) : 0));
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
@@ -605,50 +609,54 @@ int64_t bias_entries(const AttnArgs &a)
     return (int64_t)a.n_scen * a.n_beh * ((int64_t)a.bias.n_pos + a.bias.n_time);
 }
 
-template <int QB, bool RAW>
+template <bool SPLIT, bool RAW>
 size_t bias_lds_bytes(const AttnArgs &a)
 {
     const int64_t entries = bias_entries(a);
-    return (size_t)bias_flags_at<QB, RAW>(entries <= kBiasLdsFloats ? (int)entries : 0) + NW * 4;
+    return (size_t)bias_flags_at<SPLIT, RAW>(entries <= kBiasLdsFloats ? (int)entries : 0) + NW * 4;
 }
 
 // (LDS is given out by 1280 bytes)
-bool three_per_cu(size_t lds)
+template <bool RAW>
+bool three_per_cu(const AttnArgs &a)
 {
     constexpr size_t kLds = 160 * 1024, kUnit = 1280;
-    return (lds + kUnit - 1) / kUnit * kUnit * 3 <= kLds;
+    return (bias_lds_bytes<true, RAW>(a) + kUnit - 1) / kUnit * kUnit * 3 <= kLds;
 }
 
-template <int QB, bool SUMI, bool CAUSAL, bool RAW = false>
-hipError_t launch_bias(const AttnArgs &a, hipStream_t s)
+template <int QB>
+int64_t bias_workgroups(const AttnArgs &a)
 {
     constexpr int TQ = NW * 32 * QB;
-    const int n_qtiles = (a.max_rows_per_user + TQ - 1) / TQ;
-    const int64_t grid = (int64_t)8 * n_qtiles * ((a.cache.B * a.H + 7) / 8);
+    return (int64_t)8 * ((a.max_rows_per_user + TQ - 1) / TQ) * (((int64_t)a.cache.B * a.H + 7) / 8);
+}
+
+// three: the instance whose registers are held to what three workgroups per CU leave (QB = 1; their LDS: three_per_cu)
+template <int QB, bool SUMI, bool CAUSAL, bool RAW = false>
+hipError_t launch_bias(const AttnArgs &a, bool three, hipStream_t s)
+{
+    constexpr int TQ = NW * 32 * QB;
+    const int64_t grid = bias_workgroups<QB>(a);
     if (grid <= 0 || grid > 0x7fffffff) return hipErrorInvalidValue;
-    const KParams p = make_params(a, n_qtiles);
+    const KParams p = make_params(a, (a.max_rows_per_user + TQ - 1) / TQ);
     const bool in_lds = bias_entries(a) <= kBiasLdsFloats;
-    const size_t lds = bias_lds_bytes<QB, RAW>(a);
     auto go = [&](auto in_lds_tag, auto per_cu) {
-        constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value, RAW, decltype(per_cu)::value>;
-        const hipError_t e = raise_lds_limit<kernel>(bias_flags_at<QB, RAW>(kBiasLdsFloats) + NW * 4);
+        constexpr int PER_CU = decltype(per_cu)::value;
+        constexpr auto kernel = attn_bias_kernel<QB, SUMI, CAUSAL, decltype(in_lds_tag)::value, RAW, PER_CU>;
+        const hipError_t e = raise_lds_limit<kernel>(bias_flags_at<two_rings<RAW, PER_CU>, RAW>(kBiasLdsFloats) + NW * 4);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NW * 64), lds, s, p);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NW * 64), (bias_lds_bytes<two_rings<RAW, PER_CU>, RAW>(a)), s, p);
         return hipGetLastError();
     };
     using Two = std::integral_constant<int, 2>;
     using Three = std::integral_constant<int, 3>;
-    // The history pass: a third workgroup per CU where the tables leave it room in LDS and there are that
-    // many.  From rows it costs the compiler the order it likes best: us with two / three, subsequences of 256, one row of 33 + 20 entries,
-    // full and causal: 64 users x 1024 142 / 125, 146 / 126; 30 x 1000 74.3 / 67.4, 74.6 / 68.3; 8 x 2000 (1024 workgroups) 41.9 / 41.5, 42.3 /
-    // 41.6; 100 x 100 (800) 32.9 / 34.9, 33.6 / 36.4; 4 x 300 14.2 / 14.2, 14.4 / 15.2; 32 rows of 33 + 12, 64 x 1024 137 / 120, 139 / 119.
-    const bool three = three_per_cu(lds) && grid >= 1024;
-    if constexpr (RAW) {
+    if constexpr (QB == 1) {
         if (in_lds) return three ? go(std::true_type{}, Three{}) : go(std::true_type{}, Two{});
+        if constexpr (SUMI)
+            if (three) return go(std::false_type{}, Three{});
         return go(std::false_type{}, Two{});
     } else {
-        using LdsHist = std::integral_constant<int, SUMI ? 2 : 3>;
-        return in_lds ? go(std::true_type{}, LdsHist{}) : go(std::false_type{}, Two{});
+        return in_lds ? go(std::true_type{}, Two{}) : go(std::false_type{}, Two{});
     }
 }
 
@@ -662,19 +670,25 @@ hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
     // 16, 8 heads (768) 21.9 / 24.9.  Same bits.
     // Where three workgroups of 128 fit a CU (the tables), the busiest CU's share of queries decides: 512 of 24 users 49.9 / 40.9, 256 of 40 49.4 /
     // 39.5, 300 of 64 104 / 79, 1000 of 20 against 4000 234 / 205; equal shares: 512 of 32 54.3 / 55.2, 200 of 64 54.4 / 58.5, 1024 of 16 51.6 / 52.7,
-    // 512 of 64 111 / 111, with 17 + 8 entries 101 / 105.  Where two do: poorly filled tiles only (512 of 64, 129 + 20
+    // 512 of 64 111 / 111, with 17 + 8 entries 101 / 105; tables beyond LDS (257 + 20): 512 of 24 84.9 / 62.1, 300 of 64 168.6 / 115.5, up to 200 of 100
+    // that differ 137.9 / 131.7 (142.8 where registers leave room for two).  Where two do: poorly filled tiles only (512 of 64, 129 + 20
     // entries, 118 / 137).
+    // A third workgroup where there are more than two per CU: with two / three, 128 of 72 users 52.5 / 43.6, of 64 (512) 37.3 / 37.0, of 48 30.9 / 31.3, up
+    // to 300 of 32 that differ (about 500 with work) 28.8 / 35.6 (three on some CUs, one on others), beyond LDS 45.4 / 50.2.
     if (sumi) {
         const int64_t B = a.cache.B, H = a.H;
-        const bool few = B * H * ((a.max_rows_per_user + 127) / 128) <= 512;
+        const bool few = B * H * ((a.max_rows_per_user + 127) / 128) <= 512, fit = three_per_cu<false>(a);
         auto rows = [&](int tile) {  // (of users that differ, about half a tile each is padding)
             return a.uni_cand >= 0 ? B * ((a.uni_cand + tile - 1) / tile * tile) : a.total_q_rows + B * (tile / 2);
         };
         const int64_t narrow = H * rows(128) / 128, wide = H * rows(256) / 256;
-        const bool better = three_per_cu(bias_lds_bytes<1, false>(a)) ? (narrow + 255) / 256 < (wide + 255) / 256 * 2 : 6 * narrow <= 10 * wide;
-        return few || a.max_rows_per_user <= 128 || better ? launch_bias<1, true, false>(a, s) : launch_bias<2, true, false>(a, s);
+        const bool better = fit ? (narrow + 255) / 256 < (wide + 255) / 256 * 2 : 6 * narrow <= 10 * wide;
+        return few || a.max_rows_per_user <= 128 || better ? launch_bias<1, true, false>(a, fit && narrow > 512, s)
+                                                           : launch_bias<2, true, false>(a, false, s);
     }
-    return a.causal ? launch_bias<1, false, true>(a, s) : launch_bias<1, false, false>(a, s);
+    // History from the cache: three where they fit.  (100 x 100 in one, 800 workgroups, 33.3 us with three, 35.5 with two.)
+    const bool three = three_per_cu<false>(a);
+    return a.causal ? launch_bias<1, false, true>(a, three, s) : launch_bias<1, false, false>(a, three, s);
 }
 
 // From rows with the tables in LDS.  With look-ups in global memory the cache writer and a launch that reads the cache are the faster
@@ -689,7 +703,12 @@ bool attn_hist_rows_bias_bf16_takes(const AttnArgs &a)
 
 hipError_t launch_attn_hist_rows_bias_bf16(const AttnArgs &a, hipStream_t s)
 {
-    return a.causal ? launch_bias<1, false, true, true>(a, s) : launch_bias<1, false, false, true>(a, s);
+    // A third workgroup per CU where the tables leave it room in LDS and there are that
+    // many.  From rows it costs the compiler the order it likes best: us with two / three, subsequences of 256, one row of 33 + 20 entries,
+    // full and causal: 64 users x 1024 142 / 125, 146 / 126; 30 x 1000 74.3 / 67.4, 74.6 / 68.3; 8 x 2000 (1024 workgroups) 41.9 / 41.5, 42.3 /
+    // 41.6; 100 x 100 (800) 32.9 / 34.9, 33.6 / 36.4; 4 x 300 14.2 / 14.2, 14.4 / 15.2; 32 rows of 33 + 12, 64 x 1024 137 / 120, 139 / 119.
+    const bool three = three_per_cu<true>(a) && bias_workgroups<1>(a) >= 1024;
+    return a.causal ? launch_bias<1, false, true, true>(a, three, s) : launch_bias<1, false, false, true>(a, three, s);
 }
 
 }  // namespace climber

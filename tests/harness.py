@@ -2,7 +2,9 @@
 arrays through the oracle, compare.  No arithmetic of the method lives here."""
 from __future__ import annotations
 
+import ctypes as C
 import sys
+from collections import namedtuple
 
 import numpy as np
 
@@ -24,6 +26,52 @@ oracle = _Oracle()
 def say(*a):
     print(*a, flush=True)
     sys.stdout.flush()
+
+
+class _KernelNode(C.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", C.c_uint32 * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint32 * 3), ("params", C.c_void_p),
+                ("lds", C.c_uint32)]
+
+
+class _FuncAttributes(C.Structure):  # hipFuncAttributes
+    _fields_ = [("binary_version", C.c_int), ("cache_mode", C.c_int), ("const_bytes", C.c_size_t), ("local_bytes", C.c_size_t),
+                ("max_lds", C.c_int), ("max_threads", C.c_int), ("regs", C.c_int), ("carveout", C.c_int), ("ptx", C.c_int),
+                ("static_lds", C.c_size_t)]
+
+
+Launch = namedtuple("Launch", "kernel grid lds regs")  # mangled name, workgroups, dynamic LDS bytes, registers a lane
+
+
+def launches(call):
+    """The kernels that a call launches: once for real, then captured into a graph that never runs."""
+    import torch
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call()
+    with open("/proc/self/maps") as f:
+        hip = C.CDLL(next(line.split()[-1] for line in f if "libamdhip64.so" in line))
+    hip.hipKernelNameRefByPtr.restype = C.c_char_p
+
+    def ok(rc):
+        assert rc == 0, f"HIP error {rc}"
+
+    graph, n = C.c_void_p(g.raw_cuda_graph()), C.c_size_t(0)
+    ok(hip.hipGraphGetNodes(graph, None, C.byref(n)))
+    nodes = (C.c_void_p * n.value)()
+    ok(hip.hipGraphGetNodes(graph, nodes, C.byref(n)))
+    out = []
+    for node in nodes:
+        kind, k, a = C.c_int(-1), _KernelNode(), _FuncAttributes()
+        ok(hip.hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)))
+        if kind.value != 0:  # hipGraphNodeTypeKernel
+            continue
+        ok(hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(k)))
+        ok(hip.hipFuncGetAttributes(C.byref(a), C.c_void_p(k.func)))
+        name = hip.hipKernelNameRefByPtr(C.c_void_p(k.func), None)
+        out.append(Launch(name.decode(), k.grid[0] * k.grid[1] * k.grid[2], k.lds, a.regs))
+    return out
 
 
 def torch_dtype(spec_dtype):

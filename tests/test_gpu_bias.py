@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from harness import GpuAttention, max_abs, oracle, say, valid_rows
+from harness import GpuAttention, launches, max_abs, oracle, say, valid_rows
 
 pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-4, "bf16": 2e-2}
@@ -31,14 +31,18 @@ class GpuBias(GpuAttention):
         return o.float().cpu().numpy()
 
     def sumi_bias(self):
-        t, w = self.torch, self.w
+        m_total = int(self.w["cand_off"][-1])
+        o = self.torch.full((max(m_total, 1), self.d), float("nan"), dtype=self.dt, device="cuda:0")
+        self.launch_sumi_bias(o)
+        self.torch.cuda.synchronize()
+        return o[:m_total].float().cpu().numpy()
+
+    def launch_sumi_bias(self, o):
+        w = self.w
         m_total = int(w["cand_off"][-1])
         m_max = int(np.diff(w["cand_off"]).max()) if m_total else 0
-        o = t.full((max(m_total, 1), self.d), float("nan"), dtype=self.dt, device="cuda:0")
         self.P.climber_attn_sumi_bias(self.cfg, self.tau, self.cache, 0, self.qc, self.kc, self.vc, self.cand_off,
                                       m_total, m_max, self.cscen, self.cbeh, o, self.rb)
-        t.cuda.synchronize()
-        return o[:m_total].float().cpu().numpy()
 
 
 def oracle_hist_bias(w, causal=False):
@@ -332,10 +336,11 @@ def test_bf16_bias_history_with_tables_that_just_leave_room_for_three_workgroups
     check_one_launch_writes_the_bits_of_two(spec, n_pos, 20, causal)
 
 
-@pytest.mark.parametrize("B,M,n_pos,n_time", [(33, 300, 65, 12), (24, 512, 65, 12), (32, 512, 33, 12), (33, 300, 97, 20), (33, 129, 33, 12)])
+@pytest.mark.parametrize("B,M,n_pos,n_time", [(33, 300, 65, 12), (24, 512, 65, 12), (32, 512, 33, 12), (33, 300, 97, 20), (33, 129, 33, 12),
+                                              (24, 512, 257, 20), (33, 300, 257, 20)])
 def test_bf16_bias_candidate_tiles_by_the_share_of_the_busiest_cu(B, M, n_pos, n_time):
     # tiles of 128 where they leave the busiest CU fewer queries or fill better (tables that leave room for three workgroups per CU, 65 + 12
-    # entries, and that do not, 97 + 20), of 256 else (512 of 32; 129 of 33), against single users, which take 128: the same bits.  Histories of
+    # entries, and that do not, 97 + 20; beyond LDS, 257 + 20), of 256 else (512 of 32; 129 of 33), against single users, which take 128: the same bits.  Histories of
     # one to five tiles of 64 keys: both rings' ends
     spec = W.shrink(W.CONFIG2, name=f"bias-share-{B}-{M}", B=B, L=320, L_min=20, sub_len=128, M=M, H=8, pad_to=64, nan_padding=True, seed=1300 + M)
     w = W.add_bias_inputs(W.make_attention(spec), n_pos=n_pos, n_time=n_time)
@@ -351,3 +356,21 @@ def test_bf16_bias_candidate_tiles_by_the_share_of_the_busiest_cu(B, M, n_pos, n
         g = GpuBias(part)
         g.history(want_output=False)
         assert np.array_equal(g.sumi_bias(), full[c])
+
+
+@pytest.mark.parametrize("B,M,M_min,n_pos,three", [(24, 512, None, 257, True), (33, 300, None, 257, True), (30, 300, 75, 257, False), (8, 512, None, 257, False),
+                                                   (24, 512, None, 33, True), (33, 300, None, 33, True), (16, 512, None, 33, False), (33, 300, None, 129, False)])
+def test_bf16_bias_candidates_have_the_third_workgroup_that_the_choice_of_tiles_counts_on(B, M, M_min, n_pos, three):
+    # 128-query tiles because three workgroups of them fit a CU, with the tables in LDS (33 + 12 entries of 32 rows) and beyond it (257 + 12): then
+    # registers (512 a SIMD) and LDS (160 KiB a CU, given out by 1280 bytes) hold three.  No more than two a CU, or tables that leave room
+    # for two (129 + 12): the instance for two
+    spec = W.shrink(W.CONFIG2, name=f"bias-three-{B}-{M}-{n_pos}", B=B, L=64, L_min=64, sub_len=0, M=M, M_min=M_min, H=8, pad_to=64, seed=1400 + M)
+    g = GpuBias(W.add_bias_inputs(W.make_attention(spec), n_pos=n_pos, n_time=12))
+    g.history(want_output=False)
+    o = g.torch.empty((int(g.w["cand_off"][-1]), g.d), dtype=g.dt, device="cuda:0")
+    run = launches(lambda: g.launch_sumi_bias(o))
+    say([tuple(k) for k in run])
+    assert len(run) == 1 and "attn_bias_kernelILi1ELb1" in run[0].kernel
+    assert run[0].kernel.split("EEEv")[0].endswith("Li3" if three else "Li2")
+    if three:
+        assert run[0].regs <= 168 and (run[0].lds + 1279) // 1280 * 1280 * 3 <= 160 * 1024
