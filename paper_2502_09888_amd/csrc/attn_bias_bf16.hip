@@ -652,7 +652,7 @@ hipError_t launch_bias(const AttnArgs &a, bool three, hipStream_t s)
     using Three = std::integral_constant<int, 3>;
     if constexpr (QB == 1) {
         if (in_lds) return three ? go(std::true_type{}, Three{}) : go(std::true_type{}, Two{});
-        if constexpr (SUMI)
+        if constexpr (SUMI || (CAUSAL && !RAW))
             if (three) return go(std::false_type{}, Three{});
         return go(std::false_type{}, Two{});
     } else {
@@ -686,7 +686,9 @@ hipError_t launch_attn_bias_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
         return few || a.max_rows_per_user <= 128 || better ? launch_bias<1, true, false>(a, fit && narrow > 512, s)
                                                            : launch_bias<2, true, false>(a, false, s);
     }
-    // History from the cache: three where they fit.  (100 x 100 in one, 800 workgroups, 33.3 us with three, 35.5 with two.)
+    // History from the cache: three where they fit; tables beyond LDS: under the causal flag, whose tiles' walks differ.  Us with two / three, 100 x
+    // 100 in one (800 workgroups) 35.5 / 33.3; tables beyond LDS, causal, 64 x 1024 in one 402 / 370, 16 x 1000 in two 97 / 93, 8 x 1000 in four
+    // 48.8 / 49.1; not causal, 64 x 1024 in one 512 / 465, but 16 x 1000 (1024 workgroups) 137 / 144.
     const bool three = three_per_cu<false>(a);
     return a.causal ? launch_bias<1, false, true>(a, three, s) : launch_bias<1, false, false>(a, three, s);
 }

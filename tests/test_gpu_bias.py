@@ -374,3 +374,16 @@ def test_bf16_bias_candidates_have_the_third_workgroup_that_the_choice_of_tiles_
     assert run[0].kernel.split("EEEv")[0].endswith("Li3" if three else "Li2")
     if three:
         assert run[0].regs <= 168 and (run[0].lds + 1279) // 1280 * 1280 * 3 <= 160 * 1024
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_bf16_bias_history_from_the_cache_beyond_lds_takes_the_third_workgroup_under_the_causal_flag(causal):
+    # (what a call that asks for two launches, or puts its outputs over the keys or values, takes; without the flag two per CU)
+    spec = W.shrink(W.CONFIG2, name="bias-cached-three", B=5, L=300, L_min=200, sub_len=0, M=1, H=8, pad_to=64, seed=1500)
+    g = GpuBias(W.add_bias_inputs(W.make_attention(spec), n_pos=257, n_time=12), causal=causal)
+    g.cfg.flags |= 2
+    o = g.torch.empty((g.qh.shape[0], g.d), dtype=g.dt, device="cuda:0")
+    run = launches(lambda: g.P.climber_attn_history_bias(g.cfg, g.tau, g.qh, g.kh, g.vh, g.scen, g.beh, g.cache, 0, o, g.rb))
+    say([tuple(k) for k in run])
+    k = next(k for k in run if "attn_bias_kernel" in k.kernel)
+    assert k.kernel.split("EEEv")[0].endswith("Li3" if causal else "Li2") and (k.regs <= 168 or not causal)
