@@ -257,14 +257,17 @@ __global__ __launch_bounds__(512, 4) void bgf_gate_kernel(const __bf16 *gb, cons
 
 }  // namespace
 
-// A workgroup streams both weights for its 32 candidates, whoever else does, so few of them are better served by the tiles.  Us a call,
-// one launch / three: 8192 candidates x 4 blocks of 512, d_gate 256 333 / 341, 12000 484 / 498, 6000 267 / 275, 4200 253 / 256, 2100 136 / 138,
-// 1500 119 / 112; x 8 12000 927 / 941, 6000 487 / 486, 4200 433 / 424; of 256 x 4 2100 72 / 76, 1500 69 / 67; d_gate 128, x 4 of 512 4200 242 / 256, 1500
-// 109 / 109, 1000 98 / 98.
+// A workgroup streams both weights for its 32 candidates, whoever else does, so few of them are better served by the tiles: up to 2048
+// candidates by those of gemm_small_bf16.hip, further on with a wide G, whose weights the macro tiles read less often.  Us a call, one launch / three,
+// G as blocks x d_model.  d_gate 256: 4 x 512 2000 131.7 / 124.6, 2300 142.0 / 146.8, 8192 336 / 346, 4 x 256 2000 70.5 / 69.5, 2500 73.6 / 77.5;
+// 6 x 512 5000 347 / 339, 7000 471 / 473, 8 x 512 5000 467 / 460, 6000 516 / 520, 8192 665 / 679, 16 x 512 5000 1011 / 991, 6000 1173 / 1172.  d_gate 128:
+// 4 x 512 1000 and 1500 even, 2300 131.9 / 134.0, 8192 324 / 340, 8 x 512 1000 141 / 137, 1500 163 / 165, 2500 276 / 273, 4000 even, 8192 643 /
+// 672, 16 x 512 2000 445 / 421, 4000 772 / 759, 5000 945 / 1005, 1 x 256 1500 36.4 / 40.2.
 bool bgf_gate_takes(int64_t m, int nd, int dg)
 {
     if (nd % 256 != 0) return false;
-    return dg == 128 ? m >= 1500 : dg == 256 && m >= (nd <= 2048 ? 2000 : 6000);
+    if (dg == 128) return m >= (nd <= 4096 ? 1500 : 5000);
+    return dg == 256 && (nd <= 2048 ? m > 2048 : m >= 6000);
 }
 
 hipError_t launch_bgf_gate(const void *gb, const float *g, const void *w_down, const void *w_up, const float *w_head, float b_head, float *y,

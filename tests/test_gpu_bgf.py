@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from harness import GpuStack, max_abs, oracle, oracle_stack_config, say, stack_config
+from harness import GpuStack, launches, max_abs, oracle, oracle_stack_config, say, stack_config
 
 pytestmark = pytest.mark.gpu
 
@@ -102,9 +102,9 @@ def test_multi_block_scoring_end_to_end():
 
 
 @pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 128, 2049, 33), (512, 3, 256, 2731, 1), (256, 8, 128, 1025, 16), (256, 2, 256, 4129, 40),
-                                                (256, 3, 256, 2031, 64), (256, 1, 128, 1500, 9), (512, 5, 256, 6001, 32)])
+                                                (256, 3, 256, 2095, 64), (256, 1, 128, 1500, 9), (512, 5, 256, 6001, 32)])
 def test_few_and_many_candidates_give_the_same_bits(d, nb, dg, m, part):
-    # more than 8192 rows: the projection forms the fp32 rows' sums itself, and the tail is one launch; 1500 or 2000 candidates and more: so
+    # more than 8192 rows: the projection forms the fp32 rows' sums itself, and the tail is one launch; from 1500, 2049 or 6000 candidates on: so
     # are the gate and the head, the last 32 of them in part, an even and an odd number of steps; few: launches of their own
     import torch
     import paper_2502_09888_amd as P
@@ -118,3 +118,21 @@ def test_few_and_many_candidates_give_the_same_bits(d, nb, dg, m, part):
         few = dict(w, scen=np.ascontiguousarray(w["scen"][lo:lo + part]))
         y1, sc1 = gpu_bgf(P, torch, cfg, few, w["e"][lo:lo + part])
         assert np.array_equal(y1, y[lo:lo + part]) and np.array_equal(sc1, sc[lo:lo + part])
+
+
+@pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 2048, False), (512, 4, 256, 2049, True), (512, 8, 256, 5999, False), (512, 8, 256, 6000, True),
+                                               (512, 8, 128, 1499, False), (512, 8, 128, 1500, True), (512, 16, 128, 4999, False), (512, 16, 128, 5000, True)])
+def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, m, one):
+    import torch
+    import paper_2502_09888_amd as P
+    spec = W.StackSpec("bgf-launches", B=1, L=128, sub_len=0, M=1, n_layers=1, d_model=d, H=d // 64, dh=64, d_ffn=256, n_scen=8, n_beh=4, seed=59)
+    cfg, bf = stack_config(spec), dict(dtype=torch.bfloat16, device="cuda:0")
+    atl = {k: torch.zeros(s, **bf) for k, s in (("g1", d), ("wqkv", (d, 3 * d)), ("wo", (d, d)), ("g2", d), ("w1", (d, 256)), ("w2", (256, d)))}
+    wd, wu = torch.zeros(nb * d, dg, **bf), torch.zeros(dg, nb * d, **bf)
+    wh, ts, e = torch.zeros(nb * d, device="cuda:0"), torch.ones(8, device="cuda:0"), torch.ones(m, nb, d, device="cuda:0")
+    sc, score = torch.zeros(m, dtype=torch.int32, device="cuda:0"), torch.empty(m, device="cuda:0")
+    ws = torch.empty(P.climber_bgf_workspace_bytes(cfg, nb, dg, m), dtype=torch.uint8, device="cuda:0")
+    run = launches(lambda: P.climber_bgf_score(cfg, atl, wd, wu, wh, ts, 0.5, nb, dg, e, sc, m, None, score, ws))
+    say([tuple(k)[:2] for k in run])
+    assert (score == 0.5).all()
+    assert any("bgf_gate_kernel" in k.kernel for k in run) == one and any("bgf_gate_head_kernel" in k.kernel for k in run) != one
