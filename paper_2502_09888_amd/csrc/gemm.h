@@ -122,7 +122,8 @@ struct TailArgs {
     int x16_split;    // a multiple of 64
 };
 bool layer_tail_takes(int M, int D, int F);  // shapes it has a kernel for and is the faster way
-bool layer_tail_projects(int M, int D, int F, int n_cached);  // where that is the faster way; n_cached of the rows go to a cache
+// where that is the faster way; n_cached of the rows go to a cache, and if `ends` only their keys and values are wanted
+bool layer_tail_projects(int M, int D, int F, int n_cached, bool ends);
 bool layer_tail_reads_bf16(int M, int D, int F);
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s);
 

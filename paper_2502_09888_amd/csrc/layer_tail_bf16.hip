@@ -550,17 +550,26 @@ bool layer_tail_takes(int M, int D, int F)
 }
 
 // With the next layer's projection in the same launch its input rows, their row sums and that launch's start and end are saved; without,
-// it is dealt out over all CUs whatever the tail leaves idle.  Us per call with / without, d_model 512: encode of 32 users x 1024 four layers
-// 827 / 852, two 313 / 328, of 28 753 / 783, of 24 (384 tiles) 707 / 721, of 20 672 / 678 and, elsewhere, 673 / 666, of 17 672 / 654, of 16 (256 tiles, one per CU) 454 / 468, of 14 433 / 431, of 10 390 / 376;
-// packed forward (candidates' rows besides: one launch instead of three) of 9 users 422 / 455, 13 506 / 551, 20 855 / 858, 32 928 / 1001; scoring
-// alone, against the 128 x 128 tiles, 9766 rows 554 / 530, 16448 944 / 896, 24672 1020 / 1015, 30840 1173 / 1204.  d_model 256 (tiles two
-// per CU): encode of 9 users 141 / 151, 32 286 / 324, 64 530 / 581, scoring of 8481 rows 206 / 213, 32896 517 / 539.
-bool layer_tail_projects(int M, int D, int F, int n_cached)
+// it is dealt out over all CUs whatever the tail's last turn (a tile of 64 rows per CU) leaves idle.  d_model 512:
+// - Keys and values only (encode, before the last layer), where y is left out as well: always.  Us, encode of two layers with / without, users x
+//   1024 (16 tiles each): 9 users 109 / 118, 12 122 / 136, 17 220 / 235, 24 245 / 259, 33 364 / 381, 49 501 / 519, 64 569 / 601.
+// - Whole layers of an encode: from two turns on, and as many CUs as those pay for may stay idle, 32 for each but the first.  Us, four layers, all
+//   tails / the last one only: 10 users (160 tiles, 96 idle) 355 / 351, 14 (32 idle) 424 / 415, 16 (none) 448 / 444; 17 (272 tiles, 240 idle) 670 / 636, 24 (128)
+//   696 / 683, 28 (64) 755 / 752, 30 (32) 783 / 787, 32 (none) 822 / 825; 33 (528 tiles, 240) 1037 / 1011, 38 (160) 1057 / 1045, 40 (128) 1069 / 1066, 44 (64)
+//   1132 / 1140, 48 (none) 1201 / 1216; 49 (784 tiles, 240) 1409 / 1399, 56 (128) 1452 / 1456, 64 (none) 1601 / 1619.
+// - Packed forward: the candidates' rows besides, which are a launch of their own otherwise: 190 more.  Us, four layers, all / none: 129 tiles 354 / 371,
+//   252 511 / 552; 264 (248 idle) 764 / 742, 287 (225) 808 / 797, 297 (215) 725 / 733, 355 (157) 767 / 771, 422 842 / 879, 492 947 / 1013; 516 (252) 1092 /
+//   1100, 542 1150 / 1162, 659 1227 / 1265; 774 (250) 1558 / 1567.  271 tiles (241 idle), six layers, 1191 / 1151.
+// - Candidates alone, against the 128 x 128 tiles: 9766 rows 554 / 530, 16448 944 / 896, 24672 1020 / 1015, 30840 1173 / 1204: not.
+// d_model 256 (tiles two per CU): encode of 5 users 127 / 132, 9 141 / 151, 17 218 / 236, 32 280 / 316, 64 530 / 581, scoring of 4500 rows 195 / 193, 8481
+// 206 / 213, 32896 517 / 539: always.
+bool layer_tail_projects(int M, int D, int F, int n_cached, bool ends)
 {
     if (!layer_tail_takes(M, D, F)) return false;
     if (D == 256) return true;
-    const int tiles = (M + 63) / 64;
-    return F % 256 == 0 && M > 8192 && n_cached > 0 && (n_cached < M || tiles > 352 || (tiles > 240 && tiles <= 256));
+    if (F % 256 != 0 || M <= 8192 || n_cached == 0) return false;
+    const int tiles = (M + 63) / 64, turns = (tiles + 255) / 256, idle = turns * 256 - tiles;
+    return n_cached < M ? idle <= 32 * (turns - 1) + 190 : ends || (turns > 1 && idle <= 32 * (turns - 1));
 }
 
 bool layer_tail_reads_bf16(int M, int D, int F) { return layer_tail_takes(M, D, F) && (D == 256 || F % 256 == 0); }

@@ -285,11 +285,11 @@ int score_layers(const climber_config *cfg, const climber_weights *weights, cons
     const GivenRows given{x_cand, nullptr, (int64_t)(m_total + 63) / 64 * 64};
     TRY(rt(row_prep_bf16(x_cand, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, m_total, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
-    const bool chain = layer_tail_projects(m_total, cfg->d_model, cfg->d_ffn, 0);
+    bool projected = false;  // the layer's QKV projection is made already, by the tail before
     for (int l = 0; l < cfg->n_layers; ++l) {
-        const bool last = l + 1 == cfg->n_layers;
+        const bool last = l + 1 == cfg->n_layers, chain = !last && layer_tail_projects(m_total, cfg->d_model, cfg->d_ffn, 0, false);
         NextQkv next{};
-        if (chain && !last) {
+        if (chain) {
             next.wqkv = packed_layer(cfg, ws, l + 1).wqkv;
             next.out.rows = ws.qkv, next.out.ld_rows = 3 * cfg->d_model;
         }
@@ -297,7 +297,8 @@ int score_layers(const climber_config *cfg, const climber_weights *weights, cons
         TRY(run_layer(cfg, packed_layer(cfg, ws, l), tau + l * tl, l, CLIMBER_MODE_CANDIDATE,
                       const_cast<climber_kv_cache *>(cache), ws.x32, l == 0 ? x_cand : (const void *)ws.xb,
                       last ? y_cand : ws.x32, !last, cand_scen, cand_beh, cand_off, m_total, m_max,
-                      m_total, ws, s, chain && l > 0, next.wqkv ? &next : nullptr, as_given && l == 0 ? &given : nullptr));
+                      m_total, ws, s, projected, chain ? &next : nullptr, as_given && l == 0 ? &given : nullptr));
+        projected = chain;
     }
     return CLIMBER_OK;
 }
@@ -417,22 +418,26 @@ int climber_history_encode(const climber_config *cfg, const climber_weights *wei
     const GivenRows given{x_hist, nullptr, rows};
     TRY(rt(row_prep_bf16(x_hist, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, rows, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
-    const bool chain = layer_tail_projects((int)rows, cfg->d_model, cfg->d_ffn, cfg->flags & CLIMBER_QKV_VIA_ROWS ? 0 : (int)rows);
+    const bool direct = !(cfg->flags & CLIMBER_QKV_VIA_ROWS);  // (the cache holds rows)
+    bool projected = false;  // the layer's QKV projection is made already, by the tail before
     for (int l = 0; l < cfg->n_layers; ++l) {
-        const bool last = l + 1 == cfg->n_layers;  // nothing reads the last layer's history output
+        const bool last = l + 1 == cfg->n_layers;                // nothing reads the last layer's history output
+        const bool ends = direct && l + 2 == cfg->n_layers;      // the next layer: keys and values only
+        const bool chain = !last && layer_tail_projects((int)rows, cfg->d_model, cfg->d_ffn, direct ? (int)rows : 0, ends);
         NextQkv next{};
-        if (chain && !last) {
+        if (chain) {
             next.wqkv = packed_layer(cfg, ws, l + 1).wqkv;
             if (cache_direct_target(cfg, cache, l + 1, &next.out.qc)) {
                 next.out.n_cached = (int)rows, next.out.q = ws.qkv, next.out.ld_q = cfg->d_model;
-                if (l + 2 == cfg->n_layers) next.out.qc.which0 = 1, next.y_first = rows;  // (keys and values only)
+                if (ends) next.out.qc.which0 = 1, next.y_first = rows;
             } else {
                 next.out.rows = ws.qkv, next.out.ld_rows = 3 * cfg->d_model;
             }
         }
         TRY(run_layer(cfg, packed_layer(cfg, ws, l), tau + l * tl, l, CLIMBER_MODE_HISTORY, cache,
                       ws.x32, l == 0 ? x_hist : (const void *)ws.xb, last ? nullptr : ws.x32, !last, scen,
-                      beh, nullptr, 0, 0, rows, ws, s, chain && l > 0, next.wqkv ? &next : nullptr, as_given && l == 0 ? &given : nullptr));
+                      beh, nullptr, 0, 0, rows, ws, s, projected, chain ? &next : nullptr, as_given && l == 0 ? &given : nullptr));
+        projected = chain;
     }
     return CLIMBER_OK;
 }
@@ -557,9 +562,10 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
     // a tail over all rows makes the next layer's projection too, keys and values of the history into the cache that its
     // attention has read by then (T is a multiple of 64)
-    const bool chain = direct && layer_tail_projects((int)R, d, cfg->d_ffn, (int)T);
+    bool projected = false;  // the layer's QKV projections are made already, by the tail before
     for (int l = 0; l < cfg->n_layers; ++l) {
-        const bool last = l + 1 == cfg->n_layers;
+        const bool last = l + 1 == cfg->n_layers, ends = l + 2 == cfg->n_layers && !y_hist;  // ends: the next layer's history: keys and values only
+        const bool chain = direct && !last && layer_tail_projects((int)R, d, cfg->d_ffn, (int)T, ends);
         const PackedLayer pw = packed_layer(cfg, ws, l);
         const float *tau_l = tau + l * tl;
         const size_t crow = (size_t)T * 3 * d * 2;  // the candidates' part of the projection output
@@ -571,13 +577,13 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
             // history rows: the projection's epilogue writes keys and values into layer 0 of the scratch
             // cache as operand fragments and the queries as rows of d (none of them when nothing follows);
             // the candidates' rows get a projection launch of their own
-            if (!chain || l == 0) {
+            if (!projected) {
                 QkvOut to{};
                 to.qc = qc, to.qc.which0 = hist_out ? 0 : 1, to.n_cached = (int)T, to.q = ws.qkv, to.ld_q = d;
                 TRY(project_qkv(cfg, pw, xh, T, nin, to, s));
             }
             if (hist_out) TRY(attn_history_cached(cfg, tau_l, ws.qkv, d, scen, beh, scratch_cache, 0, ws.o, d, s));
-            if (!chain || l == 0) {
+            if (!projected) {
                 const RowNormIn nin_c{ws.ss + (size_t)T * np, np, 1.f / (float)d, cfg->rms_eps};
                 QkvOut to{};
                 to.rows = ws.qkv + crow, to.ld_rows = 3 * d;
@@ -600,14 +606,14 @@ int climber_sumi_forward(const climber_config *cfg, const climber_weights *weigh
         if (nr == 0) continue;
         float *x = ws.x32 + (size_t)r0 * d;
         NextQkv next{};
-        if (chain && !last) {
-            const bool ends = l + 2 == cfg->n_layers && !y_hist;  // (the history: keys and values only)
+        if (chain) {
             next.wqkv = packed_layer(cfg, ws, l + 1).wqkv;
             next.out.qc = qc, next.out.qc.which0 = ends, next.out.n_cached = (int)T, next.y_first = ends ? T : 0;
             next.out.q = ws.qkv, next.out.ld_q = d, next.out.rows = ws.qkv + crow, next.out.ld_rows = 3 * d;
         }
-        TRY(layer_tail(cfg, pw, x, hist_out ? x : y_cand, !last, r0, nr, ws, s, next.wqkv ? &next : nullptr,
+        TRY(layer_tail(cfg, pw, x, hist_out ? x : y_cand, !last, r0, nr, ws, s, chain ? &next : nullptr,
                        as_given && l == 0 ? &given : nullptr));
+        projected = chain;
     }
     if (y_hist && T) TRY(rt(hipMemcpyAsync(y_hist, ws.x32, (size_t)T * d * 4, hipMemcpyDeviceToDevice, s)));
     if (y_hist && m_total)

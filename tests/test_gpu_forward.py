@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from harness import GpuStack, max_abs, oracle, oracle_stack_config, say
+from harness import GpuStack, launches, max_abs, oracle, oracle_stack_config, say
 
 pytestmark = pytest.mark.gpu
 
@@ -294,6 +294,7 @@ def test_packed_forward_candidates_with_and_without_history_outputs(layers, flag
     (512, 256, 3, (384, 77, 300, 129, 512, 64, 1) * 6, 8200, 0),     # histories and candidates, each more than 8192 rows
     (512, 256, 1, (384, 130) * 17, 4133, 0), (256, 128, 1, (384,) * 11, 4097, 0),  # one layer: the inputs are its residual
     (512, 768, 2, (448,) * 19, 127, 0),                              # a uniform batch, few candidates
+    (512, 256, 3, (512, 500, 449) * 21, 65, 0),                      # encode: two turns of tiles, every tail of it with a projection
     (512, 384, 3, (500, 33) * 15, 33, 0),                            # no kernel with a projection at this d_ffn: launches of their own
     (256, 128, 3, (200, 31, 0, 96, 130) * 9, 4161, 0), (256, 384, 2, (320,) * 14, 1, 1), (256, 256, 3, (320, 65) * 12, 31, 4)])
 def test_projection_behind_the_tail_gives_the_bits_of_separate_launches(d, F, layers, lens, cands, flags):
@@ -376,3 +377,30 @@ def test_one_layer_scores_written_over_its_inputs(d, m):
         outs.append(y.clone())
     torch.cuda.synchronize()
     assert all(torch.equal(o, outs[-1]) for o in outs) and outs[-1].abs().max() > 0
+
+
+@pytest.mark.parametrize("users, cands, encode, forward", [(9, 8, 1, 3), (16, 0, 1, 1), (17, 8, 1, 0), (19, 8, 1, 3), (24, 0, 1, 1), (31, 0, 3, 3), (33, 8, 1, 3),
+                                                           (40, 0, 1, 1), (44, 0, 3, 3)])
+def test_tails_make_the_next_projection_where_that_was_measured_to_be_faster(users, cands, encode, forward):
+    # four layers, d_model 512, 16 tiles a user: how many tails of an encode and of a packed forward (without candidates: the same) do.
+    # Keys and values only (encode's last) always; whole layers by how full the last turn of 256 tiles is
+    import torch
+    import paper_2502_09888_amd as P
+    cfg, dev = P.Config(n_layers=4, n_heads=8, d_ffn=256, n_scen=1, n_beh=1, sub_len=256), "cuda:0"
+    lens, rows, m = [1024] * users, 1024 * users, cands * users
+    w = [{k: torch.zeros(s, dtype=torch.bfloat16, device=dev) for k, s in
+          (("g1", 512), ("wqkv", (512, 1536)), ("wo", (512, 512)), ("g2", 512), ("w1", (512, 256)), ("w2", (256, 512)))} for _ in range(4)]
+    buf = torch.empty(P.climber_kv_cache_bytes(cfg, lens), dtype=torch.uint8, device=dev)
+    cache = P.climber_kv_cache_create(cfg, lens, lens, buf)
+    ws = torch.empty(P.climber_workspace_bytes(cfg, rows + m), dtype=torch.uint8, device=dev)
+    x, xc, y = (torch.zeros(n, 512, dtype=t, device=dev) for n, t in ((rows, torch.bfloat16), (max(m, 1), torch.bfloat16), (max(m, 1), torch.float32)))
+    (ids, cids), tau = (torch.zeros(n, dtype=torch.int32, device=dev) for n in (rows, max(m, 1))), torch.ones(4, 1, 1, device=dev)
+    off = torch.arange(users + 1, dtype=torch.int32, device=dev) * cands
+
+    def tails(call):
+        names = [k.kernel for k in launches(call)]
+        say(names)
+        return sum("layer_tail_kernelILi512ELi2ELi8ELi8ELi0ELb1E" in n for n in names)
+
+    assert tails(lambda: P.climber_history_encode(cfg, w, tau, x, ids, ids, cache, ws)) == encode
+    assert tails(lambda: P.climber_sumi_forward(cfg, w, tau, x, ids, ids, xc, off, m, cands, cids, cids, cache, None, y, ws)) == forward
