@@ -117,13 +117,30 @@ class GpuAttention:
         t = self.torch
         o = t.full((self.qh.shape[0], self.d), float("nan"), dtype=self.dt, device="cuda:0") \
             if want_output else None
-        self.P.climber_attn_history(self.cfg, self.tau, self.qh, self.kh, self.vh, self.scen,
-                                    self.beh, self.cache, 0, o)
+        self.launch_history(o)
         t.cuda.synchronize()
         return None if o is None else o.float().cpu().numpy()
 
+    def launch_history(self, o):
+        self.P.climber_attn_history(self.cfg, self.tau, self.qh, self.kh, self.vh, self.scen,
+                                    self.beh, self.cache, 0, o)
+
+    def history_launches(self):
+        o = self.torch.empty((self.qh.shape[0], self.d), dtype=self.dt, device="cuda:0")
+        return launches(lambda: self.launch_history(o))
+
     def sumi(self, sel=None):
         """Score all candidates (sel None) or, per user, the candidate sub-range sel=(lo, hi)."""
+        call, o, m_total = self.sumi_call(sel)
+        call()
+        self.torch.cuda.synchronize()
+        return o[:m_total].float().cpu().numpy()
+
+    def sumi_launches(self, sel=None):
+        return launches(self.sumi_call(sel)[0])
+
+    def sumi_call(self, sel):
+        """(what scores them, its outputs, their number)"""
         t, w = self.torch, self.w
         if sel is None:
             qc, kc, vc, cs, cb, off = self.qc, self.kc, self.vc, self.cscen, self.cbeh, self.cand_off
@@ -144,10 +161,8 @@ class GpuAttention:
         m_total = int(off_h[-1])
         m_max = int(np.diff(off_h).max()) if m_total else 0
         o = t.full((max(m_total, 1), self.d), float("nan"), dtype=self.dt, device="cuda:0")
-        self.P.climber_attn_sumi(self.cfg, self.tau, self.cache, 0, qc, kc, vc, off, m_total, m_max,
-                                 cs, cb, o)
-        t.cuda.synchronize()
-        return o[:m_total].float().cpu().numpy()
+        return (lambda: self.P.climber_attn_sumi(self.cfg, self.tau, self.cache, 0, qc, kc, vc, off, m_total, m_max,
+                                                 cs, cb, o)), o, m_total
 
 
 def oracle_history(w, causal=False):

@@ -13,7 +13,14 @@ TOL = {"f32": 1e-4, "bf16": 2e-2}
 TWO_KERNEL = 2   # config flag: history pass as cache writer + tiled attention
 
 
-def check_all(w, causal=False, hist=True, flags=0):
+WAVE, SPLIT, TILES = "attn_wave_kernel", "attn_split_kernel", "attn_bf16_kernel"
+
+
+def takes(run, kernel):
+    return any(kernel in k.kernel for k in run)
+
+
+def check_all(w, causal=False, hist=True, flags=0, hist_takes=None, sumi_takes=None):
     spec = w["spec"]
     say(f"[case] {spec.name} dtype={spec.dtype} B={spec.B} L={spec.L} sub={spec.sub_len} M={spec.M} "
         f"H={spec.H} dh={spec.dh} qk_scale={spec.qk_scale} causal={causal} flags={flags} seed={spec.seed}")
@@ -29,6 +36,8 @@ def check_all(w, causal=False, hist=True, flags=0):
         assert np.all(oh[~ok] == 0)
     else:
         g.history(want_output=False)
+    assert hist_takes is None or takes(g.history_launches(), hist_takes)
+    assert sumi_takes is None or takes(g.sumi_launches(), sumi_takes)
     os_ = g.sumi()
     ref = oracle_sumi(w)
     e = max_abs(os_, ref)
@@ -139,8 +148,8 @@ def test_bf16_ragged_lengths_nan_padding():
 
 def test_bf16_causal_history():
     # history token i sees j <= i of its subsequence.  Subsequences of 128 (the one-kernel pass: wave w
-    # stops after key block w) and 256 (so few of them: tiles from rows), under the two-kernel flag a wave
-    # per 32 queries, one undivided sequence spanning several query
+    # stops after key block w) and 256 (so few of them: tiles from rows), under the two-kernel flag keys shared
+    # out among waves, one undivided sequence spanning several query
     # tiles, ragged lengths with NaN padding, large logits (the running-maximum pass of these
     # kernels); the candidate pass on the cache that the causal history call wrote.
     for name, kw in (("bf16-causal-sub128", dict(B=3, L=384, sub_len=128, M=40, H=2, seed=41)),
@@ -223,6 +232,21 @@ def test_bf16_randomized_shapes_scales_routes():
         check_all(W.make_attention(spec), causal=bool(rng.integers(0, 2)), flags=int(rng.choice([0, TWO_KERNEL])))
 
 
+def test_bf16_randomized_shapes_by_a_wave_per_32_queries():
+    # batches of a size between those whose keys are shared out among waves and those that fill tiles; logits, routes and lengths as above
+    rng, wave = np.random.Generator(np.random.Philox(20250211)), 0
+    for i in range(16):
+        L = int(rng.integers(130, 500))
+        M = int(rng.choice([150, 170, 200]))
+        spec = W.shrink(W.CONFIG2, name=f"bf16-wave-sweep-{i}", B=int(rng.integers(7, 10)), L=L, L_min=int(rng.integers(0, L + 1)),
+                        sub_len=int(rng.choice([0, 128, 256])), M=M, M_min=int(rng.integers(1, M + 1)), H=8, pad_to=64,
+                        nan_padding=bool(rng.integers(0, 2)), n_scen=int(rng.integers(1, 9)), n_beh=int(rng.integers(1, 5)),
+                        qk_scale=float(rng.choice([0.125, 0.125, 0.3, 0.7, 1.5, 6.0])), seed=6200 + i)
+        g, _ = check_all(W.make_attention(spec), causal=bool(rng.integers(0, 2)), flags=int(rng.choice([0, TWO_KERNEL])))
+        wave += takes(g.history_launches(), WAVE) + takes(g.sumi_launches(), WAVE)
+    assert wave >= 12
+
+
 def test_bf16_single_subsequence_and_odd_lengths():
     spec = W.shrink(W.CONFIG2, name="bf16-onesub", B=2, L=333, L_min=77, sub_len=0, M=70, H=1,
                     nan_padding=True, seed=23)
@@ -268,7 +292,8 @@ def test_bf16_candidate_isolation_and_chunking_are_bitwise():
 @pytest.mark.parametrize("L,sub", [(1, 0), (32, 0), (33, 0), (64, 128), (65, 0), (97, 128), (128, 0), (129, 128), (161, 0), (289, 256),
                                    (700, 512)])
 def test_few_and_many_queries_give_the_same_bits(L, sub):
-    # few queries: a wave per 32 of them, groups of four 32-key blocks; many: 256-query tiles on a ring of 64-key
+    # few queries: a wave per 32 of them, groups of four 32-key blocks (up to 200 candidates of histories from 128 on: a tile's keys shared out
+    # among waves); many: 256-query tiles on a ring of 64-key
     # tiles.  Histories at the edges of blocks, groups and tiles; candidate counts at the edges of the wave's 32
     spec = W.shrink(W.CONFIG2, name=f"bf16-few-{L}", B=1, L=L, sub_len=sub, M=8400, H=4, pad_to=64, nan_padding=True, seed=700 + L)
     w = W.make_attention(spec)
@@ -276,17 +301,19 @@ def test_few_and_many_queries_give_the_same_bits(L, sub):
     oh, ok = g.history(), valid_rows(w)
     assert max_abs(oh[ok], oracle_history(w)[ok]) < 2e-2 and np.all(oh[~ok] == 0)
     full = g.sumi()
-    for n in (1, 31, 33, 200):
-        part = g.sumi(sel=(7, 7 + n))
-        assert np.array_equal(part, full[7:7 + n])
-        if n == 200:
-            assert max_abs(part, oracle_sumi(w)[7:7 + n]) < 2e-2
+    assert takes(g.sumi_launches(), TILES)
+    for lo, n in ((7, 1), (7, 31), (7, 33), (7, 200), (0, 1100)):  # (1100 from 0: the form is chosen for 64 queries, here the same 64)
+        part = g.sumi(sel=(lo, lo + n))
+        assert takes(g.sumi_launches(sel=(lo, lo + n)), SPLIT if n <= 200 and L >= 128 else WAVE)
+        assert np.array_equal(part, full[lo:lo + n])
+        if n >= 200:
+            assert max_abs(part, oracle_sumi(w)[lo:lo + n]) < 2e-2
 
 
 def test_few_and_many_queries_choose_the_same_form_of_the_softmax():
     # two rows whose temperature wants the scale in fp32 (exponents of 7 in the mean) among rows that fold it into
     # the query: one in the second half of 64 queries, one in the first half of the next.  The choice is made for 64
-    # queries at a time, however many are in the launch.
+    # queries at a time, however many are in the launch: keys shared out among waves, a wave per 32 queries, tiles.
     spec = W.shrink(W.CONFIG2, name="bf16-mixed-forms", B=1, L=700, sub_len=0, M=8400, H=4, pad_to=64, seed=717)
     w = W.make_attention(spec)
     w["tau"] = np.full_like(w["tau"], 2.0)
@@ -295,9 +322,11 @@ def test_few_and_many_queries_choose_the_same_form_of_the_softmax():
     w["cscen"][[40, 70]] = w["cbeh"][[40, 70]] = 0
     g = GpuAttention(w)
     g.history()
-    full, part = g.sumi(), g.sumi(sel=(0, 192))
-    assert np.array_equal(part, full[:192])
-    assert max_abs(part, oracle_sumi(w)[:192]) < 2e-2
+    full = g.sumi()
+    for n, kernel in ((192, SPLIT), (1100, WAVE)):
+        part = g.sumi(sel=(0, n))
+        assert takes(g.sumi_launches(sel=(0, n)), kernel) and np.array_equal(part, full[:n])
+    assert takes(g.sumi_launches(), TILES) and max_abs(part, oracle_sumi(w)[:1100]) < 2e-2
 
 
 @pytest.mark.parametrize("L,L_min,n_scen", [(128, 128, 8), (129, 129, 17), (160, 160, 8), (191, 0, 8), (255, 255, 8), (256, 256, 17), (257, 257, 8),
@@ -317,6 +346,7 @@ def test_keys_shared_out_among_waves_give_the_bits_of_other_launches(L, L_min, n
     full = g.sumi()
     for n in (1, 33, 200, 1100):
         part = g.sumi(sel=(7, 7 + n))
+        assert takes(g.sumi_launches(sel=(7, 7 + n)), WAVE if n == 1100 else SPLIT)
         assert np.array_equal(part, full[g.last_idx])
 
 
@@ -330,34 +360,41 @@ def test_keys_shared_out_among_waves_where_one_key_outgrows_the_rest(L):
     g = GpuAttention(w)
     g.history()
     full, part = g.sumi(), g.sumi(sel=(0, 70))
+    assert takes(g.sumi_launches(), WAVE) and takes(g.sumi_launches(sel=(0, 70)), SPLIT)
     assert np.isfinite(full).all() and np.array_equal(part, full[:70])
     assert max_abs(part, oracle_sumi(w)[:70]) < 2e-2
 
 
-@pytest.mark.parametrize("L", [20, 40, 70, 100, 130, 257])
+@pytest.mark.parametrize("L", [20, 40, 70, 100, 130, 190, 257])
 def test_few_queries_keep_an_infinite_value_infinite(L):
     # one to nine blocks of 32 keys, odd and even: a value of the last one that every row sees, by the wave per 32
-    # queries and by the tiles
+    # queries, from 128 keys on by the waves that share them, and by the tiles
     spec = W.shrink(W.CONFIG2, name=f"bf16-inf-{L}", B=1, L=L, sub_len=0, M=8400, H=4, pad_to=64, nan_padding=True, seed=760 + L)
     w = W.make_attention(spec)
     w["vh"] = w["vh"].copy()
     w["vh"][L - 1, 2, 5] = np.inf
     g = GpuAttention(w)
     oh, ok = g.history(), valid_rows(w)
-    full, part = g.sumi(), g.sumi(sel=(0, 192))
-    at = 2 * 64 + 5
-    assert np.all(oh[ok][:, at] == np.inf) and np.all(part[:, at] == np.inf)
-    assert np.array_equal(part, full[:192]) and np.isfinite(np.delete(oh[ok], at, 1)).all()
+    full, at = g.sumi(), 2 * 64 + 5
+    for n, kernel in ((192, SPLIT if L >= 128 else WAVE), (1100, WAVE)):
+        part = g.sumi(sel=(0, n))
+        assert takes(g.sumi_launches(sel=(0, n)), kernel) and np.all(part[:, at] == np.inf) and np.array_equal(part, full[:n])
+    assert np.all(oh[ok][:, at] == np.inf) and np.isfinite(np.delete(oh[ok], at, 1)).all()
 
 
-@pytest.mark.parametrize("L,sub", [(31, 0), (64, 0), (130, 0), (385, 0), (530, 384), (1100, 512), (1100, 0)])
+@pytest.mark.parametrize("L,sub,B,H,rows,cache", [(31, 0, 2, 2, TILES, WAVE), (64, 0, 2, 2, TILES, WAVE), (130, 0, 2, 2, TILES, WAVE),
+                                                  (130, 0, 7, 8, TILES, WAVE), (150, 0, 2, 2, TILES, SPLIT), (385, 0, 2, 2, TILES, SPLIT), (410, 0, 2, 2, SPLIT, SPLIT), (385, 0, 3, 8, TILES, WAVE),
+                                                  (530, 384, 2, 2, TILES, SPLIT), (550, 384, 2, 8, TILES, WAVE), (1100, 512, 2, 2, TILES, WAVE),
+                                                  (1100, 0, 2, 2, WAVE, WAVE)])
 @pytest.mark.parametrize("flags", [0, TWO_KERNEL])
-def test_few_queries_causal_history(L, sub, flags):
-    # tiles from rows (but for 1100 in one subsequence), and a wave per 32 queries from the cache
-    spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=2, L=L, sub_len=sub, M=4, H=2, pad_to=64, L_min=max(1, L - 20),
+def test_few_queries_causal_history(L, sub, B, H, rows, cache, flags):
+    # tiles from rows or, from the cache, a wave per 32 queries or a tile's keys shared out among waves
+    spec = W.shrink(W.CONFIG2, name=f"bf16-few-causal-{L}", B=B, L=L, sub_len=sub, M=4, H=H, pad_to=64, L_min=max(1, L - 20),
                     nan_padding=True, seed=730 + L)
     w = W.make_attention(spec)
-    oh, ok = GpuAttention(w, causal=True, flags=flags).history(), valid_rows(w)
+    g = GpuAttention(w, causal=True, flags=flags)
+    oh, ok = g.history(), valid_rows(w)
+    assert takes(g.history_launches(), cache if flags else rows)
     assert max_abs(oh[ok], oracle_history(w, causal=True)[ok]) < 2e-2 and np.all(oh[~ok] == 0)
 
 
@@ -442,43 +479,44 @@ def sigma_t(spec, w):
 
 
 @pytest.mark.parametrize("qk_scale", [0.25, 0.5, 1.0, 2.0])
-@pytest.mark.parametrize("M,B,H", [(40, 2, 2), (300, 2, 2), (100, 36, 4), (300, 14, 8)])
-def test_bf16_logit_scale_sweep(qk_scale, M, B, H):
+@pytest.mark.parametrize("M,B,H,kernel", [(40, 2, 2, SPLIT), (300, 2, 2, SPLIT), (40, 24, 8, WAVE), (300, 4, 8, WAVE), (100, 36, 4, TILES), (300, 14, 8, TILES)])
+def test_bf16_logit_scale_sweep(qk_scale, M, B, H, kernel):
     # N(0,1) inputs with logit scales between the unit-scale benchmark (0.125) and the overflow case:
     # the regime in which the pass that folds the temperature into a bf16 query is still accepted for
-    # some rows while its rounding error (relative 2^-9 of a logit) grows with the logits.  Two users
-    # take a wave per 32 candidates, 36 of 100 the 128-query tile (576 waves would be more than 512),
-    # 14 of 300 the 256-query tile (1120, 1024); history on both routes.
+    # some rows while its rounding error (relative 2^-9 of a logit) grows with the logits.  Two users' keys are
+    # shared out among waves, 24 of 40 and 4 of 300 take a wave per 32 candidates, 36 of 100 the 128-query tile (576 waves would be
+    # more than 512), 14 of 300 the 256-query tile (1120, 1024); history on both routes.
     spec = W.shrink(W.CONFIG2, name=f"bf16-logits-{qk_scale}-M{M}-B{B}", B=B, L=512, sub_len=128, M=M, H=H,
                     qk_scale=qk_scale, seed=50 + M)
     w = W.make_attention(spec)
     say(f"  logit std at the smallest temperature: {sigma_t(spec, w):.1f} (log2 units)")
-    check_all(w)
-    check_all(w, flags=TWO_KERNEL)
+    check_all(w, sumi_takes=kernel)
+    check_all(w, flags=TWO_KERNEL, hist_takes=SPLIT if B == 2 else WAVE if B == 4 else TILES)
 
 
-@pytest.mark.parametrize("B,H", [(3, 2), (14, 8)])
-def test_bf16_large_logits_in_wide_tile_and_mixed_batch(B, H):
-    # logits in the hundreds with M > 128 (a wave per 32 candidates; and, with 14 users of 8 heads, the 256-query
-    # tile: both redo their rows with a running maximum),
+@pytest.mark.parametrize("B,H,kernel", [(3, 2, SPLIT), (4, 8, WAVE), (14, 8, TILES)])
+def test_bf16_large_logits_in_wide_tile_and_mixed_batch(B, H, kernel):
+    # logits in the hundreds with M > 128 (keys shared out among waves; with 4 users of 8 heads a wave per 32 candidates, with 14 the
+    # 256-query tile: all redo their rows with a running maximum),
     # then a batch in which only user 0 has large logits: some workgroups of the launch fall back,
     # the others do not
     spec = W.shrink(W.CONFIG2, name="bf16-biglogits-wide", B=B - 1 if B == 3 else B, L=384, sub_len=128, M=300, H=H,
                     qk_scale=12.0, seed=28)
-    check_all(W.make_attention(spec))
+    check_all(W.make_attention(spec), sumi_takes=kernel)
     spec = W.shrink(W.CONFIG2, name="bf16-mixed-logits", B=B, L=384, sub_len=128, M=300, H=H, seed=29)
     w = W.make_attention(spec)
     c0, c1 = w["cand_off"][0], w["cand_off"][1]
     w["qc"][c0:c1] *= 64.0             # power of two: still exactly representable
     w["qh"][:w["tok_off"][1]] *= 64.0
-    check_all(w)
-    check_all(w, flags=TWO_KERNEL)
+    check_all(w, sumi_takes=kernel)
+    check_all(w, flags=TWO_KERNEL, hist_takes=kernel if B < 14 else None)
 
 
-def test_bf16_rows_whose_logits_are_all_very_negative():
+@pytest.mark.parametrize("B,H,kernel", [(2, 2, SPLIT), (7, 8, WAVE)])
+def test_bf16_rows_whose_logits_are_all_very_negative(B, H, kernel):
     # every key points away from every query: all logits of a row are far below zero (beyond the
     # exponent range once scaled), bidirectional and causal (one-key rows), both history routes
-    spec = W.shrink(W.CONFIG2, name="bf16-negative-logits", B=2, L=256, sub_len=128, M=150, H=2,
+    spec = W.shrink(W.CONFIG2, name="bf16-negative-logits", B=B, L=256, sub_len=128, M=150, H=H,
                     qk_scale=12.0, seed=30)
     w = W.make_attention(spec)
     rng = np.random.Generator(np.random.Philox(3000))
@@ -488,8 +526,8 @@ def test_bf16_rows_whose_logits_are_all_very_negative():
         w[q] = W.round_bf16(u + 0.1 * w[q])
         w[k] = W.round_bf16(-u + 0.1 * w[k])
     w["kh"] = W.round_bf16(-u + 0.1 * rng.standard_normal(w["kh"].shape).astype(np.float32))
-    check_all(w)
-    check_all(w, flags=TWO_KERNEL)
+    check_all(w, sumi_takes=kernel)
+    check_all(w, flags=TWO_KERNEL, hist_takes=kernel)
     check_all(w, causal=True)
 
 
@@ -578,12 +616,13 @@ def test_bf16_tiles_redo_the_rows_that_one_key_outgrows(B, M, rows):
 @pytest.mark.parametrize("B,L,L_min,sub,H,pad", [(1, 1, 1, 0, 1, 64), (3, 63, 0, 384, 2, 64), (3, 65, 64, 0, 1, 64), (4, 129, 0, 512, 2, 64),
                                                  (5, 300, 1, 0, 4, 64), (2, 448, 256, 0, 2, 128), (6, 700, 0, 640, 3, 64), (2, 1024, 900, 512, 8, 64),
                                                  (30, 1100, 400, 512, 8, 64), (25, 1500, None, 0, 8, 128), (40, 830, None, 384, 8, 64), (16, 1000, None, 512, 8, 64),
-                                                 (3, 500, 1, 256, 4, 64), (14, 1000, 100, 256, 8, 64), (5, 300, 0, 128, 4, 64)])
+                                                 (3, 500, 1, 256, 4, 64), (14, 1000, 100, 256, 8, 64), (5, 300, 0, 128, 4, 64),
+                                                 (8, 300, 1, 0, 8, 64), (7, 448, 256, 0, 8, 128), (6, 500, 1, 256, 8, 64), (9, 300, 0, 128, 8, 64)])
 @pytest.mark.parametrize("causal", [False, True])
 def test_history_from_rows_writes_the_bits_of_two_launches(B, L, L_min, sub, H, pad, causal):
     # outputs and the whole cache, over what was in both before: tiles of 128 queries (few of them, subsequences of odd multiples of 128)
     # and of 256 (four), histories down to none, at the edges of blocks and tiles, tiles of padding only; NaN in the padding; subsequences
-    # of 256 and 128, few of them and many
+    # of 256 and 128, few of them and many; from the cache by all three kernels
     import torch
     spec = W.shrink(W.CONFIG2, name=f"bf16-rows-{L}-{sub}", B=B, L=L, L_min=L_min, sub_len=sub, M=1, H=H, pad_to=pad, nan_padding=True, seed=840 + L)
     w = W.make_attention(spec)
@@ -607,11 +646,11 @@ def test_history_from_rows_writes_the_bits_of_two_launches(B, L, L_min, sub, H, 
         assert torch.equal(g.buf[-payload:], out[0][1])
 
 
-@pytest.mark.parametrize("B,H", [(2, 2), (30, 8)])
-def test_history_from_rows_redoes_a_tile_that_one_key_outgrows(B, H):
+@pytest.mark.parametrize("B,H,kernel", [(2, 2, SPLIT), (4, 8, WAVE), (30, 8, TILES)])
+def test_history_from_rows_redoes_a_tile_that_one_key_outgrows(B, H, kernel):
     # 2^115 above the other keys of the row (window 2^100): the whole tile (of 128 queries; with 30 users, 960 tiles of 256)
-    # walks once more over the rows, up to a last tile of keys that ends in NaN; and over the cache (two users: a wave per 32
-    # queries).  TOL: see above.
+    # walks once more over the rows, up to a last tile of keys that ends in NaN; and over the cache (two users: keys shared out among
+    # waves, four: a wave per 32 queries).  TOL: see above.
     spec = W.shrink(W.CONFIG2, name=f"bf16-rows-redo-{B}", B=B, L=1000, sub_len=512, M=1, H=H, pad_to=64, nan_padding=True, seed=850)
     w = W.make_attention(spec)
     w["tau"], w["qh"] = np.ones_like(w["tau"]), w["qh"].copy()
@@ -621,16 +660,16 @@ def test_history_from_rows_redoes_a_tile_that_one_key_outgrows(B, H):
             w["qh"][t0 + r] = W.round_bf16(w["kh"][t0 + key] * (80 / (w["kh"][t0 + key] ** 2).sum(-1, keepdims=True) * 8))
     w["vh"] = w["vh"].clip(-3.9375, 3.9375)
     for flags in (0, TWO_KERNEL):
-        check_all(w, flags=flags)
-        check_all(w, causal=True, flags=flags)
+        check_all(w, flags=flags, hist_takes=kernel if flags else None)
+        check_all(w, causal=True, flags=flags, hist_takes=kernel if flags else None)
 
 
-@pytest.mark.parametrize("B", [2, 36])
+@pytest.mark.parametrize("B", [2, 3, 36])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("flags", [0, TWO_KERNEL])
 def test_bf16_history_row_of_a_tiny_temperature_among_ordinary_ones(B, causal, flags):
-    # a temperature of 1e-10 (exponents of 2e7: the row is its best key's value) in one row of a tile, the others as usual: a wave
-    # per 32 queries, tiles from rows and from the cache.  Under the causal flag the row sees keys of its tile's first block
+    # a temperature of 1e-10 (exponents of 2e7: the row is its best key's value) in one row of a tile, the others as usual: keys shared
+    # out among waves (2 users), a wave per 32 queries (3, two kernels), tiles from rows and from the cache.  Under the causal flag the row sees keys of its tile's first block
     # only.  TOL: see above (an output is one value row, below 4: its own rounding is 2^-7).
     spec = W.shrink(W.CONFIG2, name=f"bf16-tiny-tau-{B}", B=B, L=700, sub_len=512, M=4, H=4, pad_to=64, nan_padding=True, seed=860)
     w = W.make_attention(spec)
@@ -644,7 +683,7 @@ def test_bf16_history_row_of_a_tiny_temperature_among_ordinary_ones(B, causal, f
             k = w["kh"][int(w["tok_off"][b]) + key]
             w["scen"][at] = 1
             w["qh"][at] = W.round_bf16(k * (0.01 / (k ** 2).sum(-1, keepdims=True)))
-    check_all(w, causal=causal, flags=flags)
+    check_all(w, causal=causal, flags=flags, hist_takes=SPLIT if B == 2 else WAVE if B == 3 and flags else TILES)
 
 
 @pytest.mark.parametrize("B,M,H", [(36, 100, 4), (16, 530, 4), (24, 500, 8)])
