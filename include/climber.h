@@ -77,10 +77,10 @@ extern "C" {
 #define CLIMBER_BF16 1
 
 #define CLIMBER_HIST_CAUSAL 1 /* flags bit 0: history token i only sees j <= i of its subsequence */
-/* Path selection, results equal to within rounding.  The bf16 history pass has two routes where
- * sub_len is 128 or 256: one kernel that stores the cache blocks and attends (default), or cache
- * writer + tiled attention (the route of every other sub_len). */
-#define CLIMBER_HIST_TWO_KERNEL 2 /* flags bit 1: always take the cache writer + tiled attention route */
+/* Path selection, results equal to within rounding.  The bf16 history pass has two routes: one launch that stores the
+ * cache blocks and attends, where it is the faster way and the outputs allow it (default), or cache writer + attention
+ * from the cache. */
+#define CLIMBER_HIST_TWO_KERNEL 2 /* flags bit 1: always take the cache writer + attention route */
 /* The stack's fused QKV projection writes history keys / values into the cache from its epilogue
  * (default), or stores them as rows that the history pass then copies into the cache. */
 #define CLIMBER_QKV_VIA_ROWS 4    /* flags bit 2: keys / values go through rows */
@@ -211,7 +211,7 @@ typedef struct climber_rel_bias {
 } climber_rel_bias;
 
 /* climber_attn_history / climber_attn_sumi with the bias term (bias != NULL; everything else as
- * documented there).  The bf16 history pass takes the cache writer + tiled attention route.
+ * documented there).
  * Additional errors: CLIMBER_ERR_NULL (bias or a pointer it needs), _SHAPE (n_pos even or < 1,
  * n_time < 1), _ALIGN (hist_pos / hist_ts). */
 int climber_attn_history_bias(const climber_config *cfg, const float *tau_layer, const void *q,

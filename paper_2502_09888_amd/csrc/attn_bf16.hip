@@ -698,7 +698,7 @@ bool hist_wide_tiles(const AttnArgs &a)
 
 // Launches of few queries go to attn_wave_bf16.hip: at most one wave of 32 per SIMD (1024), fewer where the tiles are well
 // filled or the walk is too short to hide a launch's ends.  Us per call there / here, 8 heads.
-//   candidates, more than 128 or up to 64 a user: 200 of one user against 1000 (56 waves) 11.8 / 19.4, 256 of 16 (1024)
+//   candidates, more than 128 or up to 64 a user: 200 of 8 against 1000 (448 waves) 14.3 / 20.0, 256 of 16 (1024)
 //     against 1024 17.8 / 20.9, against 256 9.0 / 9.0, against 128 9.0 / 8.0; 64 of 64 (1024) against 512 14.8 / 15.8,
 //     against 128 9.2 / 7.6; 10 of 66 (528) against 193, the history pass with it, 40.7 / 44.9; 256 of 32 (2048) 31 / 27
 //   65 to 128 (128-query tiles, full ones): 128 of 8 (256) against 1024 11.5 / 12.8, of 16 (512) 13.4 / 14.0, against 512

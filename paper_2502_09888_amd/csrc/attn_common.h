@@ -52,7 +52,7 @@ struct KParams {
     int B, H, n_scen, n_beh, sub_len, n_qtiles;
     int uni_len, uni_pad;  // >= 0: every user has this valid / padded history length
     int uni_cand;          // >= 0: every user has this many candidates (SUMI)
-    int pilot_pairs;       // attn_wave_bf16.hip: the choice of the softmax form is made for 64 queries
+    int pilot_pairs;       // attn_wave_bf16.hip, attn_split_bf16.hip: the choice of the softmax form is made for 64 queries
     float scale_log2e, inv_qk_scale;
     BiasArgs bias;  // relative attention bias (attn_bias_bf16.hip)
     int bias_H;

@@ -293,7 +293,9 @@ __global__ __launch_bounds__((NP + 2) * 64, 2) void attn_split_kernel(const KPar
         }
         lt = st.l[0] + xhalf(st.l[0]);
     }
-    meet();  // nobody reads the tile's rows any more: the output may lie on them
+    // No wave of the workgroup reads the tile's rows any more: a history tile's output may lie on its key and value rows.  (Candidates'
+    // outputs lie apart from their inputs: with pilot_pairs the neighbouring workgroup reads these query rows, in no order.)
+    meet();
     uint8_t *half = tr + db * 32 * kHalfPitch;
     const float inv = 1.f / lt;
 #pragma unroll

@@ -1,7 +1,9 @@
 // bf16 MFMA attention for launches of few queries (gfx950): the SUMI candidate pass and the block-diagonal
 // history pass of Climber (arXiv 2502.09888, Eq. (3), Sec. 3.1.2, Sec. 3.2) where the 128- and 256-query tiles
-// of attn_bf16.hip make too few workgroups: a request's 200 candidates are eight workgroups there, one per head,
-// and the launch takes as long as one of them walks over the history.
+// of attn_bf16.hip make too few workgroups: 200 candidates of eight users are 64 workgroups there, one per head,
+// and the launch takes as long as one of them walks over the history.  (Fewer still share a tile's keys out among waves,
+// attn_split_bf16.hip.)  Us there / here, 8 heads: those 200 against 1000 20.0 / 14.3, of 12 users against 4000 59.6 / 36.6, 256 of 16 against
+// 1024 21.9 / 18.9; history pass of one user's 4096 in one subsequence 52.5 / 45.8.
 //
 // One wave = one workgroup = 32 queries of one (user, head).  The cache holds keys and values as MFMA operand
 // fragments, so the wave loads them from global memory (L2; the waves of a head run on one XCD) straight into
@@ -26,7 +28,7 @@ using namespace attn;
 constexpr int kRing = 2;  // blocks of 32 keys (and as many of 32 values) in flight or in use
 
 // (Two waves per SIMD in the bounds, although a launch has at most one: with all the registers to itself the candidate pass
-// uses no scratch memory and takes 13.3 us instead of 11.7 for 200 candidates, the history pass of 4096 rows 50 instead of 47.)
+// uses no scratch memory and takes 15.3 us instead of 14.3 for 200 candidates of 8 users, the history pass of 4096 rows 48.4 instead of 45.8.)
 template <bool SUMI, bool CAUSAL>
 __global__ __launch_bounds__(64, 2) void attn_wave_kernel(const KParams p)
 {

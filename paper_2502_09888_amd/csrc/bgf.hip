@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void bgf_attention_kernel(const __bf16 *qkv, _
     }
 }
 
-// g: fp32 [m][nd] (the fusion layer's output), pre: bf16 [m][nd] (f_gate(G) before the sigmoid);
+// four values of Y = G (.) sigmoid(pre), and their part of the head's sum
 __device__ __forceinline__ float4 gated(const float4 &g, const bf16x4 &pre)
 {
     float4 y;
@@ -97,7 +97,8 @@ __device__ __forceinline__ float head_sum(const float4 &y, const float4 &w, floa
     return fmaf(y.x, w.x, fmaf(y.y, w.y, fmaf(y.z, w.z, fmaf(y.w, w.w, sum))));
 }
 
-// y (nullable): fp32 [m][nd]; score: [m].  One wavefront per candidate.
+// g: fp32 [m][nd] (the fusion layer's output), pre: bf16 [m][nd] (f_gate(G) before the sigmoid); y (nullable): fp32 [m][nd];
+// score: [m].  One wavefront per candidate.
 __global__ __launch_bounds__(256) void bgf_gate_head_kernel(const float *g, const __bf16 *pre, const float *w_head,
                                                             float b_head, float *y, float *score, int64_t m, int nd)
 {
@@ -122,8 +123,10 @@ __global__ __launch_bounds__(256) void bgf_gate_head_kernel(const float *g, cons
 // hidden, the rows by way of registers into a double buffer of 256 columns, weights from L2 into registers.  Up: 256 columns a
 // step, a wave per 32 of them; their bf16 values meet G in LDS, where a wave takes whole rows as bgf_gate_head_kernel does: the same
 // bits as by the three launches.  8192 candidates x 4 blocks of 512, d_gate 256: 66 us instead of 25 + 19 + 30, of which the bytes of G and
-// Y take 33 and the weights' way from L2 (2 MB a workgroup) about as long; fragments further ahead (16 instead of 8) and G two steps
-// ahead change nothing.  Registers for two workgroups per CU (344 -> 333 us the call; three spilled).
+// Y take 33 and the weights' way from L2 (2 MB a workgroup) about as long (waves issue or wait to issue half of their time, matrix
+// cores busy 10 %); fragments further ahead (16 instead of 8) and G two steps ahead change nothing.  Registers for two workgroups
+// per CU, us the call with / without: 8500 candidates 432 / 437, 9500 438 / 444, 12000 x 4 of 256 202 / 205; up to 8192, a workgroup per CU, the
+// three spilled registers cost 1 % (4200 254.5 / 251.6).
 template <int DG>
 __global__ __launch_bounds__(512, 4) void bgf_gate_kernel(const __bf16 *gb, const float *g, const __bf16 *w_down, const __bf16 *w_up,
                                                           const float *w_head, float b_head, float *y, float *score, int m, int nd)
