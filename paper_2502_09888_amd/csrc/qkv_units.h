@@ -37,6 +37,91 @@ static __device__ __forceinline__ u32x4 unit_frag(__amdgpu_buffer_rsrc_t w, int 
     return __builtin_amdgcn_raw_buffer_load_b128(w, lane * 16, at + (2 * unit + e % 2) * (K / 16 * 1024) + e / 2 * 1024, 0);
 }
 
+static __device__ __forceinline__ uint32_t pack2(float x, float y)
+{
+    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+    bf16x2 v;
+    v[0] = (__bf16)x, v[1] = (__bf16)y;
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// acc = the tile's rows times the 64 columns of `unit`, as (rows, weights) if V, else (weights, rows).  `ring` holds the unit's
+// first 2 R fragments, at the end those of `next`; a_base: LdsRows::base of the lane.
+template <int K, int RB, int R, bool V>
+static __device__ __forceinline__ void unit_product(f32x16 (&acc)[RB][2], const uint8_t *rows, __amdgpu_buffer_rsrc_t w, int w_at, u32x4 (&ring)[2 * R],
+                                                    uint32_t a_base, int unit, int next, int lane)
+{
+    constexpr int S = K / 16;
+    static_assert(S % R == 0 && S / R >= 2, "");
+    uint32_t base = a_base;
+    asm("" : "+v"(base));
+    bf16x8 fa[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) fa[i] = LdsRows<K>::frag(rows, base, 0, i);
+    auto steps = [&](int s0, auto first_tag, auto last_tag) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value;
+        static_for<R>([&](auto t_tag) __attribute__((always_inline)) {
+            constexpr int t = decltype(t_tag)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<2 * RB>([&](auto n_tag) __attribute__((always_inline)) {
+                constexpr int i = decltype(n_tag)::value / 2, j = decltype(n_tag)::value % 2;
+                const bf16x8 wf = __builtin_bit_cast(bf16x8, ring[2 * t + j]);
+                const f32x16 c = FIRST && t == 0 ? f32x16{} : acc[i][j];
+                acc[i][j] = V ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], wf, c, 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, fa[i], c, 0, 0, 0);
+                if constexpr (j == 1 && !(LAST && t == R - 1)) fa[i] = LdsRows<K>::frag(rows, base, s0 + t + 1, i);
+                if constexpr (i == RB - 1)
+                    ring[2 * t + j] = LAST ? unit_frag<K>(w, w_at, next, 2 * t + j, lane) : unit_frag<K>(w, w_at, unit, 2 * (s0 + R + t) + j, lane);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+    };
+    steps(0, std::true_type{}, std::false_type{});
+#pragma unroll 1
+    for (int s0 = R; s0 + R < S; s0 += R) steps(s0, std::false_type{}, std::false_type{});
+    steps(S - R, std::false_type{}, std::true_type{});
+}
+
+// rows of a row block's accumulators (weights, rows) as chunks, times rs: x[2 j + a] = columns 32 j + 16 a + 8 (lane / 32) .. + 7 of row lane % 32
+static __device__ __forceinline__ void row_chunks(const f32x16 (&acc)[2], float rs, bool zero, u32x4 (&x)[4])
+{
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            uint32_t y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                y[e] = pack2(acc[j][8 * a + 2 * e] * rs, acc[j][8 * a + 2 * e + 1] * rs);
+                if (zero) y[e] = 0;
+            }
+            const auto p = __builtin_amdgcn_permlane32_swap(y[0], y[2], false, false);
+            const auto q = __builtin_amdgcn_permlane32_swap(y[1], y[3], false, false);
+            x[2 * j + a] = u32x4{p[0], q[0], p[1], q[1]};
+        }
+}
+
+// chunks -> whole rows: x[n] = chunk row_chunk(lane) of row 8 n + lane % 8
+static __device__ __forceinline__ void whole_rows(u32x4 (&x)[4])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        uint32_t y[4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const auto p = __builtin_amdgcn_permlane16_swap(x[2 * j][e], x[2 * j + 1][e], false, false);
+            y[j] = p[0], y[2 + j] = p[1];
+        }
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int x0 = (int)y[2 * m], x1 = (int)y[2 * m + 1];
+            x[2 * m][e] = (uint32_t)__builtin_amdgcn_update_dpp(x0, x1, 0x128, 0xf, 0xc, false);      // row_ror:8
+            x[2 * m + 1][e] = (uint32_t)__builtin_amdgcn_update_dpp(x1, x0, 0x128, 0xf, 0x3, false);
+        }
+    }
+}
+static __device__ __forceinline__ int row_chunk(int lane) { return 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + (lane >> 5); }
+
 // Units u, u + step, ... below `end` of the rows m0 .. m0 + 32 RB - 1 (RB even; scale: a factor per row in LDS).  `ring` holds the
 // first 2 R fragments of unit u.  CACHE: the rows go to the cache, which holds all of them (user: of every 64), else to
 // out.rows, from row out.n_cached on, as far as there are any (below M).
@@ -45,83 +130,11 @@ static __device__ __forceinline__ void qkv_units(const uint8_t *rows, const floa
                                                  u32x4 (&ring)[2 * R], int u, int step, int end, const QkvOut &out,
                                                  const CacheUser (&user)[RB / 2], int m0, int M, int lane)
 {
-    constexpr int S = K / 16;
-    static_assert(S % R == 0 && S / R >= 2 && RB % 2 == 0, "");
-    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+    static_assert(RB % 2 == 0, "");
     const int l32 = lane & 31, hf = lane >> 5;
     const uint32_t a_base = LdsRows<K>::base(l32, hf);
     f32x16 acc[RB][2];
-    bf16x8 fa[RB];
-    auto pack2 = [](float x, float y) __attribute__((always_inline)) {
-        bf16x2 v;
-        v[0] = (__bf16)x, v[1] = (__bf16)y;
-        return __builtin_bit_cast(uint32_t, v);
-    };
-    auto product = [&](int unit, int next, auto v_tag) __attribute__((always_inline)) {
-        constexpr bool V = decltype(v_tag)::value;
-        uint32_t base = a_base;
-        asm("" : "+v"(base));
-#pragma unroll
-        for (int i = 0; i < RB; ++i) fa[i] = LdsRows<K>::frag(rows, base, 0, i);
-        auto steps = [&](int s0, auto first_tag, auto last_tag) __attribute__((always_inline)) {
-            constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value;
-            static_for<R>([&](auto t_tag) __attribute__((always_inline)) {
-                constexpr int t = decltype(t_tag)::value;
-                __builtin_amdgcn_sched_barrier(0);
-                static_for<2 * RB>([&](auto n_tag) __attribute__((always_inline)) {
-                    constexpr int i = decltype(n_tag)::value / 2, j = decltype(n_tag)::value % 2;
-                    const bf16x8 wf = __builtin_bit_cast(bf16x8, ring[2 * t + j]);
-                    const f32x16 c = FIRST && t == 0 ? f32x16{} : acc[i][j];
-                    acc[i][j] = V ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], wf, c, 0, 0, 0)
-                                  : __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, fa[i], c, 0, 0, 0);
-                    if constexpr (j == 1 && !(LAST && t == R - 1)) fa[i] = LdsRows<K>::frag(rows, base, s0 + t + 1, i);
-                    if constexpr (i == RB - 1)
-                        ring[2 * t + j] = LAST ? unit_frag<K>(w, w_at, next, 2 * t + j, lane) : unit_frag<K>(w, w_at, unit, 2 * (s0 + R + t) + j, lane);
-                    __builtin_amdgcn_sched_barrier(0);
-                });
-            });
-        };
-        steps(0, std::true_type{}, std::false_type{});
-#pragma unroll 1
-        for (int s0 = R; s0 + R < S; s0 += R) steps(s0, std::false_type{}, std::false_type{});
-        steps(S - R, std::false_type{}, std::true_type{});
-    };
-    // rows of the accumulators' row block i as chunks: x[2 j + a] = columns 32 j + 16 a + 8 (lane / 32) .. + 7 of row lane % 32
-    auto chunks = [&](int i, float rs, bool zero, u32x4 (&x)[4]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                uint32_t y[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    y[e] = pack2(acc[i][j][8 * a + 2 * e] * rs, acc[i][j][8 * a + 2 * e + 1] * rs);
-                    if (zero) y[e] = 0;
-                }
-                const auto p = __builtin_amdgcn_permlane32_swap(y[0], y[2], false, false);
-                const auto q = __builtin_amdgcn_permlane32_swap(y[1], y[3], false, false);
-                x[2 * j + a] = u32x4{p[0], q[0], p[1], q[1]};
-            }
-    };
-    // chunks -> whole rows: x[n] = chunk 4 (lane / 8 % 2) + 2 (lane / 16 % 2) + lane / 32 of row 8 n + lane % 8
-    auto whole_rows = [&](u32x4 (&x)[4]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            uint32_t y[4];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const auto p = __builtin_amdgcn_permlane16_swap(x[2 * j][e], x[2 * j + 1][e], false, false);
-                y[j] = p[0], y[2 + j] = p[1];
-            }
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                const int x0 = (int)y[2 * m], x1 = (int)y[2 * m + 1];
-                x[2 * m][e] = (uint32_t)__builtin_amdgcn_update_dpp(x0, x1, 0x128, 0xf, 0xc, false);      // row_ror:8
-                x[2 * m + 1][e] = (uint32_t)__builtin_amdgcn_update_dpp(x1, x0, 0x128, 0xf, 0x3, false);
-            }
-        }
-    };
-    const int chunk = 4 * ((lane >> 3) & 1) + 2 * ((lane >> 4) & 1) + hf;
+    const int chunk = row_chunk(lane);
 #pragma unroll 1
     for (; u < end; u += step) {
         const int next = u + step < end ? u + step : u, col = u * 64, d = out.qc.d;
@@ -131,7 +144,7 @@ static __device__ __forceinline__ void qkv_units(const uint8_t *rows, const floa
             return out.qc.layer_base + ((size_t)b.t0 * out.qc.H + (size_t)h * b.l_pad) * 256 + (size_t)((m0 + 32 * i - b.t0) / 32) * 8192 + lane * 16;
         };
         if (CACHE && which == 2) {
-            product(u, next, std::true_type{});
+            unit_product<K, RB, R, true>(acc, rows, w, w_at, ring, a_base, u, next, lane);
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
                 if (m0 + 32 * i >= M) break;
@@ -160,13 +173,13 @@ static __device__ __forceinline__ void qkv_units(const uint8_t *rows, const floa
                 }
             }
         } else {
-            product(u, next, std::false_type{});
+            unit_product<K, RB, R, false>(acc, rows, w, w_at, ring, a_base, u, next, lane);
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
                 const int r0 = m0 + 32 * i;
                 if (r0 >= M) break;
                 u32x4 x[4];
-                chunks(i, scale[32 * i + l32], CACHE && r0 + l32 - user[i / 2].t0 >= user[i / 2].l_valid, x);
+                row_chunks(acc[i], scale[32 * i + l32], CACHE && r0 + l32 - user[i / 2].t0 >= user[i / 2].l_valid, x);
                 if (which == 1) {
                     uint8_t *to = block(i);
 #pragma unroll

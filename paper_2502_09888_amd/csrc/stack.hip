@@ -500,16 +500,20 @@ int climber_bgf_score(const climber_config *cfg, const climber_bgf_weights *w, c
     const RowNormIn nin{ws.ss, np, 1.f / (float)d, cfg->rms_eps};
     const RowNormOut no_out{nullptr, nullptr, 0};
     // G = ATL(E) on the m * n_blocks rows: the layer of the stack with the fusion attention in the middle
-    QkvOut to{};
-    to.rows = ws.qkv, to.ld_rows = 3 * d;
-    if (gemm_resident_sums((int)R, d)) {
-        TRY(rt(gemm_resident_bf16(kRowsF32, e, pw.wqkv, (int)R, d, nin, to, s)));
+    if (bgf_front_takes(m_total, nb, d)) {
+        TRY(rt(launch_bgf_front(e, pw.wqkv, ws.o, cand_scen, w->tau_scen, cfg->n_scen, m_total, nb, d, cfg->qk_scale, nin.inv_d, nin.eps, s)));
     } else {
-        TRY(rt(row_prep_f32(e, ws.xb, ws.ss, np, R, d, s)));
-        TRY(project_qkv(&one, pw, ws.xb, R, nin, to, s));
+        QkvOut to{};
+        to.rows = ws.qkv, to.ld_rows = 3 * d;
+        if (gemm_resident_sums((int)R, d)) {
+            TRY(rt(gemm_resident_bf16(kRowsF32, e, pw.wqkv, (int)R, d, nin, to, s)));
+        } else {
+            TRY(rt(row_prep_f32(e, ws.xb, ws.ss, np, R, d, s)));
+            TRY(project_qkv(&one, pw, ws.xb, R, nin, to, s));
+        }
+        TRY(rt(launch_bgf_attention(ws.qkv, ws.o, cand_scen, w->tau_scen, cfg->n_scen, m_total, nb, cfg->n_heads,
+                                    cfg->qk_scale, s)));
     }
-    TRY(rt(launch_bgf_attention(ws.qkv, ws.o, cand_scen, w->tau_scen, cfg->n_scen, m_total, nb, cfg->n_heads,
-                                cfg->qk_scale, s)));
     TRY(layer_tail(&one, pw, e, ws.x32, true, 0, R, ws, s));
     if (bgf_gate_takes(m_total, nd, dg))
         return rt(launch_bgf_gate(ws.xb, ws.x32, down_p, up_p, w->w_head, w->b_head, y, score, m_total, nd, dg, s));

@@ -120,6 +120,39 @@ def test_few_and_many_candidates_give_the_same_bits(d, nb, dg, m, part):
         assert np.array_equal(y1, y[lo:lo + part]) and np.array_equal(sc1, sc[lo:lo + part])
 
 
+@pytest.mark.parametrize("d, nb, m", [(512, 2, 2001), (256, 2, 2063), (512, 3, 2049), (256, 3, 2069), (512, 4, 1000), (256, 4, 1017), (512, 5, 1229),
+                                      (256, 5, 1235), (512, 6, 667), (256, 6, 675), (512, 7, 572), (256, 7, 577), (512, 8, 500), (256, 8, 509)])
+def test_projection_and_attention_in_one_launch_give_the_bits_of_two(d, nb, m):
+    # two blocks a workgroup of as many whole candidates as 32 lanes hold, the last of them with one or a few: against calls
+    # for few candidates, which take a launch each.  A candidate of NaN and one of infinities reach no other's rows.
+    import torch
+    import paper_2502_09888_amd as P
+    spec = W.StackSpec(f"bgf-front-{d}-{nb}", B=1, L=128, sub_len=0, M=1, n_layers=1, d_model=d, H=d // 64, dh=64, d_ffn=256, n_scen=8, n_beh=4, seed=61)
+    say(f"[case] {spec.name} m={m}")
+    w = W.make_bgf(spec, nb, 128, m)
+    cfg, dev, bf = stack_config(spec), "cuda:0", torch.bfloat16
+    atl = {n.lower(): torch.from_numpy(w["atl"][n]).to(dev).to(bf).contiguous() for n in ("g1", "Wqkv", "Wo", "g2", "W1", "W2")}
+    wd, wu = (torch.from_numpy(w[n]).to(dev).to(bf).contiguous() for n in ("w_down", "w_up"))
+    wh, ts, scen = (torch.from_numpy(w[n]).to(dev) for n in ("w_head", "tau_scen", "scen"))
+    e = torch.from_numpy(w["e"]).to(dev)
+    e[5], e[m - 2] = float("nan"), float("inf")
+    ws = torch.empty(P.climber_bgf_workspace_bytes(cfg, nb, 128, m), dtype=torch.uint8, device=dev)
+
+    def call(lo, n):
+        y, score, part, sc = torch.zeros(n, nb, d, device=dev), torch.zeros(n, device=dev), e[lo:lo + n].clone(), scen[lo:lo + n].clone()
+        return lambda: P.climber_bgf_score(cfg, atl, wd, wu, wh, ts, 0.25, nb, 128, part, sc, n, y, score, ws), y, score
+
+    go, y, score = call(0, m)
+    run = launches(go)
+    assert any("bgf_front_kernel" in k.kernel for k in run) and not any("bgf_attention_kernel" in k.kernel for k in run)
+    go()
+    for lo, n in ((0, 5), (6, 34), (m - 40, 38), (m - 1, 1)):
+        few, y1, score1 = call(lo, n)
+        few()
+        assert y1.isfinite().all() and torch.equal(y1, y[lo:lo + n]) and torch.equal(score1, score[lo:lo + n])
+    assert score[[5, m - 2]].isnan().all()
+
+
 @pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 2048, False), (512, 4, 256, 2049, True), (512, 8, 256, 5999, False), (512, 8, 256, 6000, True),
                                                (512, 8, 128, 1499, False), (512, 8, 128, 1500, True), (512, 16, 128, 4999, False), (512, 16, 128, 5000, True)])
 def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, m, one):
