@@ -87,7 +87,7 @@ template <int D, int RB, int NW, int R, int PRE, bool QKV, bool X16>
 __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(const TailArgs p)
 {
     static_assert(!X16 || RB * (D / NW / 32) <= 4, "the residual's blocks are all requested ahead");
-    static_assert(!QKV || (D / NW == 64 && RB % 2 == 0 && !PRE), "");
+    static_assert(!QKV || D / NW == 64, "");
     constexpr int ROWS = 32 * RB, CW = D / NW, NJ = CW / 32;   // rows of the tile; columns and column blocks of a wave
     constexpr int kChunk = 32 * NW;                            // hidden columns of a chunk
     constexpr int S = D / 16, T = kChunk / 16;                 // k-steps of the products over h and over a chunk
@@ -115,12 +115,15 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
     if (PRE && wave == NW) {  // pieces in the order of use: Wo, W1 of chunk 0; per chunk W1 of the next, W2 of this one
         constexpr int PO = D * D * 2 / 8192, P1 = NW * S / 8, P2 = (D / 32) * (T / 8);
         static_assert(S % 8 == 0 && T % 8 == 0, "whole pieces");
-        const int n_pieces = PO + n_chunks * (P1 + P2), sharers = ((int)gridDim.x + 7) / 8;
+        const int n_layer = PO + n_chunks * (P1 + P2), sharers = ((int)gridDim.x + 7) / 8;
+        const int q_skip = QKV && m0 < p.next.n_cached ? p.next.qc.which0 * PO : 0, n_pieces = n_layer + (QKV ? 3 * PO - q_skip : 0);  // (the next layer's queries: nobody's)
         int k = blockIdx.x / 8;  // (workgroups go round the eight XCDs)
         auto request = [&](int end) __attribute__((always_inline)) {
             for (; k < min(end, n_pieces); k += sharers) {
                 int at = k * 8192, r = k - PO - P1;
-                if (r >= 0) {
+                if (QKV && k >= n_layer) {
+                    at = p.wq + (k - n_layer + q_skip) * 8192;
+                } else if (r >= 0) {
                     const int ch = r / (P1 + P2);
                     r %= P1 + P2;
                     const int c = r - (ch + 1 < n_chunks ? P1 : 0);
@@ -130,7 +133,7 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
                     at = p.w1 + (k - PO) * 8192;
                 }
                 __builtin_amdgcn_global_load_lds((glb_u8 *)((const uint8_t *)p.wo + at + lane * 128),
-                                                 (lds_u8 *)lds + tail_lds_bytes<D, RB, NW>(), 4, 0, 0);
+                                                 (lds_u8 *)lds + tail_lds_bytes<D, RB, NW>() + (QKV ? tail_scale_bytes<D, RB>() : 0), 4, 0, 0);
             }
         };
         int ahead = PO + P1 + (P1 + P2);
@@ -141,7 +144,8 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_s_barrier();
         }
-        __builtin_amdgcn_s_barrier();
+        request(n_pieces);
+        for (int i = 0; i < (QKV ? 3 : 1); ++i) __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): nothing may land in LDS that is no longer the workgroup's
         return;
     }
@@ -513,9 +517,9 @@ __global__ __launch_bounds__((NW + PRE) * 64, 2 + PRE) void layer_tail_kernel(co
                     write_a(X, kXPitch, i, col0 + 32 * j + 8 * g, v);
                 }
         if (tid < ROWS) y_scale[tid] = row_scale(RowNormIn{y_ss, D / 64, p.inv_d, p.eps}, tid);
-        CacheUser user[RB / 2];
+        CacheUser user[(RB + 1) / 2];
 #pragma unroll
-        for (int b = 0; b < RB / 2; ++b) user[b] = cached ? cache_user(p.next.qc, min(m0 + 64 * b, p.next.n_cached - 64)) : CacheUser{0, 64, 0};
+        for (int b = 0; b < (RB + 1) / 2; ++b) user[b] = cached ? cache_user(p.next.qc, min(m0 + 64 * b, p.next.n_cached - 32)) : CacheUser{0, 64, 0};
         lds_barrier();  // y is there
         if (cached) qkv_units<D, RB, R / 2, true>(X, y_scale, w, p.wq, ring, u0, NW, 3 * D / 64, p.next, user, m0, M, lane);
         else qkv_units<D, RB, R / 2, false>(X, y_scale, w, p.wq, ring, u0, NW, 3 * D / 64, p.next, user, m0, M, lane);
@@ -561,13 +565,18 @@ bool layer_tail_takes(int M, int D, int F)
 //   252 511 / 552; 264 (248 idle) 764 / 742, 287 (225) 808 / 797, 297 (215) 725 / 733, 355 (157) 767 / 771, 422 842 / 879, 492 947 / 1013; 516 (252) 1092 /
 //   1100, 542 1150 / 1162, 659 1227 / 1265; 774 (250) 1558 / 1567.  271 tiles (241 idle), six layers, 1191 / 1151.
 // - Candidates alone, against the 128 x 128 tiles: 9766 rows 554 / 530, 16448 944 / 896, 24672 1020 / 1015, 30840 1173 / 1204: not.
+// - Tiles of 32 rows (up to 8192 of them), with / without: with a history always, us, four layers, encode of 4500 rows 237 / 242, 6000 252 / 263, 7168 263 / 274, 8192
+//   280 / 296, packed forward of 5200 352 / 364, 7200 386 / 410.  Candidates alone where the 128 x 128 tiles of their own launch begin a third turn and do not
+//   fill it: 4480 rows 378 / 376, 4800 409 / 405; 5440 416 / 431, 6400 410 / 423 and 456 / 463, 7200 444 / 456; 8192 455 / 453.
 // d_model 256 (tiles two per CU): encode of 5 users 127 / 132, 9 141 / 151, 17 218 / 236, 32 280 / 316, 64 530 / 581, scoring of 4500 rows 195 / 193, 8481
 // 206 / 213, 32896 517 / 539: always.
 bool layer_tail_projects(int M, int D, int F, int n_cached, bool ends)
 {
     if (!layer_tail_takes(M, D, F)) return false;
     if (D == 256) return true;
-    if (F % 256 != 0 || M <= 8192 || n_cached == 0) return false;
+    if (F % 256 != 0) return false;
+    if (M <= 8192) return n_cached > 0 || (M > 5376 && M <= 7680);
+    if (n_cached == 0) return false;
     const int tiles = (M + 63) / 64, turns = (tiles + 255) / 256, idle = turns * 256 - tiles;
     return n_cached < M ? idle <= 32 * (turns - 1) + 190 : ends || (turns > 1 && idle <= 32 * (turns - 1));
 }
@@ -579,8 +588,9 @@ hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s)
     if (a.M < 1 || a.F < 128 || a.F % 128 != 0) return hipErrorInvalidValue;
     if (a.x16 && (!layer_tail_reads_bf16(a.M, a.D, a.F) || a.x16_split % 64 != 0)) return hipErrorInvalidValue;
     if (a.wq) {
-        if (!layer_tail_takes(a.M, a.D, a.F) || (a.D == 512 && (a.F % 256 != 0 || a.M <= 8192)) || a.next.n_cached % 64 != 0 || a.y_first % 64 != 0) return hipErrorInvalidValue;
-        return a.D == 512 ? launch_tail<512, 2, 8, 8, 0, true>(a, s) : launch_tail<256, 2, 4, 8, 0, true>(a, s);
+        if (!layer_tail_takes(a.M, a.D, a.F) || (a.D == 512 && a.F % 256 != 0) || a.next.n_cached % 64 != 0 || a.y_first % 64 != 0) return hipErrorInvalidValue;
+        if (a.D == 256) return launch_tail<256, 2, 4, 8, 0, true>(a, s);
+        return a.M <= 8192 ? launch_tail<512, 1, 8, 8, 1, true>(a, s) : launch_tail<512, 2, 8, 8, 0, true>(a, s);
     }
     // d_model 512: eight waves need chunks of 256; no more than a 32-row tile per CU: those (fewer rows in line behind one
     // another).  Four waves hold twice the columns each, and h has to wait in memory.  Us, stack calls of four layers, eight

@@ -128,9 +128,8 @@ static __device__ __forceinline__ int row_chunk(int lane) { return 4 * ((lane >>
 template <int K, int RB, int R, bool CACHE>
 static __device__ __forceinline__ void qkv_units(const uint8_t *rows, const float *scale, __amdgpu_buffer_rsrc_t w, int w_at,
                                                  u32x4 (&ring)[2 * R], int u, int step, int end, const QkvOut &out,
-                                                 const CacheUser (&user)[RB / 2], int m0, int M, int lane)
+                                                 const CacheUser (&user)[(RB + 1) / 2], int m0, int M, int lane)
 {
-    static_assert(RB % 2 == 0, "");
     const int l32 = lane & 31, hf = lane >> 5;
     const uint32_t a_base = LdsRows<K>::base(l32, hf);
     f32x16 acc[RB][2];

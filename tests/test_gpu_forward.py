@@ -350,6 +350,44 @@ def test_projection_behind_the_tail_gives_the_bits_of_separate_launches(d, F, la
         assert torch.equal(yh1[:lens[i]], yh[t0[i]:t0[i] + lens[i]])
 
 
+@pytest.mark.parametrize("F, layers, lens, cands, flags", [
+    (256, 3, (384, 77, 300, 129, 512, 64, 1) * 3, 1, 0),      # just above 4096 rows with the history, ragged
+    (512, 2, (448,) * 18, 65, 0),                             # a uniform batch, 8129 rows: encode with 8064
+    (256, 4, (200, 31, 0, 96, 130) * 3, 5377, 0),             # candidates alone from where their own launch begins a third turn, empty histories
+    (2048, 2, (64, 1, 40), 7649, 0), (256, 2, (320, 65) * 10, 31, 4)])
+def test_projection_behind_tails_of_32_rows_gives_the_bits_of_separate_launches(F, layers, lens, cands, flags):
+    # as above from 4097 to 8192 rows, where a ninth wave requests this projection's weights as well
+    test_projection_behind_the_tail_gives_the_bits_of_separate_launches(512, F, layers, lens, cands, flags)
+
+
+@pytest.mark.parametrize("users, cands, encode, forward, score", [(5, 4, 3, 3, 0), (7, 600, 3, 3, 0), (8, 0, 3, 3, 0), (8, 672, 3, 3, 0), (8, 673, 3, 3, 3),
+                                                                 (8, 960, 3, 3, 3), (8, 961, 3, 3, 0), (8, 1024, 3, 3, 0)])
+def test_tails_of_32_rows_make_the_next_projection_where_that_was_measured_to_be_faster(users, cands, encode, forward, score):
+    # four layers, d_model 512: how many tails of an encode, a packed forward and a scoring call do
+    import torch
+    import paper_2502_09888_amd as P
+    cfg, dev = P.Config(n_layers=4, n_heads=8, d_ffn=256, n_scen=1, n_beh=1, sub_len=256), "cuda:0"
+    lens, rows, m = [1024] * users, 1024 * users, cands * users
+    w = [{k: torch.zeros(s, dtype=torch.bfloat16, device=dev) for k, s in
+          (("g1", 512), ("wqkv", (512, 1536)), ("wo", (512, 512)), ("g2", 512), ("w1", (512, 256)), ("w2", (256, 512)))} for _ in range(4)]
+    buf = torch.empty(P.climber_kv_cache_bytes(cfg, lens), dtype=torch.uint8, device=dev)
+    cache = P.climber_kv_cache_create(cfg, lens, lens, buf)
+    ws = torch.empty(P.climber_workspace_bytes(cfg, rows + m), dtype=torch.uint8, device=dev)
+    x, xc, y = (torch.zeros(n, 512, dtype=t, device=dev) for n, t in ((rows, torch.bfloat16), (max(m, 1), torch.bfloat16), (max(m, 1), torch.float32)))
+    (ids, cids), tau = (torch.zeros(n, dtype=torch.int32, device=dev) for n in (rows, max(m, 1))), torch.ones(4, 1, 1, device=dev)
+    off = torch.arange(users + 1, dtype=torch.int32, device=dev) * cands
+
+    def tails(call):
+        names = [k.kernel for k in launches(call)]
+        say(names)
+        return sum("layer_tail_kernelILi512E" in n and ("ELi8ELi8ELi1ELb1E" in n or "ELi8ELi8ELi0ELb1E" in n) for n in names)
+
+    assert tails(lambda: P.climber_history_encode(cfg, w, tau, x, ids, ids, cache, ws)) == encode
+    assert tails(lambda: P.climber_sumi_forward(cfg, w, tau, x, ids, ids, xc, off, m, cands, cids, cids, cache, None, y, ws)) == forward
+    if m:
+        assert tails(lambda: P.climber_sumi_score(cfg, w, tau, cache, xc, off, m, cands, cids, cids, y, ws)) == score
+
+
 @pytest.mark.parametrize("d, m", [(512, 4225), (256, 4225), (512, 200)])
 def test_one_layer_scores_written_over_its_inputs(d, m):
     # outputs that begin inside the candidates' rows, before them, and apart from them: the same bits
