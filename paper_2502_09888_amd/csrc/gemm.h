@@ -127,6 +127,22 @@ bool layer_tail_projects(int M, int D, int F, int n_cached, bool ends);
 bool layer_tail_reads_bf16(int M, int D, int F);
 hipError_t layer_tail_bf16(const TailArgs &a, hipStream_t s);
 
+// layer_head_bf16.hip: the tail's beginning for few rows, one launch: h = x + o Wo (fp32 rows, apart from x) and the hidden GELU(RMSNorm(h) W1),
+// tiled (kTiledA of the down-projection).
+struct HeadArgs {
+    const void *o;
+    const float *x;
+    const void *wo;   // packed; w1 (gains multiplied in) so many bytes further on,
+    int w1, w_bytes;  // both in so many bytes
+    float *h;
+    void *u;
+    int M, D, F;
+    float inv_d, eps;
+    int n_parts;      // (layer_head_bf16's own)
+};
+bool layer_head_takes(int M, int D, int F);  // shapes it has a kernel for and is the faster way
+hipError_t layer_head_bf16(const HeadArgs &a, hipStream_t s);
+
 // What the first projection of a stack call needs of its input rows: the sum of squares of every
 // row into ss[row][0] (ss[row][1 .. n_part-1] = 0) and
 //   from bf16 rows x (the embeddings): the fp32 copy x32 (the residual stream; nullable);

@@ -159,8 +159,12 @@ int layer_tail(const climber_config *cfg, const PackedLayer &pw, const float *x,
     if (next || given) return CLIMBER_ERR_RUNTIME;  // (asked for where layer_tail_takes)
     float *h = ws.h32 + (size_t)r0 * d;
     uint8_t *u = ws.u + (size_t)r0 * F * 2;
-    TRY(rt(gemm_bf16(EPI_RESID_F32, o, d, pw.wo, M, d, d, h, d, x, d, no_in, nout, 0, s)));
-    TRY(rt(gemm_bf16(EPI_GELU_BF16, xb, d, pw.w1, M, F, d, u, F, nullptr, 0, nin, no_out, kTiledC, s)));
+    if (layer_head_takes(M, d, F)) {
+        TRY(rt(layer_head_bf16(HeadArgs{o, x, pw.wo, (int)(pw.w1 - pw.wo), (int)(pw.w2 - pw.wo), h, u, M, d, F, nin.inv_d, nin.eps, 0}, s)));
+    } else {
+        TRY(rt(gemm_bf16(EPI_RESID_F32, o, d, pw.wo, M, d, d, h, d, x, d, no_in, nout, 0, s)));
+        TRY(rt(gemm_bf16(EPI_GELU_BF16, xb, d, pw.w1, M, F, d, u, F, nullptr, 0, nin, no_out, kTiledC, s)));
+    }
     return rt(gemm_bf16(EPI_RESID_F32, u, F, pw.w2, M, d, F, y, d, h, d, no_in, norm_out ? nout : no_out, kTiledA, s));
 }
 

@@ -252,6 +252,22 @@ def test_layer_tail_with_weights_requested_ahead_gives_the_bits_of_three(d_ffn, 
     assert np.array_equal(yc[:g.m_total], g.score())
 
 
+@pytest.mark.parametrize("d_ffn, m, head", [(128, 1, True), (384, 31, True), (1024, 33, True), (1024, 1024, True), (1024, 1025, False),
+                                            (2048, 500, True), (256, 4096, True)])
+def test_projection_and_hidden_in_one_launch_give_the_bits_of_two(d_ffn, m, head):
+    # d_model 256: candidates alone in at most a workgroup per CU of 32 rows x 128 columns of the hidden, against all rows in the
+    # tail's one launch; one to 16 parts of the hidden, the last rows' block in part, the most workgroups and one block more
+    spec = W.StackSpec(f"fwd-head-{d_ffn}-{m}", B=11, L=384, sub_len=128, M=0, n_layers=2, d_model=256, H=4, dh=64, d_ffn=d_ffn, n_scen=8,
+                       n_beh=4, seed=340 + m, hist_lens=(384,) * 11, cand_counts=(m,) + (0,) * 10)
+    w, g, yc = run_forward(spec, users=(1,), want_hist=True)
+    g.encode()
+    assert np.array_equal(yc[:g.m_total], g.score())
+    import torch
+    y = torch.empty(m, 256, device="cuda:0")
+    run = launches(lambda: g.P.climber_sumi_score(g.cfg, g.layers, g.tau, g.cache, g.x_cand, g.cand_off, m, m, g.cscen, g.cbeh, y, g.ws))
+    assert any("layer_head_kernel" in k.kernel for k in run) == head
+
+
 @pytest.mark.parametrize("d, F, layers", [(128, 128, 1), (256, 384, 5), (384, 128, 4), (512, 2048, 2)])
 def test_packed_weights_are_the_operand_fragments(d, F, layers):
     # 16 bytes (column block nb, k step ks, lane): rows 16 ks + 8 (lane / 32) + 0..7 of column 32 nb + lane % 32, the gains of the
