@@ -3,7 +3,7 @@
     python -m paper_2502_09888_amd.build
 
 Each .hip file is compiled to an object next to it and the objects are linked into
-``paper_2502_09888_amd/libclimber.so``.  Packed-FP32 instruction selection is switched off for all
+``paper_2502_09888_amd/libclimber.so``; csrc/binding.c becomes the extension module ``_native.so`` beside it.  Packed-FP32 instruction selection is switched off for all
 device code.
 """
 from __future__ import annotations
@@ -11,11 +11,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libclimber.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["climber_api.hip", "attn_bf16.hip", "attn_wave_bf16.hip", "attn_split_bf16.hip", "attn_bias_bf16.hip", "attn_f32.hip", "attn_tile_f32.hip", "kv_cache.hip", "stack.hip",
            "gemm_bf16.hip", "gemm_small_bf16.hip", "gemm_resident_bf16.hip", "layer_tail_bf16.hip", "layer_head_bf16.hip", "rowwise.hip", "hist_fused_bf16.hip", "check.hip", "bgf.hip", "bgf_front_bf16.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -58,6 +60,10 @@ def build(force: bool = False, verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
+    binding = os.path.join(CSRC, "binding.c")
+    if force or _stale(NATIVE, binding):
+        subprocess.check_call([os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+                               binding, "-o", NATIVE])
     return LIB
 
 

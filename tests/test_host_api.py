@@ -189,6 +189,61 @@ def test_binding_has_no_cpu_fallback(monkeypatch, tmp_path):
         mod.load_library()
 
 
+@pytest.mark.parametrize("name", ["climber_attn_history", "climber_attn_sumi", "climber_attn_history_bias", "climber_attn_sumi_bias"])
+def test_native_binding_passes_every_argument_in_its_place(name, _lib, monkeypatch):
+    # The attention calls go through csrc/binding.c: its entry points are replaced by one that records what arrives, for tensors, device
+    # pointers and None, a stream's handle and a stream object; and what it does not convert is left to ctypes, which does or refuses.
+    import torch
+    from paper_2502_09888_amd import _native, climber as mod
+    real, args = getattr(_lib, name), getattr(_lib, name).argtypes
+    seen = []
+
+    def record(*a):
+        seen.append([C.string_at(x, C.sizeof(t._type_)) if hasattr(t, "_type_") and hasattr(t._type_, "_fields_") and x else x
+                     for x, t in zip(a, args)])
+        return -5
+    proto = C.CFUNCTYPE(C.c_int, *(C.c_void_p if hasattr(t, "_type_") and hasattr(t._type_, "_fields_") else t for t in args))
+    call = proto(record)
+    entries = [C.cast(call if n == name else getattr(_lib, n), C.c_void_p).value
+               for n in ("climber_attn_history", "climber_attn_sumi", "climber_attn_history_bias", "climber_attn_sumi_bias")]
+
+    def bind(to):
+        _native.bind(*to, P.Config, P.RelBias, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
+    t = [torch.zeros(4) for _ in range(10)]
+    c, bias = cfg(), P.rel_bias(torch.zeros(1, 1, 1, 3), torch.zeros(1, 1, 1, 2), t[0], t[1])
+    handle = type("Handle", (), {"handle": 0x7F1234567890})()
+    more = [bias] if name.endswith("bias") else []
+    if "history" in name:
+        given = [c, t[0], t[1], 0x7FFFFFFFFFFF, t[2], t[3], t[4], handle, 3, None, *more]
+    else:
+        given = [c, t[0], handle, 2, t[1], t[2], None, t[3], 70000, 2**31 - 1, t[4], t[5], FAKE, *more]
+
+    def plain(x):
+        if isinstance(x, (P.Config, P.RelBias)):
+            return C.string_at(C.byref(x), C.sizeof(x))
+        return x.data_ptr() if torch.is_tensor(x) else getattr(x, "handle", x)
+    try:
+        bind(entries)
+        for stream, arrives in ((0x55AA, 0x55AA), (type("S", (), {"cuda_stream": 77})(), 77), (0, None)):
+            with pytest.raises(P.ClimberError) as e:
+                getattr(P, name)(*given, stream=stream)
+            assert e.value.code == -5 and seen.pop() == [plain(x) for x in given] + [arrives]
+        for at in range(len(given)):  # an argument of no use: what ctypes makes of it
+            bad = list(given)
+            bad[at] = type("Wrong", (), {})()
+            with pytest.raises((AttributeError, TypeError, C.ArgumentError)):
+                getattr(P, name)(*bad, stream=0)
+        assert not seen
+        assert mod._native is _native and real.argtypes == args
+    finally:
+        bind([C.cast(getattr(_lib, n), C.c_void_p).value
+              for n in ("climber_attn_history", "climber_attn_sumi", "climber_attn_history_bias", "climber_attn_sumi_bias")])
+    none = type("Handle", (), {"handle": None})()
+    with pytest.raises(P.ClimberError) as e:  # the real one again
+        getattr(P, name)(*[none if x is handle else None if i == 1 else x for i, x in enumerate(given)], stream=0)
+    assert e.value.code == -1
+
+
 def test_bench_refuses_more_than_one_gpu():
     # one GPU per box: the benchmark says so instead of pretending to scale
     import subprocess
