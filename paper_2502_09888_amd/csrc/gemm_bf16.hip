@@ -9,8 +9,8 @@
 // of a row XOR-swizzled by (row / 4) % 4 through the choice of the global address each lane loads:
 // 16 consecutive rows of one k chunk then cover all 64 banks) or in the tiled layout of gemm.h,
 // where one copy is 1 KiB contiguous.
-// Both copies are direct global_load_lds (no register staging) into a ring of 3 or 4 k-tiles of 32,
-// one or two tiles in flight, one bare s_barrier per k-tile; the copies of a k-tile are dealt out
+// Both copies are direct global_load_lds (no register staging) into a ring of 3, 4 or 6 k-tiles of 32,
+// one to four tiles in flight behind the one that is waited for, one bare s_barrier per k-tile; the copies of a k-tile are dealt out
 // between the MFMAs of the tile two ahead of it, not queued in front of them.
 // Workgroup = 4 waves as 2 x 2; a wave owns WM x WN blocks of 32 x 32:
 //   4 x 2 (macro tile 256 x 128): 128 accumulator registers, two workgroups per CU (the projections
@@ -80,15 +80,8 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const PackJobs jobs)
 template <int N>
 __device__ __forceinline__ void wait_vm()
 {
-    if (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (N == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    else if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    else if (N == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-    else if (N == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-    else if (N == 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-    else if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    else if (N == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    else static_assert(N == 0 || N == 2 || N == 3 || N == 4 || N == 6 || N == 8 || N == 12 || N == 16, "unsupported vmcnt");
+    static_assert(N < 64, "");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // WM, WN: 32 x 32 blocks per wave along M and N.  Macro tile (2*WM*32) x (2*WN*32) x 32.
@@ -197,12 +190,9 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
     // The ring stages of tile kt and of the tile to prefetch come in as byte offsets carried by the
     // loop (derived from kt % kStages in here, every fragment address cost vector additions on the
     // path from the barrier to the first MFMA instead of being an immediate).
-    auto k_tile = [&](int kt, int st_cur, int st_fill, auto prefetch_tag) __attribute__((always_inline)) {
+    auto k_tile = [&](int kt, int st_cur, int st_fill, auto ahead_tag, auto prefetch_tag) __attribute__((always_inline)) {
         constexpr bool PREFETCH = decltype(prefetch_tag)::value;
-        const int ahead = min(kt + kStages - 1, n_kt) - (kt + 1);  // tiles that may stay in flight
-        if (kStages > 3 && ahead >= 2) wait_vm<(kStages > 3 ? 2 : 1) * NPRE>();
-        else if (ahead >= 1) wait_vm<NPRE>();
-        else wait_vm<0>();
+        wait_vm<decltype(ahead_tag)::value * NPRE>();  // tiles that may stay in flight
         __builtin_amdgcn_s_barrier();
         const uint8_t *sa = lds + st_cur;
         const uint8_t *sw = sa + kABytes;
@@ -243,8 +233,13 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(
             st_fill = st_cur;
             st_cur = st_cur + kStageBytes == kRing ? 0 : st_cur + kStageBytes;
         };
-        for (; kt + kStages - 1 < n_kt; ++kt, advance()) k_tile(kt, st_cur, st_fill, std::true_type{});
-        for (; kt < n_kt; ++kt, advance()) k_tile(kt, st_cur, st_fill, std::false_type{});
+        for (; kt + kStages - 1 < n_kt; ++kt, advance()) k_tile(kt, st_cur, st_fill, std::integral_constant<int, kStages - 2>{}, std::true_type{});
+        static_for<kStages - 1>([&](auto i_tag) __attribute__((always_inline)) {
+            constexpr int left = kStages - 2 - decltype(i_tag)::value;
+            if (n_kt - kt != left + 1) return;
+            k_tile(kt, st_cur, st_fill, std::integral_constant<int, left>{}, std::false_type{});
+            ++kt, advance();
+        });
     }
 
     __syncthreads();  // every wave is done reading the last k-tile
@@ -297,7 +292,14 @@ hipError_t dispatch(const GemmArgs &g, hipStream_t s)
     // 64 x 128 where 128 x 128 would leave CUs without a tile.  us per call with / without: one
     // request (1000 behaviours, 200 candidates, four layers) 271 / 285, 4 x 1500 behaviours with 300 candidates each 570 / 583,
     // encode of 8 x 1024 308 / 336, score of 4352 rows 421 / 436; with all CUs taken (score of 8192 rows) 565 / 558
-    if ((int64_t)(g.N / 128) * ((g.M + 127) / 128) < 256) return launch<EPI, 1, 2, 4>(g, s);
+    if ((int64_t)(g.N / 128) * ((g.M + 127) / 128) < 256) {
+        // One workgroup per CU or two, whose k-tiles come from beyond L2 behind a launch that read a cache: a longer ring where the walk is long, which
+        // a short one (K of 256 or 512) does not gain back at its start.  Us, four layers, d_model 512, ring of 4 / 6 / 8 / 12 k-tiles for the
+        // down-projection: score of 1600 rows 277 / 267 / 268 / 270, 2400 312 / 301 / 302 / 305, 4096 373 / 367 / 368 / 368, encode of 4000 209 / 208 / 209 / 210; for
+        // all projections score of 1000 197 / 197 / 199 / 204.
+        if (g.K >= 1024) return launch<EPI, 1, 2, 6>(g, s);
+        return launch<EPI, 1, 2, 4>(g, s);
+    }
     return launch<EPI, 2, 2, 4>(g, s);
 }
 

@@ -252,6 +252,21 @@ def test_layer_tail_with_weights_requested_ahead_gives_the_bits_of_three(d_ffn, 
     assert np.array_equal(yc[:g.m_total], g.score())
 
 
+@pytest.mark.parametrize("d_ffn, m", [(1024, 1537), (2048, 2049), (1280, 4096)])
+def test_down_projection_on_a_longer_ring_gives_the_bits_of_the_tail(d_ffn, m):
+    # candidates alone by 64 x 128 tiles, whose ring is six k-tiles long where K is 1024 and more, the last row's tile nearly empty;
+    # with the history's rows in the tail's one launch
+    spec = W.StackSpec(f"fwd-ring-{d_ffn}", B=11, L=384, sub_len=128, M=0, n_layers=2, d_model=512, H=8, dh=64, d_ffn=d_ffn, n_scen=8, n_beh=4,
+                       seed=440 + m, hist_lens=(384,) * 11, cand_counts=(m,) + (0,) * 10)
+    w, g, yc = run_forward(spec, users=(1,), want_hist=True)
+    g.encode()
+    assert np.array_equal(yc[:g.m_total], g.score())
+    import torch
+    y = torch.empty(m, 512, device="cuda:0")
+    run = launches(lambda: g.P.climber_sumi_score(g.cfg, g.layers, g.tau, g.cache, g.x_cand, g.cand_off, m, m, g.cscen, g.cbeh, y, g.ws))
+    assert any("gemm_bf16_kernelILi2ELi1ELi2ELi6E" in k.kernel for k in run)
+
+
 @pytest.mark.parametrize("d_ffn, m, head", [(128, 1, True), (384, 31, True), (1024, 33, True), (1024, 1024, True), (1024, 1025, False),
                                             (2048, 500, True), (256, 4096, True)])
 def test_projection_and_hidden_in_one_launch_give_the_bits_of_two(d_ffn, m, head):
