@@ -281,11 +281,12 @@ hipError_t launch(const GemmArgs &g, hipStream_t s)
 template <int EPI>
 hipError_t dispatch(const GemmArgs &g, hipStream_t s)
 {
-    // Few rows: a wave per 32 x 32 block without LDS, as long as that makes at most 1.5 workgroups per CU -- beyond, the
-    // tiles' reuse of their operands wins.  Us per call, four layers, with the line at 192 / 384 / 640 / 1024 workgroups:
-    // one request (1000 behaviours, 200 candidates, d_model 512) 298 / 270 / 273 / 299; score of 768 rows 173 / 173 / 187 /
-    // 199, 1024 206 / 175 / 176 / 211, 2560 271 / 270 / 296 / 296; d_model 256, 2048 rows 160 / 144 / 145 / 157
-    if ((int64_t)(g.N / 64) * ((g.M + 31) / 32) <= 384 && g.K % 128 == 0) return gemm_small_bf16(EPI, g, s);
+    // Few rows: a wave per 32 x 32 block without LDS, as long as that makes at most one workgroup per CU, 1.5 in the residual projections -- beyond, the
+    // tiles' reuse of their operands wins.  Us per call, four layers, d_model 512, the line at 256 / 384 / 512 workgroups:
+    // QKV and up-projection score of 400 rows 144 / 150 / 155, 512 147 / 152 / 155, 640 157 / 157 / 161, 800 163 / 163 / 164, encode of 500 104 / 107 / 111, 600
+    // 106 / 108 / 111; residual ones score of 1280 226 / 228 / 229, 1600 264 / 264 / 258, 2048 278 / 279 / 288, encode of 2000 152 / 153 / 155, d_model 256,
+    // score of 3000 190 / 185 / 186, encode of 4000 120 / 120 / 123
+    if ((int64_t)(g.N / 64) * ((g.M + 31) / 32) <= (EPI == EPI_RESID_F32 ? 384 : 256) && g.K % 128 == 0) return gemm_small_bf16(EPI, g, s);
     // macro tile 256 x 128 when that still gives every CU two workgroups, else 128 x 128
     const int64_t big_tiles = (int64_t)(g.N / 128) * ((g.M + 255) / 256);
     if (big_tiles >= 512) return launch<EPI, 4, 2, 3>(g, s);
