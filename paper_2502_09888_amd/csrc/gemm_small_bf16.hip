@@ -2,18 +2,17 @@
 // a request or a small batch, where the macro tiles of gemm_bf16.hip leave most of the chip idle and the
 // time is the latency of a workgroup's serial chain of k-tiles.
 //
-// A wave owns a 32 x 32 block of C and its whole K; two waves side by side (64 columns, what the epilogues need:
-// one head, one 64-column slice of the row sums of squares) form a workgroup.  Nothing is shared through LDS on
-// the way in: every wave loads its operand fragments from global memory (L2) straight into registers, D k-steps
-// ahead (2*D KiB in flight per wave, more than the latency of L2 times what the wave consumes), so the k-loop has
-// no barrier and no wait for other waves.  Weights come in fragment order (1 KiB per load); a fragment of A is 16
-// bytes from each of 32 rows, or 1 KiB of the tiled layout.  Bound by the loads: two fragments of 1 KiB per MFMA
-// and wave at the 64 bytes per clock of a CU's vector cache, i.e. 64 clocks per k-step of a workgroup.  FFN down
-// (N = 512, K = 2048) at 200 / 1024 rows: 8.1 / 9.1 us against 19.4 / 20.0 with 128 x 128 tiles; attention output
-// (N = K = 512) 5.0 / 5.4 against 9.4 / 9.8 (about 3.5 us of each are the launch itself).
+// A workgroup has 64 columns (what the epilogues need: one head, one 64-column slice of the row sums of squares) of 16 or 32 rows
+// and their whole K; each of its four waves 16 columns, whose weights go straight from L2 into registers, 16 k-tiles of 32 ahead (in
+// fragment order, 1 KiB a load: a quarter of the workgroup's, nobody's twice).  The rows come by way of LDS, 256 k at a time with a barrier
+// each, the loads of the next but one in flight.  Bound by the loads, at the 64 bytes per clock of a CU's vector cache: 4 KiB of weights
+// and 1 or 2 of rows per k-tile, so 16 rows cost a workgroup 5/6 of what 32 do and are taken while there are CUs for twice the workgroups.
+// One request (1000 behaviours, 200 candidates, four layers, d_model 512) 216 us; with two waves of 32 columns a workgroup, each with its own
+// fragments of all 32 rows (8 KiB per k-tile, 56 workgroups for 200 rows x 512), 244.  Score of 16 rows 86.6 / 110.9, 128 92.6 / 123.5, 256 101
+// / 126, 640 127 / 135; d_model 256 72.3 / 79.8, 81.8 / 89.8, 82.4 / 91.1, 88.4 / 98.9.  32 k-tiles ahead: 0.99.
 // Per output element the products are summed in the same order as in gemm_bf16.hip (k ascending, one
-// accumulator, the same MFMA): the two kernels give the same bits, so a row's result does not depend on how many
-// rows a launch has.
+// accumulator; an instruction of 16 x 16 x 32 sums as two of 32 x 32 x 16 do, one after the other): the two kernels give the same
+// bits, so a row's result does not depend on how many rows a launch has.
 #include "gemm_common.h"
 #include "lanes.h"
 
@@ -22,20 +21,27 @@ namespace {
 
 using namespace gemm;
 
-template <int EPI, int D>
-__global__ __launch_bounds__(128) void gemm_small_kernel(
-    const __bf16 *A, int64_t lda, const __bf16 *Wp, int M, int N, int K, void *C, int64_t ldc, const float *resid,
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+
+constexpr int NW = 4;
+
+// RB blocks of 16 rows a workgroup; K in chunks of C k-tiles of 32, of which U are a turn of the loop and of the weights' ring.
+template <int EPI, int RB, int C, int U>
+__global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
+    const __bf16 *A, int64_t lda, const __bf16 *Wp, int M, int N, int K, void *Cout, int64_t ldc, const float *resid,
     int64_t ldr, const RowNormIn nin, const RowNormOut nout, const int tiled, const QkvToCache qc, const int by_cols)
 {
     constexpr bool F32 = EPI == EPI_RESID_F32;
-    constexpr int kPitch = epilogue_pitch<EPI, 2>();
-    __shared__ __attribute__((aligned(16))) uint8_t tr[32 * kPitch];
+    constexpr int kPitch = epilogue_pitch<EPI, 2>(), kRows = 16 * RB, R = C * U, P = RB * C / NW, kBuf = RB * C * 1024, L = C < 4 ? C : 4;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kBuf + kRows * kPitch];
+    uint8_t *const tr = lds + 2 * kBuf;
 
-    const int tid = threadIdx.x, lane = tid & 63, wn = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, hf = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, kq = lane >> 4;
     // Tile of this workgroup.  Launch indices equal modulo 8 run on one XCD (one L2): the tiles are dealt so
     // that an XCD sees an eighth of the larger operand and all of the smaller one.
-    const int n_ct = N / 64, n_rt = (M + 31) / 32;
+    const int n_ct = N / 64, n_rt = (M + kRows - 1) / kRows;
     int ct, rt;
     {
         const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
@@ -46,105 +52,152 @@ __global__ __launch_bounds__(128) void gemm_small_kernel(
         }
         if (ct >= n_ct || rt >= n_rt) return;
     }
-    const int m0 = rt * 32, n0 = ct * 64;
-    const int S = K / 16;  // k-steps; a multiple of D
+    const int m0 = rt * kRows, n0 = ct * 64;
+    const int T = K / 32, n = T / C;  // k-tiles, chunks (a multiple of U)
 
-    const int row = m0 + l32;
-    const bool a_tiled = tiled & kTiledA;
-    const int a_step = a_tiled ? 512 : 32;  // elements per two k-steps
-    const __bf16 *a_src;
-    int a_odd;                              // distance from an even k-step's fragment to the odd one's
-    if (a_tiled) {
-        const int r = row & 15, x = r >> 2;
-        a_src = A + (int64_t)min(row >> 4, (M - 1) >> 4) * (K / 32) * 512 + r * 32 + (hf ^ x) * 8;
-        a_odd = (((2 + hf) ^ x) - (hf ^ x)) * 8;
-    } else {
-        a_src = A + (int64_t)min(row, M - 1) * lda + 8 * hf;
-        a_odd = 16;
-    }
-    const __bf16 *w_src = Wp + ((int64_t)(n0 / 32 + wn) * S * 64 + lane) * 8;
-
-    bf16x8 fa[D], fw[D];
-    auto load = [&](int s, int slot) __attribute__((always_inline)) {
-        fw[slot] = *(const bf16x8 *)(w_src + (int64_t)s * 512);
-        fa[slot] = *(const bf16x8 *)(a_src + (int64_t)(s >> 1) * a_step + (slot & 1 ? a_odd : 0));
-    };
+    // Rows: pieces of 16 rows x 32 k, 1 KiB, in LDS as the tiled layout has them (chunk c of row r at place c ^ r / 4 % 4 of the row's 64 bytes);
+    // of a chunk's, one after the other's to each wave.
+    const __bf16 *a_src[P];
+    const int a_step = (tiled & kTiledA) ? 512 : 32;  // elements per k-tile
 #pragma unroll
-    for (int s = 0; s < D; ++s) load(s, s);
+    for (int i = 0; i < P; ++i) {
+        const int p = NW * i + wave, g = p / C, kt = p % C;
+        if (tiled & kTiledA)
+            a_src[i] = A + ((int64_t)min((m0 >> 4) + g, (M - 1) >> 4) * T + kt) * 512 + lane * 8;
+        else
+            a_src[i] = A + (int64_t)min(m0 + 16 * g + (lane >> 2), M - 1) * lda + kt * 32 + ((lane & 3) ^ (lane >> 4)) * 8;
+    }
+    auto fetch = [&](int ch, u32x4 (&x)[P]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) x[i] = *(const u32x4 *)(a_src[i] + (int64_t)ch * (C * a_step));
+    };
+    auto put = [&](int buf, const u32x4 (&x)[P]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) *(u32x4 *)(lds + buf * kBuf + (NW * i + wave) * 1024 + lane * 16) = x[i];
+    };
+    // Weights: 16 columns x 32 k of two neighbouring fragments of 32 columns x 16 k
+    const __bf16 *w_src = Wp + ((int64_t)(n0 / 32 + (wave >> 1)) * 2 * T + (kq >> 1)) * 512 + ((kq & 1) * 32 + (wave & 1) * 16 + l15) * 8;
+    bf16x8 ring[R];
+    auto weights = [&](int t) __attribute__((always_inline)) { return *(const bf16x8 *)(w_src + (int64_t)t * 1024); };
+
+    u32x4 x0[P], x1[P];
+    fetch(0, x0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        ring[t] = weights(t);
+        if (t + 1 == C) fetch(min(1, n - 1), x1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 
     // what the epilogue needs of global memory is requested behind the first operands: the partial sums of
-    // squares of the input rows (the lane's accumulators belong to row l32 of the tile), or the residual rows
+    // squares of the input rows (the lane's accumulators belong to rows l15 of the blocks), or the residual rows
     const bool scaled = !F32 && nin.ss, ss_fast = scaled && (nin.n_part == 8 || nin.n_part == 4);
-    float4 raw_ss[2] = {};
+    float4 raw_ss[RB][2] = {};
     if (ss_fast) {
-        const float *p = nin.ss + (int64_t)min(row, M - 1) * nin.n_part;
-        raw_ss[0] = *(const float4 *)p;
-        raw_ss[1] = *(const float4 *)(p + (nin.n_part == 8 ? 4 : 0));
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const float *p = nin.ss + (int64_t)min(m0 + 16 * i + l15, M - 1) * nin.n_part;
+            raw_ss[i][0] = *(const float4 *)p;
+            raw_ss[i][1] = *(const float4 *)(p + (nin.n_part == 8 ? 4 : 0));
+        }
     }
-    float4 rsd[4];
+    float4 rsd[RB];
     if constexpr (F32) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int id = (4 * wn + it) * 64 + lane, r = id >> 4, cc = id & 15;
-            rsd[it] = *(const float4 *)(resid + (int64_t)min(m0 + r, M - 1) * ldr + n0 + cc * 4);
-        }
+        for (int i = 0; i < RB; ++i)
+            rsd[i] = *(const float4 *)(resid + (int64_t)min(m0 + 16 * i + (tid >> 4), M - 1) * ldr + n0 + l15 * 4);
     }
     CacheUser user{0, 64, 0};
-    const bool to_cache = EPI == EPI_STORE_BF16 && qc.layer_base;
+    const bool to_cache = EPI == EPI_STORE_BF16 && RB == 2 && qc.layer_base;
     if (to_cache) user = cache_user(qc, __builtin_amdgcn_readfirstlane(min(m0, M - 32)));
 
-    f32x16 acc;
+    auto barrier = []() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    put(0, x0);
+    put(1, x1);
+    barrier();
+    f32x4 acc[RB];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    for (int s0 = 0; s0 + D < S; s0 += D) {
+    for (int i = 0; i < RB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int a_at = l15 * 64 + (kq ^ (l15 >> 2)) * 16;
+    auto turn = [&](int ch0, auto last_tag) __attribute__((always_inline)) {
+        constexpr bool last = decltype(last_tag)::value;
+        static_for<U>([&](auto u_tag) __attribute__((always_inline)) {
+            constexpr int u = decltype(u_tag)::value;
+            const int ch = ch0 + u;
+            const uint8_t *a = lds + (U == 2 ? u : ch & 1) * kBuf + a_at;
+            if constexpr (!last || u + 2 < U) fetch(min(ch + 2, n - 1), x0);
+            bf16x8 f[L][RB];
 #pragma unroll
-        for (int s = 0; s < D; ++s) {
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[s], fa[s], acc, 0, 0, 0);
-            load(s0 + D + s, s);
+            for (int t = 0; t < L; ++t)
+#pragma unroll
+                for (int i = 0; i < RB; ++i) f[t][i] = *(const bf16x8 *)(a + (i * C + t) * 1024);
             __builtin_amdgcn_sched_barrier(0);
-        }
-    }
 #pragma unroll
-    for (int s = 0; s < D; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[s], fa[s], acc, 0, 0, 0);
+            for (int t = 0; t < C; ++t) {
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ring[u * C + t], f[t % L][i], acc[i], 0, 0, 0);
+                    if (t + L < C) f[t % L][i] = *(const bf16x8 *)(a + (i * C + t + L) * 1024);
+                }
+                if constexpr (!last) ring[u * C + t] = weights(ch * C + t + R);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (!last || u + 2 < U) {
+                barrier();  // the chunk's rows are read, its buffer is the next but one's
+                put(U == 2 ? u : ch & 1, x0);
+            } else if constexpr (u + 1 < U) {
+                barrier();
+            }
+        });
+    };
+    int ch = 0;
+#pragma unroll 1
+    for (; ch + U < n; ch += U) turn(ch, std::false_type{});
+    turn(ch, std::true_type{});
 
-    // Epilogue (as wave_epilogue): the lane holds C[m0 + l32][n0 + 32 wn + 8g + 4hf + 0..3]; both waves stage
-    // their halves of the 64 columns, then each stores half of the block.
-    float rs = 1.f;
-    if (ss_fast) {
-        const float4 u = raw_ss[0], v = raw_ss[1];
-        const float ss = nin.n_part == 8 ? ((u.x + u.y) + (u.z + u.w)) + ((v.x + v.y) + (v.z + v.w))
-                                         : ((u.x + u.y) + u.z) + u.w;
-        rs = 1.f / sqrtf(ss * nin.inv_d + nin.eps);
-    } else if (scaled) {
-        rs = row_scale(nin, min(row, M - 1));
-    }
-    const bool zero_row = to_cache && row - user.t0 >= user.l_valid;
+    // Epilogue (as wave_epilogue): the lane holds C[m0 + 16 i + l15][n0 + 16 wave + 4 kq + 0..3]; the waves stage
+    // their quarters of the 64 columns, then each stores a quarter of the block.
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int col = 32 * wn + 8 * g + 4 * hf;
+    for (int i = 0; i < RB; ++i) {
+        const int row = m0 + 16 * i + l15, col = 16 * wave + 4 * kq;
+        uint8_t *const at = tr + (16 * i + l15) * kPitch;
         if (F32) {
-            *(float4 *)(tr + l32 * kPitch + col * 4) = float4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+            *(float4 *)(at + col * 4) = float4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
         } else {
+            float rs = 1.f;
+            if (ss_fast) {
+                const float4 u = raw_ss[i][0], v = raw_ss[i][1];
+                const float ss = nin.n_part == 8 ? ((u.x + u.y) + (u.z + u.w)) + ((v.x + v.y) + (v.z + v.w))
+                                                 : ((u.x + u.y) + u.z) + u.w;
+                rs = 1.f / sqrtf(ss * nin.inv_d + nin.eps);
+            } else if (scaled) {
+                rs = row_scale(nin, min(row, M - 1));
+            }
             __attribute__((aligned(8))) __bf16 v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float x = acc[4 * g + e] * rs;
+                const float x = acc[i][e] * rs;
                 v[e] = (__bf16)(EPI == EPI_GELU_BF16 ? gelu_erf(x) : EPI == EPI_RELU_BF16 ? fmaxf(x, 0.f) : x);
             }
-            if (zero_row) v[0] = v[1] = v[2] = v[3] = (__bf16)0.f;
-            *(uint2 *)(tr + l32 * kPitch + col * 2) = *(const uint2 *)v;
+            if (to_cache && row - user.t0 >= user.l_valid) v[0] = v[1] = v[2] = v[3] = (__bf16)0.f;
+            *(uint2 *)(at + col * 2) = *(const uint2 *)v;
         }
     }
     __syncthreads();
     if constexpr (F32) {
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int id = (4 * wn + it) * 64 + lane, r = id >> 4, cc = id & 15, out = m0 + r, col = n0 + cc * 4;
+        for (int i = 0; i < RB; ++i) {
+            const int r = 16 * i + (tid >> 4), cc = l15, out = m0 + r, col = n0 + cc * 4;
             float4 o = *(const float4 *)(tr + r * kPitch + cc * 16);
-            const float4 rd = rsd[it];
+            const float4 rd = rsd[i];
             o.x += rd.x; o.y += rd.y; o.z += rd.z; o.w += rd.w;
             if (out < M) {
-                *(float4 *)((float *)C + (int64_t)out * ldc + col) = o;
+                *(float4 *)((float *)Cout + (int64_t)out * ldc + col) = o;
                 if (nout.ss) {
                     bf16x4 ob;
                     ob[0] = (__bf16)o.x; ob[1] = (__bf16)o.y; ob[2] = (__bf16)o.z; ob[3] = (__bf16)o.w;
@@ -157,23 +210,18 @@ __global__ __launch_bounds__(128) void gemm_small_kernel(
             }
         }
     } else if (to_cache) {
-        store_block_to_cache<kPitch>(tr, qc, user, m0, n0, M, C, ldc, lane, 2 * wn, 2 * wn + 2);
-    } else {
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int it = 2 * wn + half;
-            if (EPI == EPI_GELU_BF16 && (tiled & kTiledC)) {
-                // piece `it` = (16-row group it / 2, k-tile it % 2) of the block
-                const int rr = 16 * (it >> 1) + (lane >> 2), c = (lane & 3) ^ ((lane >> 4) & 3);
-                if (m0 + rr < M)
-                    *(uint4 *)((uint8_t *)C + ((int64_t)((m0 >> 4) + (it >> 1)) * (N / 32) + (n0 >> 5) + (it & 1)) * 1024 +
-                               lane * 16) = *(const uint4 *)(tr + rr * kPitch + ((it & 1) * 4 + c) * 16);
-            } else {
-                const int id = it * 64 + lane, r = id >> 3, cc = id & 7;
-                if (m0 + r < M)
-                    *(uint4 *)((__bf16 *)C + (int64_t)(m0 + r) * ldc + n0 + cc * 8) =
-                        *(const uint4 *)(tr + r * kPitch + cc * 16);
-            }
+        store_block_to_cache<kPitch>(tr, qc, user, m0, n0, M, Cout, ldc, lane, wave, wave + 1);
+    } else if (wave < 2 * RB) {
+        if (EPI == EPI_GELU_BF16 && (tiled & kTiledC)) {
+            // piece `wave` = (16-row group wave / 2, k-tile wave % 2) of the block
+            const int rr = 16 * (wave >> 1) + (lane >> 2), c = (lane & 3) ^ (lane >> 4);
+            if (m0 + rr < M)
+                *(uint4 *)((uint8_t *)Cout + ((int64_t)((m0 >> 4) + (wave >> 1)) * (N / 32) + (n0 >> 5) + (wave & 1)) * 1024 +
+                           lane * 16) = *(const uint4 *)(tr + rr * kPitch + ((wave & 1) * 4 + c) * 16);
+        } else {
+            const int r = tid >> 3, cc = tid & 7;
+            if (m0 + r < M)
+                *(uint4 *)((__bf16 *)Cout + (int64_t)(m0 + r) * ldc + n0 + cc * 8) = *(const uint4 *)(tr + r * kPitch + cc * 16);
         }
     }
 }
@@ -181,15 +229,27 @@ __global__ __launch_bounds__(128) void gemm_small_kernel(
 template <int EPI>
 hipError_t launch_small(const GemmArgs &g, hipStream_t s)
 {
-    const int n_ct = g.N / 64, n_rt = (g.M + 31) / 32;
+    const int n_ct = g.N / 64;
+    // 16 rows a workgroup as long as that makes at most one per CU, two where K is short and no residual row waits for its sums (a direct cache write
+    // has blocks of 32).  Us a call, four layers, the line at 128 / 256 workgroups of 32 rows: d_model 512, K = 512, score of 192 rows 102.0 / 98.5, 256
+    // 104.0 / 100.7, 320 109.5 / 107.4; d_model 256, score of 400 rows 86.2 / 84.0, 640 92.6 / 88.6; with the residual projections score of 1600 rows 111.1 / 113.9;
+    // with K = 2048 (at 192) score of 640 rows 128.0 / 132.8, encode of 600 100.1 / 103.6.  At 64: score of 128 rows 92.5 / 101.4, 400 119.5 / 123.
+    const bool half = !g.qc.layer_base && (int64_t)n_ct * ((g.M + 31) / 32) <= (EPI != EPI_RESID_F32 && g.K <= 512 ? 256 : 128);
+    const int rows = half ? 16 : 32, n_rt = (g.M + rows - 1) / rows;
     const int by_cols = g.M < g.N && n_ct % 8 == 0;
     const unsigned grid = by_cols ? (unsigned)n_ct * n_rt : (unsigned)((n_rt + 7) / 8 * 8) * n_ct;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(128), 0, s, (const __bf16 *)g.A, g.lda, (const __bf16 *)g.W, g.M, g.N, g.K,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(NW * 64), 0, s, (const __bf16 *)g.A, g.lda, (const __bf16 *)g.W, g.M, g.N, g.K,
                            g.C, g.ldc, g.resid, g.ldr, g.nin, g.nout, g.tiled, g.qc, by_cols);
         return hipGetLastError();
     };
-    return g.K % 256 == 0 ? go(gemm_small_kernel<EPI, 16>) : go(gemm_small_kernel<EPI, 8>);
+    auto of = [&](auto rb) {
+        constexpr int RB = decltype(rb)::value;
+        if (g.K % 512 == 0) return go(gemm_small_kernel<EPI, RB, 8, 2>);
+        if (g.K % 256 == 0) return go(gemm_small_kernel<EPI, RB, 8, 1>);
+        return go(gemm_small_kernel<EPI, RB, 4, 1>);
+    };
+    return half ? of(std::integral_constant<int, 1>{}) : of(std::integral_constant<int, 2>{});
 }
 
 }  // namespace

@@ -252,7 +252,7 @@ def test_layer_tail_with_weights_requested_ahead_gives_the_bits_of_three(d_ffn, 
     assert np.array_equal(yc[:g.m_total], g.score())
 
 
-@pytest.mark.parametrize("d_ffn, m", [(1024, 1537), (2048, 2049), (1280, 4096)])
+@pytest.mark.parametrize("d_ffn, m", [(1024, 2049), (2048, 2305), (1280, 4096)])
 def test_down_projection_on_a_longer_ring_gives_the_bits_of_the_tail(d_ffn, m):
     # candidates alone by 64 x 128 tiles, whose ring is six k-tiles long where K is 1024 and more, the last row's tile nearly empty;
     # with the history's rows in the tail's one launch
@@ -265,6 +265,24 @@ def test_down_projection_on_a_longer_ring_gives_the_bits_of_the_tail(d_ffn, m):
     y = torch.empty(m, 512, device="cuda:0")
     run = launches(lambda: g.P.climber_sumi_score(g.cfg, g.layers, g.tau, g.cache, g.x_cand, g.cand_off, m, m, g.cscen, g.cbeh, y, g.ws))
     assert any("gemm_bf16_kernelILi2ELi1ELi2ELi6E" in k.kernel for k in run)
+
+
+@pytest.mark.parametrize("d_model, d_ffn, m, rows", [
+    (384, 128, 1, 1), (384, 384, 15, 1), (384, 640, 17, 1), (512, 768, 31, 1), (512, 1536, 33, 1), (512, 2048, 16, 1), (512, 512, 129, 1),
+    (512, 2048, 512, 1), (512, 2048, 513, 2), (512, 1024, 2017, 2), (512, 1024, 2048, 2), (384, 896, 1313, 2), (768, 640, 353, 2), (768, 256, 385, 2)])
+def test_few_rows_give_the_bits_of_the_macro_tiles(d_model, d_ffn, m, rows):
+    # candidates alone in blocks of 16 (rows 1) or 32 (rows 2) rows, against the tiles that they share with 11520 rows of history; K a multiple of 128,
+    # 256 or 512 only, one chunk of it and an odd number of chunks; the last block with 1 to all of its rows; both sides of the line between 16 and 32 rows
+    # and the largest launch of the residual projections
+    spec = W.StackSpec(f"fwd-few-{d_model}-{d_ffn}-{m}", B=30, L=384, sub_len=128, M=0, n_layers=2, d_model=d_model, H=d_model // 64, dh=64,
+                       d_ffn=d_ffn, n_scen=8, n_beh=4, seed=540 + m, hist_lens=(384,) * 30, cand_counts=(m,) + (0,) * 29)
+    w, g, yc = run_forward(spec, users=(1,), want_hist=True)
+    g.encode()
+    assert np.array_equal(yc[:g.m_total], g.score())
+    import torch
+    y = torch.empty(m, d_model, device="cuda:0")
+    run = launches(lambda: g.P.climber_sumi_score(g.cfg, g.layers, g.tau, g.cache, g.x_cand, g.cand_off, m, m, g.cscen, g.cbeh, y, g.ws))
+    assert any(f"gemm_small_kernelILi2ELi{rows}E" in k.kernel for k in run)
 
 
 @pytest.mark.parametrize("d_ffn, m, head", [(128, 1, True), (384, 31, True), (1024, 33, True), (1024, 1024, True), (1024, 1025, False),
