@@ -10,7 +10,8 @@
 //
 // Bound by its beginning (about 5 us for a launch: first touches of rows, keys and code) and then by the chain of value products, two
 // MFMAs of 32x32x16 a block that wait for each other, and a round's meeting: 0.10 us per 32 keys, 0.21 where one wave does all of it.  NP:
-// 200 candidates of one user against 1000, 8 heads, 8.7 us with 2, 9.2 with 3, 8.4 with 4, 8.6 with 6, against 4000 20.6, 22.1, 18.2, 17.5.
+// 200 candidates of one user against 1000, 8 heads, 8.7 us with 2, 9.2 with 3, 8.4 with 4, 8.6 with 6, against 4000 (values one
+// round ahead) 20.6, 22.1, 18.2, 17.5.  Keys four rounds ahead instead of two, or a round's probabilities read under the products of the round before: no faster.
 //
 // The pilot (which decides whether to fold, attn_bf16.hip), the own key and value and the SAFE pass as in attn_wave_bf16.hip.
 #include "attn_common.h"
@@ -30,7 +31,8 @@ struct Slot {  // a block's probabilities (B operands of the value product) and 
     float sum[64];
 };
 
-template <bool SUMI, bool CAUSAL>
+// VR: rounds that the values are requested ahead.
+template <bool SUMI, bool CAUSAL, int VR>
 __global__ __launch_bounds__((NP + 2) * 64, 2) void attn_split_kernel(const KParams p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t tr[2 * 32 * kHalfPitch];
@@ -219,7 +221,7 @@ __global__ __launch_bounds__((NP + 2) * 64, 2) void attn_split_kernel(const KPar
 #pragma unroll
     for (int r = 0; r < 16; ++r) O[r] = st.O[1][0][r] = 0.f;
     st.l[0] = 0.f;
-    bf16x8 v[NP][2];
+    bf16x8 v[VR][NP][2];
     auto load_block_v = [&](int blk, bf16x8 (&f)[2]) __attribute__((always_inline)) {
         const uint8_t *from = kv + (size_t)min(blk, n_blk - 1) * kBlockBytes + 4096 + (db * 64 + lane) * 16;
         f[0] = *(const bf16x8 *)from;
@@ -227,7 +229,7 @@ __global__ __launch_bounds__((NP + 2) * 64, 2) void attn_split_kernel(const KPar
     };
     if (n_blk > 0) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i) load_block_v(i, v[i]);
+        for (int i = 0; i < VR * NP; ++i) load_block_v(i, v[i / NP][i % NP]);
     }
     float w_own = 0.f;
     if (SUMI) w_own = __builtin_amdgcn_exp2f(own_dot() * (fold ? 1.f : st.c[0]));
@@ -237,7 +239,12 @@ __global__ __launch_bounds__((NP + 2) * 64, 2) void attn_split_kernel(const KPar
 #pragma unroll
             for (int e = 0; e < 4; ++e) O[4 * i + e] = fmaf(w, (float)v_own[i][e], O[4 * i + e]);
     };
-    for (int r = 0; r < n_rounds; ++r) {
+    // (one loop body, not a lambda called for each u: that one's schedule takes 17 registers more, and 0.4 us of the shortest launches)
+    for (int r0 = 0; r0 < n_rounds; r0 += VR)
+#pragma unroll
+    for (int u = 0; u < VR; ++u) {
+        const int r = r0 + u;
+        if (u > 0 && r >= n_rounds) break;
         meet();
         bf16x8 P[NP][2];
         float sum[NP];
@@ -256,12 +263,12 @@ __global__ __launch_bounds__((NP + 2) * 64, 2) void attn_split_kernel(const KPar
             }
             if (r * NP + i < n_blk) {
                 st.l[0] += sum[i];
-                O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[i][0], P[i][0], O, 0, 0, 0);
-                O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[i][1], P[i][1], O, 0, 0, 0);
+                O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[u][i][0], P[i][0], O, 0, 0, 0);
+                O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[u][i][1], P[i][1], O, 0, 0, 0);
             }
         }
 #pragma unroll
-        for (int i = 0; i < NP; ++i) load_block_v((r + 1) * NP + i, v[i]);  // (not under the condition: the waits would lose count)
+        for (int i = 0; i < NP; ++i) load_block_v((r + VR) * NP + i, v[u][i]);  // (not under the condition: the waits would lose count)
     }
     if (SUMI) {
         if (n_blk <= 8) own_v(w_own);
@@ -284,12 +291,12 @@ __global__ __launch_bounds__((NP + 2) * 64, 2) void attn_split_kernel(const KPar
         for (int blk = 0; blk < n_blk; ++blk) {
             bf16x8 P[1][2];
             load_block_k(blk, pilot_k);
-            load_block_v(blk, v[0]);
+            load_block_v(blk, v[0][0]);
             qk_block(st, pilot_k, S0);
             if (blk == n_blk - 1) mask_tail(S0, blk);
             softmax_safe(st, S0, P);
-            O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[0][0], P[0][0], O, 0, 0, 0);
-            O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[0][1], P[0][1], O, 0, 0, 0);
+            O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[0][0][0], P[0][0], O, 0, 0, 0);
+            O = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[0][0][1], P[0][1], O, 0, 0, 0);
         }
         lt = st.l[0] + xhalf(st.l[0]);
     }
@@ -325,9 +332,14 @@ hipError_t launch_attn_split_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
     KParams p = make_params(a, n_qtiles);
     p.pilot_pairs = sumi && a.max_rows_per_user > 128;
     const dim3 g((unsigned)grid), t((NP + 2) * 64);
-    if (sumi) hipLaunchKernelGGL((attn_split_kernel<true, false>), g, t, 0, s, p);
-    else if (a.causal) hipLaunchKernelGGL((attn_split_kernel<false, true>), g, t, 0, s, p);
-    else hipLaunchKernelGGL((attn_split_kernel<false, false>), g, t, 0, s, p);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, t, 0, s, p); };
+    // Values a round further ahead where the walk is long, and what is requested in vain at its end little of it.  Us the call, one round ahead / two: 200
+    // candidates against 4000 behaviours 18.6 / 17.7, 2 users x 64 20.8 / 18.6, 100 against 2000 (2 users) 11.8 / 11.5, 1500 9.9 / 9.8, 200 against 1000 8.2 / 8.2,
+    // 700 7.4 / 7.6, 4 x 64 against 256 5.6 / 6.0.  A history tile's subsequence is short, and without them even.
+    if (sumi && a.max_hist_len > 1024) go(attn_split_kernel<true, false, 2>);
+    else if (sumi) go(attn_split_kernel<true, false, 1>);
+    else if (a.causal) go(attn_split_kernel<false, true, 1>);
+    else go(attn_split_kernel<false, false, 1>);
     return hipGetLastError();
 }
 

@@ -350,6 +350,17 @@ def test_keys_shared_out_among_waves_give_the_bits_of_other_launches(L, L_min, n
         assert np.array_equal(part, full[g.last_idx])
 
 
+@pytest.mark.parametrize("L,L_min,n_scen", [(1025, 1025, 8), (1056, 40, 8), (1153, 1153, 8), (1300, 0, 17), (2048, 2048, 8)])
+def test_values_two_rounds_ahead_give_the_bits_of_other_launches(L, L_min, n_scen):
+    # histories of more than 1024: odd and even numbers of rounds, the last one with one to four blocks, users with one round and none
+    test_keys_shared_out_among_waves_give_the_bits_of_other_launches(L, L_min, n_scen)
+
+
+@pytest.mark.parametrize("L", [1030, 1160])
+def test_values_two_rounds_ahead_where_one_key_outgrows_the_rest(L):
+    test_keys_shared_out_among_waves_where_one_key_outgrows_the_rest(L)
+
+
 @pytest.mark.parametrize("L", [150, 300])
 def test_keys_shared_out_among_waves_where_one_key_outgrows_the_rest(L):
     # rows whose logits leave every window: the running-maximum pass, by both of the waves that add up, against a wave per 32 queries
