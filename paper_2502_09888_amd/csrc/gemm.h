@@ -81,7 +81,13 @@ struct GemmArgs {
     QkvToCache qc;
 };
 // gemm_small_bf16.hip: few rows.  N % 64 == 0, K % 128 == 0.
+bool gemm_small_takes(int epi, int M, int N, int K);  // instead of the macro tiles
 hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s);
+// The fused QKV projection of few rows as a call has them (x: bf16 [M][K]) with what row_prep_bf16 does for them: their sums of squares and
+// their fp32 copy [M][K] in x32 (in_norm: inv_d and eps).  N >= K.
+bool gemm_small_sums(int M, int N, int K);
+hipError_t gemm_small_given(const void *x, float *x32, const void *w_packed, int M, int N, int K, void *C, int64_t ldc, const RowNormIn &in_norm,
+                            const QkvToCache &to_cache, hipStream_t s);
 
 // Where the fused QKV projection of a call's rows goes: rows [0, n_cached), the history's, keys and values into the cache and
 // queries to rows of q; the others as rows of `rows`, row n_cached first.  n_cached: none, or qc.rows.

@@ -281,14 +281,7 @@ hipError_t launch(const GemmArgs &g, hipStream_t s)
 template <int EPI>
 hipError_t dispatch(const GemmArgs &g, hipStream_t s)
 {
-    // Few rows: 64 columns of 16 or 32 rows a workgroup (gemm_small_bf16.hip), until the tiles' reuse of their operands wins: from one workgroup of 32 rows
-    // per CU on for QKV, from two for the residual projections, from 2.5 for the up-projection, whose tiled store is a workgroup's own.  Us per call, four layers,
-    // d_model 512.  QKV, the line at 256 / 512 / 640 workgroups: score of 560 rows 124.8 / 127.1, 640 127 / 128, 800 128 / - / 134, 1000 131 / - / 131 (768: 136).  Up, at 256
-    // / 512 / 640: score of 320 rows 113.5 / 109.5, 400 119.5 / 115.3, 560 - / 127.1 / 124.5, 640 - / 128.1 / 127.4 (768 / 1024: request of 1000 behaviours 223
-    // / 228 instead of 217).  Residual, at 384 / 512 / 640 or more: score of 1600 rows 204 / 182, 2000 203 / 185, 2400 223.3 / - / 222, 3200 251 / - / 262, encode of
-    // 2048 rows 152.5 / 138; d_model 256, score of 3200 160.7 / 147.6, 4096 158.8 / 154.
-    if ((int64_t)(g.N / 64) * ((g.M + 31) / 32) <= (EPI == EPI_RESID_F32 ? 512 : EPI == EPI_GELU_BF16 ? 640 : 256) && g.K % 128 == 0)
-        return gemm_small_bf16(EPI, g, s);
+    if (gemm_small_takes(EPI, g.M, g.N, g.K)) return gemm_small_bf16(EPI, g, s);
     // macro tile 256 x 128 when that still gives every CU two workgroups, else 128 x 128
     const int64_t big_tiles = (int64_t)(g.N / 128) * ((g.M + 255) / 256);
     if (big_tiles >= 512) return launch<EPI, 4, 2, 3>(g, s);

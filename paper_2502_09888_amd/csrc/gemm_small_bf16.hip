@@ -27,15 +27,19 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 constexpr int NW = 4;
 
 // RB blocks of 16 rows a workgroup; K in chunks of C k-tiles of 32, of which U are a turn of the loop and of the weights' ring.
-template <int EPI, int RB, int C, int U>
+// OWN: the rows are a call's inputs.  Their sums of squares are formed here, in row_prep_bf16's order, and their fp32 copy goes to x32,
+// 64 columns by each of the first K / 64 workgroups of a row block: instead of a launch before, which the smallest calls take 4 us for.  K of 256 or 512.
+template <int EPI, int RB, int C, int U, bool OWN>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     const __bf16 *A, int64_t lda, const __bf16 *Wp, int M, int N, int K, void *Cout, int64_t ldc, const float *resid,
-    int64_t ldr, const RowNormIn nin, const RowNormOut nout, const int tiled, const QkvToCache qc, const int by_cols)
+    int64_t ldr, const RowNormIn nin, const RowNormOut nout, const int tiled, const QkvToCache qc, const int by_cols, float *x32)
 {
     constexpr bool F32 = EPI == EPI_RESID_F32;
     constexpr int kPitch = epilogue_pitch<EPI, 2>(), kRows = 16 * RB, R = C * U, P = RB * C / NW, kBuf = RB * C * 1024, L = C < 4 ? C : 4;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kBuf + kRows * kPitch];
     uint8_t *const tr = lds + 2 * kBuf;
+    __shared__ float parts[OWN ? NW : 1][RB][64][2], scale[kRows];
+    static_assert(!OWN || (C == 8 && EPI == EPI_STORE_BF16), "");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l15 = lane & 15, kq = lane >> 4;
@@ -92,7 +96,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
 
     // what the epilogue needs of global memory is requested behind the first operands: the partial sums of
     // squares of the input rows (the lane's accumulators belong to rows l15 of the blocks), or the residual rows
-    const bool scaled = !F32 && nin.ss, ss_fast = scaled && (nin.n_part == 8 || nin.n_part == 4);
+    const bool scaled = !F32 && !OWN && nin.ss, ss_fast = scaled && (nin.n_part == 8 || nin.n_part == 4);
     float4 raw_ss[RB][2] = {};
     if (ss_fast) {
 #pragma unroll
@@ -119,7 +123,41 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     };
     put(0, x0);
     put(1, x1);
+    if constexpr (OWN) {
+        // row_prep_bf16 adds the squares of four columns c and c + 256, then of column groups 32, 16, 8, 4, 2 and 1 apart: k-tiles 8 apart (the next chunk),
+        // 4 (the wave's next), 2 and 1 (other waves), and the row's other places
+#pragma unroll
+        for (int g = 0; g < RB; ++g)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                float v[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    auto sum = [&](const u32x4 &x) __attribute__((always_inline)) {
+                        const uint32_t a = x[2 * e], b = x[2 * e + 1];
+                        return sumsq4(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u), __uint_as_float(b << 16), __uint_as_float(b & 0xffff0000u));
+                    };
+                    v[i] = sum(x0[2 * g + i]);
+                    if (U == 2) v[i] += sum(x1[2 * g + i]);
+                }
+                parts[wave][g][lane][e] = v[0] + v[1];
+            }
+    }
     barrier();
+    if constexpr (OWN) {
+        if (wave < RB) {
+            float v[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                auto of = [&](int w) __attribute__((always_inline)) { return parts[w][wave][lane][e]; };
+                v[e] = (of(0) + of(2)) + (of(1) + of(3));
+                v[e] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[e]), 0x4E, 0xf, 0xf, false));  // quad_perm [2,3,0,1]
+                v[e] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[e]), 0xB1, 0xf, 0xf, false));  // quad_perm [1,0,3,2]
+            }
+            const float ss = v[0] + v[1];
+            if ((lane & 3) == 0) scale[16 * wave + (lane >> 2)] = 1.f / sqrtf(ss * nin.inv_d + nin.eps);
+        }
+    }
     f32x4 acc[RB];
 #pragma unroll
     for (int i = 0; i < RB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -160,6 +198,17 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     for (; ch + U < n; ch += U) turn(ch, std::false_type{});
     turn(ch, std::true_type{});
 
+    if constexpr (OWN) {
+        if (ct < K / 64) {
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+                const int r = tid >> 4, cc = l15, kt = 2 * ct + (cc >> 3), out = m0 + 16 * i + r;
+                const bf16x4 v = *(const bf16x4 *)(lds + (kt / C) * kBuf + (i * C + kt % C) * 1024 + r * 64 + (((cc >> 1) & 3) ^ (r >> 2)) * 16 + (cc & 1) * 8);
+                if (out < M) *(float4 *)(x32 + (int64_t)out * K + 64 * ct + 4 * cc) = float4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+            }
+        }
+        barrier();  // the rows' scales
+    }
     // Epilogue (as wave_epilogue): the lane holds C[m0 + 16 i + l15][n0 + 16 wave + 4 kq + 0..3]; the waves stage
     // their quarters of the 64 columns, then each stores a quarter of the block.
 #pragma unroll
@@ -169,7 +218,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
         if (F32) {
             *(float4 *)(at + col * 4) = float4{acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
         } else {
-            float rs = 1.f;
+            float rs = OWN ? scale[16 * i + l15] : 1.f;
             if (ss_fast) {
                 const float4 u = raw_ss[i][0], v = raw_ss[i][1];
                 const float ss = nin.n_part == 8 ? ((u.x + u.y) + (u.z + u.w)) + ((v.x + v.y) + (v.z + v.w))
@@ -226,8 +275,8 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     }
 }
 
-template <int EPI>
-hipError_t launch_small(const GemmArgs &g, hipStream_t s)
+template <int EPI, bool OWN = false>
+hipError_t launch_small(const GemmArgs &g, hipStream_t s, float *x32 = nullptr)
 {
     const int n_ct = g.N / 64;
     // 16 rows a workgroup as long as that makes at most one per CU, two where K is short and no residual row waits for its sums (a direct cache write
@@ -240,19 +289,46 @@ hipError_t launch_small(const GemmArgs &g, hipStream_t s)
     const unsigned grid = by_cols ? (unsigned)n_ct * n_rt : (unsigned)((n_rt + 7) / 8 * 8) * n_ct;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(NW * 64), 0, s, (const __bf16 *)g.A, g.lda, (const __bf16 *)g.W, g.M, g.N, g.K,
-                           g.C, g.ldc, g.resid, g.ldr, g.nin, g.nout, g.tiled, g.qc, by_cols);
+                           g.C, g.ldc, g.resid, g.ldr, g.nin, g.nout, g.tiled, g.qc, by_cols, x32);
         return hipGetLastError();
     };
     auto of = [&](auto rb) {
         constexpr int RB = decltype(rb)::value;
-        if (g.K % 512 == 0) return go(gemm_small_kernel<EPI, RB, 8, 2>);
-        if (g.K % 256 == 0) return go(gemm_small_kernel<EPI, RB, 8, 1>);
-        return go(gemm_small_kernel<EPI, RB, 4, 1>);
+        if (g.K % 512 == 0) return go(gemm_small_kernel<EPI, RB, 8, 2, OWN>);
+        if constexpr (OWN) {
+            return go(gemm_small_kernel<EPI, RB, 8, 1, true>);
+        } else {
+            if (g.K % 256 == 0) return go(gemm_small_kernel<EPI, RB, 8, 1, false>);
+            return go(gemm_small_kernel<EPI, RB, 4, 1, false>);
+        }
     };
     return half ? of(std::integral_constant<int, 1>{}) : of(std::integral_constant<int, 2>{});
 }
 
 }  // namespace
+
+bool gemm_small_takes(int epi, int M, int N, int K)
+{
+    // Few rows: until the tiles' (gemm_bf16.hip) reuse of their operands wins: from one workgroup of 32 rows
+    // per CU on for QKV, from two for the residual projections, from 2.5 for the up-projection, whose tiled store is a workgroup's own.  Us per call, four layers,
+    // d_model 512.  QKV, the line at 256 / 512 / 640 workgroups: score of 560 rows 124.8 / 127.1, 640 127 / 128, 800 128 / - / 134, 1000 131 / - / 131 (768: 136).  Up, at 256
+    // / 512 / 640: score of 320 rows 113.5 / 109.5, 400 119.5 / 115.3, 560 - / 127.1 / 124.5, 640 - / 128.1 / 127.4 (768 / 1024: request of 1000 behaviours 223
+    // / 228 instead of 217).  Residual, at 384 / 512 / 640 or more: score of 1600 rows 204 / 182, 2000 203 / 185, 2400 223.3 / - / 222, 3200 251 / - / 262, encode of
+    // 2048 rows 152.5 / 138; d_model 256, score of 3200 160.7 / 147.6, 4096 158.8 / 154.
+    return K % 128 == 0 && (int64_t)(N / 64) * ((M + 31) / 32) <= (epi == EPI_RESID_F32 ? 512 : epi == EPI_GELU_BF16 ? 640 : 256);
+}
+
+bool gemm_small_sums(int M, int N, int K)
+{
+    return (K == 256 || K == 512) && !gemm_resident_takes(M, K, false) && !gemm_resident_takes(M, K, true) && gemm_small_takes(EPI_STORE_BF16, M, N, K);
+}
+
+hipError_t gemm_small_given(const void *x, float *x32, const void *w_packed, int M, int N, int K, void *C, int64_t ldc, const RowNormIn &in_norm,
+                            const QkvToCache &to_cache, hipStream_t s)
+{
+    if (M < 1 || N % 64 != 0 || N < K || (K != 256 && K != 512)) return hipErrorInvalidValue;
+    return launch_small<EPI_STORE_BF16, true>(GemmArgs{x, K, w_packed, M, N, K, C, ldc, nullptr, 0, in_norm, RowNormOut{}, 0, to_cache}, s, x32);
+}
 
 hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s)
 {

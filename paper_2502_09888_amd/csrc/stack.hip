@@ -182,6 +182,15 @@ int project_qkv(const climber_config *cfg, const PackedLayer &pw, const void *in
                         no_out, 0, s, &out.qc));
 }
 
+// the first layer's, of the rows as the call has them: instead of row_prep_bf16 and project_qkv where gemm_small_sums says so
+int project_given(const climber_config *cfg, const PackedLayer &pw, const void *x, float *x32, int64_t rows, const RowNormIn &nin, const QkvOut &out,
+                  hipStream_t s)
+{
+    const int d = cfg->d_model, skip = out.qc.which0 * d;
+    return rt(gemm_small_given(x, x32, pw.wqkv + (size_t)skip * d * 2, (int)rows, 3 * d - skip, d, out.n_cached ? out.q : out.rows,
+                               out.n_cached ? out.ld_q : out.ld_rows, nin, out.qc, s));
+}
+
 // one layer on `rows` rows.  x_in: fp32 rows (the residual stream); xb_in / ws.ss: their bf16 copy and
 // row sums of squares (from the previous layer's last projection or from a row_prep kernel).
 // norm_out: also emit the bf16 copy and sums of squares of x_out (the next layer needs them).
@@ -287,9 +296,15 @@ int score_layers(const climber_config *cfg, const climber_weights *weights, cons
     const bool as_given = layer_tail_reads_bf16(m_total, cfg->d_model, cfg->d_ffn) &&
                           (cfg->n_layers > 1 || !overlap(x_cand, (size_t)m_total * cfg->d_model * 2, y_cand, (size_t)m_total * cfg->d_model * 4));
     const GivenRows given{x_cand, nullptr, (int64_t)(m_total + 63) / 64 * 64};
-    TRY(rt(row_prep_bf16(x_cand, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, m_total, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
-    bool projected = false;  // the layer's QKV projection is made already, by the tail before
+    bool projected = !as_given && gemm_small_sums(m_total, 3 * cfg->d_model, cfg->d_model);  // the layer's QKV projection is made already: below, or by the tail before
+    if (projected) {
+        QkvOut to{};
+        to.rows = ws.qkv, to.ld_rows = 3 * cfg->d_model;
+        TRY(project_given(cfg, packed_layer(cfg, ws, 0), x_cand, ws.x32, m_total, RowNormIn{ws.ss, cfg->d_model / 64, 1.f / (float)cfg->d_model, cfg->rms_eps}, to, s));
+    } else {
+        TRY(rt(row_prep_bf16(x_cand, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, m_total, cfg->d_model, s)));
+    }
     for (int l = 0; l < cfg->n_layers; ++l) {
         const bool last = l + 1 == cfg->n_layers, chain = !last && layer_tail_projects(m_total, cfg->d_model, cfg->d_ffn, 0, false);
         NextQkv next{};
@@ -420,10 +435,17 @@ int climber_history_encode(const climber_config *cfg, const climber_weights *wei
     TRY(stage_weights(cfg, weights, ws, s));
     const bool as_given = layer_tail_reads_bf16((int)rows, cfg->d_model, cfg->d_ffn);
     const GivenRows given{x_hist, nullptr, rows};
-    TRY(rt(row_prep_bf16(x_hist, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, rows, cfg->d_model, s)));
     const size_t tl = (size_t)cfg->n_scen * cfg->n_beh;
     const bool direct = !(cfg->flags & CLIMBER_QKV_VIA_ROWS);  // (the cache holds rows)
-    bool projected = false;  // the layer's QKV projection is made already, by the tail before
+    bool projected = direct && !as_given && gemm_small_sums((int)rows, 3 * cfg->d_model, cfg->d_model);  // the layer's QKV projection is made already: below, or by the tail before
+    if (projected) {
+        QkvOut to{};
+        if (!cache_direct_target(cfg, cache, 0, &to.qc)) return CLIMBER_ERR_RUNTIME;
+        to.n_cached = (int)rows, to.q = ws.qkv, to.ld_q = cfg->d_model, to.qc.which0 = cfg->n_layers > 1 ? 0 : 1;
+        TRY(project_given(cfg, packed_layer(cfg, ws, 0), x_hist, ws.x32, rows, RowNormIn{ws.ss, cfg->d_model / 64, 1.f / (float)cfg->d_model, cfg->rms_eps}, to, s));
+    } else {
+        TRY(rt(row_prep_bf16(x_hist, as_given ? nullptr : ws.x32, ws.ss, cfg->d_model / 64, rows, cfg->d_model, s)));
+    }
     for (int l = 0; l < cfg->n_layers; ++l) {
         const bool last = l + 1 == cfg->n_layers;                // nothing reads the last layer's history output
         const bool ends = direct && l + 2 == cfg->n_layers;      // the next layer: keys and values only

@@ -285,6 +285,27 @@ def test_few_rows_give_the_bits_of_the_macro_tiles(d_model, d_ffn, m, rows):
     assert any(f"gemm_small_kernelILi2ELi{rows}E" in k.kernel for k in run)
 
 
+@pytest.mark.parametrize("d_model, layers, lens, cands, sums", [(512, 1, (64,), (1,), True), (256, 2, (1, 64), (15, 2), True), (512, 3, (130, 60), (129, 31), True),
+                                                                (256, 2, (560, 0, 40), (672, 0, 0), True), (512, 2, (320,), (320,), True),
+                                                                (512, 2, (321,), (321,), False), (384, 2, (100,), (33,), False)])
+def test_first_projection_of_few_rows_makes_their_sums_and_copies(d_model, layers, lens, cands, sums):
+    # few rows of 256 or 512 columns: the first layer's projection forms the sums of squares and the fp32 residual rows itself, in
+    # blocks of 16 or 32 rows for candidates, of 32 into the cache; against the packed forward and the encode by way of rows, which have a launch
+    # for them: one row to the most there are, and one block more; NaN in the padding
+    spec = W.StackSpec(f"fwd-sums-{d_model}-{sum(cands)}", B=len(lens), L=0, sub_len=128, M=0, n_layers=layers, d_model=d_model, H=d_model // 64, dh=64,
+                       d_ffn=512, n_scen=8, n_beh=4, seed=640 + sum(cands), pad_to=64, hist_lens=lens, cand_counts=cands, nan_padding=True)
+    w, g, yc = run_forward(spec, users=(0,), want_hist=True)
+    other = GpuStack(w, flags=4)
+    other.encode()
+    assert np.array_equal(yc[:g.m_total], other.score())
+    g.encode()
+    assert np.array_equal(yc[:g.m_total], g.score())
+    import torch
+    y = torch.empty(g.m_total, d_model, device="cuda:0")
+    for call in (g.encode, lambda: g.P.climber_sumi_score(g.cfg, g.layers, g.tau, g.cache, g.x_cand, g.cand_off, g.m_total, g.m_max, g.cscen, g.cbeh, y, g.ws)):
+        assert any("row_prep_kernel" in k.kernel for k in launches(call)) != sums
+
+
 @pytest.mark.parametrize("d_ffn, m, head", [(128, 1, True), (384, 31, True), (1024, 33, True), (1024, 1024, True), (1024, 1025, False),
                                             (2048, 500, True), (256, 4096, True)])
 def test_projection_and_hidden_in_one_launch_give_the_bits_of_two(d_ffn, m, head):
