@@ -28,7 +28,7 @@ constexpr int NW = 4;
 
 // RB blocks of 16 rows a workgroup; K in chunks of C k-tiles of 32, of which U are a turn of the loop and of the weights' ring.
 // OWN: the rows are a call's inputs.  Their sums of squares are formed here, in row_prep_bf16's order, and their fp32 copy goes to x32,
-// 64 columns by each of the first K / 64 workgroups of a row block: instead of a launch before, which the smallest calls take 4 us for.  K of 256 or 512.
+// 64 columns by each of the first K / 64 workgroups of a row block: instead of a launch before, 2 to 2.5 us.  K of 256 or 512.
 template <int EPI, int RB, int C, int U, bool OWN>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     const __bf16 *A, int64_t lda, const __bf16 *Wp, int M, int N, int K, void *Cout, int64_t ldc, const float *resid,
@@ -320,7 +320,10 @@ bool gemm_small_takes(int epi, int M, int N, int K)
 
 bool gemm_small_sums(int M, int N, int K)
 {
-    return (K == 256 || K == 512) && !gemm_resident_takes(M, K, false) && !gemm_resident_takes(M, K, true) && gemm_small_takes(EPI_STORE_BF16, M, N, K);
+    // A launch less is worth a first projection of up to three workgroups per CU.  Us a call of four layers, the line at 256 / 768 workgroups: score of 336 rows of
+    // 512 113.8 / 111.4, 680 126.7 / 124.8, 1000 130.6 / 128.7, of 256 680 92.9 / 90.4, 1600 111.4 / 109.9; encode of 512 rows 90.5 / 87.1, 1000 102.3 / 100.6 (one
+    // layer 11.1 / 8.0), of 256 2048 87.4 / 85.9; from there to 1024 even (score of 1200 rows of 512 167.4 / 167.4).
+    return (K == 256 || K == 512) && !gemm_resident_takes(M, K, false) && !gemm_resident_takes(M, K, true) && (int64_t)(N / 64) * ((M + 31) / 32) <= 768;
 }
 
 hipError_t gemm_small_given(const void *x, float *x32, const void *w_packed, int M, int N, int K, void *C, int64_t ldc, const RowNormIn &in_norm,

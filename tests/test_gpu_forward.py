@@ -286,8 +286,9 @@ def test_few_rows_give_the_bits_of_the_macro_tiles(d_model, d_ffn, m, rows):
 
 
 @pytest.mark.parametrize("d_model, layers, lens, cands, sums", [(512, 1, (64,), (1,), True), (256, 2, (1, 64), (15, 2), True), (512, 3, (130, 60), (129, 31), True),
-                                                                (256, 2, (560, 0, 40), (672, 0, 0), True), (512, 2, (320,), (320,), True),
-                                                                (512, 2, (321,), (321,), False), (384, 2, (100,), (33,), False)])
+                                                                (256, 2, (560, 0, 40), (672, 0, 0), True), (512, 2, (1024,), (1024,), True),
+                                                                (512, 2, (1025,), (1025,), False), (256, 2, (1984, 1), (2048, 0), True),
+                                                                (384, 2, (100,), (33,), False)])
 def test_first_projection_of_few_rows_makes_their_sums_and_copies(d_model, layers, lens, cands, sums):
     # few rows of 256 or 512 columns: the first layer's projection forms the sums of squares and the fp32 residual rows itself, in
     # blocks of 16 or 32 rows for candidates, of 32 into the cache; against the packed forward and the encode by way of rows, which have a launch
