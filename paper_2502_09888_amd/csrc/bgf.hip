@@ -260,16 +260,16 @@ __global__ __launch_bounds__(512, 4) void bgf_gate_kernel(const __bf16 *gb, cons
 
 }  // namespace
 
-// A workgroup streams both weights for its 32 candidates, whoever else does, so few of them are better served by the tiles: up to 2048
-// candidates by those of gemm_small_bf16.hip, further on with a wide G, whose weights the macro tiles read less often.  Us a call, one launch / three,
-// G as blocks x d_model.  d_gate 256: 4 x 512 2000 131.7 / 124.6, 2300 142.0 / 146.8, 8192 336 / 346, 4 x 256 2000 70.5 / 69.5, 2500 73.6 / 77.5;
-// 6 x 512 5000 347 / 339, 7000 471 / 473, 8 x 512 5000 467 / 460, 6000 516 / 520, 8192 665 / 679, 16 x 512 5000 1011 / 991, 6000 1173 / 1172.  d_gate 128:
-// 4 x 512 1000 and 1500 even, 2300 131.9 / 134.0, 8192 324 / 340, 8 x 512 1000 141 / 137, 1500 163 / 165, 2500 276 / 273, 4000 even, 8192 643 /
-// 672, 16 x 512 2000 445 / 421, 4000 772 / 759, 5000 945 / 1005, 1 x 256 1500 36.4 / 40.2.
+// A workgroup streams both weights for its 32 candidates, whoever else does, so few of them are better served by the projections for few rows
+// (gemm_small_bf16.hip), further on with a wide G, whose weights the macro tiles read less often.  Us a call, one launch / three, G as blocks x
+// d_model.  d_gate 256: 4 x 512 2100 121.5 / 116.9, 2900 131.7 / 127.5, 3900 151.2 / 150.8, 4400 222 / 226, 2 x 512 2100 87.9 / 87.3, 4000 99.6 / 101.0, 1 x 512 2100 68.9
+// / 70.3, 4000 79.1 / 82.6, 2 x 256 2100 54.6 / 56.4, 6 x 512 5800 387.0 / 386.4, 6300 400 / 403, 8 x 512 6100 447 / 443.  d_gate 128: 1 x 256 1500 34.9 / 37.4, 2 x 256
+// 1500 45.8 / 47.2, 2 x 512 1500 75.7 / 74.8, 2400 83.3 / 83.8, 4 x 512 1500 99.1 / 93.2, 2600 124.8 / 121.2, 3400 135.6 / 135.9, 4096 147.6 / 150.0, 6 x 512 2047 139 / 133,
+// 3000 221 / 224, 8 x 512 2000 165 / 157, 3400 264 / 263, 4000 290 / 293, 16 x 512 5000 882 / 914.
 bool bgf_gate_takes(int64_t m, int nd, int dg)
 {
     if (nd % 256 != 0) return false;
-    if (dg == 128) return m >= (nd <= 4096 ? 1500 : 5000);
+    if (dg == 128) return m >= (nd > 4096 ? 5000 : nd > 1024 && nd <= 3072 ? 2800 : 1500);
     return dg == 256 && (nd <= 2048 ? m > 2048 : m >= 6000);
 }
 

@@ -169,3 +169,8 @@ def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, 
     say([tuple(k)[:2] for k in run])
     assert (score == 0.5).all()
     assert any("bgf_gate_kernel" in k.kernel for k in run) == one and any("bgf_gate_head_kernel" in k.kernel for k in run) != one
+
+
+@pytest.mark.parametrize("d, nb, m, one", [(512, 2, 1499, False), (512, 2, 1500, True), (256, 5, 2799, False), (256, 5, 2800, True), (512, 6, 2799, False), (512, 6, 2800, True)])
+def test_the_narrow_gate_is_three_launches_further_on_with_rows_of_1280_to_3072(d, nb, m, one):
+    test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, 128, m, one)
