@@ -8,8 +8,8 @@
 // keys.  So every addition is made in the order in which the other kernels make it, and the bits are theirs: no merging of partial
 // outputs, and one form of the softmax for all keys.  A round's probabilities are added up while the next round's are made.
 //
-// Bound by its beginning (about 5 us for a launch: first touches of rows, keys and code) and then by the chain of value products, two
-// MFMAs of 32x32x16 a block that wait for each other, and a round's meeting: 0.10 us per 32 keys, 0.21 where one wave does all of it.  NP:
+// Bound by its beginning (about 5 us for a launch: first touches of rows, keys and code) and then by a round's chain, exponentials,
+// LDS, meeting, value products that wait for each other: 0.10 us per 32 keys, 0.21 where one wave does all of it.  NP:
 // 200 candidates of one user against 1000, 8 heads, 8.7 us with 2, 9.2 with 3, 8.4 with 4, 8.6 with 6, against 4000 (values one
 // round ahead) 20.6, 22.1, 18.2, 17.5.  Keys four rounds ahead instead of two, or a round's probabilities read under the products of the round before: no faster.
 //

@@ -158,8 +158,8 @@ __global__ __launch_bounds__(NW * 64) void layer_head_kernel(const HeadArgs p)
 
 }  // namespace
 
-// At most a workgroup per CU.  Us a call, four layers, one launch / two: score of 8 rows 87.5 / 94.2, 200 99.6 / 109, 512 106 / 113, 800 113 / 120, 1000 117 / 121, 1200
-// (304 workgroups) 130 / 121, 2048 140 / 126, encode of 100 rows 68.1 / 74.5, 500 71.7 / 77.0, 1000 82.5 / 85.8, 1500 102 / 92.
+// At most a workgroup per CU.  Us a call, four layers, one launch / two: score of 16 rows 69.7 / 72.8, 64 76.2 / 75.6, 200 78.3 / 79.2, 320 81.2 / 82.7, 512 84.2 / 85.0,
+// 800 92.8 / 94.6, 1000 95.7 / 96.5, 1200 (304 workgroups) 115.3 / 103.4, encode of 128 rows 62.3 / 62.7, 600 70.8 / 72.4, 1000 74.4 / 73.6.
 bool layer_head_takes(int M, int d, int F) { return d == D && F % kHidden == 0 && F > 0 && (M + 31) / 32 * (int64_t)(F / kHidden) <= 256; }
 
 hipError_t layer_head_bf16(const HeadArgs &a, hipStream_t s)
