@@ -83,10 +83,11 @@ struct GemmArgs {
 // gemm_small_bf16.hip: few rows.  N % 64 == 0, K % 128 == 0.
 bool gemm_small_takes(int epi, int M, int N, int K);  // instead of the macro tiles
 hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s);
-// The fused QKV projection of few rows as a call has them (x: bf16 [M][K]) with what row_prep_bf16 does for them: their sums of squares and
-// their fp32 copy [M][K] in x32 (in_norm: inv_d and eps).  N >= K.
+// The fused QKV projection of few rows as a call has them (x: [M][K], fp32 with kRowsF32, else bf16) with what row_prep_f32 or row_prep_bf16 does for
+// them: their sums of squares and, of bf16 rows, their fp32 copy [M][K] in x32 (in_norm: inv_d and eps).  N >= K.
 bool gemm_small_sums(int M, int N, int K);
-hipError_t gemm_small_given(const void *x, float *x32, const void *w_packed, int M, int N, int K, void *C, int64_t ldc, const RowNormIn &in_norm,
+enum RowsIn { kRowsSummed, kRowsF32 };
+hipError_t gemm_small_given(RowsIn in, const void *x, float *x32, const void *w_packed, int M, int N, int K, void *C, int64_t ldc, const RowNormIn &in_norm,
                             const QkvToCache &to_cache, hipStream_t s);
 
 // Where the fused QKV projection of a call's rows goes: rows [0, n_cached), the history's, keys and values into the cache and
@@ -100,7 +101,6 @@ struct QkvOut {
 
 // gemm_resident_bf16.hip: the fused QKV projection of many rows.  A: [M][K], bf16 with their sums of squares in in_norm.ss, or fp32
 // rows, whose sums it forms itself (row_prep_f32's bits; in_norm: inv_d and eps); N = 3 K.
-enum RowsIn { kRowsSummed, kRowsF32 };
 bool gemm_resident_takes(int M, int K, bool cached);   // rows with their sums
 bool gemm_resident_sums(int M, int K);                 // fp32 rows, instead of a launch for their sums before
 hipError_t gemm_resident_bf16(RowsIn in, const void *A, const void *w_packed, int M, int K, const RowNormIn &in_norm, const QkvOut &out,

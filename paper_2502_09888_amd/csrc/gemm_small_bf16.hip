@@ -27,14 +27,17 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 constexpr int NW = 4;
 
 // RB blocks of 16 rows a workgroup; K in chunks of C k-tiles of 32, of which U are a turn of the loop and of the weights' ring.
-// OWN: the rows are a call's inputs.  Their sums of squares are formed here, in row_prep_bf16's order, and their fp32 copy goes to x32,
-// 64 columns by each of the first K / 64 workgroups of a row block: instead of a launch before, 2 to 2.5 us.  K of 256 or 512.
-template <int EPI, int RB, int C, int U, bool OWN>
+// IN: the rows are a call's inputs in place of bf16 rows with their sums.  Their sums of squares are formed here, in the order of row_prep_kernel, and of
+// bf16 rows the fp32 copy goes to x32, 64 columns by each of the first K / 64 workgroups of a row block; fp32 rows are rounded on their way into
+// LDS: instead of a launch before, 2 to 2.5 us.  K of 256 or 512.
+enum { kSummed = 0, kGivenBf16 = 1, kGivenF32 = 2 };
+template <int EPI, int RB, int C, int U, int IN>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     const __bf16 *A, int64_t lda, const __bf16 *Wp, int M, int N, int K, void *Cout, int64_t ldc, const float *resid,
     int64_t ldr, const RowNormIn nin, const RowNormOut nout, const int tiled, const QkvToCache qc, const int by_cols, float *x32)
 {
-    constexpr bool F32 = EPI == EPI_RESID_F32;
+    constexpr bool F32 = EPI == EPI_RESID_F32, OWN = IN != kSummed;
+    constexpr int X = IN == kGivenF32 ? 2 : 1;  // loads per lane and piece
     constexpr int kPitch = epilogue_pitch<EPI, 2>(), kRows = 16 * RB, R = C * U, P = RB * C / NW, kBuf = RB * C * 1024, L = C < 4 ? C : 4;
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kBuf + kRows * kPitch];
     uint8_t *const tr = lds + 2 * kBuf;
@@ -61,30 +64,42 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
 
     // Rows: pieces of 16 rows x 32 k, 1 KiB, in LDS as the tiled layout has them (chunk c of row r at place c ^ r / 4 % 4 of the row's 64 bytes);
     // of a chunk's, one after the other's to each wave.
-    const __bf16 *a_src[P];
-    const int a_step = (tiled & kTiledA) ? 512 : 32;  // elements per k-tile
+    const uint8_t *a_src[P];
+    const int a_step = (tiled & kTiledA) ? 1024 : 64 * X;  // bytes per k-tile
 #pragma unroll
     for (int i = 0; i < P; ++i) {
         const int p = NW * i + wave, g = p / C, kt = p % C;
         if (tiled & kTiledA)
-            a_src[i] = A + ((int64_t)min((m0 >> 4) + g, (M - 1) >> 4) * T + kt) * 512 + lane * 8;
+            a_src[i] = (const uint8_t *)A + ((int64_t)min((m0 >> 4) + g, (M - 1) >> 4) * T + kt) * 1024 + lane * 16;
         else
-            a_src[i] = A + (int64_t)min(m0 + 16 * g + (lane >> 2), M - 1) * lda + kt * 32 + ((lane & 3) ^ (lane >> 4)) * 8;
+            a_src[i] = (const uint8_t *)A + ((int64_t)min(m0 + 16 * g + (lane >> 2), M - 1) * lda + kt * 32 + ((lane & 3) ^ (lane >> 4)) * 8) * (2 * X);
     }
-    auto fetch = [&](int ch, u32x4 (&x)[P]) __attribute__((always_inline)) {
+    auto fetch = [&](int ch, u32x4 (&x)[P][X]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < P; ++i) x[i] = *(const u32x4 *)(a_src[i] + (int64_t)ch * (C * a_step));
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int e = 0; e < X; ++e) x[i][e] = *(const u32x4 *)(a_src[i] + (int64_t)ch * (C * a_step) + 16 * e);
     };
-    auto put = [&](int buf, const u32x4 (&x)[P]) __attribute__((always_inline)) {
+    auto put = [&](int buf, const u32x4 (&x)[P][X]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < P; ++i) *(u32x4 *)(lds + buf * kBuf + (NW * i + wave) * 1024 + lane * 16) = x[i];
+        for (int i = 0; i < P; ++i) {
+            uint8_t *const to = lds + buf * kBuf + (NW * i + wave) * 1024 + lane * 16;
+            if constexpr (IN == kGivenF32) {
+                bf16x8 v;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = (__bf16)__uint_as_float(x[i][e >> 2][e & 3]);
+                *(bf16x8 *)to = v;
+            } else {
+                *(u32x4 *)to = x[i][0];
+            }
+        }
     };
     // Weights: 16 columns x 32 k of two neighbouring fragments of 32 columns x 16 k
     const __bf16 *w_src = Wp + ((int64_t)(n0 / 32 + (wave >> 1)) * 2 * T + (kq >> 1)) * 512 + ((kq & 1) * 32 + (wave & 1) * 16 + l15) * 8;
     bf16x8 ring[R];
     auto weights = [&](int t) __attribute__((always_inline)) { return *(const bf16x8 *)(w_src + (int64_t)t * 1024); };
 
-    u32x4 x0[P], x1[P];
+    u32x4 x0[P][X], x1[P][X];
     fetch(0, x0);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -124,7 +139,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     put(0, x0);
     put(1, x1);
     if constexpr (OWN) {
-        // row_prep_bf16 adds the squares of four columns c and c + 256, then of column groups 32, 16, 8, 4, 2 and 1 apart: k-tiles 8 apart (the next chunk),
+        // row_prep_kernel adds the squares of four columns c and c + 256, then of column groups 32, 16, 8, 4, 2 and 1 apart: k-tiles 8 apart (the next chunk),
         // 4 (the wave's next), 2 and 1 (other waves), and the row's other places
 #pragma unroll
         for (int g = 0; g < RB; ++g)
@@ -133,9 +148,14 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
                 float v[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    auto sum = [&](const u32x4 &x) __attribute__((always_inline)) {
-                        const uint32_t a = x[2 * e], b = x[2 * e + 1];
-                        return sumsq4(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u), __uint_as_float(b << 16), __uint_as_float(b & 0xffff0000u));
+                    auto sum = [&](const u32x4 (&x)[X]) __attribute__((always_inline)) {
+                        if constexpr (IN == kGivenF32) {
+                            const u32x4 f = x[e];
+                            return sumsq4(__uint_as_float(f[0]), __uint_as_float(f[1]), __uint_as_float(f[2]), __uint_as_float(f[3]));
+                        } else {
+                            const uint32_t a = x[0][2 * e], b = x[0][2 * e + 1];
+                            return sumsq4(__uint_as_float(a << 16), __uint_as_float(a & 0xffff0000u), __uint_as_float(b << 16), __uint_as_float(b & 0xffff0000u));
+                        }
                     };
                     v[i] = sum(x0[2 * g + i]);
                     if (U == 2) v[i] += sum(x1[2 * g + i]);
@@ -194,12 +214,13 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
         });
     };
     int ch = 0;
+    if constexpr (!OWN)  // (these K are one turn)
 #pragma unroll 1
-    for (; ch + U < n; ch += U) turn(ch, std::false_type{});
+        for (; ch + U < n; ch += U) turn(ch, std::false_type{});
     turn(ch, std::true_type{});
 
     if constexpr (OWN) {
-        if (ct < K / 64) {
+        if (IN == kGivenBf16 && ct < K / 64) {
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
                 const int r = tid >> 4, cc = l15, kt = 2 * ct + (cc >> 3), out = m0 + 16 * i + r;
@@ -275,7 +296,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_small_kernel(
     }
 }
 
-template <int EPI, bool OWN = false>
+template <int EPI, int IN = kSummed>
 hipError_t launch_small(const GemmArgs &g, hipStream_t s, float *x32 = nullptr)
 {
     const int n_ct = g.N / 64;
@@ -294,12 +315,12 @@ hipError_t launch_small(const GemmArgs &g, hipStream_t s, float *x32 = nullptr)
     };
     auto of = [&](auto rb) {
         constexpr int RB = decltype(rb)::value;
-        if (g.K % 512 == 0) return go(gemm_small_kernel<EPI, RB, 8, 2, OWN>);
-        if constexpr (OWN) {
-            return go(gemm_small_kernel<EPI, RB, 8, 1, true>);
+        if (g.K % 512 == 0) return go(gemm_small_kernel<EPI, RB, 8, 2, IN>);
+        if constexpr (IN != kSummed) {
+            return go(gemm_small_kernel<EPI, RB, 8, 1, IN>);
         } else {
-            if (g.K % 256 == 0) return go(gemm_small_kernel<EPI, RB, 8, 1, false>);
-            return go(gemm_small_kernel<EPI, RB, 4, 1, false>);
+            if (g.K % 256 == 0) return go(gemm_small_kernel<EPI, RB, 8, 1, kSummed>);
+            return go(gemm_small_kernel<EPI, RB, 4, 1, kSummed>);
         }
     };
     return half ? of(std::integral_constant<int, 1>{}) : of(std::integral_constant<int, 2>{});
@@ -322,15 +343,16 @@ bool gemm_small_sums(int M, int N, int K)
 {
     // A launch less is worth a first projection of up to three workgroups per CU.  Us a call of four layers, the line at 256 / 768 workgroups: score of 336 rows of
     // 512 113.8 / 111.4, 680 126.7 / 124.8, 1000 130.6 / 128.7, of 256 680 92.9 / 90.4, 1600 111.4 / 109.9; encode of 512 rows 90.5 / 87.1, 1000 102.3 / 100.6 (one
-    // layer 11.1 / 8.0), of 256 2048 87.4 / 85.9; from there to 1024 even (score of 1200 rows of 512 167.4 / 167.4).
+    // layer 11.1 / 8.0), of 256 2048 87.4 / 85.9; fusion of 64 candidates x 4 of 512 46.5 / 43.6, 250 53.7 / 53.1, 1000 x 2 of 256 39.6 / 38.5; from there to 1024 even (score of 1200 rows of 512 167.4 / 167.4).
     return (K == 256 || K == 512) && !gemm_resident_takes(M, K, false) && !gemm_resident_takes(M, K, true) && (int64_t)(N / 64) * ((M + 31) / 32) <= 768;
 }
 
-hipError_t gemm_small_given(const void *x, float *x32, const void *w_packed, int M, int N, int K, void *C, int64_t ldc, const RowNormIn &in_norm,
+hipError_t gemm_small_given(RowsIn in, const void *x, float *x32, const void *w_packed, int M, int N, int K, void *C, int64_t ldc, const RowNormIn &in_norm,
                             const QkvToCache &to_cache, hipStream_t s)
 {
     if (M < 1 || N % 64 != 0 || N < K || (K != 256 && K != 512)) return hipErrorInvalidValue;
-    return launch_small<EPI_STORE_BF16, true>(GemmArgs{x, K, w_packed, M, N, K, C, ldc, nullptr, 0, in_norm, RowNormOut{}, 0, to_cache}, s, x32);
+    const GemmArgs g{x, K, w_packed, M, N, K, C, ldc, nullptr, 0, in_norm, RowNormOut{}, 0, to_cache};
+    return in == kRowsF32 ? launch_small<EPI_STORE_BF16, kGivenF32>(g, s) : launch_small<EPI_STORE_BF16, kGivenBf16>(g, s, x32);
 }
 
 hipError_t gemm_small_bf16(int epi, const GemmArgs &g, hipStream_t s)

@@ -187,7 +187,7 @@ int project_given(const climber_config *cfg, const PackedLayer &pw, const void *
                   hipStream_t s)
 {
     const int d = cfg->d_model, skip = out.qc.which0 * d;
-    return rt(gemm_small_given(x, x32, pw.wqkv + (size_t)skip * d * 2, (int)rows, 3 * d - skip, d, out.n_cached ? out.q : out.rows,
+    return rt(gemm_small_given(kRowsSummed, x, x32, pw.wqkv + (size_t)skip * d * 2, (int)rows, 3 * d - skip, d, out.n_cached ? out.q : out.rows,
                                out.n_cached ? out.ld_q : out.ld_rows, nin, out.qc, s));
 }
 
@@ -531,7 +531,9 @@ int climber_bgf_score(const climber_config *cfg, const climber_bgf_weights *w, c
     } else {
         QkvOut to{};
         to.rows = ws.qkv, to.ld_rows = 3 * d;
-        if (gemm_resident_sums((int)R, d)) {
+        if (gemm_small_sums((int)R, 3 * d, d)) {
+            TRY(rt(gemm_small_given(kRowsF32, e, nullptr, pw.wqkv, (int)R, 3 * d, d, to.rows, to.ld_rows, nin, to.qc, s)));
+        } else if (gemm_resident_sums((int)R, d)) {
             TRY(rt(gemm_resident_bf16(kRowsF32, e, pw.wqkv, (int)R, d, nin, to, s)));
         } else {
             TRY(rt(row_prep_f32(e, ws.xb, ws.ss, np, R, d, s)));

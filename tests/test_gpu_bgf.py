@@ -120,6 +120,14 @@ def test_few_and_many_candidates_give_the_same_bits(d, nb, dg, m, part):
         assert np.array_equal(y1, y[lo:lo + part]) and np.array_equal(sc1, sc[lo:lo + part])
 
 
+@pytest.mark.parametrize("d, nb, m, part", [(512, 4, 300, 1), (512, 4, 300, 9), (512, 4, 300, 256), (512, 3, 700, 113), (512, 8, 600, 128), (256, 4, 600, 5),
+                                            (256, 4, 600, 512), (256, 1, 2100, 673), (256, 9, 300, 227)])
+def test_first_projection_of_few_fp32_rows_makes_their_sums(d, nb, m, part):
+    # the fusion layer's projection of few rows forms the sums of squares of its fp32 rows, in blocks of 16 or 32 of them, the last in part, up
+    # to the most rows there are; against a call of more, which rounds and sums them in a launch before or in the projection of many rows
+    test_few_and_many_candidates_give_the_same_bits(d, nb, 128, m, part)
+
+
 @pytest.mark.parametrize("d, nb, m", [(512, 2, 2001), (256, 2, 2063), (512, 3, 2049), (256, 3, 2069), (512, 4, 1000), (256, 4, 1017), (512, 5, 1229),
                                       (256, 5, 1235), (512, 6, 667), (256, 6, 675), (512, 7, 572), (256, 7, 577), (512, 8, 500), (256, 8, 509)])
 def test_projection_and_attention_in_one_launch_give_the_bits_of_two(d, nb, m):
