@@ -334,9 +334,10 @@ hipError_t launch_attn_split_bf16(const AttnArgs &a, bool sumi, hipStream_t s)
     const dim3 g((unsigned)grid), t((NP + 2) * 64);
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, t, 0, s, p); };
     // Values a round further ahead where the walk is long, and what is requested in vain at its end little of it.  Us the call, one round ahead / two: 200
-    // candidates against 4000 behaviours 18.6 / 17.7, 2 users x 64 20.8 / 18.6, 100 against 2000 (2 users) 11.8 / 11.5, 1500 9.9 / 9.8, 200 against 1000 8.2 / 8.2,
-    // 700 7.4 / 7.6, 4 x 64 against 256 5.6 / 6.0.  A history tile's subsequence is short, and without them even.
-    if (sumi && a.max_hist_len > 1024) go(attn_split_kernel<true, false, 2>);
+    // candidates against 4000 behaviours 18.5 / 18.0, two users x 64 20.9 / 18.6, eight x 20 against 1000 to 4000 18.7 / 16.7, three x 32 against 2500 14.5 /
+    // 13.4, 200 against 2500 13.2 / 13.1, 2000 11.5 / 11.5, 1500 9.9 / 10.0, five users against 355 to 1421 8.6 / 8.8, 4 x 64 against 256 5.6 / 6.0.  A history
+    // tile's subsequence is short, and without them even.
+    if (sumi && a.max_hist_len > 2048) go(attn_split_kernel<true, false, 2>);
     else if (sumi) go(attn_split_kernel<true, false, 1>);
     else if (a.causal) go(attn_split_kernel<false, true, 1>);
     else go(attn_split_kernel<false, false, 1>);

@@ -350,13 +350,13 @@ def test_keys_shared_out_among_waves_give_the_bits_of_other_launches(L, L_min, n
         assert np.array_equal(part, full[g.last_idx])
 
 
-@pytest.mark.parametrize("L,L_min,n_scen", [(1025, 1025, 8), (1056, 40, 8), (1153, 1153, 8), (1300, 0, 17), (2048, 2048, 8)])
+@pytest.mark.parametrize("L,L_min,n_scen", [(2049, 2049, 8), (2080, 40, 8), (2177, 2177, 8), (2305, 0, 17)])
 def test_values_two_rounds_ahead_give_the_bits_of_other_launches(L, L_min, n_scen):
-    # histories of more than 1024: odd and even numbers of rounds, the last one with one to four blocks, users with one round and none
+    # histories of more than 2048: odd and even numbers of rounds, the last one with one to four blocks, users with one round and none
     test_keys_shared_out_among_waves_give_the_bits_of_other_launches(L, L_min, n_scen)
 
 
-@pytest.mark.parametrize("L", [1030, 1160])
+@pytest.mark.parametrize("L", [2060, 2190])
 def test_values_two_rounds_ahead_where_one_key_outgrows_the_rest(L):
     test_keys_shared_out_among_waves_where_one_key_outgrows_the_rest(L)
 
