@@ -126,7 +126,8 @@ def load_library():
     native.bind(*(C.cast(f, vp).value for f in (lib.climber_attn_history, lib.climber_attn_sumi, lib.climber_attn_history_bias,
                                                 lib.climber_attn_sumi_bias)),
                 Config, RelBias, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
-    _lib, _native = lib, native
+    _native = native  # (first: another thread's call goes by _lib alone)
+    _lib = lib
     return lib
 
 

@@ -244,6 +244,29 @@ def test_native_binding_passes_every_argument_in_its_place(name, _lib, monkeypat
     assert e.value.code == -1
 
 
+def test_library_that_other_threads_see_has_its_binding(monkeypatch):
+    # after every instruction of load_library: a thread that finds the library there calls through the binding
+    import sys
+    from paper_2502_09888_amd import climber as mod
+    monkeypatch.setattr(mod, "_lib", None)
+    monkeypatch.setattr(mod, "_native", None)
+    states = []
+
+    def trace(frame, event, arg):
+        if frame.f_code is not mod.load_library.__code__:
+            return None
+        frame.f_trace_opcodes = True
+        states.append((mod._lib is not None, mod._native is not None))
+        return trace
+    old = sys.gettrace()
+    sys.settrace(trace)
+    try:
+        mod.load_library()
+    finally:
+        sys.settrace(old)
+    assert (False, False) in states and (True, True) in states and (True, False) not in states
+
+
 def test_bench_refuses_more_than_one_gpu():
     # one GPU per box: the benchmark says so instead of pretending to scale
     import subprocess
