@@ -65,7 +65,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libclimber.so; raises if it has not been built (no fallback exists)."""
-    global _lib, _native
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -121,14 +121,28 @@ def load_library():
     lib.climber_sumi_score_static.restype = C.c_int
     lib.climber_sumi_score_static.argtypes = [cfgp, C.POINTER(_Weights), vp, vp, vp, vp, i32, i32, vp,
                                               vp, vp, vp]
-    import torch
-    from . import _native as native
-    native.bind(*(C.cast(f, vp).value for f in (lib.climber_attn_history, lib.climber_attn_sumi, lib.climber_attn_history_bias,
-                                                lib.climber_attn_sumi_bias)),
-                Config, RelBias, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
-    _native = native  # (first: another thread's call goes by _lib alone)
+    try:
+        _load_native(lib)
+    except ImportError:  # the host's calls do without; an attention call raises it
+        pass
     _lib = lib
     return lib
+
+
+def _load_native(lib):
+    """csrc/binding.c over the library's attention calls."""
+    global _native
+    from . import _native as native
+    try:
+        import torch
+        current = torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
+    except (ImportError, AttributeError):  # then a call names its stream, or _stream raises it
+        current = None, None
+    native.bind(*(C.cast(f, C.c_void_p).value for f in (lib.climber_attn_history, lib.climber_attn_sumi, lib.climber_attn_history_bias,
+                                                        lib.climber_attn_sumi_bias)),
+                Config, RelBias, *current)
+    _native = native
+    return native
 
 
 def _ptr(t) -> Optional[int]:
@@ -208,23 +222,21 @@ def climber_kv_cache_rows(cache: KVCache) -> int:
 
 def climber_attn_history(cfg: Config, tau_layer, q, k, v, scen, beh, cache: KVCache, layer: int,
                          o_hist=None, stream=None) -> None:
-    lib = _lib or load_library()
-    code = _native.attn_history(cfg, tau_layer, q, k, v, scen, beh, cache.handle, layer, o_hist, stream)
+    code = (_native or _load_native(load_library())).attn_history(cfg, tau_layer, q, k, v, scen, beh, cache.handle, layer, o_hist, stream)
     if code is None:
-        code = lib.climber_attn_history(C.byref(cfg), _ptr(tau_layer), _ptr(q), _ptr(k), _ptr(v), _ptr(scen), _ptr(beh),
-                                        cache.handle, layer, _ptr(o_hist), _stream(stream))
+        code = load_library().climber_attn_history(C.byref(cfg), _ptr(tau_layer), _ptr(q), _ptr(k), _ptr(v), _ptr(scen), _ptr(beh),
+                                                   cache.handle, layer, _ptr(o_hist), _stream(stream))
     if code:
         raise ClimberError(code, "climber_attn_history")
 
 
 def climber_attn_sumi(cfg: Config, tau_layer, cache: KVCache, layer: int, q_c, k_c, v_c, cand_off,
                       m_total: int, m_max: int, cand_scen, cand_beh, o_c, stream=None) -> None:
-    lib = _lib or load_library()
-    code = _native.attn_sumi(cfg, tau_layer, cache.handle, layer, q_c, k_c, v_c, cand_off, m_total, m_max, cand_scen, cand_beh, o_c,
-                             stream)
+    code = (_native or _load_native(load_library())).attn_sumi(cfg, tau_layer, cache.handle, layer, q_c, k_c, v_c, cand_off, m_total, m_max,
+                                                               cand_scen, cand_beh, o_c, stream)
     if code is None:
-        code = lib.climber_attn_sumi(C.byref(cfg), _ptr(tau_layer), cache.handle, layer, _ptr(q_c), _ptr(k_c), _ptr(v_c),
-                                     _ptr(cand_off), m_total, m_max, _ptr(cand_scen), _ptr(cand_beh), _ptr(o_c), _stream(stream))
+        code = load_library().climber_attn_sumi(C.byref(cfg), _ptr(tau_layer), cache.handle, layer, _ptr(q_c), _ptr(k_c), _ptr(v_c),
+                                                _ptr(cand_off), m_total, m_max, _ptr(cand_scen), _ptr(cand_beh), _ptr(o_c), _stream(stream))
     if code:
         raise ClimberError(code, "climber_attn_sumi")
 
@@ -321,11 +333,10 @@ def rel_bias(pos_table, time_table, hist_pos, hist_ts, cand_pos=None, cand_ts=No
 
 def climber_attn_history_bias(cfg: Config, tau_layer, q, k, v, scen, beh, cache: KVCache, layer: int,
                               o_hist, bias: RelBias, stream=None) -> None:
-    lib = _lib or load_library()
-    code = _native.attn_history_bias(cfg, tau_layer, q, k, v, scen, beh, cache.handle, layer, o_hist, bias, stream)
+    code = (_native or _load_native(load_library())).attn_history_bias(cfg, tau_layer, q, k, v, scen, beh, cache.handle, layer, o_hist, bias, stream)
     if code is None:
-        code = lib.climber_attn_history_bias(C.byref(cfg), _ptr(tau_layer), _ptr(q), _ptr(k), _ptr(v), _ptr(scen), _ptr(beh),
-                                             cache.handle, layer, _ptr(o_hist), C.byref(bias), _stream(stream))
+        code = load_library().climber_attn_history_bias(C.byref(cfg), _ptr(tau_layer), _ptr(q), _ptr(k), _ptr(v), _ptr(scen), _ptr(beh),
+                                                        cache.handle, layer, _ptr(o_hist), C.byref(bias), _stream(stream))
     if code:
         raise ClimberError(code, "climber_attn_history_bias")
 
@@ -333,13 +344,12 @@ def climber_attn_history_bias(cfg: Config, tau_layer, q, k, v, scen, beh, cache:
 def climber_attn_sumi_bias(cfg: Config, tau_layer, cache: KVCache, layer: int, q_c, k_c, v_c, cand_off,
                            m_total: int, m_max: int, cand_scen, cand_beh, o_c, bias: RelBias,
                            stream=None) -> None:
-    lib = _lib or load_library()
-    code = _native.attn_sumi_bias(cfg, tau_layer, cache.handle, layer, q_c, k_c, v_c, cand_off, m_total, m_max, cand_scen, cand_beh, o_c,
-                                  bias, stream)
+    code = (_native or _load_native(load_library())).attn_sumi_bias(cfg, tau_layer, cache.handle, layer, q_c, k_c, v_c, cand_off, m_total, m_max,
+                                                                    cand_scen, cand_beh, o_c, bias, stream)
     if code is None:
-        code = lib.climber_attn_sumi_bias(C.byref(cfg), _ptr(tau_layer), cache.handle, layer, _ptr(q_c), _ptr(k_c), _ptr(v_c),
-                                          _ptr(cand_off), m_total, m_max, _ptr(cand_scen), _ptr(cand_beh), _ptr(o_c), C.byref(bias),
-                                          _stream(stream))
+        code = load_library().climber_attn_sumi_bias(C.byref(cfg), _ptr(tau_layer), cache.handle, layer, _ptr(q_c), _ptr(k_c), _ptr(v_c),
+                                                     _ptr(cand_off), m_total, m_max, _ptr(cand_scen), _ptr(cand_beh), _ptr(o_c), C.byref(bias),
+                                                     _stream(stream))
     if code:
         raise ClimberError(code, "climber_attn_sumi_bias")
 

@@ -245,18 +245,18 @@ def test_native_binding_passes_every_argument_in_its_place(name, _lib, monkeypat
 
 
 def test_library_that_other_threads_see_has_its_binding(monkeypatch):
-    # after every instruction of load_library: a thread that finds the library there calls through the binding
+    # after every instruction of loading the two: a thread that finds neither, or the library alone, calls through the binding
     import sys
     from paper_2502_09888_amd import climber as mod
     monkeypatch.setattr(mod, "_lib", None)
     monkeypatch.setattr(mod, "_native", None)
-    states = []
+    states = {}
 
     def trace(frame, event, arg):
-        if frame.f_code is not mod.load_library.__code__:
+        if frame.f_code not in (mod.load_library.__code__, mod._load_native.__code__):
             return None
         frame.f_trace_opcodes = True
-        states.append((mod._lib is not None, mod._native is not None))
+        states[mod._lib is not None, mod._native is not None] = mod._lib, mod._native
         return trace
     old = sys.gettrace()
     sys.settrace(trace)
@@ -264,7 +264,53 @@ def test_library_that_other_threads_see_has_its_binding(monkeypatch):
         mod.load_library()
     finally:
         sys.settrace(old)
-    assert (False, False) in states and (True, True) in states and (True, False) not in states
+    assert (True, True) in states and len(states) > 1
+    none = type("Handle", (), {"handle": None})()
+    for lib, native in states.values():
+        monkeypatch.setattr(mod, "_lib", lib)
+        monkeypatch.setattr(mod, "_native", native)
+        with pytest.raises(P.ClimberError) as e:
+            P.climber_attn_history(cfg(), None, FAKE, FAKE, FAKE, FAKE, FAKE, none, 0, None, stream=0)
+        assert e.value.code == -1
+
+
+def run_python(code):
+    import subprocess
+    import sys
+    return subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+
+
+def test_host_calls_need_neither_torch_nor_the_extension():
+    r = run_python("""
+import sys
+sys.modules["torch"] = sys.modules["paper_2502_09888_amd._native"] = None
+import paper_2502_09888_amd as P
+P.load_library()
+assert P.climber_kv_cache_bytes(P.Config(n_heads=4, sub_len=128, qk_scale=0.125), [512]) > 0
+assert P.climber_workspace_bytes(P.Config(n_heads=8, d_ffn=2048, sub_len=256), 1024) > 0
+assert "unknown" not in P.climber_strerror(-1)
+print("done")
+""")
+    assert r.returncode == 0 and r.stdout == "done\n", r.stderr
+
+
+def test_attention_calls_of_a_named_stream_need_no_torch():
+    r = run_python("""
+import sys
+sys.modules["torch"] = None
+import paper_2502_09888_amd as P
+none = type("Handle", (), {"handle": None})()
+call = lambda stream: P.climber_attn_sumi(P.Config(), 256, none, 0, 256, 256, 256, 256, 8, 8, 256, 256, 256, stream)
+try:
+    call(0)
+except P.ClimberError as e:
+    print(e.code)
+try:
+    call(None)
+except ImportError as e:
+    print(e.name)
+""")
+    assert r.returncode == 0 and r.stdout == "-1\ntorch\n", r.stderr
 
 
 def test_bench_refuses_more_than_one_gpu():
