@@ -3,8 +3,8 @@
     python -m paper_2502_09888_amd.build
 
 Each .hip file is compiled to an object next to it and the objects are linked into
-``paper_2502_09888_amd/libclimber.so``; csrc/binding.c becomes the extension module ``_native.so`` beside it.  Packed-FP32 instruction selection is switched off for all
-device code.
+``paper_2502_09888_amd/libclimber.so``; csrc/binding.c becomes the extension module ``_native`` beside it, named for the
+interpreter that builds it.  Packed-FP32 instruction selection is switched off for all device code.
 """
 from __future__ import annotations
 
@@ -13,11 +13,12 @@ import subprocess
 import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from importlib.machinery import EXTENSION_SUFFIXES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libclimber.so")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + EXTENSION_SUFFIXES[0])
 SOURCES = ["climber_api.hip", "attn_bf16.hip", "attn_wave_bf16.hip", "attn_split_bf16.hip", "attn_bias_bf16.hip", "attn_f32.hip", "attn_tile_f32.hip", "kv_cache.hip", "stack.hip",
            "gemm_bf16.hip", "gemm_small_bf16.hip", "gemm_resident_bf16.hip", "layer_tail_bf16.hip", "layer_head_bf16.hip", "rowwise.hip", "hist_fused_bf16.hip", "check.hip", "bgf.hip", "bgf_front_bf16.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

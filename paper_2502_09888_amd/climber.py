@@ -5,10 +5,12 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from importlib.machinery import EXTENSION_SUFFIXES
 from typing import Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libclimber.so")
+_NATIVE_PATH = os.path.join(_HERE, "_native" + EXTENSION_SUFFIXES[0])  # (another interpreter's has another name)
 
 F32, BF16 = 0, 1
 MODE_HISTORY, MODE_CANDIDATE = 0, 1
@@ -63,14 +65,18 @@ def library_path() -> str:
     return _LIB_PATH
 
 
+def _built(path: str) -> None:
+    if not os.path.exists(path):
+        raise ImportError(f"{path} is missing: build it with `python -m paper_2502_09888_amd.build`"
+                          " (there is no CPU fallback)")
+
+
 def load_library():
     """Load libclimber.so; raises if it has not been built (no fallback exists)."""
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
-        raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2502_09888_amd.build`"
-                          " (there is no CPU fallback)")
+    _built(_LIB_PATH)
     lib = C.CDLL(_LIB_PATH)
     vp, i32, i64, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_size_t
     cfgp = C.POINTER(Config)
@@ -132,6 +138,7 @@ def load_library():
 def _load_native(lib):
     """csrc/binding.c over the library's attention calls."""
     global _native
+    _built(_NATIVE_PATH)
     from . import _native as native
     try:
         import torch

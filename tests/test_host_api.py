@@ -15,7 +15,7 @@ FAKE = 0x7F0000000000  # 256-byte aligned, never dereferenced on the host
 
 @pytest.fixture(scope="module", autouse=True)
 def _lib():
-    if not os.path.exists(P.library_path()):
+    if not (os.path.exists(P.library_path()) and os.path.exists(hip_build.NATIVE)):
         hip_build.build()
     return P.load_library()
 
@@ -292,6 +292,18 @@ assert "unknown" not in P.climber_strerror(-1)
 print("done")
 """)
     assert r.returncode == 0 and r.stdout == "done\n", r.stderr
+
+
+def test_extension_is_this_interpreters_and_a_missing_one_says_how_to_build_it(monkeypatch, tmp_path):
+    from importlib.machinery import EXTENSION_SUFFIXES
+    from paper_2502_09888_amd import _native, climber as mod
+    assert os.path.samefile(_native.__file__, hip_build.NATIVE) and hip_build.NATIVE.endswith(EXTENSION_SUFFIXES[0])
+    assert EXTENSION_SUFFIXES[0] != ".so"
+    monkeypatch.setattr(mod, "_NATIVE_PATH", str(tmp_path / "_native.so"))
+    monkeypatch.setattr(mod, "_native", None)
+    none = type("Handle", (), {"handle": None})()
+    with pytest.raises(ImportError, match="paper_2502_09888_amd.build"):
+        P.climber_attn_history(cfg(), None, FAKE, FAKE, FAKE, FAKE, FAKE, none, 0, None, stream=0)
 
 
 def test_attention_calls_of_a_named_stream_need_no_torch():
