@@ -56,7 +56,8 @@ __device__ __forceinline__ void quad_of(const u32x4 (&x)[4], u32x4 (&y)[4])
 }
 
 // sum += a[d] b[d] over d in their order, b of row J of the lane's candidate.  In assembly because the compiler makes a move and a multiply-add
-// of it; the waits are what a lane-crossing read of a register just written takes, here and of the sum.
+// of it; the waits are what a lane-crossing read of a register just written takes, here and of the sum.  (Early clobber: the sums are written while rows are still to be read, and
+// may not share a register with one of the same value.)
 #define CLIMBER_DPP " quad_perm:[%[p0],%[p1],%[p2],%[p3]] row_mask:0xf bank_mask:0xf\n\t"
 template <int S, int J>
 __device__ __forceinline__ float dot_of_row(const float (&a)[8], const float (&b)[8])
@@ -67,7 +68,7 @@ __device__ __forceinline__ float dot_of_row(const float (&a)[8], const float (&b
         "v_fmac_f32_dpp %0, %1, %9" CLIMBER_DPP "v_fmac_f32_dpp %0, %2, %10" CLIMBER_DPP "v_fmac_f32_dpp %0, %3, %11" CLIMBER_DPP
         "v_fmac_f32_dpp %0, %4, %12" CLIMBER_DPP "v_fmac_f32_dpp %0, %5, %13" CLIMBER_DPP "v_fmac_f32_dpp %0, %6, %14" CLIMBER_DPP
         "v_fmac_f32_dpp %0, %7, %15" CLIMBER_DPP "v_fmac_f32_dpp %0, %8, %16" CLIMBER_DPP "s_nop 1"
-        : "+v"(sum)
+        : "+&v"(sum)
         : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]),
           "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), [p0] "n"(p0), [p1] "n"(p0), [p2] "n"(p2), [p3] "n"(p2));
     return sum;
@@ -81,7 +82,7 @@ __device__ __forceinline__ void add_of_row(float p, const float (&b)[8], float (
         "v_fmac_f32_dpp %0, %8, %16" CLIMBER_DPP "v_fmac_f32_dpp %1, %9, %16" CLIMBER_DPP "v_fmac_f32_dpp %2, %10, %16" CLIMBER_DPP
         "v_fmac_f32_dpp %3, %11, %16" CLIMBER_DPP "v_fmac_f32_dpp %4, %12, %16" CLIMBER_DPP "v_fmac_f32_dpp %5, %13, %16" CLIMBER_DPP
         "v_fmac_f32_dpp %6, %14, %16" CLIMBER_DPP "v_fmac_f32_dpp %7, %15, %16" CLIMBER_DPP
-        : "+v"(out[0]), "+v"(out[1]), "+v"(out[2]), "+v"(out[3]), "+v"(out[4]), "+v"(out[5]), "+v"(out[6]), "+v"(out[7])
+        : "+&v"(out[0]), "+&v"(out[1]), "+&v"(out[2]), "+&v"(out[3]), "+&v"(out[4]), "+&v"(out[5]), "+&v"(out[6]), "+&v"(out[7])
         : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]), "v"(p), [p0] "n"(p0), [p1] "n"(p0), [p2] "n"(p2),
           [p3] "n"(p2));
 }

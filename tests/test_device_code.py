@@ -56,3 +56,29 @@ def test_bias_attention_waits_for_its_lds_reads_before_a_ring_stage_is_filled_ag
                 seen += 1
                 assert any("lgkmcnt(0)" in w for w in waits), (name, i, waits)
     assert seen > 0
+
+
+def test_inline_assembly_of_several_instructions_keeps_its_inputs():
+    # an output that an earlier instruction writes may share its register with an input that a later one reads, where the compiler knows
+    # both to have one value, unless it is marked as an early clobber
+    seen = 0
+    for f in sorted(os.listdir(hb.CSRC)):
+        if not f.endswith((".hip", ".h")):
+            continue
+        text = re.sub(r"//[^\n]*", "", open(os.path.join(hb.CSRC, f)).read())
+        macros = dict(re.findall(r"#define (CLIMBER_\w+) (\".*\")$", text, flags=re.M))
+        for m in re.finditer(r"\basm\b(?: volatile)?\s*\(", text):
+            end, depth = m.end(), 1
+            while depth:
+                depth += {"(": 1, ")": -1}.get(text[end], 0)
+                end += 1
+            block = text[m.end():end - 1]
+            for name, value in macros.items():
+                block = block.replace(name, value)
+            template, *operands = re.split(r"\s:\s", block)
+            if template.count("\\n") == 0 or len(operands) < 2:
+                continue
+            seen += 1
+            outs = re.findall(r'"([=+][^"]*)"', operands[0])
+            assert outs and all("&" in o for o in outs), (f, " ".join(block.split())[:120])
+    assert seen >= 3
