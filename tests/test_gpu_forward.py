@@ -425,14 +425,14 @@ def test_projection_behind_the_tail_gives_the_bits_of_separate_launches(d, F, la
     (256, 3, (384, 77, 300, 129, 512, 64, 1) * 3, 1, 0),      # just above 4096 rows with the history, ragged
     (512, 2, (448,) * 18, 65, 0),                             # a uniform batch, 8129 rows: encode with 8064
     (256, 4, (200, 31, 0, 96, 130) * 3, 5377, 0),             # candidates alone from where their own launch begins a third turn, empty histories
-    (2048, 2, (64, 1, 40), 7649, 0), (256, 2, (320, 65) * 10, 31, 4)])
+    (2048, 2, (64, 1, 40), 7649, 0), (512, 2, (64, 0), 8128, 0), (256, 2, (320, 65) * 10, 31, 4)])
 def test_projection_behind_tails_of_32_rows_gives_the_bits_of_separate_launches(F, layers, lens, cands, flags):
     # as above from 4097 to 8192 rows, where a ninth wave requests this projection's weights as well
     test_projection_behind_the_tail_gives_the_bits_of_separate_launches(512, F, layers, lens, cands, flags)
 
 
 @pytest.mark.parametrize("users, cands, encode, forward, score", [(5, 4, 3, 3, 0), (7, 600, 3, 3, 0), (8, 0, 3, 3, 0), (8, 672, 3, 3, 0), (8, 673, 3, 3, 3),
-                                                                 (8, 960, 3, 3, 3), (8, 961, 3, 3, 0), (8, 1024, 3, 3, 0)])
+                                                                 (8, 960, 3, 3, 3), (8, 961, 3, 3, 3), (8, 1024, 3, 3, 3), (8, 1025, 3, 0, 0)])
 def test_tails_of_32_rows_make_the_next_projection_where_that_was_measured_to_be_faster(users, cands, encode, forward, score):
     # four layers, d_model 512: how many tails of an encode, a packed forward and a scoring call do
     import torch
