@@ -158,9 +158,19 @@ __global__ __launch_bounds__(NW * 64) void layer_head_kernel(const HeadArgs p)
 
 }  // namespace
 
-// At most a workgroup per CU.  Us a call, four layers, one launch / two: score of 16 rows 69.7 / 72.8, 64 76.2 / 75.6, 200 78.3 / 79.2, 320 81.2 / 82.7, 512 84.2 / 85.0,
-// 800 92.8 / 94.6, 1000 95.7 / 96.5, 1200 (304 workgroups) 115.3 / 103.4, encode of 128 rows 62.3 / 62.7, 600 70.8 / 72.4, 1000 74.4 / 73.6.
-bool layer_head_takes(int M, int d, int F) { return d == D && F % kHidden == 0 && F > 0 && (M + 31) / 32 * (int64_t)(F / kHidden) <= 256; }
+// At most a workgroup per CU, and with two to six parts of the hidden, where the output projection made over counts for more, at most 512 rows.  Us
+// a call, four layers, one launch / two, as calls / as nodes of a graph (where the launch saved costs no host time).  d_ffn 1024: score of 16 rows
+// 79.2 / 86.0, 80.1 / 81.7, 64 90.0 / 90.7, 91.3 / 91.4, 320 93.6 / 95.6, 95.2 / 96.8, 600 98.7 / 102.7, 100.2 / 103.9, 1000 111.5 / 112.8, 112.3 /
+// 113.9, encode of 128 rows 60.4 / 66.4, 60.2 even, 400 65.0 / 69.3, 66.3 / 64.2, 1000 75.9 / 75.7, 77.3 / 76.7; 2048: score of 400 100.9 / 107.2,
+// 102.1 / 108.2, encode of 400 71.0 / 80.4, 71.8 / 76.6.  512: score of 200 85.0 / 86.0, 85.3 / 85.9, 512 92.2 / 91.1, 92.7 / 92.3, 800 101.3 /
+// 99.3, 102.0 / 99.4, 1000 102.7 / 100.4, 103.3 / 101.5, encode of 400 60.5 / 67.3, 59.5 / 58.9, 1000 68.2 / 68.5, 69.8 / 66.6; 256: score of 128
+// 83.6 / 85.2, 81.1 / 85.0, 700 95.0 / 94.1, 94.1 / 93.0, 4096 161.6 / 159.3, 162.9 / 160.6, encode of 600 61.1 / 66.8, 60.2 / 57.2; 896: score of
+// 600 100.6 / 104.2, 102.1 / 105.1; 128: 512 86.9 / 85.6, 85.2 / 83.3, 1500 114.6 / 119.8, 114.4 / 118.9, 4096 145.7 / 156.5, 147.4 / 157.9.  1024
+// with 304 workgroups (1200 rows) 115.3 / 103.4.
+bool layer_head_takes(int M, int d, int F)
+{
+    return d == D && F % kHidden == 0 && F > 0 && (M <= 512 || F == kHidden || F >= 896) && (M + 31) / 32 * (int64_t)(F / kHidden) <= 256;
+}
 
 hipError_t layer_head_bf16(const HeadArgs &a, hipStream_t s)
 {
