@@ -261,16 +261,22 @@ __global__ __launch_bounds__(512, 4) void bgf_gate_kernel(const __bf16 *gb, cons
 }  // namespace
 
 // A workgroup streams both weights for its 32 candidates, whoever else does, so few of them are better served by the projections for few rows
-// (gemm_small_bf16.hip), further on with a wide G, whose weights the macro tiles read less often.  Us a call, one launch / three, G as blocks x
-// d_model.  d_gate 256: 4 x 512 2100 121.5 / 116.9, 2900 131.7 / 127.5, 3900 151.2 / 150.8, 4400 222 / 226, 2 x 512 2100 87.9 / 87.3, 4000 99.6 / 101.0, 1 x 512 2100 68.9
-// / 70.3, 4000 79.1 / 82.6, 2 x 256 2100 54.6 / 56.4, 6 x 512 5800 387.0 / 386.4, 6300 400 / 403, 8 x 512 6100 447 / 443.  d_gate 128: 1 x 256 1500 34.9 / 37.4, 2 x 256
-// 1500 45.8 / 47.2, 2 x 512 1500 75.7 / 74.8, 2400 83.3 / 83.8, 4 x 512 1500 99.1 / 93.2, 2600 124.8 / 121.2, 3400 135.6 / 135.9, 4096 147.6 / 150.0, 6 x 512 2047 139 / 133,
-// 3000 221 / 224, 8 x 512 2000 165 / 157, 3400 264 / 263, 4000 290 / 293, 16 x 512 5000 882 / 914.
+// (gemm_small_bf16.hip), further on with a wide G, whose weights the macro tiles read less often.  The lines lie where the two sides
+// meet: between 768 and 4096 columns at 2500 to 4300 candidates, earlier with Y than without it.  Us a call, one launch / three, G as blocks x d_model, with
+// Y; in brackets without.
+// d_gate 256: 1 x 512 1500 58.2 / 58.6, 3 x 256 2100 63.8 / 65.0; 2 x 512 2100 91.6 / 90.6, 3200 95.1 / 94.9 [93.3 / 92.7], 4000 107.2 / 108.2, 3 x 512
+// 2100 105.4 / 102.5, 2900 123.9 / 125.7, 4 x 512 2100 129.2 / 126.0, 2900 140.4 / 138.2, 3300 144.8 / 144.5 [141.8 / 139.9], 3700 153.6 / 155.1 [150.2
+// / 149.2], 4400 228.5 / 233.8, 6 x 512 3000 241.5 / 239.5, 3400 249.9 / 251.2 [247.7 / 245.2], 4600 291.2 / 302.4 [286.0 / 287.4], 5800 387.1 / 402.7
+// [369.7 / 377.5], 8 x 512 3500 284.7 / 293.3 [282.0 / 277.0], 4300 386.5 / 398.0 [372.7 / 372.2], 5300 442.8 / 443.5; 12 x 512 3900 574 / 549, 6000 829
+// / 826, 16 x 512 5000 1038 / 1007, 6000 1204 / 1198.
+// d_gate 128: 1 x 256 1500 34.9 / 37.4, 2 x 512 1500 80.5 / 80.3; 3 x 512 2000 107.9 / 105.9, 2600 112.7 / 112.6, 4 x 512 2000 111.0 / 106.7, 2800 127.3
+// / 127.1, 3400 141.2 / 141.7, 6 x 512 2000 144.0 / 137.3, 2800 231.3 / 231.2; 7 x 512 2000 159.1 / 151.9, 3000 239.4 / 238.7, 3400 247.5 / 251.2, 8 x
+// 512 2000 177.9 / 167.4, 3000 254.4 / 253.8, 3400 264.8 / 270.0; 10 x 512 4000 470 / 457, 5000 602 / 616, 16 x 512 4000 789 / 760, 5000 968 / 998.
 bool bgf_gate_takes(int64_t m, int nd, int dg)
 {
     if (nd % 256 != 0) return false;
-    if (dg == 128) return m >= (nd > 4096 ? 5000 : nd > 1024 && nd <= 3072 ? 2800 : 1500);
-    return dg == 256 && (nd <= 2048 ? m > 2048 : m >= 6000);
+    if (dg == 128) return m >= (nd > 4096 ? 5000 : nd > 3072 ? 3200 : nd > 1024 ? 2800 : 1500);
+    return dg == 256 && m >= (nd > 4096 ? 6000 : nd > 768 ? 3400 : 2049);
 }
 
 hipError_t launch_bgf_gate(const void *gb, const float *g, const void *w_down, const void *w_up, const float *w_head, float b_head, float *y,

@@ -161,8 +161,9 @@ def test_projection_and_attention_in_one_launch_give_the_bits_of_two(d, nb, m):
     assert score[[5, m - 2]].isnan().all()
 
 
-@pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 2048, False), (512, 4, 256, 2049, True), (512, 8, 256, 5999, False), (512, 8, 256, 6000, True),
-                                               (512, 8, 128, 1499, False), (512, 8, 128, 1500, True), (512, 16, 128, 4999, False), (512, 16, 128, 5000, True)])
+@pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 3399, False), (512, 4, 256, 3400, True), (256, 3, 256, 2048, False), (256, 3, 256, 2049, True),
+                                               (512, 8, 256, 3399, False), (512, 8, 256, 3400, True), (512, 9, 256, 5999, False), (512, 9, 256, 6000, True),
+                                               (512, 8, 128, 3199, False), (512, 8, 128, 3200, True), (512, 16, 128, 4999, False), (512, 16, 128, 5000, True)])
 def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, m, one):
     import torch
     import paper_2502_09888_amd as P
