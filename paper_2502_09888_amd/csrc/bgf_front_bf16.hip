@@ -4,13 +4,13 @@
 // logits a head, twice the bytes of the rows themselves.
 //
 // A workgroup has two blocks of 32 rows (whole candidates, as many as fit: 32 rows for N_b of 2, 4 or 8, 30 of 3 or 5, 28 of 7, 24 of 6)
-// in LDS as gemm_resident_bf16.hip has, and a wave runs over heads: their queries, keys and values are three units of
+// in LDS as gemm_resident_bf16.hip has, and a wave one head (d_model 512: two workgroups share a block's rows): its queries, keys and values are three units of
 // qkv_units.h whose accumulators become chunks of 8 features of one row per lane, so that a logit is a few products per lane
 // and one exchange between the half-waves, and another row of the candidate is another lane: by DPP where a candidate has 2, 4 or 8
 // lanes (6 and 7 rows: 8 lanes), else through the LDS crossbar.  Rounded to bf16 in between, and summed in the order of
 // bgf_attention_kernel: same bits.
 // 8192 candidates x 4 of 512: 76 us where the two launches take 82 + 23; without the loads of its rows 69, without the attention 68, without
-// either 60: the products, whose weights take 27 of the vector cache's time (1.5 MB a workgroup).
+// either 60: the products, whose weights take 27 of the vector cache's time (0.8 MB a workgroup).
 #include "bgf.h"
 #include "launch.h"
 #include "qkv_units.h"
@@ -90,15 +90,16 @@ __device__ __forceinline__ void add_of_row(float p, const float (&b)[8], float (
 
 template <int K, int NB>
 __global__ __launch_bounds__(NW * 64, 2) void bgf_front_kernel(const float *e, const __bf16 *Wp, __bf16 *o, const int32_t *scen, const float *tau_scen,
-                                                               int n_scen, int m, float scale_log2e, float inv_d, float eps, int splits)
+                                                               int n_scen, int m, float scale_log2e, float inv_d, float eps)
 {
     constexpr int S = lanes_of<NB>(), CB = 32 / S, U = CB * NB, H = K / 64;  // candidates and rows of a block, heads
+    static_assert(H % NW == 0, "a head for each wave");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     float *const scale = (float *)(lds + 32 * RB * K * 2);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, hf = lane >> 5;
-    const int turn = (int)blockIdx.x >> 3, part = turn % splits;  // (parts of a tile on one XCD)
-    const int c0 = (turn / splits * 8 + ((int)blockIdx.x & 7)) * (RB * CB);  // the tile's first candidate
+    const int turn = (int)blockIdx.x >> 3, part = turn % (H / NW);  // (parts of a tile on one XCD)
+    const int c0 = (turn / (H / NW) * 8 + ((int)blockIdx.x & 7)) * (RB * CB);  // the tile's first candidate
     if (c0 >= m) return;
     const int n_rows = min(m - c0, RB * CB) * NB;  // of the tile; lane l of block i has row i U + l / S N_b + l % S, where there is one
     auto slot_row = [&](int r) __attribute__((always_inline)) { return min(min(r / S, CB - 1) * NB + min(r % S, NB - 1), U - 1); };
@@ -106,8 +107,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bgf_front_kernel(const float *e, c
 
     const __amdgpu_buffer_rsrc_t w = __builtin_amdgcn_make_buffer_rsrc((void *)Wp, 0, 3 * K * K * 2, 0x00020000);
     u32x4 ring[2 * R];
-    int h = H / splits * part + wave;
-    const int end = H / splits * (part + 1);
+    const int h = NW * part + wave;
     {   // rows into LDS, rounded; their sums of squares: as gemm_resident_bf16.hip
         constexpr int P = K / 256, kTurn = 32 * RB / NW;
         const int r0 = wave * kTurn;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bgf_front_kernel(const float *e, c
             if (lane == k) scale[r0 + k] = 1.f / sqrtf(sum[k] * inv_d + eps);
     }
 #pragma unroll
-    for (int f = 0; f < 2 * R; ++f) ring[f] = unit_frag<K>(w, 0, min(h, H - 1), f, lane);
+    for (int f = 0; f < 2 * R; ++f) ring[f] = unit_frag<K>(w, 0, h, f, lane);
     const int mine = min(l32 / S, CB - 1);  // the lane's candidate of a block
     float cs[RB];
 #pragma unroll
@@ -151,102 +151,99 @@ __global__ __launch_bounds__(NW * 64, 2) void bgf_front_kernel(const float *e, c
 
     const uint32_t a_base = LdsRows<K>::base(l32, hf);
     f32x16 acc[RB][2];
-#pragma unroll 1
-    for (; h < end; h += NW) {
-        u32x4 q[RB][4], k[RB][4], v[RB][4];
-        auto unit = [&](int u, int next, u32x4 (&x)[RB][4]) __attribute__((always_inline)) {
-            unit_product<K, RB, R, false>(acc, lds, w, 0, ring, a_base, u, next, lane);
+    u32x4 q[RB][4], k[RB][4], v[RB][4];
+    auto unit = [&](int u, auto more_tag, u32x4 (&x)[RB][4]) __attribute__((always_inline)) {
+        unit_product<K, RB, R, false, decltype(more_tag)::value>(acc, lds, w, 0, ring, a_base, u, H + u, lane);
 #pragma unroll
-            for (int i = 0; i < RB; ++i) row_chunks(acc[i], scale[32 * i + l32], false, x[i]);
+        for (int i = 0; i < RB; ++i) row_chunks(acc[i], scale[32 * i + l32], false, x[i]);
+    };
+    unit(h, std::true_type{}, q);
+    unit(H + h, std::true_type{}, k);
+    unit(2 * H + h, std::false_type{}, v);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+        float t[NB], mx = -INFINITY;
+        auto logit = [&](auto j_tag, const float (&dot)[4]) __attribute__((always_inline)) {
+            constexpr int j = decltype(j_tag)::value;
+            float s[4];
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(dot[n]), __float_as_uint(dot[n]), false, false);
+                s[n] = __uint_as_float(both[0]) + __uint_as_float(both[1]);
+            }
+            t[j] = ((s[0] + s[1]) + (s[2] + s[3])) * cs[i];  // log2 units
+            mx = fmaxf(mx, t[j]);
         };
-        unit(h, H + h, q);
-        unit(H + h, 2 * H + h, k);
-        unit(2 * H + h, h + NW < end ? h + NW : h, v);
+        float sum = 0.f, out[4][8] = {};
+        if constexpr (by_dpp<NB>()) {
+            float a[4][8], b[4][8];
+            u32x4 x[4];
+            spread(q[i], a);
+            static_for<(NB + 3) / 4>([&](auto g_tag) __attribute__((always_inline)) {
+                constexpr int G = decltype(g_tag)::value;
+                quad_of<S, G>(k[i], x);
+                spread(x, b);
+                static_for<(NB - 4 * G < 4 ? NB - 4 * G : 4)>([&](auto j_tag) __attribute__((always_inline)) {
+                    constexpr int j = 4 * G + decltype(j_tag)::value;
+                    float dot[4];
 #pragma unroll
-        for (int i = 0; i < RB; ++i) {
-            float t[NB], mx = -INFINITY;
-            auto logit = [&](auto j_tag, const float (&dot)[4]) __attribute__((always_inline)) {
-                constexpr int j = decltype(j_tag)::value;
-                float s[4];
-#pragma unroll
-                for (int n = 0; n < 4; ++n) {
-                    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(dot[n]), __float_as_uint(dot[n]), false, false);
-                    s[n] = __uint_as_float(both[0]) + __uint_as_float(both[1]);
-                }
-                t[j] = ((s[0] + s[1]) + (s[2] + s[3])) * cs[i];  // log2 units
-                mx = fmaxf(mx, t[j]);
-            };
-            float sum = 0.f, out[4][8] = {};
-            if constexpr (by_dpp<NB>()) {
-                float a[4][8], b[4][8];
-                u32x4 x[4];
-                spread(q[i], a);
-                static_for<(NB + 3) / 4>([&](auto g_tag) __attribute__((always_inline)) {
-                    constexpr int G = decltype(g_tag)::value;
-                    quad_of<S, G>(k[i], x);
-                    spread(x, b);
-                    static_for<(NB - 4 * G < 4 ? NB - 4 * G : 4)>([&](auto j_tag) __attribute__((always_inline)) {
-                        constexpr int j = 4 * G + decltype(j_tag)::value;
-                        float dot[4];
-#pragma unroll
-                        for (int n = 0; n < 4; ++n) dot[n] = dot_of_row<S, j>(a[n], b[n]);
-                        logit(std::integral_constant<int, j>{}, dot);
-                    });
+                    for (int n = 0; n < 4; ++n) dot[n] = dot_of_row<S, j>(a[n], b[n]);
+                    logit(std::integral_constant<int, j>{}, dot);
                 });
-                static_for<(NB + 3) / 4>([&](auto g_tag) __attribute__((always_inline)) {
-                    constexpr int G = decltype(g_tag)::value;
-                    quad_of<S, G>(v[i], x);
-                    spread(x, b);
-                    static_for<(NB - 4 * G < 4 ? NB - 4 * G : 4)>([&](auto j_tag) __attribute__((always_inline)) {
-                        constexpr int j = 4 * G + decltype(j_tag)::value;
-                        const float p = exp2f(t[j] - mx);
-                        sum += p;
-#pragma unroll
-                        for (int n = 0; n < 4; ++n) add_of_row<S, j>(p, b[n], out[n]);
-                    });
-                });
-            } else {
-                const int at = (hf * 32 + mine * S) * 4;
-                static_for<NB>([&](auto j_tag) __attribute__((always_inline)) {
-                    constexpr int j = decltype(j_tag)::value;
-                    float dot[4] = {};
-#pragma unroll
-                    for (int n = 0; n < 4; ++n)
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) {
-                            const uint32_t b = (uint32_t)__builtin_amdgcn_ds_bpermute(at + 4 * j, (int)k[i][n][d]);
-                            dot[n] = fmaf(high(q[i][n][d]), high(b), fmaf(low(q[i][n][d]), low(b), dot[n]));
-                        }
-                    logit(j_tag, dot);
-                    __builtin_amdgcn_sched_barrier(0);  // (or the registers do not hold what is taken ahead)
-                });
-                static_for<NB>([&](auto j_tag) __attribute__((always_inline)) {
-                    constexpr int j = decltype(j_tag)::value;
+            });
+            static_for<(NB + 3) / 4>([&](auto g_tag) __attribute__((always_inline)) {
+                constexpr int G = decltype(g_tag)::value;
+                quad_of<S, G>(v[i], x);
+                spread(x, b);
+                static_for<(NB - 4 * G < 4 ? NB - 4 * G : 4)>([&](auto j_tag) __attribute__((always_inline)) {
+                    constexpr int j = 4 * G + decltype(j_tag)::value;
                     const float p = exp2f(t[j] - mx);
                     sum += p;
 #pragma unroll
-                    for (int n = 0; n < 4; ++n)
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) {
-                            const uint32_t b = (uint32_t)__builtin_amdgcn_ds_bpermute(at + 4 * j, (int)v[i][n][d]);
-                            out[n][2 * d] = fmaf(p, low(b), out[n][2 * d]);
-                            out[n][2 * d + 1] = fmaf(p, high(b), out[n][2 * d + 1]);
-                        }
-                    __builtin_amdgcn_sched_barrier(0);
+                    for (int n = 0; n < 4; ++n) add_of_row<S, j>(p, b[n], out[n]);
                 });
-            }
-            const float inv = 1.f / sum;
-            u32x4 x[4];
+            });
+        } else {
+            const int at = (hf * 32 + mine * S) * 4;
+            static_for<NB>([&](auto j_tag) __attribute__((always_inline)) {
+                constexpr int j = decltype(j_tag)::value;
+                float dot[4] = {};
 #pragma unroll
-            for (int n = 0; n < 4; ++n)
+                for (int n = 0; n < 4; ++n)
 #pragma unroll
-                for (int d = 0; d < 4; ++d) x[n][d] = pack2(out[n][2 * d] * inv, out[n][2 * d + 1] * inv);
-            whole_rows(x);
+                    for (int d = 0; d < 4; ++d) {
+                        const uint32_t b = (uint32_t)__builtin_amdgcn_ds_bpermute(at + 4 * j, (int)k[i][n][d]);
+                        dot[n] = fmaf(high(q[i][n][d]), high(b), fmaf(low(q[i][n][d]), low(b), dot[n]));
+                    }
+                logit(j_tag, dot);
+                __builtin_amdgcn_sched_barrier(0);  // (or the registers do not hold what is taken ahead)
+            });
+            static_for<NB>([&](auto j_tag) __attribute__((always_inline)) {
+                constexpr int j = decltype(j_tag)::value;
+                const float p = exp2f(t[j] - mx);
+                sum += p;
 #pragma unroll
-            for (int n = 0; n < 4; ++n) {
-                const int l = 8 * n + (lane & 7), row = i * U + l / S * NB + l % S;
-                if (l / S < CB && l % S < NB && row < n_rows) *(u32x4 *)(o + (row0 + row) * K + h * 64 + row_chunk(lane) * 8) = x[n];
-            }
+                for (int n = 0; n < 4; ++n)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        const uint32_t b = (uint32_t)__builtin_amdgcn_ds_bpermute(at + 4 * j, (int)v[i][n][d]);
+                        out[n][2 * d] = fmaf(p, low(b), out[n][2 * d]);
+                        out[n][2 * d + 1] = fmaf(p, high(b), out[n][2 * d + 1]);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+        const float inv = 1.f / sum;
+        u32x4 x[4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) x[n][d] = pack2(out[n][2 * d] * inv, out[n][2 * d + 1] * inv);
+        whole_rows(x);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const int l = 8 * n + (lane & 7), row = i * U + l / S * NB + l % S;
+            if (l / S < CB && l % S < NB && row < n_rows) *(u32x4 *)(o + (row0 + row) * K + h * 64 + row_chunk(lane) * 8) = x[n];
         }
     }
 }
@@ -258,9 +255,9 @@ hipError_t launch(const float *e, const void *wqkv, void *o, const int32_t *scen
     constexpr auto kernel = bgf_front_kernel<K, NB>;
     const hipError_t err = raise_lds_limit<kernel>(front_lds_bytes<K>());
     if (err != hipSuccess) return err;
-    const int per = RB * (32 / lanes_of<NB>()), tiles = (int)((m + per - 1) / per), splits = K / 64 / NW;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + 7) / 8 * 8 * splits)), dim3(NW * 64), front_lds_bytes<K>(), s, e, (const __bf16 *)wqkv,
-                       (__bf16 *)o, scen, tau_scen, n_scen, (int)m, qk_scale * 1.4426950408889634f, inv_d, eps, splits);
+    const int per = RB * (32 / lanes_of<NB>()), tiles = (int)((m + per - 1) / per), parts = K / 64 / NW;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + 7) / 8 * 8 * parts)), dim3(NW * 64), front_lds_bytes<K>(), s, e, (const __bf16 *)wqkv,
+                       (__bf16 *)o, scen, tau_scen, n_scen, (int)m, qk_scale * 1.4426950408889634f, inv_d, eps);
     return hipGetLastError();
 }
 

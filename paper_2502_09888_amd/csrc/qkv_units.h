@@ -46,8 +46,8 @@ static __device__ __forceinline__ uint32_t pack2(float x, float y)
 }
 
 // acc = the tile's rows times the 64 columns of `unit`, as (rows, weights) if V, else (weights, rows).  `ring` holds the unit's
-// first 2 R fragments, at the end those of `next`; a_base: LdsRows::base of the lane.
-template <int K, int RB, int R, bool V>
+// first 2 R fragments, at the end, if MORE, those of `next`; a_base: LdsRows::base of the lane.
+template <int K, int RB, int R, bool V, bool MORE = true>
 static __device__ __forceinline__ void unit_product(f32x16 (&acc)[RB][2], const uint8_t *rows, __amdgpu_buffer_rsrc_t w, int w_at, u32x4 (&ring)[2 * R],
                                                     uint32_t a_base, int unit, int next, int lane)
 {
@@ -70,7 +70,7 @@ static __device__ __forceinline__ void unit_product(f32x16 (&acc)[RB][2], const 
                 acc[i][j] = V ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], wf, c, 0, 0, 0)
                               : __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, fa[i], c, 0, 0, 0);
                 if constexpr (j == 1 && !(LAST && t == R - 1)) fa[i] = LdsRows<K>::frag(rows, base, s0 + t + 1, i);
-                if constexpr (i == RB - 1)
+                if constexpr (i == RB - 1 && (MORE || !LAST))
                     ring[2 * t + j] = LAST ? unit_frag<K>(w, w_at, next, 2 * t + j, lane) : unit_frag<K>(w, w_at, unit, 2 * (s0 + R + t) + j, lane);
                 __builtin_amdgcn_sched_barrier(0);
             });
