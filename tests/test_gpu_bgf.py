@@ -2,6 +2,8 @@
 multi-block scoring it closes: one block (own weights, own cache) per subsequence, the candidate scored
 against each block on its own, the N_b block outputs fused into a score.  Reference: the oracle's bgf()
 and its stack functions, same seeded inputs; tolerance 2e-2 max-abs (unit-scale values)."""
+import re
+
 import numpy as np
 import pytest
 
@@ -9,9 +11,11 @@ import workloads as W
 from harness import GpuStack, launches, max_abs, oracle, oracle_stack_config, say, stack_config
 
 pytestmark = pytest.mark.gpu
+GIVEN_F32 = re.compile(r"gemm_small_kernelI\w*Li2EEEv")   # (its last template argument)
 
 
-def gpu_bgf(P, torch, cfg, w, e):
+def gpu_bgf(P, torch, cfg, w, e, run=None):
+    """Y and scores; run: a list that receives the mangled names of the kernels launched."""
     dev, bf = "cuda:0", torch.bfloat16
     m, nb, dg = e.shape[0], w["n_blocks"], w["d_gate"]
     atl = {n.lower(): torch.from_numpy(w["atl"][n]).to(dev).to(bf).contiguous() for n in ("g1", "Wqkv", "Wo", "g2", "W1", "W2")}
@@ -30,6 +34,8 @@ def gpu_bgf(P, torch, cfg, w, e):
     P.climber_bgf_score(cfg, atl, wd, wu, wh, ts, float(w["b_head"]), nb, dg, et, sc, m, None, score2, ws)
     torch.cuda.synchronize()
     assert torch.equal(score, score2)
+    if run is not None:
+        run += [k.kernel for k in launches(lambda: P.climber_bgf_score(cfg, atl, wd, wu, wh, ts, float(w["b_head"]), nb, dg, et, sc, m, y, score, ws))]
     return y.cpu().numpy(), score.cpu().numpy()
 
 
@@ -104,8 +110,13 @@ def test_multi_block_scoring_end_to_end():
 @pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 128, 2049, 33), (512, 3, 256, 2731, 1), (256, 8, 128, 1025, 16), (256, 2, 256, 4129, 40),
                                                 (256, 3, 256, 2095, 64), (256, 1, 128, 1500, 9), (512, 5, 256, 6001, 32)])
 def test_few_and_many_candidates_give_the_same_bits(d, nb, dg, m, part):
-    # more than 8192 rows: the projection forms the fp32 rows' sums itself, and the tail is one launch; from 1500, 2049 or 6000 candidates on: so
-    # are the gate and the head, the last 32 of them in part, an even and an odd number of steps; few: launches of their own
+    # 4000 rows or more of 2 to 8 blocks: projection and attention are one launch, above 4096 rows the tail is, from the lines of the gate on it is,
+    # the last 32 candidates of it in part; few candidates: launches of their own
+    few_against_many(d, nb, dg, m, part)
+
+
+def few_against_many(d, nb, dg, m, part):
+    """Both calls' launches, after a comparison of their bits."""
     import torch
     import paper_2502_09888_amd as P
     spec = W.StackSpec(f"bgf-many-{d}", B=1, L=128, sub_len=0, M=1, n_layers=1, d_model=d, H=d // 64, dh=64, d_ffn=256, n_scen=8, n_beh=4,
@@ -113,19 +124,45 @@ def test_few_and_many_candidates_give_the_same_bits(d, nb, dg, m, part):
     say(f"[case] {spec.name} n_blocks={nb} m={m}")
     w = W.make_bgf(spec, nb, dg, m)
     cfg = stack_config(spec)
-    y, sc = gpu_bgf(P, torch, cfg, w, w["e"])
+    many, ran = [], []
+    y, sc = gpu_bgf(P, torch, cfg, w, w["e"], many)
     for lo in (0, m - part):
         few = dict(w, scen=np.ascontiguousarray(w["scen"][lo:lo + part]))
-        y1, sc1 = gpu_bgf(P, torch, cfg, few, w["e"][lo:lo + part])
-        assert np.array_equal(y1, y[lo:lo + part]) and np.array_equal(sc1, sc[lo:lo + part])
+        y1, sc1 = gpu_bgf(P, torch, cfg, few, w["e"][lo:lo + part], ran)
+        assert np.isfinite(y1).all() and np.array_equal(y1, y[lo:lo + part]) and np.array_equal(sc1, sc[lo:lo + part])
+    return ran, many
+
+
+def ran_among(run, part):
+    return any(part in k for k in run)
+
+
+@pytest.mark.parametrize("d, nb, dg, m, part", [(512, 9, 128, 913, 1), (512, 9, 256, 911, 40), (512, 16, 128, 521, 33), (512, 1, 256, 8193, 64), (256, 16, 128, 513, 5),
+                                                (256, 1, 128, 8257, 9), (256, 9, 256, 1000, 300)])
+def test_projection_of_many_fp32_rows_makes_their_sums(d, nb, dg, m, part):
+    # one block or more than eight, more than 8192 rows: the projection with its rows in LDS rounds them and forms their sums, the last 64 of them in part,
+    # and the attention is a launch of its own; against calls of few rows, whose projection is another kernel
+    few, many = few_against_many(d, nb, dg, m, part)
+    assert ran_among(many, f"gemm_resident_kernelILi{d}E") and ran_among(many, f"bgf_attention_kernelILi{nb}E") and not ran_among(many, "row_prep_kernel")
+    assert not ran_among(few, "gemm_resident_kernel")
+
+
+@pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 256, 3425, 33), (512, 8, 256, 3401, 1), (512, 3, 128, 2815, 31), (512, 7, 128, 3210, 40)])
+def test_one_launch_of_a_wide_gate_gives_the_bits_of_three(d, nb, dg, m, part):
+    # from its lines on, the last 32 candidates in part, an even and an odd number of steps
+    few, many = few_against_many(d, nb, dg, m, part)
+    assert ran_among(many, f"bgf_gate_kernelILi{dg}E") and ran_among(few, "bgf_gate_head_kernel") and not ran_among(few, "bgf_gate_kernel")
 
 
 @pytest.mark.parametrize("d, nb, m, part", [(512, 4, 300, 1), (512, 4, 300, 9), (512, 4, 300, 256), (512, 3, 700, 113), (512, 8, 600, 128), (256, 4, 600, 5),
                                             (256, 4, 600, 512), (256, 1, 2100, 673), (256, 9, 300, 227)])
 def test_first_projection_of_few_fp32_rows_makes_their_sums(d, nb, m, part):
     # the fusion layer's projection of few rows forms the sums of squares of its fp32 rows, in blocks of 16 or 32 of them, the last in part, up
-    # to the most rows there are; against a call of more, which rounds and sums them in a launch before or in the projection of many rows
-    test_few_and_many_candidates_give_the_same_bits(d, nb, 128, m, part)
+    # to the most rows there are; against a call of more, which has a launch for that before, or (4800 rows of 8 blocks) one launch to the attention
+    few, many = few_against_many(d, nb, 128, m, part)
+    own = lambda run: any("gemm_small_kernel" in k and GIVEN_F32.search(k) for k in run)
+    assert own(few) and not ran_among(few, "row_prep_kernel")
+    assert not own(many) and ran_among(many, "row_prep_kernel") != ran_among(many, "bgf_front_kernel")
 
 
 @pytest.mark.parametrize("d, nb, m", [(512, 2, 2001), (256, 2, 2063), (512, 3, 2049), (256, 3, 2069), (512, 4, 1000), (256, 4, 1017), (512, 5, 1229),
