@@ -6,7 +6,8 @@
 // and their whole K; each of its four waves 16 columns, whose weights go straight from L2 into registers, 16 k-tiles of 32 ahead (in
 // fragment order, 1 KiB a load: a quarter of the workgroup's, nobody's twice).  The rows come by way of LDS, 256 k at a time with a barrier
 // each, the loads of the next but one in flight.  Bound by the loads, at the 64 bytes per clock of a CU's vector cache: 4 KiB of weights
-// and 1 or 2 of rows per k-tile, so 16 rows cost a workgroup 5/6 of what 32 do and are taken while there are CUs for twice the workgroups.
+// and 1 or 2 of rows per k-tile, so 16 rows cost a workgroup 5/6 of what 32 do and are taken while there are CUs for twice the workgroups.  (Beside them
+// LDS: bank conflicts of 133 to 176 % of its active cycles, by the rows' places, which are the tiled layout's and suit reads of 32 x 32 x 16.)
 // One request (1000 behaviours, 200 candidates, four layers, d_model 512) 216 us; with two waves of 32 columns a workgroup, each with its own
 // fragments of all 32 rows (8 KiB per k-tile, 56 workgroups for 200 rows x 512), 244.  Score of 16 rows 86.6 / 110.9, 128 92.6 / 123.5, 256 101
 // / 126, 640 127 / 135; d_model 256 72.3 / 79.8, 81.8 / 89.8, 82.4 / 91.1, 88.4 / 98.9.  32 k-tiles ahead: 0.99.

@@ -565,11 +565,12 @@ bool layer_tail_takes(int M, int D, int F)
 //   252 511 / 552; 264 (248 idle) 764 / 742, 287 (225) 808 / 797, 297 (215) 725 / 733, 355 (157) 767 / 771, 422 842 / 879, 492 947 / 1013; 516 (252) 1092 /
 //   1100, 542 1150 / 1162, 659 1227 / 1265; 774 (250) 1558 / 1567.  271 tiles (241 idle), six layers, 1191 / 1151.
 // - Candidates alone, against the 128 x 128 tiles: 9766 rows 554 / 530, 16448 944 / 896, 24672 1020 / 1015, 30840 1173 / 1204: not.
-// - Tiles of 32 rows (up to 8192 of them), with / without: with a history always, us, four layers, encode of 4500 rows 237 / 242, 6000 252 / 263, 7168 263 / 274, 8192
-//   280 / 296, packed forward of 5200 352 / 364, 7200 386 / 410.  Candidates alone from where the 128 x 128 tiles of their own launch begin
-//   a third turn: d_ffn 2048, 16 users x 1024, 5120 rows 359.7 / 357.6, 5376 363.6 / 362.2, 5440 364.7 / 377.4, 6400 379.5 / 387.6, 7680 401.0 / 409.7, 7792 403.0 /
-//   417.5, 8192 411.2 / 421.0; the same line with 64 x 256 (5376 312.4 / 308.6, 5440 315.4 / 321.7, 8192 352.9 / 357.1), 8 x 3000 (8192 521 / 533), and with d_ffn 256 (5376
-//   233.1 / 228.5, 5440 235.1 / 245.0, 7400 253.2 / 257.5, 8192 260.8 / 265.3), 512, 1024 and 4096 (8192 586.8 / 595.7).
+// - Tiles of 32 rows (up to 8192 of them), with / without: with a history always, us, four layers, encode of 4500 rows 237 / 242, 6000 252 / 263, 7168
+//   263 / 274, 8192 280 / 296, packed forward of 5200 352 / 364, 7200 386 / 410 (encode of 5120 to 8192 rows with d_ffn 256 to 4096: 0.93 to 0.97).
+//   Candidates alone from where the 128 x 128 tiles of their own launch begin a third turn: d_ffn 2048, 16 users x 1024, 5120 rows 359.7 / 357.6, 5376
+//   363.6 / 362.2, 5440 364.7 / 377.4, 6400 379.5 / 387.6, 7680 401.0 / 409.7, 7792 403.0 / 417.5, 8192 411.2 / 421.0; the same line with 64 x 256 (5376
+//   312.4 / 308.6, 5440 315.4 / 321.7, 8192 352.9 / 357.1), 8 x 3000 (8192 521 / 533), and with d_ffn 256 (5376 233.1 / 228.5, 5440 235.1 / 245.0, 7400
+//   253.2 / 257.5, 8192 260.8 / 265.3), 512, 1024 and 4096 (8192 586.8 / 595.7).
 // d_model 256 (tiles two per CU): encode of 5 users 127 / 132, 9 141 / 151, 17 218 / 236, 32 280 / 316, 64 530 / 581, scoring of 4500 rows 195 / 193, 8481
 // 206 / 213, 32896 517 / 539: always.
 bool layer_tail_projects(int M, int D, int F, int n_cached, bool ends)

@@ -217,8 +217,8 @@ def test_layer_output_over_its_own_input(d, F, m):
 def test_projection_kernels_for_few_and_many_rows_give_the_same_bits(users, m):
     # the packed forward runs users x 384 history rows and the candidates through one launch, at a width without a
     # one-launch tail: 3840 rows 64 x 128 tiles, 11520 rows 128 x 128, 44160 rows 256 x 128, up-projection (tiled store)
-    # and both residual ones; the scoring call runs the candidates alone (a wave per 32 x 32 block): a row's bits do not
-    # depend on which; candidate counts at the edges of the 32-row blocks, one of them the smallest launch there is
+    # and both residual ones; the scoring call runs the candidates alone (16 rows x 64 columns a workgroup): a row's bits do
+    # not depend on which; candidate counts at the edges of 32 rows, one of them the smallest launch there is
     spec = W.StackSpec(f"fwd-tiles-{users}-{m}", B=users, L=384, sub_len=128, M=0, n_layers=2, d_model=384, H=6, dh=64, d_ffn=768,
                        n_scen=8, n_beh=4, seed=95 + m, hist_lens=(384,) * users, cand_counts=(m,) + (0,) * (users - 1))
     w, g, yc = run_forward(spec, users=(0,), want_hist=True)
