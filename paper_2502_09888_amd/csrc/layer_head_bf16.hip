@@ -158,18 +158,19 @@ __global__ __launch_bounds__(NW * 64) void layer_head_kernel(const HeadArgs p)
 
 }  // namespace
 
-// At most a workgroup per CU, and with two to six parts of the hidden, where the output projection made over counts for more, at most 512 rows.  Us
-// a call, four layers, one launch / two, as calls / as nodes of a graph (where the launch saved costs no host time).  d_ffn 1024: score of 16 rows
-// 79.2 / 86.0, 80.1 / 81.7, 64 90.0 / 90.7, 91.3 / 91.4, 320 93.6 / 95.6, 95.2 / 96.8, 600 98.7 / 102.7, 100.2 / 103.9, 1000 111.5 / 112.8, 112.3 /
-// 113.9, encode of 128 rows 60.4 / 66.4, 60.2 even, 400 65.0 / 69.3, 66.3 / 64.2, 1000 75.9 / 75.7, 77.3 / 76.7; 2048: score of 400 100.9 / 107.2,
-// 102.1 / 108.2, encode of 400 71.0 / 80.4, 71.8 / 76.6.  512: score of 200 85.0 / 86.0, 85.3 / 85.9, 512 92.2 / 91.1, 92.7 / 92.3, 800 101.3 /
-// 99.3, 102.0 / 99.4, 1000 102.7 / 100.4, 103.3 / 101.5, encode of 400 60.5 / 67.3, 59.5 / 58.9, 1000 68.2 / 68.5, 69.8 / 66.6; 256: score of 128
-// 83.6 / 85.2, 81.1 / 85.0, 700 95.0 / 94.1, 94.1 / 93.0, 4096 161.6 / 159.3, 162.9 / 160.6, encode of 600 61.1 / 66.8, 60.2 / 57.2; 896: score of
-// 600 100.6 / 104.2, 102.1 / 105.1; 128: 512 86.9 / 85.6, 85.2 / 83.3, 1500 114.6 / 119.8, 114.4 / 118.9, 4096 145.7 / 156.5, 147.4 / 157.9.  1024
-// with 304 workgroups (1200 rows) 115.3 / 103.4.
+// At most a workgroup per CU, and with two to six parts of the hidden, where the output projection made over counts for more, at most 1536 rows.  Us a
+// call, four layers, one launch / two, as calls / as nodes of a graph (where the launch saved costs no host time).  d_ffn 1024: score of 16 rows 79.2 /
+// 86.0, 80.1 / 81.7, 64 90.0 / 90.7, 91.3 / 91.4, 320 93.6 / 95.6, 95.2 / 96.8, 600 98.7 / 102.7, 100.2 / 103.9, 1000 111.5 / 112.8, 112.3 / 113.9,
+// encode of 128 rows 60.4 / 66.4, 60.2 even, 400 65.0 / 69.3, 66.3 / 64.2, 1000 75.9 / 75.7, 77.3 / 76.7; 2048: score of 400 100.9 / 107.2, 102.1 /
+// 108.2, encode of 400 71.0 / 80.4, 71.8 / 76.6; 768: encode of 1024 72.6 / 74.1, 74.1 / 75.1, 1280 81.8 / 80.5, 83.3 / 81.4.  512: score of 200 85.0 /
+// 86.0, 85.3 / 85.9, 1000 102.7 / 100.4, 103.3 / 101.5, encode of 400 60.5 / 67.3, 59.5 / 58.9, 1024 68.6 / 66.4, 69.5 / 67.6, 1152 76.6 / 77.3, 76.9 /
+// 77.8, 1536 80.7 / 79.5, 81.7 / 80.2, 2048 87.2 / 82.3, 88.3 / 83.4; 256: score of 128 83.6 / 85.2, 81.1 / 85.0, 2048 100.7 / 99.0, 101.5 / 99.9, 4096
+// 161.6 / 159.3, 162.9 / 160.6, encode of 700 62.5 / 70.3, 61.4 / 59.9, 1280 73.4 / 81.1, 73.0 / 74.5, 2048 81.0 / 79.8, 81.6 / 79.9, 4096 102.9 /
+// 100.2, 105.1 / 101.4; 128: score of 512 86.9 / 85.6, 85.2 / 83.3, 1500 114.6 / 119.8, 114.4 / 118.9, 4096 145.7 / 156.5, 147.4 / 157.9.  1024 with 304
+// workgroups (1200 rows) 115.3 / 103.4.
 bool layer_head_takes(int M, int d, int F)
 {
-    return d == D && F % kHidden == 0 && F > 0 && (M <= 512 || F == kHidden || F >= 896) && (M + 31) / 32 * (int64_t)(F / kHidden) <= 256;
+    return d == D && F % kHidden == 0 && F > 0 && (M <= 1536 || F == kHidden || F >= 896) && (M + 31) / 32 * (int64_t)(F / kHidden) <= 256;
 }
 
 hipError_t layer_head_bf16(const HeadArgs &a, hipStream_t s)
