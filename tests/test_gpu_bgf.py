@@ -147,7 +147,7 @@ def test_projection_of_many_fp32_rows_makes_their_sums(d, nb, dg, m, part):
     assert not ran_among(few, "gemm_resident_kernel")
 
 
-@pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 256, 3425, 33), (512, 8, 256, 3401, 1), (512, 3, 128, 2815, 31), (512, 7, 128, 3210, 40)])
+@pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 256, 3425, 33), (512, 7, 256, 6017, 1), (256, 5, 256, 2717, 28), (512, 3, 128, 2815, 31), (512, 7, 128, 3210, 40)])
 def test_one_launch_of_a_wide_gate_gives_the_bits_of_three(d, nb, dg, m, part):
     # from its lines on, the last 32 candidates in part, an even and an odd number of steps
     few, many = few_against_many(d, nb, dg, m, part)
@@ -199,7 +199,7 @@ def test_projection_and_attention_in_one_launch_give_the_bits_of_two(d, nb, m):
 
 
 @pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 3399, False), (512, 4, 256, 3400, True), (256, 3, 256, 2048, False), (256, 3, 256, 2049, True),
-                                               (512, 8, 256, 3399, False), (512, 8, 256, 3400, True), (512, 9, 256, 5999, False), (512, 9, 256, 6000, True),
+                                               (512, 2, 256, 2699, False), (256, 7, 256, 2700, True), (512, 8, 256, 5999, False), (512, 8, 256, 6000, True),
                                                (512, 8, 128, 3199, False), (512, 8, 128, 3200, True), (512, 16, 128, 4999, False), (512, 16, 128, 5000, True)])
 def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, m, one):
     import torch
