@@ -158,20 +158,13 @@ __global__ __launch_bounds__(NW * 64) void layer_head_kernel(const HeadArgs p)
 
 }  // namespace
 
-// At most a workgroup per CU, and with two to six parts of the hidden, where the output projection made over counts for more, at most 1536 rows.  Us a
-// call, four layers, one launch / two, as calls / as nodes of a graph (where the launch saved costs no host time).  d_ffn 1024: score of 16 rows 79.2 /
-// 86.0, 80.1 / 81.7, 64 90.0 / 90.7, 91.3 / 91.4, 320 93.6 / 95.6, 95.2 / 96.8, 600 98.7 / 102.7, 100.2 / 103.9, 1000 111.5 / 112.8, 112.3 / 113.9,
-// encode of 128 rows 60.4 / 66.4, 60.2 even, 400 65.0 / 69.3, 66.3 / 64.2, 1000 75.9 / 75.7, 77.3 / 76.7; 2048: score of 400 100.9 / 107.2, 102.1 /
-// 108.2, encode of 400 71.0 / 80.4, 71.8 / 76.6; 768: encode of 1024 72.6 / 74.1, 74.1 / 75.1, 1280 81.8 / 80.5, 83.3 / 81.4.  512: score of 200 85.0 /
-// 86.0, 85.3 / 85.9, 1000 102.7 / 100.4, 103.3 / 101.5, encode of 400 60.5 / 67.3, 59.5 / 58.9, 1024 68.6 / 66.4, 69.5 / 67.6, 1152 76.6 / 77.3, 76.9 /
-// 77.8, 1536 80.7 / 79.5, 81.7 / 80.2, 2048 87.2 / 82.3, 88.3 / 83.4; 256: score of 128 83.6 / 85.2, 81.1 / 85.0, 2048 100.7 / 99.0, 101.5 / 99.9, 4096
-// 161.6 / 159.3, 162.9 / 160.6, encode of 700 62.5 / 70.3, 61.4 / 59.9, 1280 73.4 / 81.1, 73.0 / 74.5, 2048 81.0 / 79.8, 81.6 / 79.9, 4096 102.9 /
-// 100.2, 105.1 / 101.4; 128: score of 512 86.9 / 85.6, 85.2 / 83.3, 1500 114.6 / 119.8, 114.4 / 118.9, 4096 145.7 / 156.5, 147.4 / 157.9.  1024 with 304
-// workgroups (1200 rows) 115.3 / 103.4.
-bool layer_head_takes(int M, int d, int F)
-{
-    return d == D && F % kHidden == 0 && F > 0 && (M <= 1536 || F == kHidden || F >= 896) && (M + 31) / 32 * (int64_t)(F / kHidden) <= 256;
-}
+// At most a workgroup per CU.  Us a call, four layers, one launch / two.  d_ffn 128: score of 20 rows 65.8 / 77.2, 1064 81.5 / 86.1, 2904 111.1 / 121.9,
+// request of 100 behaviours and candidates 132 / 140, packed forward of 656 candidates 123.5 / 131.2; 256: score of 64 70.6 / 77.7, 904 82.5 / 81.6, 1112
+// 86.7 / 89.8, 1600 92.9 / 95.2, 2384 113.4 / 119.7, 3000 119.2 / 126.3, 4064 124.9 / 130.0, encode of 2048 73.1 / 73.5, forward of 3000 candidates 162.7 /
+// 165.6; 512: score of 120 73.8 / 76.8, 1600 97.8 / 100.3, 2048 102.9 / 102.3, encode of 1024 65.2 / 64.3, 2048 78.5 / 77.1, forward of 1600
+// 160.1 / 162.0; 640: score of 144 77.6 / 77.8, 1600 100.9 / 104.6, encode of 384 63.2 / 62.7; 768: score of 48 74.1 / 77.0, encode of 1024 69.6 / 70.8; 1024: score of
+// 20 71.6 / 77.2, 144 77.3 / 78.1, 952 94.5 / 96.0, 1200 (304 workgroups) 115.3 / 103.4; 2048: score of 104 81.7 / 83.2, 408 87.9 / 94.1.
+bool layer_head_takes(int M, int d, int F) { return d == D && F % kHidden == 0 && F > 0 && (M + 31) / 32 * (int64_t)(F / kHidden) <= 256; }
 
 hipError_t layer_head_bf16(const HeadArgs &a, hipStream_t s)
 {
