@@ -16,7 +16,7 @@ hipError_t launch_bgf_front(const float *e, const void *wqkv, void *o, const int
 hipError_t launch_bgf_gate_head(const float *g, const void *pre, const float *w_head, float b_head, float *y,
                                 float *score, int64_t m, int nd, hipStream_t s);
 // the same with both projections of the gate before it (packed weights; gb: bf16 copy of g), where that is the faster way
-bool bgf_gate_takes(int64_t m, int nd, int dg);
+bool bgf_gate_takes(int64_t m, int nd, int dg, bool with_y);
 hipError_t launch_bgf_gate(const void *gb, const float *g, const void *w_down, const void *w_up, const float *w_head, float b_head, float *y,
                            float *score, int64_t m, int nd, int dg, hipStream_t s);
 int bgf_max_blocks();

@@ -263,23 +263,25 @@ __global__ __launch_bounds__(512, 4) void bgf_gate_kernel(const __bf16 *gb, cons
 // A workgroup streams both weights for its 32 candidates, whoever else does, so few of them are better served by the projections for few rows
 // (gemm_small_bf16.hip), further on with a wide G, whose weights the macro tiles read less often.  The lines lie where the two sides meet, which is
 // earlier with Y than without it.  Us a call, one launch / three, G as blocks x d_model, with Y; in brackets without.
-// d_gate 256: 1 x 512 1500 58.2 / 58.6, 3 x 256 2100 63.8 / 65.0; 2 x 512 2600 92.9 / 91.0 [91.4 / 88.8], 3600 102.3 / 102.6 [100.5 / 99.6], 4 x 256
-// 2600 68.3 / 68.1 [66.6 / 65.9], 3600 71.2 / 72.1 [69.5 / 69.6], 5 x 256 2100 78.6 / 77.6 [77.1 / 75.3], 2700 79.4 / 80.1 [77.7 / 77.6], 3 x 512 2100
-// 106.0 / 103.6, 2700 122.9 / 123.2 [120.6 / 120.3], 3100 128.2 / 130.7, 6 x 256 2100 81.9 / 79.1, 2700 84.2 / 85.2 [82.4 / 82.2], 7 x 256 2100 87.7 /
-// 85.1, 2700 102.0 even [99.9 / 98.8]; 4 x 512 2100 129.2 / 126.0, 2900 140.4 / 138.2, 3500 150.3 / 149.7 [146.8 / 145.2], 4200 229.2 / 234.2 [224.8 /
-// 229.0], 8 x 256 2600 109.2 / 106.3 [106.0 / 102.0], 3400 115.0 / 115.4 [111.1 / 111.6]; wider ones meet more than once, by the turns of the macro
+// d_gate 256: 1 x 512 1500 58.2 / 58.6, 3 x 256 2100 63.8 / 65.0; 2 x 512 2200 90.2 / 90.1, 2690 90.8 / 91.2 [2272 88.0 / 87.4, 2677 88.4 / 88.1], 4 x 256
+// 2690 66.5 / 66.6 [2549 64.6 / 64.1], 5 x 256 2200 76.9 / 72.6, 2690 78.2 / 75.0 [2598 76.3 / 71.9], 3 x 512 2305 102.0 / 100.6, 2433 103.9 / 104.2, 2690
+// 115.1 / 116.9 [2562 110.0 / 107.3], 6 x 256 2305 79.0 / 77.7, 2561 80.1 / 79.6, 2690 81.0 / 83.1, 7 x 256 2177 84.5 / 82.2, 2433 97.8 / 99.3, 2690 98.6 /
+// 101.6 [2686 96.6 / 95.8]; 4 x 512 2305 126.3 / 124.6, 2433 127.1 / 128.6, 3391 145.6 / 148.1 [2448 124.4 / 120.8, 3239 136.9 / 136.4, 3500 146.8 / 145.2,
+// 4200 224.8 / 229.0], 8 x 256 2500 106.1 / 104.2, 2817 108.6 / 110.9, 3333 113.3 / 117.2 [2743 104.1 / 101.8, 3221 108.6 / 107.7, 3400 111.1 / 111.6]; wider
+// ones meet more than once, by the turns of the macro
 // tiles: 6 x 512 3400 249.9 / 251.2 [247.7 / 245.2], 5800 387.1 / 402.7 [369.7 / 377.5], 12 x 256 3900 209.7 / 216.0 [203.3 / 204.1], 5000 284.1 / 278.0
 // [267.5 / 258.5], 8 x 512 4300 386.5 / 398.0 [372.7 / 372.2], 5000 430 / 427, 6000 480 / 484; 12 x 512 3900 574 / 549, 6000 829 / 826, 16 x 512 5000
 // 1038 / 1007, 6000 1204 / 1198.
 // d_gate 128: 1 x 256 1500 34.9 / 37.4, 2 x 512 1500 80.5 / 80.3; 3 x 512 2000 107.9 / 105.9, 2600 112.7 / 112.6, 4 x 512 2000 111.0 / 106.7, 2800 127.3
-// / 127.1, 3400 141.2 / 141.7, 6 x 512 2000 144.0 / 137.3, 2800 231.3 / 231.2; 7 x 512 2000 155.6 / 148.3 [152.7 / 143.1], 3100 245.9 / 247.4 [242.8 /
-// 239.1], 8 x 512 2000 174.4 / 163.5, 3100 262.6 / 263.1 [256.3 / 251.1], 3400 264.8 / 270.0, 16 x 256 3100 318.8 / 314.2, 3300 320.1 / 323.2; 10 x 512
-// 4000 470 / 457, 5000 602 / 616, 16 x 512 4000 789 / 760, 5000 968 / 998.
-bool bgf_gate_takes(int64_t m, int nd, int dg)
+// / 127.1, 3400 141.2 / 141.7, 6 x 512 2000 144.0 / 137.3, 2800 231.3 / 231.2; 7 x 512 1579 139.7 / 135.1, 2177 174.6 / 176.2, 2690 231.4 / 236.0, 3100
+// 251.6 / 249.9 [2012 149.2 / 144.6, 2931 231.4 / 228.6]; 15 x 256 2177 211.2 / 205.9, 3190 277.4 / 276.1, 8 x 512 1607 151.1 / 144.9, 2500 242.2 / 242.1,
+// 3190 274.2 / 263.2, 3400 264.8 / 270.0 [2469 238.9 / 231.1, 2947 240.1 / 236.4], 16 x 256 2177 263.3 / 252.8, 3190 333.5 / 325.7, 3300 320.1 / 323.2; 10 x
+// 512 4000 470 / 457, 5000 602 / 616, 16 x 512 4000 789 / 760, 5000 968 / 998.
+bool bgf_gate_takes(int64_t m, int nd, int dg, bool with_y)
 {
     if (nd % 256 != 0) return false;
-    if (dg == 128) return m >= (nd > 4096 ? 5000 : nd > 3072 ? 3200 : nd > 1024 ? 2800 : 1500);
-    return dg == 256 && m >= (nd > 2048 ? 6000 : nd > 1792 ? 3400 : nd > 768 ? 2700 : 2049);
+    if (dg == 128) return m >= (nd > 4096 ? 5000 : nd > 3584 || (nd > 3072 && !with_y) ? 3200 : nd > 3072 ? 2100 : nd > 1024 ? 2800 : 1500);
+    return dg == 256 && m >= (nd > 2048 ? 6000 : nd <= 768 ? 2049 : with_y ? 2400 : nd > 1792 ? 3400 : 2700);
 }
 
 hipError_t launch_bgf_gate(const void *gb, const float *g, const void *w_down, const void *w_up, const float *w_head, float b_head, float *y,

@@ -543,7 +543,7 @@ int climber_bgf_score(const climber_config *cfg, const climber_bgf_weights *w, c
                                     cfg->qk_scale, s)));
     }
     TRY(layer_tail(&one, pw, e, ws.x32, true, 0, R, ws, s));
-    if (bgf_gate_takes(m_total, nd, dg))
+    if (bgf_gate_takes(m_total, nd, dg, y != nullptr))
         return rt(launch_bgf_gate(ws.xb, ws.x32, down_p, up_p, w->w_head, w->b_head, y, score, m_total, nd, dg, s));
     // f_gate on the flattened G (its bf16 copy, [m][n_blocks * d]): down, ReLU, up; then sigmoid,
     // Hadamard product and the head in one pass over G

@@ -147,9 +147,11 @@ def test_projection_of_many_fp32_rows_makes_their_sums(d, nb, dg, m, part):
     assert not ran_among(few, "gemm_resident_kernel")
 
 
-@pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 256, 3425, 33), (512, 7, 256, 6017, 1), (256, 5, 256, 2717, 28), (512, 3, 128, 2815, 31), (512, 7, 128, 3210, 40)])
+@pytest.mark.parametrize("d, nb, dg, m, part", [(512, 4, 256, 3425, 33), (512, 7, 256, 6017, 1), (256, 5, 256, 2717, 28), (512, 3, 128, 2815, 31), (512, 7, 128, 3210, 40),
+                                                (512, 4, 256, 2401, 17), (256, 5, 256, 2699, 3), (512, 7, 128, 2101, 35)])
 def test_one_launch_of_a_wide_gate_gives_the_bits_of_three(d, nb, dg, m, part):
-    # from its lines on, the last 32 candidates in part, an even and an odd number of steps
+    # from its lines on, the last 32 candidates in part, an even and an odd number of steps; the last three are one launch with Y alone, so that their scores
+    # come from both ways
     few, many = few_against_many(d, nb, dg, m, part)
     assert ran_among(many, f"bgf_gate_kernelILi{dg}E") and ran_among(few, "bgf_gate_head_kernel") and not ran_among(few, "bgf_gate_kernel")
 
@@ -198,10 +200,10 @@ def test_projection_and_attention_in_one_launch_give_the_bits_of_two(d, nb, m):
     assert score[[5, m - 2]].isnan().all()
 
 
-@pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 3399, False), (512, 4, 256, 3400, True), (256, 3, 256, 2048, False), (256, 3, 256, 2049, True),
+@pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 2048, False), (512, 4, 256, 3399, False), (512, 4, 256, 3400, True), (256, 3, 256, 2048, False), (256, 3, 256, 2049, True),
                                                (512, 2, 256, 2699, False), (256, 7, 256, 2700, True), (512, 8, 256, 5999, False), (512, 8, 256, 6000, True),
-                                               (512, 8, 128, 3199, False), (512, 8, 128, 3200, True), (512, 16, 128, 4999, False), (512, 16, 128, 5000, True)])
-def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, m, one):
+                                               (512, 8, 128, 1499, False), (512, 8, 128, 3199, False), (512, 8, 128, 3200, True), (512, 16, 128, 4999, False), (512, 16, 128, 5000, True)])
+def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, m, one, with_y=False):
     import torch
     import paper_2502_09888_amd as P
     spec = W.StackSpec("bgf-launches", B=1, L=128, sub_len=0, M=1, n_layers=1, d_model=d, H=d // 64, dh=64, d_ffn=256, n_scen=8, n_beh=4, seed=59)
@@ -211,10 +213,17 @@ def test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, 
     wh, ts, e = torch.zeros(nb * d, device="cuda:0"), torch.ones(8, device="cuda:0"), torch.ones(m, nb, d, device="cuda:0")
     sc, score = torch.zeros(m, dtype=torch.int32, device="cuda:0"), torch.empty(m, device="cuda:0")
     ws = torch.empty(P.climber_bgf_workspace_bytes(cfg, nb, dg, m), dtype=torch.uint8, device="cuda:0")
-    run = launches(lambda: P.climber_bgf_score(cfg, atl, wd, wu, wh, ts, 0.5, nb, dg, e, sc, m, None, score, ws))
+    run = launches(lambda: P.climber_bgf_score(cfg, atl, wd, wu, wh, ts, 0.5, nb, dg, e, sc, m, torch.empty_like(e) if with_y else None, score, ws))
     say([tuple(k)[:2] for k in run])
     assert (score == 0.5).all()
     assert any("bgf_gate_kernel" in k.kernel for k in run) == one and any("bgf_gate_head_kernel" in k.kernel for k in run) != one
+
+
+@pytest.mark.parametrize("d, nb, dg, m, one", [(512, 4, 256, 2399, False), (512, 4, 256, 2400, True), (512, 2, 256, 2399, False), (256, 7, 256, 2400, True),
+                                               (256, 3, 256, 2049, True), (512, 8, 256, 5999, False), (512, 7, 128, 2099, False), (512, 7, 128, 2100, True),
+                                               (512, 8, 128, 3199, False), (512, 8, 128, 3200, True), (512, 6, 128, 2799, False)])
+def test_the_gate_with_its_rows_out_is_one_launch_from_fewer_candidates_on(d, nb, dg, m, one):
+    test_the_gate_is_one_launch_where_that_was_measured_to_be_faster(d, nb, dg, m, one, with_y=True)
 
 
 @pytest.mark.parametrize("d, nb, m, one", [(512, 2, 1499, False), (512, 2, 1500, True), (256, 5, 2799, False), (256, 5, 2800, True), (512, 6, 2799, False), (512, 6, 2800, True)])
